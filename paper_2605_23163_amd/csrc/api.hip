@@ -87,6 +87,28 @@ fdd_status check_attn_shape(const fdd_attn_params* p)
 
 }  // namespace
 
+// Workgroups per row tile of the fp32 path.  A round of workgroups takes ceil(tiles / (8 S)) tiles per wavefront, two
+// wavefronts per SIMD at 36 D/8 cycles of matrix pipe a tile (4.0 us per pair at D = 128), after about 4 us of start,
+// first loads and LDS merge; S > 1 adds the merge kernel (about 4 us, and the partials' way to memory and back).  The
+// smallest estimate wins, fewer splits on ties.  Measured on both sides of the choice, us per call at Hq = 28, Hkv = 4,
+// D = 128, B = 32 (choice in brackets): N = 1, L = 2048: S = 8 24.1, [9] 22.6, 12 33.7; N = 1, L = 16384: 8 78.8,
+// [9] 73.1, 12 106; N = 4, L = 4096: 1 138, [2] 80.0, 3 106; N = 8, L = 4096: [1] 139, 2 152.
+static int f32_splits(long long row_tiles, long long tiles, int D)
+{
+    const double tile_us = 2.0 * 36 * D / 2300.0;
+    double best = 0.0;
+    int s_best = 1;
+    for (int s = 1; s <= 64 && (s == 1 || (s - 1) * kF32Waves < tiles); ++s) {
+        const long long rounds = (row_tiles * s + kNumCU - 1) / kNumCU;
+        const long long per_wave = (tiles + (long long)s * kF32Waves - 1) / ((long long)s * kF32Waves);
+        double us = (double)rounds * ((double)per_wave * tile_us + 4.0);
+        if (s > 1) us += 4.0 + (double)row_tiles * s * kF32RowTile * D * 8.0 / 4e6;
+        if (s == 1 || us < best) { best = us; s_best = s; }
+        if (row_tiles * s >= 4 * kNumCU) break;      // more rounds gain nothing
+    }
+    return s_best;
+}
+
 bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
 {
     AttnPlan pl;
@@ -96,8 +118,8 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
         pl.mtile_rows = 256;
         pl.key_tile = 64;
     } else {
-        pl.mtile_rows = 16;
-        pl.key_tile = 32;
+        pl.mtile_rows = kF32RowTile;
+        pl.key_tile = 16;
     }
     pl.MT = (pl.R + pl.mtile_rows - 1) / pl.mtile_rows;
     pl.TP = (p.L + pl.key_tile - 1) / pl.key_tile;
@@ -174,12 +196,12 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
     } else {
         pl.TPU = pl.TP > 0 ? pl.TP : 1;
         pl.U = NM * pl.TPU;
+        const long long rows_per_rollout = std::max(1ll, (long long)pl.R / p.N);
+        const long long span = std::min<long long>(p.N, (pl.mtile_rows + rows_per_rollout - 1) / rows_per_rollout + 1);
+        const long long tiles = pl.TP + span * ((p.E + pl.key_tile - 1) / pl.key_tile + (p.B + pl.key_tile - 1) / pl.key_tile);
         int s = p.splits;
-        if (s == 0) {
-            s = (int)(kNumCU / NM);
-            if (s > 64) s = 64;
-        }
-        if (s > pl.TP) s = pl.TP;
+        if (s == 0) s = f32_splits(NM, tiles, p.D);
+        if (s > tiles) s = (int)tiles;
         if (s < 1) s = 1;
         pl.splits = s;
         pl.W = 0;

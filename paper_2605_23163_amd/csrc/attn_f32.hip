@@ -1,20 +1,49 @@
 // Shared-prefix block-causal attention, fp32 storage and arithmetic, and the
-// split merge used by both storage types.
+// merge of its splits.
 //
-// The fp32 path exists for exactness checks on small problems (the bf16
-// matrix-core kernel is the performance path).  It computes the same thing
-// (paper, "Block-Causal Diffusion" and "Shared prefix") with plain fp32 FMAs:
-// a workgroup owns 16 stacked query rows of one KV head and one piece of the
-// key range, stages 32-key K/V tiles in LDS, and keeps the streaming-softmax
-// state (m, l, o) per row.
+// The same thing as the bf16 kernel computes (paper, "Block-Causal Diffusion"
+// and "Shared prefix"), with fp32 products and sums on the matrix cores
+// (v_mfma_f32_16x16x4_f32).
+//
+// How the work is laid out
+//   * A workgroup owns 32 stacked query rows of one KV head (see AttnPlan); its
+//     8 wavefronts share the KEYS out among themselves, 16 at a time, each with
+//     a streaming-softmax state (m, l, o) of its own, and merge through LDS at
+//     the end.  `splits` workgroups share one row tile when the row tiles alone
+//     leave the chip idle; then a second small kernel merges their partials.
+//   * S^T = K Q^T: a lane owns query lane % 16 of each of two 16-query blocks and
+//     keys 4 (lane / 16) .. + 3, so the probabilities are the B operand of
+//     O^T += V^T P^T as they lie.  The channels are dealt to the k-steps (and to
+//     the rows of O^T) such that every operand is a 16-byte piece of a K or V row:
+//     the fragments come straight from global memory, no LDS, no barrier.
+//   * What bounds it: the matrix pipe (64 flop per cycle and SIMD; a 16-byte
+//     fragment load feeds 8 matrix instructions of 32 cycles, so 8 wavefronts that
+//     share nothing ask for 32 bytes per cycle and CU, half of what the vector
+//     cache delivers).  Splitting keys instead of rows over the wavefronts costs no
+//     time then, and makes the row tiles small: 32 rows fill the chip without (or
+//     with few) splits, whose partials would cost a pass over memory each.
+//   * A fragment register is requested again for the next tile as soon as it has
+//     been used: a whole step, 4096 cycles at D = 128, of latency is covered.
+//   * Measured at N = 8, B = 32, L = 4096, Hq = 28, Hkv = 4, D = 128 (15.1 GFLOP): 152 us,
+//     100 TFLOP/s of the 153 a large fp32 matrix product reaches here; 224 of 256 CUs
+//     are used, the matrix pipe of a used CU 78 % of its cycles, and the same loop
+//     without loads and exponentials takes 140 us.  (Scalar fused multiply-adds from
+//     LDS tiles: 687 us.)  No faster: K through a private LDS ring (157 us), the next
+//     tile's scores under this tile's exponentials (157 us), priorities that keep the
+//     two wavefronts of a SIMD level (157 us).
 #include "fdd_internal.h"
+
+#include <atomic>
 
 namespace fdd {
 namespace {
 
-constexpr int KT = 32;     // keys per tile
-constexpr int RT = 16;     // rows per workgroup
-constexpr int THREADS = 256;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int KT = 16;                 // keys per tile
+constexpr int RT = kF32RowTile;        // rows per workgroup: two 16-query blocks
+constexpr int WAVES = kF32Waves;       // wavefronts of a workgroup, sharing the keys
+constexpr int THREADS = WAVES * 64;
 
 struct Args {
     const float* q;
@@ -28,12 +57,14 @@ struct Args {
     const float* ek;   // per-rollout extension [N, Ecap, Hkv, D]
     const float* ev;
     int E, Ecap;
-    int batch;         // independent problems in this launch; element strides between their arrays:
-    long long q_bs, p_bs, b_bs, e_bs, o_bs;
-    int N, B, L, Hq, Hkv, G, R, MT, TP, S;
-    int causal;   // in-block keys are visible up to the query's own position only
-    float c;   // scale * log2(e)
+    long long q_bs, p_bs, b_bs, e_bs, o_bs;   // element strides between the arrays of independent problems
+    int N, B, L, Hq, Hkv, G, R, MT, S;
+    int W, per_xcd;    // workgroups; ceil(W / 8)
+    int causal;        // in-block keys are visible up to the query's own position only
+    float c;           // scale * log2(e)
     const int32_t* qpos;   // stacked rows are the listed block positions only (ascending n*B + b), or nullptr: all of them
+    int ext_per, per;      // private tiles per rollout: of its extension, in all (extension, then block)
+    FastDiv dMT, dS, dHkv, dG, dB, dPer, dParts;   // divisions by launch constants
 };
 
 // block position n*B + b of entry `e` of the list of query positions (clamped into range), or e itself without a list
@@ -42,194 +73,310 @@ __device__ __forceinline__ int position_of(const int32_t* qpos, int e, int NB)
     return qpos ? min(max(qpos[e], 0), NB - 1) : e;
 }
 
+// the same pointer, known to be wave-uniform (kept in scalar registers)
+__device__ __forceinline__ const char* uniform(const char* p)
+{
+    const uint64_t u = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+    return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
+}
+
+template <int D>
+struct F32Cfg {
+    static constexpr int MERGE_FLOATS = WAVES * RT * D;   // outputs of all wavefronts, in register order
+    static constexpr int LDS_BYTES = (MERGE_FLOATS + 2 * WAVES * RT + 2 * RT) * 4;   // + (m, l) per wavefront and row, and per row
+};
+
 template <int D>
 __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
 {
-    constexpr int DP = D + 4;          // padded row length (floats), keeps float4 alignment
-    constexpr int DPT = D / 16;        // output channels per thread
-    __shared__ __align__(16) float qs[RT * DP];
-    __shared__ __align__(16) float ks[KT * DP];
-    __shared__ __align__(16) float vs[KT * DP];
-    __shared__ float ps[RT * (KT + 1)];
+#if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
+    constexpr int NJ = D / 16;         // 16-byte fragment loads per tile and operand
+    constexpr int NT = D / 64;         // 64-channel blocks of the output
+    extern __shared__ __align__(16) float smem[];
 
-    const int tid = threadIdx.x;
-    const int mt = blockIdx.x;
-    const int split = blockIdx.y;
-    // grid z runs over (problem of the batch, KV head); the pointers are moved to the problem's arrays
-    const int khv = blockIdx.z;
-    const int pb = khv / a.Hkv;
-    const int kh = khv - pb * a.Hkv;
-    a.q += pb * a.q_bs;
-    a.pk += pb * a.p_bs;
-    a.pv += pb * a.p_bs;
-    a.bk += pb * a.b_bs;
-    a.bv += pb * a.b_bs;
-    a.ek += pb * a.e_bs;
-    a.ev += pb * a.e_bs;
-    a.out += pb * a.o_bs;
-    const int BG = a.B * a.G;
+    // workgroups are dealt to the 8 XCDs round-robin: those of one XCD own neighbouring row tiles of one
+    // (KV head, split), which walk the same keys
+    const int wg = (int)(blockIdx.x % kNumXCD) * a.per_xcd + (int)(blockIdx.x / kNumXCD);
+    if (wg >= a.W) return;
+    const int rest = fast_div(wg, a.dMT), mt = wg - rest * a.MT;
+    const int khv = fast_div(rest, a.dS), split = rest - khv * a.S;
+    const int pb = fast_div(khv, a.dHkv), kh = khv - pb * a.Hkv;     // problem of the batch, KV head
 
-    const int r_loc = tid / 16;         // row of this thread inside the workgroup tile
-    const int sub = tid % 16;           // 16 threads cooperate on a row
-    const int row = mt * RT + r_loc;
-    const bool row_ok = row < a.R;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c16 = lane & 15, g4 = lane >> 4;
     const int NB = a.N * a.B;
-    const int nb = row_ok ? position_of(a.qpos, row / a.G, NB) : 0;
-    const int g = row_ok ? row % a.G : 0;
-    const int my_rollout = row_ok ? nb / a.B : -1;
-    const int my_b = row_ok ? nb % a.B : 0;
+    const uint32_t stride4 = (uint32_t)(a.Hkv * D * 4);     // bytes between consecutive keys
+
+    // ---- query rows of this lane: c16 of both 16-query blocks --------------------------------------
+    f32x4 qf[2][NJ];
+    int my_rollout[2], my_b[2];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+        const int row = min(mt * RT + qb * 16 + c16, a.R - 1);
+        const int sel = fast_div(row, a.dG), g = row - sel * a.G;
+        const int nb = position_of(a.qpos, sel, NB);
+        my_rollout[qb] = fast_div(nb, a.dB);
+        my_b[qb] = nb - my_rollout[qb] * a.B;
+        const float* qp = a.q + pb * a.q_bs + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * D + 4 * g4;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) qf[qb][j] = *reinterpret_cast<const f32x4*>(qp + 16 * j);
+    }
+
+    // ---- key tiles of this wavefront ---------------------------------------------------------------
+    // prefix tiles, then for every rollout the rows belong to: extension tiles, block tiles
     // (rows are in ascending order of position, hence of rollout)
-    const int wg_row_hi = min(mt * RT + RT - 1, a.R - 1);
-    const int wg_n_lo = a.qpos ? position_of(a.qpos, (mt * RT) / a.G, NB) / a.B : (mt * RT) / BG;
-    const int wg_n_hi = a.qpos ? position_of(a.qpos, wg_row_hi / a.G, NB) / a.B : wg_row_hi / BG;
+    const int row_hi = min(mt * RT + RT, a.R) - 1;
+    const int n_lo = __builtin_amdgcn_readfirstlane(fast_div(position_of(a.qpos, fast_div(mt * RT, a.dG), NB), a.dB));
+    const int n_hi = __builtin_amdgcn_readfirstlane(fast_div(position_of(a.qpos, fast_div(row_hi, a.dG), NB), a.dB));
+    const int TP = (a.L + KT - 1) / KT;
+    const int n_tiles = TP + (n_hi - n_lo + 1) * a.per;
+    const int part = split * WAVES + wave;                  // (tiles * parts stays below 2^31 for every accepted shape)
+    const int t_lo = __builtin_amdgcn_readfirstlane(fast_div(n_tiles * part, a.dParts));
+    const int t_hi = __builtin_amdgcn_readfirstlane(fast_div(n_tiles * (part + 1), a.dParts));
 
-    // stage the query rows
-    for (int i = tid; i < RT * (D / 4); i += THREADS) {
-        const int r = i / (D / 4), c4 = i % (D / 4);
-        const int rr = mt * RT + r;
-        float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (rr < a.R) {
-            const int nb_ = position_of(a.qpos, rr / a.G, NB), g_ = rr % a.G;
-            x = *reinterpret_cast<const float4*>(a.q + ((size_t)nb_ * a.Hq + (size_t)kh * a.G + g_) * D + c4 * 4);
-        }
-        *reinterpret_cast<float4*>(&qs[r * DP + c4 * 4]) = x;
-    }
-
-    const int t0 = (int)(((long long)split * a.TP) / a.S);
-    const int t1 = (int)(((long long)(split + 1) * a.TP) / a.S);
-    const int n_prefix = t1 - t0;
-    const int ext_per = (a.E + KT - 1) / KT;                  // tiles of a rollout's extension
-    const int tail_per = ext_per + (a.B + KT - 1) / KT;       // private tiles per rollout: extension, then block
-    const int n_tail = (split == a.S - 1) ? (wg_n_hi - wg_n_lo + 1) * tail_per : 0;
-    const size_t kv_stride = (size_t)a.Hkv * D;
-
-    float o[DPT];
-#pragma unroll
-    for (int j = 0; j < DPT; ++j) o[j] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
-
-    for (int i = 0; i < n_prefix + n_tail; ++i) {
+    struct Tile {
+        const char* k;    // first key's row of this KV head
+        const char* v;
+        int valid;        // keys that exist
+        int rollout;      // whose rows may see it (-1: every row)
+        int key0;         // block position of the first key (block tiles under the causal mask), else hugely negative
+    };
+    auto tile_at = [&](int t) {
+        Tile r;
+        long long row;
+        long long bs;
         const float *kp, *vp;
-        int valid, rollout, blk0 = 0;
-        bool in_block = false;
-        if (i < n_prefix) {
-            const int key0 = (t0 + i) * KT;
-            kp = a.pk + (size_t)key0 * kv_stride + (size_t)kh * D;
-            vp = a.pv + (size_t)key0 * kv_stride + (size_t)kh * D;
-            valid = min(KT, a.L - key0);
-            rollout = -1;
+        r.key0 = -(1 << 30);
+        if (t < TP) {
+            kp = a.pk; vp = a.pv; bs = a.p_bs;
+            row = (long long)t * KT;
+            r.valid = min(KT, a.L - t * KT);
+            r.rollout = -1;
         } else {
-            const int j = i - n_prefix;
-            const int n = wg_n_lo + j / tail_per;
-            const int w = j % tail_per;
-            rollout = n;
-            if (w < ext_per) {
-                const int key0 = w * KT;
-                const size_t off = ((size_t)n * a.Ecap + key0) * kv_stride + (size_t)kh * D;
-                kp = a.ek + off;
-                vp = a.ev + off;
-                valid = min(KT, a.E - key0);
+            const int j = t - TP, i = fast_div(j, a.dPer), w = j - i * a.per;
+            r.rollout = n_lo + i;
+            if (w < a.ext_per) {
+                kp = a.ek; vp = a.ev; bs = a.e_bs;
+                row = (long long)r.rollout * a.Ecap + w * KT;
+                r.valid = min(KT, a.E - w * KT);
             } else {
-                const int key0 = (w - ext_per) * KT;
-                const size_t off = ((size_t)n * a.B + key0) * kv_stride + (size_t)kh * D;
-                kp = a.bk + off;
-                vp = a.bv + off;
-                valid = min(KT, a.B - key0);
-                blk0 = key0;
-                in_block = true;
+                const int k0 = (w - a.ext_per) * KT;
+                kp = a.bk; vp = a.bv; bs = a.b_bs;
+                row = (long long)r.rollout * a.B + k0;
+                r.valid = min(KT, a.B - k0);
+                if (a.causal) r.key0 = k0;
             }
         }
-        __syncthreads();   // previous tile fully consumed (and qs written, first time)
-        for (int x = tid; x < KT * (D / 4); x += THREADS) {
-            const int key = x / (D / 4), c4 = x % (D / 4);
-            float4 kk = make_float4(0.f, 0.f, 0.f, 0.f), vv = kk;
-            if (key < valid) {
-                kk = *reinterpret_cast<const float4*>(kp + (size_t)key * kv_stride + c4 * 4);
-                vv = *reinterpret_cast<const float4*>(vp + (size_t)key * kv_stride + c4 * 4);
-            }
-            *reinterpret_cast<float4*>(&ks[key * DP + c4 * 4]) = kk;
-            *reinterpret_cast<float4*>(&vs[key * DP + c4 * 4]) = vv;
-        }
-        __syncthreads();
+        const long long off = ((long long)pb * bs + row * a.Hkv * D + (long long)kh * D) * 4;
+        r.k = uniform(reinterpret_cast<const char*>(kp) + off);
+        r.v = uniform(reinterpret_cast<const char*>(vp) + off);
+        r.valid = __builtin_amdgcn_readfirstlane(r.valid);
+        r.rollout = __builtin_amdgcn_readfirstlane(r.rollout);
+        r.key0 = __builtin_amdgcn_readfirstlane(r.key0);
+        return r;
+    };
 
-        // scores of KT/16 keys per thread: keys sub, sub+16, ...
-        const bool sees = rollout < 0 || rollout == my_rollout;
-        constexpr int KPT = KT / 16;
-        float sc[KPT];
-        float mx = -INFINITY;
+    // Fragments of a tile.  K: row c16, channels 16 j + 4 g4 ..; V: row 4 g4 + v, channels 64 t + 4 c16 ..
+    // (rows beyond `valid` repeat the last valid one: finite values, masked below, nothing read out of bounds)
+    f32x4 kf[NJ], vf[NJ];
+    auto k_off = [&](const Tile& t) { return (uint32_t)min(c16, t.valid - 1) * stride4 + (uint32_t)(16 * g4); };
+    auto v_off = [&](const Tile& t, int v) { return (uint32_t)min(4 * g4 + v, t.valid - 1) * stride4 + (uint32_t)(16 * c16); };
+    auto load = [&](const char* base, uint32_t off) {
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, 0x7fffffff, 0x00020000);
+        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
+    };
+
+    f32x4 o[2][NT][4];       // [query block][64-channel block][e]: channels 64 t + 16 g4 + 4 v + e of query c16
 #pragma unroll
-        for (int j = 0; j < KPT; ++j) {
-            const int key = sub + 16 * j;
-            float acc = 0.f;
-            for (int d = 0; d < D; d += 4) {
-                const float4 qq = *reinterpret_cast<const float4*>(&qs[r_loc * DP + d]);
-                const float4 kk = *reinterpret_cast<const float4*>(&ks[key * DP + d]);
-                acc = fmaf(qq.x, kk.x, acc);
-                acc = fmaf(qq.y, kk.y, acc);
-                acc = fmaf(qq.z, kk.z, acc);
-                acc = fmaf(qq.w, kk.w, acc);
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[qb][t][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_ref[2] = {-INFINITY, -INFINITY};   // reference the exponentials are taken against (raw score units)
+    float l_run[2] = {0.f, 0.f};               // this lane's share of the running sum
+
+    if (t_lo < t_hi) {
+        Tile now = tile_at(t_lo);
+        {
+            const uint32_t off = k_off(now);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                kf[j] = load(now.k, off + 64 * j);
+                __builtin_amdgcn_sched_barrier(0);     // (the order of the loop's requests, which the waits in it count)
             }
-            const bool later = a.causal && in_block && blk0 + key > my_b;
-            sc[j] = (sees && key < valid && !later) ? acc : -INFINITY;
-            mx = fmaxf(mx, sc[j]);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int tt = 0; tt < NT; ++tt) {
+                    vf[v * NT + tt] = load(now.v, v_off(now, v) + 256 * tt);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
         }
+        for (int t = t_lo; t < t_hi; ++t) {
+            // A fragment of the next tile is requested as soon as the matrix instructions that read its
+            // predecessor are issued: every request has a whole step to arrive.  (The last tile is requested
+            // once more at the end, from the caches.)
+            const Tile next = tile_at(min(t + 1, t_hi - 1));
+            const uint32_t next_k = k_off(next);
+            f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-        for (int w = 8; w >= 1; w >>= 1) mx = fmaxf(mx, __shfl_xor(mx, w, 16));
-        const float m_new = fmaxf(m_run, mx);
-        const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-        const float alpha = exp2f((m_run - m_use) * a.c);
-        float psum = 0.f;
+            for (int j = 0; j < NJ; ++j) {
 #pragma unroll
-        for (int j = 0; j < KPT; ++j) {
-            const float p = exp2f((sc[j] - m_use) * a.c);
-            psum += p;
-            ps[r_loc * (KT + 1) + sub + 16 * j] = p;
-        }
+                for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int w = 8; w >= 1; w >>= 1) psum += __shfl_xor(psum, w, 16);
-        l_run = l_run * alpha + psum;
-        m_run = m_new;
-        __syncthreads();   // ps visible to the 16 threads of the row
+                    for (int qb = 0; qb < 2; ++qb)
+                        s[qb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][i], qf[qb][j][i], s[qb], 0, 0, 0);
+                kf[j] = load(next.k, next_k + 64 * j);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // register v of a query block is key 4 g4 + v
+            if (now.valid < KT || now.rollout >= 0) {
 #pragma unroll
-        for (int j = 0; j < DPT; ++j) o[j] *= alpha;
-        for (int key = 0; key < KT; ++key) {
-            const float p = ps[r_loc * (KT + 1) + key];
+                for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-            for (int j = 0; j < DPT; ++j) o[j] = fmaf(p, vs[key * DP + sub * DPT + j], o[j]);
+                    for (int v = 0; v < 4; ++v) {
+                        const int key = 4 * g4 + v;
+                        const bool sees = (now.rollout < 0) | (now.rollout == my_rollout[qb]);
+                        const bool hidden = !sees | (key >= now.valid) | (now.key0 + key > my_b[qb]);
+                        s[qb][v] = hidden ? -INFINITY : s[qb][v];
+                    }
+            }
+            // The reference is raised when a score outgrows it by more than 2^8 (the same softmax; fp32 keeps its
+            // relative precision), for a whole row at a time: its keys lie in the four lanes c16 + 16 i.
+            float mx[2];
+            bool need = false;
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+                mx[qb] = fmaxf(fmaxf(s[qb][0], s[qb][1]), fmaxf(s[qb][2], s[qb][3]));
+                need |= (mx[qb] > m_ref[qb]) & ((mx[qb] - m_ref[qb]) * a.c > 8.f);
+            }
+            if (__any(need)) {
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb) {
+                    float m = fmaxf(m_ref[qb], mx[qb]);
+                    m = fmaxf(m, __shfl_xor(m, 16, 64));
+                    m = fmaxf(m, __shfl_xor(m, 32, 64));
+                    const float alpha = m == -INFINITY ? 1.f : exp2f((m_ref[qb] - m) * a.c);
+                    m_ref[qb] = m;
+                    l_run[qb] *= alpha;
+#pragma unroll
+                    for (int tt = 0; tt < NT; ++tt)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o[qb][tt][e] *= alpha;
+                }
+            }
+            f32x4 p[2];
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+                const float mc = (m_ref[qb] == -INFINITY ? 0.f : m_ref[qb]) * a.c;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) p[qb][v] = __builtin_amdgcn_exp2f(fmaf(s[qb][v], a.c, -mc));
+                l_run[qb] += (p[qb][0] + p[qb][1]) + (p[qb][2] + p[qb][3]);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const uint32_t next_v = v_off(next, v);
+#pragma unroll
+                for (int tt = 0; tt < NT; ++tt) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int qb = 0; qb < 2; ++qb)
+                            o[qb][tt][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[v * NT + tt][e], p[qb][v], o[qb][tt][e], 0, 0, 0);
+                    vf[v * NT + tt] = load(next.v, next_v + 256 * tt);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            now = next;
         }
     }
 
-    if (!row_ok) return;
-    if (a.S == 1) {
-        float* op = a.out + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * D + sub * DPT;
-        const float inv = 1.f / l_run;
+    // ---- merge of the wavefronts through LDS ----------------------------------------------------------
+    float* const so = smem;                                  // [wave][qb][t][v][lane] x 4 channels
+    float* const sm = smem + F32Cfg<D>::MERGE_FLOATS;        // [wave][row]: m, then the wavefront's weight
+    float* const sl = sm + WAVES * RT;                       // [wave][row]: l
+    float* const row_l = sl + WAVES * RT;                    // [row]: l of the workgroup
+    float* const row_m = row_l + RT;                         // [row]: m of the workgroup
 #pragma unroll
-        for (int j = 0; j < DPT; ++j) op[j] = o[j] * inv;
-    } else {
-        const size_t prow = (((size_t)khv * a.MT + mt) * a.S + split) * RT + r_loc;
-        float* wo = a.ws_o + prow * D + sub * DPT;
+    for (int qb = 0; qb < 2; ++qb) {
+        float l = l_run[qb];
+        l += __shfl_xor(l, 16, 64);
+        l += __shfl_xor(l, 32, 64);
+        if (g4 == 0) {
+            sm[wave * RT + qb * 16 + c16] = m_ref[qb];
+            sl[wave * RT + qb * 16 + c16] = l;
+        }
 #pragma unroll
-        for (int j = 0; j < DPT; ++j) wo[j] = o[j];
-        if (sub == 0) {
-            a.ws_ml[prow * 2 + 0] = m_run;
-            a.ws_ml[prow * 2 + 1] = l_run;
+        for (int tt = 0; tt < NT; ++tt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                *reinterpret_cast<f32x4*>(so + ((((wave * 2 + qb) * NT + tt) * 4 + v) * 64 + lane) * 4) =
+                    f32x4{o[qb][tt][0][v], o[qb][tt][1][v], o[qb][tt][2][v], o[qb][tt][3][v]};
+    }
+    __syncthreads();
+    if (tid < RT) {
+        float m = -INFINITY, l = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) m = fmaxf(m, sm[w * RT + tid]);
+        const float m_use = m == -INFINITY ? 0.f : m;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const float x = exp2f((sm[w * RT + tid] - m_use) * a.c);
+            l = fmaf(sl[w * RT + tid], x, l);
+            sm[w * RT + tid] = x;
+        }
+        row_l[tid] = l;
+        row_m[tid] = m;
+    }
+    __syncthreads();
+    constexpr int CHUNKS = 2 * NT * 4 * 64;      // 16-byte pieces of the row tile
+#pragma unroll
+    for (int i0 = 0; i0 < CHUNKS; i0 += THREADS) {
+        const int i = i0 + tid;
+        if (CHUNKS % THREADS != 0 && i >= CHUNKS) break;
+        const int ln = i & 63, v = (i >> 6) & 3, tt = (i >> 8) % NT, qb = (i >> 8) / NT;
+        const int r = qb * 16 + (ln & 15), row = mt * RT + r;
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const f32x4 x = *reinterpret_cast<const f32x4*>(so + (w * CHUNKS + i) * 4);
+            const float y = sm[w * RT + r];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = fmaf(x[e], y, acc[e]);
+        }
+        if (row >= a.R) continue;
+        const int ch = 64 * tt + 16 * (ln >> 4) + 4 * v;
+        if (a.S == 1) {
+            const int sel = fast_div(row, a.dG), g = row - sel * a.G;
+            const int nb = position_of(a.qpos, sel, NB);
+            const float inv = 1.f / row_l[r];
+            *reinterpret_cast<f32x4*>(a.out + pb * a.o_bs + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * D + ch) = acc * inv;
+        } else {
+            const size_t prow = (((size_t)khv * a.MT + mt) * a.S + split) * RT + r;
+            *reinterpret_cast<f32x4*>(a.ws_o + prow * D + ch) = acc;
+            if (ch == 0) {
+                a.ws_ml[prow * 2 + 0] = row_m[r];
+                a.ws_ml[prow * 2 + 1] = row_l[r];
+            }
         }
     }
+#endif
 }
 
 // ---------------------------------------------------------------------------
-// Merge of the per-segment partials (log-sum-exp merge), for both storage types:
+// Merge of the splits' partials (log-sum-exp merge):
 //   m* = max_s m_s,  w_s = 2^((m_s - m*) c),  out = sum_s w_s o_s / sum_s w_s l_s
 // The sum runs over s in a fixed order, so results are reproducible.
 struct CombineArgs {
     const float* ws_o;
     const float* ws_ml;
-    void* out;
-    int Hq, Hkv, G, R, MT, mrows, D, bf16;
+    float* out;
+    int Hq, Hkv, G, R, MT, mrows, D;
     long long o_bs;  // elements between the outputs of the problems of a batch
-    int max_seg;     // slots per M-tile in the workspace
-    int fixed_seg;   // > 0: every M-tile has this many segments; 0: stream-K ranges
-    int TPU, base, rem;
+    int n_seg;       // splits, at least 2
     int SG;          // segment groups: the segments of a row are shared out over SG threads per channel quad
     int RB;          // rows per block; RB * SG * D/4 = 256 threads
     float c;
@@ -250,19 +397,14 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a)
     const int khv = M / a.MT, mt = M - khv * a.MT;      // (problem of the batch, KV head), M-tile
     const int pb = khv / a.Hkv, kh = khv - pb * a.Hkv;
     const int rit0 = (int)blockIdx.y * a.RB;
-    int n_seg = a.fixed_seg;
-    if (n_seg == 0) {
-        // same arithmetic as the attention kernel: workgroups whose unit range meets this M-tile
-        n_seg = wg_of_unit((M + 1) * a.TPU - 1, a.base, a.rem) - wg_of_unit(M * a.TPU, a.base, a.rem) + 1;
-    }
-    if (n_seg == 1) return;     // written in final form by its only segment
+    const int n_seg = a.n_seg;
     if (a.SG == 1 && n_seg <= 4) {
         // few segments: every thread reads the (m, l) pairs of its row itself, together with its
         // partial outputs, in one round trip to memory and without LDS (same sums, same order)
         const int rit = rit0 + r;
         const int row = mt * a.mrows + rit;
         if (rit >= a.mrows || row >= a.R) return;
-        const size_t prow = ((size_t)M * a.max_seg) * a.mrows + rit;
+        const size_t prow = ((size_t)M * a.n_seg) * a.mrows + rit;
         float2 ml[4];
         float4 x[4];
 #pragma unroll
@@ -294,25 +436,15 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a)
         const int sel = row / a.G, g = row - sel * a.G;
         const int nb = position_of(a.qpos, sel, a.NB);
         const size_t off = (size_t)(pb * a.o_bs) + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * a.D + d4 * 4;
-        if (a.bf16) {
-            typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
-            bf16x4 w4;
-            w4[0] = (__bf16)(acc.x * inv);
-            w4[1] = (__bf16)(acc.y * inv);
-            w4[2] = (__bf16)(acc.z * inv);
-            w4[3] = (__bf16)(acc.w * inv);
-            *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(a.out) + off) = w4;
-        } else {
-            *reinterpret_cast<float4*>(static_cast<float*>(a.out) + off) =
-                make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
-        }
+        *reinterpret_cast<float4*>(a.out + off) =
+            make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
         return;
     }
     float* const sm = smem;                           // [RB][n_seg] segment maxima
     float* const sl = smem + a.RB * n_seg;            // [RB][n_seg] segment sums
-    float4* const red = reinterpret_cast<float4*>(smem + ((2 * a.RB * a.max_seg + 3) & ~3));   // [RB][SG][d4n]
+    float4* const red = reinterpret_cast<float4*>(smem + ((2 * a.RB * a.n_seg + 3) & ~3));   // [RB][SG][d4n]
     float* const redl = reinterpret_cast<float*>(red + a.RB * a.SG * d4n);        // [RB][SG]
-    const size_t p0 = ((size_t)M * a.max_seg) * a.mrows + rit0;
+    const size_t p0 = ((size_t)M * a.n_seg) * a.mrows + rit0;
     for (int i = tid; i < a.RB * n_seg; i += 256) {
         const int rr = i / n_seg, s = i - rr * n_seg;
         float m = -INFINITY, l = 0.f;
@@ -379,21 +511,30 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a)
     const int sel = row / a.G, g = row - sel * a.G;
     const int nb = position_of(a.qpos, sel, a.NB);
     const size_t off = (size_t)(pb * a.o_bs) + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * a.D + d4 * 4;
-    if (a.bf16) {
-        typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
-        bf16x4 w;
-        w[0] = (__bf16)(acc.x * inv);
-        w[1] = (__bf16)(acc.y * inv);
-        w[2] = (__bf16)(acc.z * inv);
-        w[3] = (__bf16)(acc.w * inv);
-        *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(a.out) + off) = w;
-    } else {
-        *reinterpret_cast<float4*>(static_cast<float*>(a.out) + off) =
-            make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
-    }
+    *reinterpret_cast<float4*>(a.out + off) =
+        make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
 }
 
 }  // namespace
+
+template <int D>
+static hipError_t launch(const Args& a, hipStream_t s)
+{
+    const auto kern = &attn_f32_kernel<D>;
+    // the LDS limit of this instantiation is raised once per device (bit d of `done`: device d)
+    static std::atomic<uint64_t> done{0};
+    int dev = 0;
+    if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
+    const uint64_t bit = 1ull << (dev & 63);
+    if (!(done.load(std::memory_order_acquire) & bit)) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           F32Cfg<D>::LDS_BYTES);
+        if (e != hipSuccess) return e;
+        done.fetch_or(bit, std::memory_order_release);
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.per_xcd * kNumXCD)), dim3(THREADS), F32Cfg<D>::LDS_BYTES, s, a);
+    return hipGetLastError();
+}
 
 hipError_t launch_attn_f32(const fdd_attn_params& p, const AttnPlan& plan, float scale, hipStream_t s)
 {
@@ -409,19 +550,27 @@ hipError_t launch_attn_f32(const fdd_attn_params& p, const AttnPlan& plan, float
     a.ek = static_cast<const float*>(p.ext_k);
     a.ev = static_cast<const float*>(p.ext_v);
     a.E = p.E; a.Ecap = p.ext_capacity;
-    a.batch = p.batch > 1 ? p.batch : 1;
+    const int batch = p.batch > 1 ? p.batch : 1;
     a.q_bs = p.q_batch_stride; a.p_bs = p.prefix_batch_stride; a.b_bs = p.block_batch_stride;
     a.e_bs = p.ext_batch_stride; a.o_bs = p.out_batch_stride;
     a.N = p.N; a.B = p.B; a.L = p.L; a.Hq = p.Hq; a.Hkv = p.Hkv;
-    a.G = plan.G; a.R = plan.R; a.MT = plan.MT; a.TP = plan.TP; a.S = plan.splits;
+    a.G = plan.G; a.R = plan.R; a.MT = plan.MT; a.S = plan.splits;
+    a.W = p.Hkv * batch * plan.MT * plan.splits;
+    a.per_xcd = (a.W + kNumXCD - 1) / kNumXCD;
     a.c = scale * 1.4426950408889634f;
     a.causal = (p.flags & FDD_ATTN_CAUSAL_BLOCK) ? 1 : 0;
     a.qpos = p.n_q_positions > 0 ? p.q_positions : nullptr;
-    if (plan.mtile_rows != RT) return hipErrorInvalidValue;
-    const dim3 grid(plan.MT, plan.splits, p.Hkv * a.batch);
-    if (p.D == 128) hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(THREADS), 0, s, a);
-    else hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(THREADS), 0, s, a);
-    return hipGetLastError();
+    a.ext_per = (p.E + KT - 1) / KT;
+    a.per = a.ext_per + (p.B + KT - 1) / KT;
+    a.dMT = make_fastdiv((uint32_t)a.MT);
+    a.dS = make_fastdiv((uint32_t)a.S);
+    a.dHkv = make_fastdiv((uint32_t)a.Hkv);
+    a.dG = make_fastdiv((uint32_t)a.G);
+    a.dB = make_fastdiv((uint32_t)a.B);
+    a.dPer = make_fastdiv((uint32_t)a.per);
+    a.dParts = make_fastdiv((uint32_t)(a.S * WAVES));
+    if (plan.mtile_rows != RT || plan.key_tile != KT) return hipErrorInvalidValue;
+    return p.D == 128 ? launch<128>(a, s) : launch<64>(a, s);
 }
 
 hipError_t launch_attn_combine(const fdd_attn_params& p, const AttnPlan& plan, float scale, hipStream_t s)
@@ -429,27 +578,22 @@ hipError_t launch_attn_combine(const fdd_attn_params& p, const AttnPlan& plan, f
     CombineArgs a;
     a.ws_o = static_cast<const float*>(p.workspace);
     a.ws_ml = reinterpret_cast<const float*>(static_cast<const char*>(p.workspace) + plan.ws_o_bytes);
-    a.out = p.out;
+    a.out = static_cast<float*>(p.out);
     const int batch = p.batch > 1 ? p.batch : 1;
     a.Hq = p.Hq; a.Hkv = p.Hkv; a.G = plan.G; a.R = plan.R; a.MT = plan.MT;
     a.o_bs = p.out_batch_stride;
     a.qpos = p.n_q_positions > 0 ? p.q_positions : nullptr;
     a.NB = p.N * p.B;
-    a.mrows = plan.mtile_rows; a.D = p.D; a.bf16 = (p.dtype == FDD_BF16);
-    a.max_seg = plan.max_seg;
-    a.fixed_seg = a.bf16 ? plan.uniform : plan.splits;
-    a.TPU = plan.TPU;
-    a.base = a.bf16 ? (int)(plan.U / plan.W) : 1;
-    a.rem = a.bf16 ? (int)(plan.U % plan.W) : 0;
+    a.mrows = plan.mtile_rows; a.D = p.D;
+    a.n_seg = plan.splits;
     a.c = scale * 1.4426950408889634f;
     // more threads per row when the rows are few and the segments many
     const long long rows = (long long)p.Hkv * batch * plan.R;
-    const int seg_hint = a.fixed_seg > 0 ? a.fixed_seg : plan.max_seg;
     int sg = 1;
-    while (sg < 8 && sg * 2 <= seg_hint && rows * sg < 16384) sg *= 2;
+    while (sg < 8 && sg * 2 <= plan.splits && rows * sg < 16384) sg *= 2;
     a.SG = sg;
     a.RB = 256 / (sg * (p.D / 4));
-    const size_t smem = (size_t)((2 * a.RB * plan.max_seg + 3) & ~3) * sizeof(float) + (size_t)a.RB * sg * (p.D / 4) * sizeof(float4) +
+    const size_t smem = (size_t)((2 * a.RB * plan.splits + 3) & ~3) * sizeof(float) + (size_t)a.RB * sg * (p.D / 4) * sizeof(float4) +
                         (size_t)a.RB * sg * sizeof(float);
     if (smem > 60 * 1024) return hipErrorInvalidValue;
     const dim3 grid(p.Hkv * batch * plan.MT, (plan.mtile_rows + a.RB - 1) / a.RB);

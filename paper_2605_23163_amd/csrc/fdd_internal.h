@@ -22,12 +22,17 @@ constexpr int kNumXCD = 8;
 // M-tile is processed in one or more segments; segment `seg` of M-tile M
 // leaves a partial (m, l, o[D]) in slot M*max_seg + seg of the workspace
 // unless it is the M-tile's only segment.
-//   fp32 path : `splits` equal pieces per M-tile, one workgroup each.
+//   fp32 path : `splits` workgroups per M-tile, each of them kF32Waves
+//               wavefronts; the key tiles (prefix and private ones) are cut
+//               into splits * kF32Waves equal runs, one per wavefront.
 //   bf16 path : the unit is one key tile of one M-tile (TPU units per M-tile,
 //               U in total).  Either every M-tile is cut into `uniform` equal
 //               pieces, piece s covering tiles [TPU s / S, TPU (s+1) / S), or
 //               (stream-K) workgroup w of W owns the contiguous unit range
 //               [unit_begin(w), unit_begin(w+1)), which may cross M-tiles.
+constexpr int kF32RowTile = 32;    // fp32 path: stacked rows per workgroup
+constexpr int kF32Waves = 8;       // fp32 path: wavefronts per workgroup
+
 struct AttnPlan {
     int G;            // query heads per KV head
     int R;            // stacked rows per KV head
@@ -35,7 +40,7 @@ struct AttnPlan {
     int MT;           // M-tiles per KV head
     int key_tile;     // keys per streamed tile
     int TP;           // prefix tiles = ceil(L / key_tile)
-    int splits;       // fp32 path: pieces along L
+    int splits;       // fp32 path: workgroups per M-tile
     int TPU;          // bf16 path: units per M-tile = max(TP, 1)
     int W;            // bf16 path: workgroups
     int uniform;      // bf16 path: > 0 when W = Hkv*MT*uniform, i.e. equal pieces per M-tile
