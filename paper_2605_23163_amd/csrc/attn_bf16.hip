@@ -588,6 +588,11 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
                 for (int ks = 0; ks < KS; ++ks)
                     sa[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(0, kb, ks), qf[ks], sa[kb], 0, 0, 0);
             }
+            // Step 0 requests K of tile 4 into the slot that the scores above were read from: no wavefront may get
+            // there while another one is still reading.  (They can be far apart here: the first workgroups of a
+            // launch fetch these instructions from memory.)
+            FDD_SCHED_FENCE();
+            wg_barrier();
 
             // One pipelined step: probabilities and P V of tile i from s_cur while
             // the scores of tile i+1 go to s_nxt; K of tile i+4 and V of tile i+3 are requested.
