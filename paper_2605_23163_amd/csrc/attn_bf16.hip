@@ -159,7 +159,7 @@ __device__ __forceinline__ float other_half(float x)
     const unsigned u = __builtin_bit_cast(unsigned, x);
     // swaps lanes 32..63 of the first operand with lanes 0..31 of the second
     const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __builtin_bit_cast(float, (threadIdx.x & 32) ? r[0] : r[1]);
+    return __builtin_bit_cast(float, (thread_id_x() & 32) ? r[0] : r[1]);
 }
 
 // Wait until at most N of this wavefront's vector memory operations are
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
     extern __shared__ __align__(16) unsigned char lds[];
     typedef __attribute__((address_space(3))) void lds_void;
 
-    const int tid = threadIdx.x;
+    const int tid = thread_id_x();
     const int wave = tid >> 6;
     const int lane = tid & 63;
     const int l32 = lane & 31;
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
     // ---- this workgroup's share of the (M-tile, prefix tile) units ------------
     // Workgroups are dealt to the 8 XCDs round-robin by their launch index;
     // ranges are numbered so that the workgroups of one XCD own neighbours.
-    int wg = (int)(blockIdx.x % kNumXCD) * a.per_xcd + (int)(blockIdx.x / kNumXCD);
+    int wg = (int)(wg_id_x() % kNumXCD) * a.per_xcd + (int)(wg_id_x() / kNumXCD);
     if (wg >= a.W) return;
     int M, t_begin, todo, piece = 0;
     if (a.S > 0) {
@@ -246,15 +246,11 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
         } else {
             // The share of a piece follows the speed of the XCD it runs on (measured: the odd XCD of a
             // pair streams the same tiles a few per cent slower).  Every piece of the M-tile works out
-            // the same boundaries: unit TPU * (weights before it) / (all weights).
-            int cum = 0, lo = 0, hi = 0;
-            for (int p = 0; p < a.S; ++p) {
-                const int x = fast_div((khv_ * a.S + p) * a.MT + mt_, a.dPerXcd);
-                const int wgt = (x & 1) ? a.w_odd : a.w_even;
-                lo = p == piece ? cum : lo;
-                cum += wgt;
-                hi = p == piece ? cum : hi;
-            }
+            // the same boundaries: unit TPU * (weights before it) / (all weights).  Lane p looks at piece p (S <= 16).
+            const int x = fast_div((khv_ * a.S + min(lane, a.S - 1)) * a.MT + mt_, a.dPerXcd);
+            const unsigned odd = (unsigned)__builtin_amdgcn_ballot_w64(lane < a.S && (x & 1));
+            auto weight = [&](int n) { return n * a.w_even - __builtin_popcount(odd & ((1u << n) - 1u)) * (a.w_even - a.w_odd); };
+            const int lo = weight(piece), hi = weight(piece + 1), cum = weight(a.S);
             t_begin = (a.TPU * lo) / cum;
             todo = (a.TPU * hi) / cum - t_begin;
         }
@@ -267,30 +263,9 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
 
     // ---- per-lane constants of the tile movement and of the fragment reads ------
     const uint32_t stride2 = (uint32_t)(a.Hkv * D * 2);       // bytes between consecutive keys
-    // K fragment of k-step ks: row l32 of a 32-key block, 16-byte piece (2 ks + half)
-    // at its swizzled place, which is the place of k-step 0 with ks XORed in
-    const uint32_t k_fragoff0 = (uint32_t)(l32 * D * 2 + ((((l32 / C::RPL) & (C::CH - 1)) ^ half) << 4));
+    // LDS offsets of this lane's fragments (set while the first tiles of a segment are on their way)
     uint32_t k_fragoff[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k_fragoff[ks] = k_fragoff0 ^ (uint32_t)(ks << 5);
-    // packed V^T: [16-key step][half][d][8 keys]; the ring's offset is part of the register
-    // because the offset field of an LDS read ends at 64 KB
-    uint32_t v_fragoff_ring = (uint32_t)(C::V_RING + half * (D * 16) + l32 * 16);
-    FDD_PIN(v_fragoff_ring);
-    // Unpacked V, transposing reads.  In a 16-lane group, lane 4j+q points at 4
-    // channels of key row j; the read returns to lane i the 4 keys of channel i.
-    // Element e of the assembled fragment is key 16 t4 + 8 (e/4) + 4 half + e%4,
-    // the key order of the probabilities in the S^T accumulator.  Channel block
-    // db sits at the swizzled place of block 0 with db XORed in.
-    uint32_t vtr_off0;
-    {
-        const int row_l = half * 4 + ((lane & 15) >> 2);
-        const int x = ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
-        const int sw = (((row_l / C::RPL) & 3) << 2) & (C::CH - 1);
-        vtr_off0 = (uint32_t)(row_l * D * 2 + ((x ^ sw) << 4) + (lane & 1) * 8);
-    }
-    uint32_t vtr_off_ring = C::V_RING + vtr_off0;
-    FDD_PIN(vtr_off_ring);
+    uint32_t v_fragoff_ring, vtr_off0, vtr_off_ring;
     // Tile movement: piece jn of this wavefront covers rows (wave NI + jn) RPB .. of
     // a tile; this lane moves the 16 bytes that land at LDS piece (lane % CH) of
     // its row.  K: the pieces of a row are XOR-swizzled by the row's bank line.
@@ -421,6 +396,31 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
         FDD_SCHED_FENCE();
 
         // ---- the rest of the set-up ------------------------------------------------
+        {
+            int lane_f = lane;
+            FDD_PIN(lane_f);      // (computed here, not ahead of the requests)
+            const int l32 = lane_f & 31, half = lane_f >> 5;
+            // K fragment of k-step ks: row l32 of a 32-key block, 16-byte piece (2 ks + half)
+            // at its swizzled place, which is the place of k-step 0 with ks XORed in
+            const uint32_t k_fragoff0 = (uint32_t)(l32 * D * 2 + ((((l32 / C::RPL) & (C::CH - 1)) ^ half) << 4));
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) k_fragoff[ks] = k_fragoff0 ^ (uint32_t)(ks << 5);
+            // packed V^T: [16-key step][half][d][8 keys]; the ring's offset is part of the register
+            // because the offset field of an LDS read ends at 64 KB
+            v_fragoff_ring = (uint32_t)(C::V_RING + half * (D * 16) + l32 * 16);
+            FDD_PIN(v_fragoff_ring);
+            // Unpacked V, transposing reads.  In a 16-lane group, lane 4j+q points at 4
+            // channels of key row j; the read returns to lane i the 4 keys of channel i.
+            // Element e of the assembled fragment is key 16 t4 + 8 (e/4) + 4 half + e%4,
+            // the key order of the probabilities in the S^T accumulator.  Channel block
+            // db sits at the swizzled place of block 0 with db XORed in.
+            const int row_l = half * 4 + ((lane_f & 15) >> 2);
+            const int x = ((lane_f >> 4) & 1) * 2 + ((lane_f & 3) >> 1);
+            const int sw = (((row_l / C::RPL) & 3) << 2) & (C::CH - 1);
+            vtr_off0 = (uint32_t)(row_l * D * 2 + ((x ^ sw) << 4) + (lane_f & 1) * 8);
+            vtr_off_ring = C::V_RING + vtr_off0;
+            FDD_PIN(vtr_off_ring);
+        }
         int n_seg, seg;
         if (a.S > 0) {
             n_seg = a.S;
@@ -860,10 +860,10 @@ __global__ __launch_bounds__(512) void vt_pack_kernel(const uint16_t* __restrict
     constexpr int DB = D / 32;
     __shared__ __align__(16) unsigned char tile[C::V_BYTES];
     // grid (tile, KV head of a problem of the batch)
-    const int t = blockIdx.x, pb = blockIdx.y / Hkv, kh = blockIdx.y - pb * Hkv;
+    const int t = wg_id_x(), pb = wg_id_y() / Hkv, kh = wg_id_y() - pb * Hkv;
     const uint16_t* pv = pv_all + pb * p_bs;
     uint16_t* vt = vt_all + pb * vt_bs;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int tid = thread_id_x(), wave = tid >> 6, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const size_t kv_stride = (size_t)Hkv * D;
     const uint16_t* src = pv + (size_t)t * KT * kv_stride + (size_t)kh * D;
 #pragma unroll
@@ -915,8 +915,8 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
     constexpr int CPW = 2 * DB * 64;          // 16-byte chunks per wavefront of the attention kernel
     constexpr int CH = 8 * CPW;               // chunks per M-tile and segment
     extern __shared__ __align__(16) float smem[];
-    const int tid = (int)threadIdx.x;
-    const int M = (int)blockIdx.x;
+    const int tid = (int)thread_id_x();
+    const int M = (int)wg_id_x();
     int n_seg = a.fixed_seg;
     if (n_seg == 0)     // same arithmetic as the attention kernel: workgroups whose unit range meets this M-tile
         n_seg = wg_of_unit((M + 1) * a.TPU - 1, a.base, a.rem) - wg_of_unit(M * a.TPU, a.base, a.rem) + 1;
@@ -924,7 +924,7 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
     const int khv = M / a.MT, mt = M - khv * a.MT;      // (problem of the batch, KV head), M-tile
     const int pb = khv / a.Hkv, kh = khv - pb * a.Hkv;
     const int CPB = 256 / a.SG;               // chunks per block: 32 .. 256, all of one wavefront (32 rows)
-    const int c0 = (int)blockIdx.y * CPB;
+    const int c0 = (int)wg_id_y() * CPB;
     const int wave = c0 / CPW;
     const int row0 = mt * 256 + wave * 32;    // first stacked row of the block's 32 rows
     if (row0 >= a.R) return;

@@ -97,13 +97,13 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
 
     // workgroups are dealt to the 8 XCDs round-robin: those of one XCD own neighbouring row tiles of one
     // (KV head, split), which walk the same keys
-    const int wg = (int)(blockIdx.x % kNumXCD) * a.per_xcd + (int)(blockIdx.x / kNumXCD);
+    const int wg = (int)(wg_id_x() % kNumXCD) * a.per_xcd + (int)(wg_id_x() / kNumXCD);
     if (wg >= a.W) return;
     const int rest = fast_div(wg, a.dMT), mt = wg - rest * a.MT;
     const int khv = fast_div(rest, a.dS), split = rest - khv * a.S;
     const int pb = fast_div(khv, a.dHkv), kh = khv - pb * a.Hkv;     // problem of the batch, KV head
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = thread_id_x(), lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c16 = lane & 15, g4 = lane >> 4;
     const int NB = a.N * a.B;
@@ -391,12 +391,12 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a)
 {
     extern __shared__ __align__(16) float smem[];
     const int d4n = a.D / 4;
-    const int tid = (int)threadIdx.x;
+    const int tid = (int)thread_id_x();
     const int d4 = tid % d4n, sg = (tid / d4n) % a.SG, r = tid / (d4n * a.SG);
-    const int M = (int)blockIdx.x;
+    const int M = (int)wg_id_x();
     const int khv = M / a.MT, mt = M - khv * a.MT;      // (problem of the batch, KV head), M-tile
     const int pb = khv / a.Hkv, kh = khv - pb * a.Hkv;
-    const int rit0 = (int)blockIdx.y * a.RB;
+    const int rit0 = (int)wg_id_y() * a.RB;
     const int n_seg = a.n_seg;
     if (a.SG == 1 && n_seg <= 4) {
         // few segments: every thread reads the (m, l) pairs of its row itself, together with its

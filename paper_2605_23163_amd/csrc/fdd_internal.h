@@ -9,6 +9,16 @@
 
 namespace fdd {
 
+// Thread and workgroup index, high half of a 32 x 32 bit product.  threadIdx, blockIdx, gridDim and __umulhi go through
+// functions of the device library that were compiled for another floating-point mode than the files built with
+// -mno-amdgpu-ieee, and the compiler does not inline across that difference: each use is a call (a cold one at the top
+// of every workgroup), its result is not known to be the same in all lanes, and the sampler made 40 calls per four
+// entries.  The builtins are single registers and instructions.
+__device__ __forceinline__ int thread_id_x() { return (int)__builtin_amdgcn_workitem_id_x(); }
+__device__ __forceinline__ unsigned wg_id_x() { return __builtin_amdgcn_workgroup_id_x(); }
+__device__ __forceinline__ unsigned wg_id_y() { return __builtin_amdgcn_workgroup_id_y(); }
+__device__ __forceinline__ uint32_t mul_hi(uint32_t a, uint32_t b) { return (uint32_t)(((uint64_t)a * b) >> 32); }
+
 // MI355X has 256 compute units in 8 XCDs; grid-shape heuristics are sized
 // for that chip and do not query the device, so that workspace sizes are a
 // pure function of the problem shape.

@@ -27,6 +27,8 @@
 //                 position in a fixed order (sum finished in fp64), applies
 //                 the tau test and the forced single commit, and writes
 //                 tokens / mask / confidences.
+#include <algorithm>
+
 #include "fdd_internal.h"
 
 namespace fdd {
@@ -64,6 +66,9 @@ struct Args {
     u32x4* rf_bv;
     int rf_T, rf_row_vecs;  // table rows; 16-byte pieces per K/V row (0: no refresh)
     int N, B, vsplits;
+    int units;              // workgroups of a vocabulary pass: N B vsplits
+    int per;                // vocabulary entries per piece (the last pieces of a row may be shorter or empty)
+    FastDiv dVs;            // division by vsplits
     long long V;
     float tau;
     float c;                // sampled verifier: log2(e) / temperature
@@ -149,10 +154,10 @@ __device__ __forceinline__ float bf16_to_f32(uint32_t bits16) { return __uint_as
 // consecutive indices is rotated, by an amount that changes from group to group, from 8 groups to the
 // next 8 and from 64 to the next 64 (a rotation by the group's number alone repeats with the pattern:
 // config 5's 720 eligible rows of 4 pieces then give the XCDs 304..416 workgroups instead of 360 each).
-__device__ __forceinline__ unsigned unit_of_workgroup()
+__device__ __forceinline__ unsigned unit_of_workgroup(unsigned n_units)
 {
-    const unsigned u = blockIdx.x, g = u >> 3;
-    if ((g << 3) + 8u > gridDim.x) return u;           // a last, incomplete group stays as it is
+    const unsigned u = wg_id_x(), g = u >> 3;
+    if ((g << 3) + 8u > n_units) return u;           // a last, incomplete group stays as it is
     return (g << 3) + ((u + g + (g >> 3) + (g >> 6) + (g >> 9)) & 7u);
 }
 
@@ -161,15 +166,14 @@ template <typename T, bool SUM>
 __global__ __launch_bounds__(RTHREADS) void vocab_reduce_kernel(Args a)
 {
     constexpr int VEC = 16 / sizeof(T);
-    const unsigned unit = unit_of_workgroup();
-    const int row = unit / a.vsplits;
+    const unsigned unit = unit_of_workgroup((unsigned)a.units);
+    const int row = fast_div((int)unit, a.dVs);
     if (a.mask[row] != 1 || (a.scaffold && a.scaffold[row])) return;
-    const int piece = unit % a.vsplits;
-    const long long per = (a.V + a.vsplits - 1) / a.vsplits;
-    const long long v_lo = piece * per;
-    const long long v_hi = min(a.V, v_lo + per);
+    const int piece = (int)unit - row * a.vsplits;
+    const long long v_lo = (long long)piece * a.per;
+    const long long v_hi = min(a.V, v_lo + a.per);
     const T* base = static_cast<const T*>(a.logits) + (size_t)row * (size_t)a.V;
-    const int tid = threadIdx.x;
+    const int tid = thread_id_x();
 
     ThreadRun tr;
     tr.r.m = -INFINITY;
@@ -284,8 +288,8 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
     uint32_t c2 = 0u, c3 = 0u;
 #pragma unroll
     for (int round = 0; round < 10; ++round) {
-        const uint32_t hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
-        const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
+        const uint32_t hi0 = mul_hi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
+        const uint32_t hi1 = mul_hi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
         c0 = hi1 ^ c1 ^ k0;
         c1 = lo1;
         c2 = hi0 ^ c3 ^ k1;
@@ -338,15 +342,14 @@ template <typename T>
 __global__ __launch_bounds__(RTHREADS) void vocab_sample_kernel(Args a)
 {
     constexpr int VEC = 16 / sizeof(T);
-    const unsigned unit = unit_of_workgroup();
-    const int row = unit / a.vsplits;
+    const unsigned unit = unit_of_workgroup((unsigned)a.units);
+    const int row = fast_div((int)unit, a.dVs);
     if (a.mask[row] != 1 || (a.scaffold && a.scaffold[row])) return;
-    const int piece = unit % a.vsplits;
-    const long long per = (a.V + a.vsplits - 1) / a.vsplits;
-    const long long v_lo = piece * per;
-    const long long v_hi = min(a.V, v_lo + per);
+    const int piece = (int)unit - row * a.vsplits;
+    const long long v_lo = (long long)piece * a.per;
+    const long long v_hi = min(a.V, v_lo + a.per);
     const T* base = static_cast<const T*>(a.logits) + (size_t)row * (size_t)a.V;
-    const int tid = threadIdx.x;
+    const int tid = thread_id_x();
     Best r;
     r.k = -INFINITY;
     r.idx = 0x7fffffff;
@@ -430,8 +433,8 @@ constexpr int STHREADS = 64;   // one wavefront per rollout: no LDS, no workgrou
 
 __global__ __launch_bounds__(STHREADS) void block_select_kernel(Args a)
 {
-    const int n = blockIdx.x;
-    const int tid = threadIdx.x;
+    const int n = wg_id_x();
+    const int tid = thread_id_x();
     const double tau = (double)a.tau;
 
     int count = 0;
@@ -544,8 +547,8 @@ __global__ __launch_bounds__(STHREADS) void block_select_kernel(Args a)
 // drafts are left masked.
 __global__ __launch_bounds__(STHREADS) void verify_scan_kernel(Args a)
 {
-    const int n = blockIdx.x;
-    const int tid = threadIdx.x;
+    const int n = wg_id_x();
+    const int tid = thread_id_x();
     // pass 1: position of the first mismatch, and the AR token there.  A position's records and its draft are
     // requested together with its mask bytes (one memory round trip instead of three); what was requested for
     // a position that is no draft is not used.
@@ -618,6 +621,18 @@ bool make_vocab_plan(int N, int B, long long V, int dtype, bool argmax_only, Unm
     return true;
 }
 
+// Entries per piece: a multiple of 64 (128 bytes of bf16), so that the pieces of an aligned row start on whole cache
+// lines and have no entries outside whole 16-byte vectors but the row's own last ones.
+static void set_pieces(Args& a, int vsplits, long long V)
+{
+    a.vsplits = vsplits;
+    a.units = a.N * a.B * vsplits;
+    a.V = V;
+    const long long per = (V + vsplits - 1) / vsplits;
+    a.per = (int)std::min<long long>((per + 63) / 64 * 64, V);
+    a.dVs = make_fastdiv((uint32_t)vsplits);
+}
+
 hipError_t launch_unmask(const fdd_unmask_params& p, const UnmaskPlan& plan, hipStream_t s)
 {
     Args a;
@@ -636,9 +651,10 @@ hipError_t launch_unmask(const fdd_unmask_params& p, const UnmaskPlan& plan, hip
     a.rf_bv = static_cast<u32x4*>(p.refresh_block_v);
     a.rf_T = p.refresh_T;
     a.rf_row_vecs = p.refresh_block_k ? (int)((size_t)p.refresh_Hkv * p.refresh_D * (p.refresh_dtype == FDD_BF16 ? 2 : 4) / 16) : 0;
-    a.N = p.N; a.B = p.B; a.vsplits = plan.vsplits; a.V = p.V; a.tau = p.tau;
+    a.N = p.N; a.B = p.B; a.tau = p.tau;
+    set_pieces(a, plan.vsplits, p.V);
     a.c = 0.f; a.seed_lo = 0u; a.seed_hi = 0u;
-    const dim3 grid((unsigned)(plan.vsplits * p.N * p.B));
+    const dim3 grid((unsigned)a.units);
     if (p.dtype == FDD_BF16) hipLaunchKernelGGL((vocab_reduce_kernel<uint16_t, true>), grid, dim3(RTHREADS), 0, s, a);
     else hipLaunchKernelGGL((vocab_reduce_kernel<float, true>), grid, dim3(RTHREADS), 0, s, a);
     hipError_t e = hipGetLastError();
@@ -660,11 +676,12 @@ hipError_t launch_verify(const fdd_verify_params& p, const UnmaskPlan& plan, hip
     a.ws = static_cast<Partial*>(p.workspace);
     a.draft = p.draft;
     a.rf_tk = nullptr; a.rf_tv = nullptr; a.rf_bk = nullptr; a.rf_bv = nullptr; a.rf_T = 0; a.rf_row_vecs = 0;
-    a.N = p.N; a.B = p.B; a.vsplits = plan.vsplits; a.V = p.V; a.tau = 0.f;
+    a.N = p.N; a.B = p.B; a.tau = 0.f;
+    set_pieces(a, plan.vsplits, p.V);
     a.c = p.temperature > 0.f ? (float)(1.4426950408889634 / (double)p.temperature) : 0.f;
     a.seed_lo = (uint32_t)p.seed;
     a.seed_hi = (uint32_t)(p.seed >> 32);
-    const dim3 grid((unsigned)(plan.vsplits * p.N * p.B));
+    const dim3 grid((unsigned)a.units);
     if (p.temperature > 0.f) {
         if (p.dtype == FDD_BF16) hipLaunchKernelGGL(vocab_sample_kernel<uint16_t>, grid, dim3(RTHREADS), 0, s, a);
         else hipLaunchKernelGGL(vocab_sample_kernel<float>, grid, dim3(RTHREADS), 0, s, a);
