@@ -21,8 +21,8 @@
 //   vocab_sample  the sampled verifier's sibling of vocab_reduce: the value
 //                 reduced is the Gumbel-max key of every vocabulary entry
 //                 (a Philox-4x32-10 word per entry, two polynomial log2, one
-//                 fused multiply-add), so the pass is bound by the vector ALUs
-//                 rather than by HBM.
+//                 fused multiply-add), worked out only where a cheap upper bound
+//                 of it reaches the largest key met so far.
 //   block_select  one workgroup per rollout: merges the pieces of each
 //                 position in a fixed order (sum finished in fp64), applies
 //                 the tau test and the forced single commit, and writes
@@ -337,11 +337,39 @@ __device__ __forceinline__ void take(Best& a, float k, int idx)
     if (k > a.k || (k == a.k && idx < a.idx)) { a.k = k; a.idx = idx; }
 }
 
+// Upper bound of the noise of generator word r, for a fifth of its cost.  With w = 2^23 - 1/2 - (r >> 9) the uniform is
+// u = 1 - w 2^-23, and -log2 u >= (1 - u) log2 e, so the noise -log2(-log2 u) is at most 23 - log2(log2 e) - log2 w;
+// log2 w in turn is at least exponent + mantissa fraction, i.e. the bits of the float w read as a fixed-point number.
+// The slack added to the constant (1e-3) is a hundred times what flog2_def and the roundings here are off by; the bound
+// exceeds the noise by 0.09 at most for u > 1/2 (the entries that can win), by more below.  fma is monotonic, so
+// fma(x, c, noise_bound(r)) is never below the entry's key.
+constexpr float NOISE_C = 149.47223f;          // 23 + 127 - log2(log2 e) + 1e-3
+constexpr float NOISE_MAX = 23.47223f;         // the bound at its largest (r >> 9 = 2^23 - 1)
+__device__ __forceinline__ float noise_bound(uint32_t r)
+{
+    const float w = (float)(~r >> 9) + 0.5f;
+    return fmaf((float)__float_as_uint(w), -1.1920928955078125e-07f, NOISE_C);
+}
+
+constexpr int VUNROLL = 5;       // sampled verifier: 16-byte loads in flight per thread
+
 // Same work split as vocab_reduce; leaves (largest key, lowest id attaining it) per piece.
-template <typename T>
-__global__ __launch_bounds__(RTHREADS) void vocab_sample_kernel(Args a)
+// Bound by the vector ALUs: the definition of a key takes 64 operations per entry (20 of them the generator, 40 the two
+// logarithms), but only entries that can still win need theirs.  The key of the drafted token (the verifier mostly
+// agrees with it) and any key a thread of the workgroup has worked out in full are lower bounds of the row's largest: an
+// entry whose own upper bound lies below them is dropped, first by its logit alone (no generator word drawn: rows with a
+// clear winner end here), then with the bound above in place of the logarithms.  What is left (a few entries per
+// wavefront) is worked out as defined, and the row's winner is never dropped, so the verifier's token is the same bit for
+// bit.
+// Measured, bf16, 70 % of the rows live, V = 152064 (in brackets every entry worked out in full): N=8, B=32 33 us (87) with
+// a clear winner in 4 of 5 rows, 43 (87) with none; N=16, B=64 71 (231) and 117 (230); N=5, B=40, V=50001 26 (211: rows
+// that start inside a generator block took a block per entry).  Without a winner the generator's 32 x 32 bit products
+// are what is left.
+template <typename T, int VTHREADS>
+__global__ __launch_bounds__(VTHREADS) void vocab_sample_kernel(Args a)
 {
     constexpr int VEC = 16 / sizeof(T);
+    constexpr int NW = VEC + 4;               // generator words that cover VEC entries starting anywhere
     const unsigned unit = unit_of_workgroup((unsigned)a.units);
     const int row = fast_div((int)unit, a.dVs);
     if (a.mask[row] != 1 || (a.scaffold && a.scaffold[row])) return;
@@ -354,58 +382,118 @@ __global__ __launch_bounds__(RTHREADS) void vocab_sample_kernel(Args a)
     r.k = -INFINITY;
     r.idx = 0x7fffffff;
 
-    auto one = [&](long long v) {     // a single entry: its own generator block
-        const float x = sizeof(T) == 2 ? bf16_to_f32(((const uint16_t*)base)[v]) : ((const float*)base)[v];
+    // largest key worked out by any thread of the workgroup so far, as an integer of the same order
+    __shared__ int s_floor;
+    auto ordered = [](float k) { const int b = __float_as_int(k); return b ^ ((b >> 31) & 0x7fffffff); };
+    auto from_ordered = [](int o) { return __int_as_float(o ^ ((o >> 31) & 0x7fffffff)); };
+    if (tid == 0) s_floor = ordered(-INFINITY);
+    __syncthreads();
+
+    auto logit = [&](long long v) { return sizeof(T) == 2 ? bf16_to_f32(((const uint16_t*)base)[v]) : ((const float*)base)[v]; };
+    auto key_of = [&](float x, long long v) {     // a single entry: its own generator block
         uint32_t w[4];
         philox4x32_10((uint32_t)(v >> 2), (uint32_t)row, a.seed_lo, a.seed_hi, w);
-        take(r, gumbel_key(x, a.c, w[v & 3]), (int)v);
+        const uint32_t lo = (v & 1) ? w[1] : w[0], hi = (v & 1) ? w[3] : w[2];
+        return gumbel_key(x, a.c, (v & 2) ? hi : lo);
+    };
+    auto one = [&](long long v) { take(r, key_of(logit(v), v), (int)v); };
+    // the drafted token's logit is requested first: its key is a lower bound for every piece of the row
+    const int d = a.draft[row];
+    const bool d_ok = d >= 0 && d < a.V;
+    const float x_d = d_ok ? logit(d) : -INFINITY;
+    // the wavefront's largest key so far joins the workgroup's
+    auto publish = [&]() {
+        float k = r.k;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) k = fmaxf(k, __shfl_xor(k, off, 64));
+        if ((tid & 63) == 0) atomicMax(&s_floor, ordered(k));
+        return k;
     };
     if (v_lo < v_hi) {
         const size_t e_lo = (size_t)row * (size_t)a.V + (size_t)v_lo;
-        long long head = (long long)((VEC - (e_lo % VEC)) % VEC);
-        if (head > v_hi - v_lo) head = v_hi - v_lo;
+        int head = (int)((VEC - (e_lo % VEC)) % VEC);
+        if (head > v_hi - v_lo) head = (int)(v_hi - v_lo);
         const long long body0 = v_lo + head;
-        const long long nvec = (v_hi - body0) / VEC;
-        const long long tail0 = body0 + nvec * VEC;
-        if (tid < head) one(v_lo + tid);
+        const int nvec = (int)((v_hi - body0) / VEC);
+        const long long tail0 = body0 + (long long)nvec * VEC;
         const u32x4* vp = reinterpret_cast<const u32x4*>(base + body0);
-        const bool quads = (body0 & 3) == 0;      // a 16-byte vector then holds whole generator blocks
-        for (long long i = tid; i < nvec; i += RTHREADS) {
-            const u32x4 raw = __builtin_nontemporal_load(vp + i);
-            const long long v0 = body0 + i * VEC;
-            float x[VEC];
-            if (sizeof(T) == 2) {
-                const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+        const int shift = (int)(body0 & 3);       // place of a vector's first entry in its generator block (the same for all)
+
+        float floor = -INFINITY;                  // lower bound of the row's largest key, as far as the wavefront knows
+        for (int i0 = 0; i0 < nvec; i0 += VUNROLL * VTHREADS) {
+            u32x4 raw[VUNROLL];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    x[2 * j] = __uint_as_float(w[j] << 16);
-                    x[(2 * j + 1) % VEC] = __uint_as_float(w[j] & 0xffff0000u);
-                }
-            } else {
-                x[0] = __uint_as_float(raw.x);
-                x[1] = __uint_as_float(raw.y);
-                x[2 % VEC] = __uint_as_float(raw.z);
-                x[3 % VEC] = __uint_as_float(raw.w);
+            for (int u = 0; u < VUNROLL; ++u) {
+                const int i = i0 + u * VTHREADS + tid;
+                raw[u] = __builtin_nontemporal_load(vp + min(i, nvec - 1));    // (a repeated vector changes nothing)
             }
-            if (quads) {
+            __builtin_amdgcn_sched_barrier(0);    // all requested before the first is waited for
+            if (i0 == 0) {
+                // a first lower bound: every thread's largest logit of this group, with its noise
+                float xm = -INFINITY;
+                int at = 0;
 #pragma unroll
-                for (int q = 0; q < VEC / 4; ++q) {
-                    uint32_t w[4];
-                    philox4x32_10((uint32_t)((v0 >> 2) + q), (uint32_t)row, a.seed_lo, a.seed_hi, w);
+                for (int u = 0; u < VUNROLL; ++u) {
+                    const uint32_t q[4] = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) take(r, gumbel_key(x[q * 4 + j], a.c, w[j]), (int)(v0 + q * 4 + j));
+                    for (int j = 0; j < VEC; ++j) {
+                        const float x = sizeof(T) == 4 ? __uint_as_float(q[j % 4])
+                                      : (j & 1) ? __uint_as_float(q[j / 2] & 0xffff0000u) : __uint_as_float(q[j / 2] << 16);
+                        if (x > xm) { xm = x; at = u * 8 + j; }
+                    }
                 }
-            } else {
+                const long long v = body0 + (long long)min((at >> 3) * VTHREADS + tid, nvec - 1) * VEC + (at & 7);
+                take(r, key_of(xm, v), (int)v);
+                floor = publish();
+                if (d_ok) floor = fmaxf(floor, key_of(x_d, d));
+            }
+#pragma unroll
+            for (int u = 0; u < VUNROLL; ++u) {
+                if (i0 + u * VTHREADS >= nvec) break;
+                const int i = min(i0 + u * VTHREADS + tid, nvec - 1);
+                const long long v0 = body0 + (long long)i * VEC;
+                const uint32_t q[4] = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
+                float x[VEC];
+#pragma unroll
+                for (int j = 0; j < VEC; ++j)
+                    x[j] = sizeof(T) == 4 ? __uint_as_float(q[j % 4])
+                         : (j & 1) ? __uint_as_float(q[j / 2] & 0xffff0000u) : __uint_as_float(q[j / 2] << 16);
+                float xm = x[0];
+#pragma unroll
+                for (int j = 1; j < VEC; ++j) xm = fmaxf(xm, x[j]);
+                floor = fmaxf(floor, from_ordered(__builtin_amdgcn_readfirstlane(*(volatile int*)&s_floor)));
+                if (!__any(!(__fmaf_rn(xm, a.c, NOISE_MAX) < floor))) continue;
+
+                uint32_t w[NW];
+#pragma unroll
+                for (int b = 0; b < NW / 4; ++b) {
+                    if (b == VEC / 4 && shift == 0) break;        // (aligned: the last block is not touched)
+                    uint32_t o[4];
+                    philox4x32_10((uint32_t)(v0 >> 2) + b, (uint32_t)row, a.seed_lo, a.seed_hi, o);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) w[b * 4 + j] = o[j];
+                }
+                if (shift) {
+#pragma unroll
+                    for (int j = 0; j < VEC; ++j) w[j] = shift == 1 ? w[j + 1] : shift == 2 ? w[j + 2] : w[j + 3];
+                }
+                float kb[VEC];
+                float km = -INFINITY;
 #pragma unroll
                 for (int j = 0; j < VEC; ++j) {
-                    uint32_t w[4];
-                    philox4x32_10((uint32_t)((v0 + j) >> 2), (uint32_t)row, a.seed_lo, a.seed_hi, w);
-                    take(r, gumbel_key(x[j], a.c, w[(v0 + j) & 3]), (int)(v0 + j));
+                    kb[j] = __fmaf_rn(x[j], a.c, noise_bound(w[j]));
+                    km = j == 0 ? kb[0] : fmaxf(km, kb[j]);
                 }
+                if (!__any(!(km < floor))) continue;
+                const float before = r.k;
+#pragma unroll
+                for (int j = 0; j < VEC; ++j)
+                    if (__any(!(kb[j] < floor))) take(r, gumbel_key(x[j], a.c, w[j]), (int)(v0 + j));
+                if (__any(r.k > before)) floor = fmaxf(floor, publish());
             }
         }
-        const long long ntail = v_hi - tail0;
-        if (tid < ntail) one(tail0 + tid);
+        if (tid < head) one(v_lo + tid);
+        if (tid < v_hi - tail0) one(tail0 + tid);
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -413,13 +501,13 @@ __global__ __launch_bounds__(RTHREADS) void vocab_sample_kernel(Args a)
         const int oi = __shfl_xor(r.idx, off, 64);
         take(r, ok, oi);
     }
-    __shared__ Best part[RTHREADS / 64];
+    __shared__ Best part[VTHREADS / 64];
     if ((tid & 63) == 0) part[tid >> 6] = r;
     __syncthreads();
     if (tid == 0) {
         Best t = part[0];
 #pragma unroll
-        for (int w = 1; w < RTHREADS / 64; ++w) take(t, part[w].k, part[w].idx);
+        for (int w = 1; w < VTHREADS / 64; ++w) take(t, part[w].k, part[w].idx);
         Partial p;
         p.m = t.k;
         p.arg = t.idx;
@@ -683,8 +771,16 @@ hipError_t launch_verify(const fdd_verify_params& p, const UnmaskPlan& plan, hip
     a.seed_hi = (uint32_t)(p.seed >> 32);
     const dim3 grid((unsigned)a.units);
     if (p.temperature > 0.f) {
-        if (p.dtype == FDD_BF16) hipLaunchKernelGGL(vocab_sample_kernel<uint16_t>, grid, dim3(RTHREADS), 0, s, a);
-        else hipLaunchKernelGGL(vocab_sample_kernel<float>, grid, dim3(RTHREADS), 0, s, a);
+        // 512 threads per piece while the pieces are so few that 256 leave SIMDs empty (1024 pieces, us: 512 threads 43, 256
+        // 42; 200 pieces of 100 KB: 26 and 33), 256 where there are more (4096 pieces: 512 threads 80, 256 71)
+        const bool wide = a.units <= 1024;
+        if (p.dtype == FDD_BF16) {
+            if (wide) hipLaunchKernelGGL((vocab_sample_kernel<uint16_t, 512>), grid, dim3(512), 0, s, a);
+            else hipLaunchKernelGGL((vocab_sample_kernel<uint16_t, 256>), grid, dim3(256), 0, s, a);
+        } else {
+            if (wide) hipLaunchKernelGGL((vocab_sample_kernel<float, 512>), grid, dim3(512), 0, s, a);
+            else hipLaunchKernelGGL((vocab_sample_kernel<float, 256>), grid, dim3(256), 0, s, a);
+        }
     } else {
         // greedy verifier: step 3 of scaffold speculative decoding compares arg maxima only, so no exponentials
         if (p.dtype == FDD_BF16) hipLaunchKernelGGL((vocab_reduce_kernel<uint16_t, false>), grid, dim3(RTHREADS), 0, s, a);
