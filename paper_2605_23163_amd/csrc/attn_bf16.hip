@@ -894,7 +894,7 @@ __global__ __launch_bounds__(512) void vt_pack_kernel(const uint16_t* __restrict
 // with avg_s the segment's own softmax average as the attention kernel left it (bf16, accumulator order).
 // The sum over s runs in a fixed order, so results are reproducible.
 // grid (M-tiles, 16 SG): a block of 256 threads = SG segment groups x 256/SG chunks of 8 channels of one
-// wavefront's 32 rows; thread (sg, chunk) sums segments sg, sg + SG, .., four loads in flight, and the SG partial
+// wavefront's 32 rows; thread (sg, chunk) sums segments sg, sg + SG, .., UX loads in flight, and the SG partial
 // sums are added in the order sg = 0, 1, .. through LDS.  SG grows when rows are few and segments many (N = 1).
 struct MergeArgs {
     const u32x4* ws_o;
@@ -908,7 +908,8 @@ struct MergeArgs {
     float c;
 };
 
-template <int D>
+// UX averages per thread and UY (m, l) pairs per thread are requested at once (what is left, if any, in loops)
+template <int D, int UX, int UY>
 __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
 {
     constexpr int DB = D / 32;
@@ -929,43 +930,62 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
     const int row0 = mt * 256 + wave * 32;    // first stacked row of the block's 32 rows
     if (row0 >= a.R) return;
 
-    // ---- this thread's chunk; the first four segments' averages are requested before anything else, so that
-    // their latency and that of the (m, l) pairs below overlap ------------------------------------
+    // ---- everything is requested before anything is waited for: this thread's chunk of its first segments, and the
+    // (m, l) pairs of the block's rows, 8 threads per row
     const int sg = tid / CPB, cl = tid - sg * CPB;
     const int cidx = c0 + cl;                          // chunk inside the M-tile: [wave][register pair][lane]
     const int lane = cidx & 63, i2 = (cidx >> 6) % (2 * DB);
     const int r = lane & 31, half = lane >> 5;
     const bool live = row0 + r < a.R;
     const u32x4* src = a.ws_o + ((size_t)M * a.max_seg) * CH + cidx;
-    u32x4 x[4];
+    const int rr = tid >> 3, j8 = tid & 7;
+    const bool live_r = row0 + rr < a.R;
+    const float* ml = a.ws_ml + (((size_t)M * a.max_seg) * 256 + wave * 32 + rr) * 2;
+    float2 y[UY];
+    u32x4 x[UX];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < UY; ++u) {
+        const int s = j8 + 8 * u;
+        y[u] = make_float2(-INFINITY, 0.f);
+        if (live_r && s < n_seg) y[u] = *reinterpret_cast<const float2*>(ml + (size_t)s * 512);
+    }
+#pragma unroll
+    for (int u = 0; u < UX; ++u) {
         const int s = sg + u * a.SG;
         x[u] = u32x4{0u, 0u, 0u, 0u};
         if (live && s < n_seg) x[u] = src[(size_t)s * CH];
     }
+    __builtin_amdgcn_sched_barrier(0);
 
-    // ---- weights of the segments, per row: 8 threads per row ----------------------------------
+    // ---- weights of the segments, per row ------------------------------------------------------
     float* const W = smem;                            // [32][n_seg]
     {
-        const int rr = tid >> 3, j = tid & 7;
-        const bool live_r = row0 + rr < a.R;
-        const float* ml = a.ws_ml + (((size_t)M * a.max_seg) * 256 + wave * 32 + rr) * 2;
+        // (a segment that saw no key of this row has l = 0 and takes no part)
         float mx = -INFINITY;
-        for (int s = j; s < n_seg; s += 8) {
-            float2 y = make_float2(-INFINITY, 0.f);
-            if (live_r) y = *reinterpret_cast<const float2*>(ml + (size_t)s * 512);
-            if (!(y.y > 0.f)) y.x = -INFINITY;        // a segment that saw no key of this row
-            W[rr * n_seg + s] = y.x;
-            smem[32 * n_seg + rr * n_seg + s] = y.y;
-            mx = fmaxf(mx, y.x);
+#pragma unroll
+        for (int u = 0; u < UY; ++u) {
+            if (!(y[u].y > 0.f)) y[u].x = -INFINITY;
+            mx = fmaxf(mx, y[u].x);
+        }
+        for (int s = j8 + 8 * UY; s < n_seg; s += 8) {
+            float2 z = make_float2(-INFINITY, 0.f);
+            if (live_r) z = *reinterpret_cast<const float2*>(ml + (size_t)s * 512);
+            if (!(z.y > 0.f)) z.x = -INFINITY;
+            W[rr * n_seg + s] = z.x;
+            smem[32 * n_seg + rr * n_seg + s] = z.y;
+            mx = fmaxf(mx, z.x);
         }
         mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 4, 64));
         const float mref = mx == -INFINITY ? 0.f : mx;
         float sum = 0.f;
-        for (int s = j; s < n_seg; s += 8) {
+#pragma unroll
+        for (int u = 0; u < UY; ++u) {
+            y[u].y *= exp2f((y[u].x - mref) * a.c);
+            sum += y[u].y;
+        }
+        for (int s = j8 + 8 * UY; s < n_seg; s += 8) {
             const float w = smem[32 * n_seg + rr * n_seg + s] * exp2f((W[rr * n_seg + s] - mref) * a.c);
             W[rr * n_seg + s] = w;
             sum += w;
@@ -974,7 +994,10 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
         sum += __shfl_xor(sum, 2, 64);
         sum += __shfl_xor(sum, 4, 64);
         const float inv = sum > 0.f ? 1.f / sum : 0.f;
-        for (int s = j; s < n_seg; s += 8) W[rr * n_seg + s] *= inv;
+#pragma unroll
+        for (int u = 0; u < UY; ++u)
+            if (j8 + 8 * u < n_seg) W[rr * n_seg + j8 + 8 * u] = y[u].y * inv;
+        for (int s = j8 + 8 * UY; s < n_seg; s += 8) W[rr * n_seg + s] *= inv;
     }
     __syncthreads();
 
@@ -983,31 +1006,26 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
     if (live) {
-        for (int s0 = sg; s0 < n_seg; s0 += 4 * a.SG) {
-            // the next four segments of this thread are requested before the current four are summed
-            u32x4 nx[4];
+        for (int s0 = sg;;) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int s = s0 + (4 + u) * a.SG;
-                nx[u] = u32x4{0u, 0u, 0u, 0u};
-                if (s < n_seg) nx[u] = src[(size_t)s * CH];
-            }
-            float w[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < UX; ++u) {
                 const int s = s0 + u * a.SG;
-                w[u] = s < n_seg ? W[r * n_seg + s] : 0.f;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
+                const float w = s < n_seg ? W[r * n_seg + s] : 0.f;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     // (a weight of 0 belongs to a segment without a key of this row: its average is 0 as well)
-                    acc[2 * j] = fmaf(__uint_as_float(x[u][j] << 16), w[u], acc[2 * j]);
-                    acc[2 * j + 1] = fmaf(__uint_as_float(x[u][j] & 0xffff0000u), w[u], acc[2 * j + 1]);
+                    acc[2 * j] = fmaf(__uint_as_float(x[u][j] << 16), w, acc[2 * j]);
+                    acc[2 * j + 1] = fmaf(__uint_as_float(x[u][j] & 0xffff0000u), w, acc[2 * j + 1]);
                 }
+            }
+            s0 += UX * a.SG;
+            if (s0 >= n_seg) break;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = nx[u];
+            for (int u = 0; u < UX; ++u) {
+                const int s = s0 + u * a.SG;
+                x[u] = u32x4{0u, 0u, 0u, 0u};
+                if (s < n_seg) x[u] = src[(size_t)s * CH];
+            }
         }
     }
     if (a.SG > 1) {
@@ -1150,8 +1168,17 @@ hipError_t launch_attn_merge_bf16(const fdd_attn_params& p, const AttnPlan& plan
     const size_t smem = ((size_t)2 * 32 * plan.max_seg + (sg > 1 ? (size_t)256 * 8 : 0)) * sizeof(float);
     if (smem > 60 * 1024 || plan.mtile_rows != 256) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(p.Hkv * batch * plan.MT), (unsigned)(chunks / (256 / sg)));
-    if (p.D == 128) hipLaunchKernelGGL(attn_merge_bf16_kernel<128>, grid, dim3(256), smem, s, a);
-    else hipLaunchKernelGGL(attn_merge_bf16_kernel<64>, grid, dim3(256), smem, s, a);
+    // A thread requests its share of the segments at once where registers allow: with 52 segments (N=1, L=16384) one
+    // latency instead of seven, 8.3 -> 6.4 us; but for 2..9 segments the loads that are not there cost more than they
+    // save (N=16, two segments: 8 + 8 9.7 us, 2 + 1 6.8, before 7.3; N=8, nine segments: 9.7, 4 + 2 6.6, before 8.2).
+    auto go = [&](auto d) {
+        constexpr int D = decltype(d)::value;
+        if (plan.max_seg <= 8 && plan.max_seg <= 2 * sg) hipLaunchKernelGGL((attn_merge_bf16_kernel<D, 2, 1>), grid, dim3(256), smem, s, a);
+        else if (plan.max_seg <= 16 && plan.max_seg <= 4 * sg) hipLaunchKernelGGL((attn_merge_bf16_kernel<D, 4, 2>), grid, dim3(256), smem, s, a);
+        else hipLaunchKernelGGL((attn_merge_bf16_kernel<D, 8, 8>), grid, dim3(256), smem, s, a);
+    };
+    if (p.D == 128) go(std::integral_constant<int, 128>());
+    else go(std::integral_constant<int, 64>());
     return hipGetLastError();
 }
 
