@@ -445,7 +445,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
         };
         const int wave_n_lo = rollout_of_row(row0);
         const int wave_n_hi = rollout_of_row(row0 + 31);
-        const bool wave_has_rows = row0 < a.R;
+        const bool wave_has_rows = row0_wg + wave_u * 32 < a.R;
         const int wg_n_lo = __builtin_amdgcn_readfirstlane(rollout_of_row(row0_wg));
         const int wg_n_hi = __builtin_amdgcn_readfirstlane(rollout_of_row(row0_wg + MROWS - 1));
         const int tte = (a.E + KT - 1) >> 6;             // tiles of a rollout's extension
@@ -569,6 +569,15 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
             }
         };
 
+        // end of step i of the pipelined loop: K of tile i+2 and V of tile i+1 must have landed (both requested two
+        // steps ago); what this step and the previous one requested may still be on its way
+        auto wait_step = [&](int i) {
+            if (i + 4 < F) wait_vm<4 * C::NI>();
+            else if (i + 3 < F) wait_vm<3 * C::NI>();
+            else if (i + 2 < F) wait_vm<C::NI>();
+            else wait_vm<0>();
+        };
+
         bf16x8 p[4];      // probabilities of a tile as MFMA B operands, one per 16-key step
 
         // ---- full prefix tiles, software pipelined ---------------------------------
@@ -577,7 +586,22 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
         if (F >= NB) wait_vm<4 * C::NI>(); else wait_vm<0>();
         wg_barrier();
         landed = issued - 1;
-        if (F > 0) {
+        if (F > 0 && !wave_has_rows) {
+            // A wavefront without rows (the M-tile is not full) only moves its share of the tiles: the matrix pipe and
+            // the power are left to the others (8 requests of N=1, 224 of 256 rows, L=16384: 84.0 -> 82.1 us; with 112
+            // rows or fewer a SIMD has one wavefront to serve).  Same requests, waits and barriers as in the steps below.
+            wg_barrier();
+            for (int i = 0; i < F; ++i) {
+                if (i + NB < F) fetch_k(i + NB, (uint32_t)(i & (NB - 1)) * C::T_BYTES);
+                if (i + NB - 1 < F) {
+                    fetch_v(i + NB - 1, (uint32_t)((i + NB - 1) & (NB - 1)) * C::T_BYTES);
+                    issued = i + NB;
+                }
+                wait_step(i);
+                wg_barrier();
+            }
+            landed = issued - 1;
+        } else if (F > 0) {
             // prologue: scores of tile 0
             f32x16 sa[2], sb[2];
 #pragma unroll
@@ -712,12 +736,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
                     o[j % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[j % 3], p[2 + j / DB], o[j % DB], 0, 0, 0);
                     FDD_SCHED_FENCE();
                 }
-                // K of tile i+2 and V of tile i+1 must have landed (both requested two steps ago); what this
-                // step and the previous one requested may still be on its way
-                if (i + 4 < F) wait_vm<4 * C::NI>();
-                else if (i + 3 < F) wait_vm<3 * C::NI>();
-                else if (i + 2 < F) wait_vm<C::NI>();
-                else wait_vm<0>();
+                wait_step(i);
                 wg_barrier();
             };
             const std::integral_constant<int, 0> r0;
