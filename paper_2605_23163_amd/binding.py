@@ -9,6 +9,8 @@ from __future__ import annotations
 import ctypes as C
 import os
 
+import torch
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libfdd.so")
 _lib = None
@@ -79,10 +81,9 @@ def library_path() -> str:
 
 
 def load_library():
-    """Load libfdd.so (after torch, so both share one HIP runtime)."""
+    """Load libfdd.so (after torch, which brings in the HIP runtime the library links against)."""
     global _lib
     if _lib is None:
-        import torch  # noqa: F401  -- brings in the HIP runtime the library links against
         if not os.path.exists(_LIB_PATH):
             raise FileNotFoundError(
                 f"{_LIB_PATH} is missing: build it with `python -m paper_2605_23163_amd.build` "
@@ -145,13 +146,14 @@ def _check(code):
         raise FddError(code, fdd_last_error())
 
 
+_DTYPE_CODES = {torch.bfloat16: FDD_BF16, torch.float32: FDD_F32}
+
+
 def _dtype_code(t):
-    import torch
-    if t.dtype == torch.bfloat16:
-        return FDD_BF16
-    if t.dtype == torch.float32:
-        return FDD_F32
-    raise TypeError(f"unsupported element type {t.dtype}")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported element type {t.dtype}")
+    return code
 
 
 def _dev(t, name):
@@ -165,47 +167,44 @@ def _dev(t, name):
 
 
 def _stream_ptr(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is None:      # (the current stream's handle without a stream object around it)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
-def _workspace(ws, need, device):
-    import torch
-    if need == 0:
-        return None, 0
-    if ws is None:
-        ws = torch.empty(need, dtype=torch.uint8, device=device)
-    return ws, ws.numel() * ws.element_size()
+def _set_workspace(p, workspace, query, device):
+    """The caller's workspace, whose size the library checks itself, or one of the size it asks for; returns the
+    tensor, which has to live until the call has been made."""
+    if workspace is None:
+        need = query(C.byref(p))
+        if need == 0:
+            return None
+        workspace = torch.empty(need, dtype=torch.uint8, device=device)
+    p.workspace = workspace.data_ptr()
+    p.workspace_bytes = workspace.numel() * workspace.element_size()
+    return workspace
 
 
 def _attn_params(q, prefix_k, prefix_v, block_k, block_v, scaffold_mask, out, scale, splits, prefix_v_packed=None,
                  causal_block=False, ext_k=None, ext_v=None, E=0):
     N, B, Hq, D = q.shape
-    L, Hkv = prefix_k.shape[0], block_k.shape[2]
-    if tuple(prefix_k.shape[1:]) != (Hkv, D) or tuple(prefix_v.shape) != tuple(prefix_k.shape):
+    ks, bs, dt = prefix_k.shape, block_k.shape, q.dtype
+    L, Hkv = ks[0], bs[2]
+    if ks[1:] != (Hkv, D) or prefix_v.shape != ks:
         raise ValueError("prefix_k / prefix_v must be [L,Hkv,D]")
-    if tuple(block_k.shape) != (N, B, Hkv, D) or tuple(block_v.shape) != (N, B, Hkv, D):
+    if bs != (N, B, Hkv, D) or block_v.shape != bs:
         raise ValueError("block_k / block_v must be [N,B,Hkv,D]")
-    dt = _dtype_code(q)
-    for t in (prefix_k, prefix_v, block_k, block_v):
-        if t.dtype != q.dtype:
-            raise TypeError("q, k and v must share one element type")
-    p = AttnParams()
-    p.N, p.B, p.L, p.Hq, p.Hkv, p.D, p.dtype = N, B, L, Hq, Hkv, D, dt
-    p.scale = 0.0 if scale is None else float(scale)
-    p.q = _dev(q, "q")
-    p.prefix_k = _dev(prefix_k, "prefix_k") if L > 0 else None
-    p.prefix_v = _dev(prefix_v, "prefix_v") if L > 0 else None
-    p.block_k, p.block_v = _dev(block_k, "block_k"), _dev(block_v, "block_v")
-    p.scaffold_mask = _dev(scaffold_mask, "scaffold_mask")
-    p.out = _dev(out, "out") if out is not None else None
-    p.splits = int(splits)
-    p.prefix_v_packed = _dev(prefix_v_packed, "prefix_v_packed")
-    p.flags = FDD_ATTN_CAUSAL_BLOCK if causal_block else 0
+    code = _dtype_code(q)
+    if prefix_k.dtype != dt or prefix_v.dtype != dt or block_k.dtype != dt or block_v.dtype != dt:
+        raise TypeError("q, k and v must share one element type")
+    p = AttnParams(N, B, L, Hq, Hkv, D, code, 0.0 if scale is None else float(scale), _dev(q, "q"),
+                   _dev(prefix_k, "prefix_k") if L > 0 else None, _dev(prefix_v, "prefix_v") if L > 0 else None,
+                   _dev(block_k, "block_k"), _dev(block_v, "block_v"), _dev(scaffold_mask, "scaffold_mask"), _dev(out, "out"),
+                   None, 0, None, int(splits), FDD_ATTN_CAUSAL_BLOCK if causal_block else 0,
+                   _dev(prefix_v_packed, "prefix_v_packed"))
     p.E = int(E)
     if ext_k is not None:
-        if tuple(ext_k.shape) != tuple(ext_v.shape) or ext_k.shape[0] != N or tuple(ext_k.shape[2:]) != (Hkv, D):
+        if ext_k.shape != ext_v.shape or ext_k.shape[0] != N or ext_k.shape[2:] != (Hkv, D):
             raise ValueError("ext_k / ext_v must be [N,ext_capacity,Hkv,D]")
         if ext_k.dtype != q.dtype or ext_v.dtype != q.dtype:
             raise TypeError("q, k and v must share one element type")
@@ -221,7 +220,6 @@ def fdd_prefix_pack_bytes(prefix_v) -> int:
 def fdd_prefix_pack(prefix_v, packed=None, stream=None):
     """One-time relayout of the prefix V for later fdd_block_attn calls; returns
     the packed buffer (None when there is nothing to pack)."""
-    import torch
     lib = load_library()
     L, Hkv, D = prefix_v.shape
     need = lib.fdd_prefix_pack_bytes(L, Hkv, D, _dtype_code(prefix_v))
@@ -253,7 +251,6 @@ def fdd_block_attn(q, prefix_k, prefix_v, block_k, block_v, scaffold_mask=None, 
     rollout has committed since the fork.
     ``q_positions``: int32 device tensor of ascending flat positions n*B+b; only
     their rows of ``out`` are written (pass ``out`` then)."""
-    import torch
     lib = load_library()
     if out is None:
         out = torch.empty_like(q)
@@ -264,10 +261,7 @@ def fdd_block_attn(q, prefix_k, prefix_v, block_k, block_v, scaffold_mask=None, 
             raise ValueError("q_positions must be a contiguous 1-D int32 tensor")
         p.q_positions = _dev(q_positions, "q_positions")
         p.n_q_positions = q_positions.numel()
-    need = lib.fdd_block_attn_workspace(C.byref(p))
-    ws, nbytes = _workspace(workspace, need, q.device)
-    p.workspace = ws.data_ptr() if ws is not None else None
-    p.workspace_bytes = nbytes
+    ws = _set_workspace(p, workspace, lib.fdd_block_attn_workspace, q.device)  # noqa: F841
     p.stream = _stream_ptr(stream)
     _check(lib.fdd_block_attn(C.byref(p)))
     return out
@@ -305,16 +299,12 @@ def fdd_block_attn_batched(q, prefix_k, prefix_v, block_k, block_v, out=None, sc
     """A batch of independent fdd_block_attn problems of one shape in a single launch.  Every array carries a
     leading batch dimension: q [P,N,B,Hq,D], prefix_k/v [P,L,Hkv,D], block_k/v [P,N,B,Hkv,D], and
     prefix_v_packed [P, fdd_prefix_pack_bytes] if given.  Nothing is shared between the problems."""
-    import torch
     lib = load_library()
     if out is None:
         out = torch.empty_like(q)
     p = _batched_params(q, prefix_k, prefix_v, block_k, block_v, out, scale, splits, prefix_v_packed, causal_block,
                         ext_k, ext_v, E)
-    need = lib.fdd_block_attn_workspace(C.byref(p))
-    ws, nbytes = _workspace(workspace, need, q.device)
-    p.workspace = ws.data_ptr() if ws is not None else None
-    p.workspace_bytes = nbytes
+    ws = _set_workspace(p, workspace, lib.fdd_block_attn_workspace, q.device)  # noqa: F841
     p.stream = _stream_ptr(stream)
     _check(lib.fdd_block_attn(C.byref(p)))
     return out
@@ -325,7 +315,7 @@ def _unmask_params(logits, mask, scaffold_mask, tokens, tau, confidences, n_unma
     p = UnmaskParams()
     if refresh is not None:
         tk, tv, bk, bv = refresh
-        if tuple(bk.shape[:2]) != (N, B) or tk.shape[1:] != bk.shape[2:] or tv.shape != tk.shape or bv.shape != bk.shape:
+        if bk.shape[:2] != (N, B) or tk.shape[1:] != bk.shape[2:] or tv.shape != tk.shape or bv.shape != bk.shape:
             raise TypeError("refresh = (table_k [T,Hkv,D], table_v, block_k [N,B,Hkv,D], block_v)")
         p.refresh_table_k, p.refresh_table_v = _dev(tk, "table_k"), _dev(tv, "table_v")
         p.refresh_block_k, p.refresh_block_v = _dev(bk, "block_k"), _dev(bv, "block_v")
@@ -355,13 +345,12 @@ def fdd_unmask_step(logits, mask, scaffold_mask, tau, tokens, confidences=None, 
 
     Returns (tokens, confidences, n_unmasked, committed).
     """
-    import torch
     lib = load_library()
     N, B, V = logits.shape
     for t, dt, nm in ((mask, torch.uint8, "mask"), (tokens, torch.int32, "tokens")):
-        if t.dtype != dt or tuple(t.shape) != (N, B):
+        if t.dtype != dt or t.shape != (N, B):
             raise TypeError(f"{nm} must be {dt} [N,B]")
-    if scaffold_mask is not None and (scaffold_mask.dtype != torch.uint8 or tuple(scaffold_mask.shape) != (N, B)):
+    if scaffold_mask is not None and (scaffold_mask.dtype != torch.uint8 or scaffold_mask.shape != (N, B)):
         raise TypeError("scaffold_mask must be uint8 [N,B]")
     dev = logits.device
     if confidences is None:
@@ -371,10 +360,7 @@ def fdd_unmask_step(logits, mask, scaffold_mask, tau, tokens, confidences=None, 
     if committed is None:
         committed = torch.empty((N, B), dtype=torch.uint8, device=dev)
     p = _unmask_params(logits, mask, scaffold_mask, tokens, tau, confidences, n_unmasked, committed, refresh)
-    need = lib.fdd_unmask_workspace(C.byref(p))
-    ws, nbytes = _workspace(workspace, need, dev)
-    p.workspace = ws.data_ptr() if ws is not None else None
-    p.workspace_bytes = nbytes
+    ws = _set_workspace(p, workspace, lib.fdd_unmask_workspace, dev)  # noqa: F841
     p.stream = _stream_ptr(stream)
     _check(lib.fdd_unmask_step(C.byref(p)))
     return tokens, confidences, n_unmasked, committed
@@ -408,11 +394,10 @@ def fdd_verify_step(ar_logits, mask, scaffold_mask, draft, tokens, n_accepted=No
     """Accept scan of scaffold speculative decoding; ``tokens`` and ``mask`` are
     updated in place.  ``temperature`` > 0 selects the sampled verifier with the
     random stream ``seed``.  Returns (tokens, n_accepted, accepted)."""
-    import torch
     lib = load_library()
     N, B, V = ar_logits.shape
     for t, dt, nm in ((mask, torch.uint8, "mask"), (tokens, torch.int32, "tokens"), (draft, torch.int32, "draft")):
-        if t.dtype != dt or tuple(t.shape) != (N, B):
+        if t.dtype != dt or t.shape != (N, B):
             raise TypeError(f"{nm} must be {dt} [N,B]")
     dev = ar_logits.device
     if n_accepted is None:
@@ -426,10 +411,7 @@ def fdd_verify_step(ar_logits, mask, scaffold_mask, draft, tokens, n_accepted=No
     p.scaffold_mask = _dev(scaffold_mask, "scaffold_mask")
     p.draft, p.mask, p.tokens = _dev(draft, "draft"), _dev(mask, "mask"), _dev(tokens, "tokens")
     p.n_accepted, p.accepted = _dev(n_accepted, "n_accepted"), _dev(accepted, "accepted")
-    need = lib.fdd_verify_workspace(C.byref(p))
-    ws, nbytes = _workspace(workspace, need, dev)
-    p.workspace = ws.data_ptr() if ws is not None else None
-    p.workspace_bytes = nbytes
+    ws = _set_workspace(p, workspace, lib.fdd_verify_workspace, dev)  # noqa: F841
     p.stream = _stream_ptr(stream)
     _check(lib.fdd_verify_step(C.byref(p)))
     return tokens, n_accepted, accepted
@@ -437,7 +419,6 @@ def fdd_verify_step(ar_logits, mask, scaffold_mask, draft, tokens, n_accepted=No
 
 def fdd_fork_block(src, N, dst=None, stream=None):
     """dst[n] = src for n < N: the private block state of N forked rollouts."""
-    import torch
     lib = load_library()
     if dst is None:
         dst = torch.empty((N,) + tuple(src.shape), dtype=src.dtype, device=src.device)
@@ -477,7 +458,6 @@ def fdd_block_commit(block_k, block_v, ext_k, ext_v, E, stream=None):
 
 def fdd_traj_mean(traj, out=None, stream=None):
     """Equal-weight mean of the N rollout trajectories: traj [N, ...] float32 -> [...]."""
-    import torch
     lib = load_library()
     if traj.dtype != torch.float32:
         raise TypeError("trajectories are float32")
