@@ -557,13 +557,28 @@ __global__ __launch_bounds__(STHREADS) void block_select_kernel(Args a)
     int best_b = 0x7fffffff;
     int best_tok = -1;
 
-    // the wavefront refreshes the K/V row of position i, which now holds token `tok` (see fdd_block_kv_update)
-    auto refresh_row = [&](size_t i, int tok) {
-        int t = tok % a.rf_T;
-        if (t < 0) t += a.rf_T;
+    // the wavefront refreshes the K/V rows of up to RB positions at once (see fdd_block_kv_update): all loads are on
+    // their way before the first store, so the rows share one memory latency (one by one, K before V, each row took two)
+    constexpr int RB = 4;
+    auto refresh_rows = [&](int n_rows, const size_t (&pos)[RB], const int (&tok)[RB]) {
         for (int c = tid; c < a.rf_row_vecs; c += STHREADS) {
-            a.rf_bk[i * a.rf_row_vecs + c] = a.rf_tk[(size_t)t * a.rf_row_vecs + c];
-            a.rf_bv[i * a.rf_row_vecs + c] = a.rf_tv[(size_t)t * a.rf_row_vecs + c];
+            u32x4 k[RB], v[RB];
+#pragma unroll
+            for (int u = 0; u < RB; ++u) {
+                if (u < n_rows) {
+                    int t = tok[u] % a.rf_T;
+                    if (t < 0) t += a.rf_T;
+                    k[u] = a.rf_tk[(size_t)t * a.rf_row_vecs + c];
+                    v[u] = a.rf_tv[(size_t)t * a.rf_row_vecs + c];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < RB; ++u) {
+                if (u < n_rows) {
+                    a.rf_bk[pos[u] * a.rf_row_vecs + c] = k[u];
+                    a.rf_bv[pos[u] * a.rf_row_vecs + c] = v[u];
+                }
+            }
         }
     };
 
@@ -625,22 +640,33 @@ __global__ __launch_bounds__(STHREADS) void block_select_kernel(Args a)
         if (a.rf_row_vecs > 0) {
             unsigned long long m = __ballot(com != 0);
             while (m) {
-                const int j = __ffsll((long long)m) - 1;
-                m &= m - 1;
-                refresh_row((size_t)n * a.B + b0 + j, __shfl(arg, j, 64));
+                size_t pos[RB] = {};
+                int tok[RB] = {}, n_rows = 0;
+#pragma unroll
+                for (int u = 0; u < RB; ++u) {
+                    if (m) {
+                        const int j = __builtin_ctzll(m);
+                        m &= m - 1;
+                        pos[u] = (size_t)n * a.B + b0 + j;
+                        tok[u] = __builtin_amdgcn_readlane(arg, j);
+                        n_rows = u + 1;
+                    }
+                }
+                refresh_rows(n_rows, pos, tok);
             }
         }
     }
-    // wavefront reduction: commits are summed; the best candidate is the one of
-    // highest confidence, lowest position on ties
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        count += __shfl_xor(count, off, 64);
-        const double oc = __shfl_xor(best_conf, off, 64);
-        const int ob = __shfl_xor(best_b, off, 64);
-        const int ot = __shfl_xor(best_tok, off, 64);
-        if (oc > best_conf || (oc == best_conf && ob < best_b)) { best_conf = oc; best_b = ob; best_tok = ot; }
-    }
+    // wavefront reduction: commits are summed; the best candidate is the one of highest confidence, lowest position on
+    // ties (a confidence is positive, so its 64 bits order as an integer: upper half, then lower half, then position)
+    count = (int)wave_reduce((uint32_t)count, [](uint32_t p, uint32_t q) { return p + q; });
+    auto larger = [](uint32_t p, uint32_t q) { return p > q ? p : q; };
+    const uint64_t bits = best_conf > 0.0 ? (uint64_t)__double_as_longlong(best_conf) : 0u;
+    const uint32_t hi = (uint32_t)(bits >> 32), lo = (uint32_t)bits;
+    const uint32_t hi_best = wave_reduce(hi, larger);
+    const uint32_t lo_best = wave_reduce(hi == hi_best ? lo : 0u, larger);
+    const int b_lane = best_b;
+    best_b = wave_min(hi == hi_best && lo == lo_best ? b_lane : 0x7fffffff);
+    best_tok = __builtin_amdgcn_readlane(best_tok, __builtin_ctzll(__ballot(b_lane == best_b)));
     // (count and the best candidate are now the same in every lane)
     if (count == 0 && best_tok >= 0) {
         // nothing reached tau: commit the most confident eligible position
@@ -650,7 +676,11 @@ __global__ __launch_bounds__(STHREADS) void block_select_kernel(Args a)
             a.mask[i] = 0;
             if (a.committed) a.committed[i] = 1;
         }
-        if (a.rf_row_vecs > 0) refresh_row(i, best_tok);
+        if (a.rf_row_vecs > 0) {
+            const size_t pos[RB] = {i};
+            const int tok[RB] = {best_tok};
+            refresh_rows(1, pos, tok);
+        }
         count = 1;
     }
     if (tid == 0 && a.n_unmasked) a.n_unmasked[n] = count;
