@@ -390,8 +390,8 @@ constexpr int VUNROLL = 5;       // sampled verifier: 16-byte loads in flight pe
 // clear winner end here), then with the bound above in place of the logarithms.  What is left (a few entries per
 // wavefront) is worked out as defined, and the row's winner is never dropped, so the verifier's token is the same bit for
 // bit.
-// Measured, bf16, 70 % of the rows live, V = 152064 (in brackets every entry worked out in full): N=8, B=32 33 us (87) with
-// a clear winner in 4 of 5 rows, 43 (87) with none; N=16, B=64 71 (231) and 117 (230); N=5, B=40, V=50001 26 (211: rows
+// Measured, bf16, 70 % of the rows live, V = 152064 (in brackets every entry worked out in full): N=8, B=32 32 us (87) with
+// a clear winner in 4 of 5 rows, 42 (87) with none; N=16, B=64 70 (231) and 112 (230); N=5, B=40, V=50001 25 (211: rows
 // that start inside a generator block took a block per entry).  Without a winner the generator's 32 x 32 bit products
 // are what is left.
 template <typename T, int VTHREADS>
