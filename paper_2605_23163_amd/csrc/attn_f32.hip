@@ -132,9 +132,9 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
     const int n_hi = __builtin_amdgcn_readfirstlane(fast_div(position_of(a.qpos, fast_div(row_hi, a.dG), NB), a.dB));
     const int TP = (a.L + KT - 1) / KT;
     const int n_tiles = TP + (n_hi - n_lo + 1) * a.per;
-    const int part = split * WAVES + wave;                  // (tiles * parts stays below 2^31 for every accepted shape)
-    const int t_lo = __builtin_amdgcn_readfirstlane(fast_div(n_tiles * part, a.dParts));
-    const int t_hi = __builtin_amdgcn_readfirstlane(fast_div(n_tiles * (part + 1), a.dParts));
+    const int part = split * WAVES + wave, parts = a.S * WAVES;
+    const int t_lo = __builtin_amdgcn_readfirstlane(key_cut(n_tiles, part, parts, a.dParts));
+    const int t_hi = __builtin_amdgcn_readfirstlane(key_cut(n_tiles, part + 1, parts, a.dParts));
 
     struct Tile {
         const char* k;    // first key's row of this KV head

@@ -87,9 +87,18 @@ inline FastDiv make_fastdiv(uint32_t d)
     f.shift = s - 1;
     return f;
 }
-__device__ __forceinline__ int fast_div(int n, const FastDiv& f)
+__host__ __device__ __forceinline__ int fast_div(int n, const FastDiv& f)
 {
     return (int)((uint32_t)(((uint64_t)((uint32_t)n + 1u) * f.mul) >> 32) >> f.shift);
+}
+
+// fp32 path: first key tile of wavefront `part` of the `parts` that share a row tile's n_tiles, floor(n_tiles part / parts).
+// (A list of two far positions makes a row tile walk the private tiles of every rollout between them, up to 2^26 in all:
+// n_tiles * part may pass 2^31, the remainder's product stays below parts^2 = 2^18.)
+__host__ __device__ inline int key_cut(int n_tiles, int part, int parts, const FastDiv& by_parts)
+{
+    const int base = fast_div(n_tiles, by_parts), rem = n_tiles - base * parts;
+    return base * part + fast_div(rem * part, by_parts);
 }
 
 // Stream-K ranges: U units over W workgroups, base = U / W, rem = U % W; the

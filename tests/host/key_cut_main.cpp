@@ -1,0 +1,29 @@
+// Checks the cut of an fp32 row tile's key tiles among its wavefronts (key_cut in fdd_internal.h, which the kernel
+// calls) against 64-bit arithmetic, up to the most tiles a call can have.  Host code only; built and run by
+// tests/test_f32_limits.py.
+#include <cstdio>
+
+#include "fdd_internal.h"
+
+int main()
+{
+    using namespace fdd;
+    // row tiles: none or one tile, fewer tiles than wavefronts, the cases' sizes, a list of two far positions of
+    // 2^22 .. 2^24 rollouts (the row tile walks the private tiles of every rollout between them), the type's limit
+    const int tiles[] = {0, 1, 7, 8, 9, 63, 64, 258, 1026, 32770, 524288, (1 << 22) + 64, (1 << 23) + 512, (1 << 25) + 3,
+                         (1 << 26) + 511, 0x7fffffff};
+    long bad = 0;
+    for (int n : tiles)
+        for (int splits : {1, 2, 3, 9, 17, 64}) {
+            const int parts = splits * kF32Waves;
+            const FastDiv d = make_fastdiv((uint32_t)parts);
+            for (int part = 0; part <= parts; ++part) {
+                const long long want = (long long)n * part / parts;
+                const int got = key_cut(n, part, parts, d);
+                if (got != want && bad++ < 5) std::printf("tiles %d part %d of %d: %d, should be %lld\n", n, part, parts, got, want);
+            }
+        }
+    if (bad) return 1;
+    std::puts("key cut: ok");
+    return 0;
+}

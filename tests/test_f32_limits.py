@@ -1,0 +1,26 @@
+"""Index arithmetic of the fp32 attention path at the largest shapes a call can have.  It is plain integer code that the
+kernel and its launch share with the host programs under tests/host/, so it is checked there, without a GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def run_host(name, tmp_path):
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not (os.path.exists(hipcc) or shutil.which(hipcc)):
+        pytest.skip("hipcc not found")
+    exe = str(tmp_path / name)
+    for cmd in ([hipcc, "--offload-host-only", "-O1", "-std=c++17", "-I" + os.path.join(ROOT, "include"),
+                 "-I" + os.path.join(ROOT, "paper_2605_23163_amd", "csrc"), "-x", "hip",
+                 os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", exe], [exe]):
+        p = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        assert p.returncode == 0, " ".join(cmd) + "\n" + p.stdout[-4000:]
+    return p.stdout
+
+
+def test_key_tiles_are_cut_without_overflow(tmp_path):
+    assert "key cut: ok" in run_host("key_cut_main", tmp_path)
