@@ -59,7 +59,8 @@ struct Args {
     int E, Ecap;
     long long q_bs, p_bs, b_bs, e_bs, o_bs;   // element strides between the arrays of independent problems
     int N, B, L, Hq, Hkv, G, R, MT, S;
-    int W, per_xcd;    // workgroups; ceil(W / 8)
+    int W, per_xcd;    // workgroups; launched workgroups / 8
+    unsigned grid_x;   // workgroups per row of the launch grid
     int causal;        // in-block keys are visible up to the query's own position only
     float c;           // scale * log2(e)
     const int32_t* qpos;   // stacked rows are the listed block positions only (ascending n*B + b), or nullptr: all of them
@@ -97,7 +98,8 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
 
     // workgroups are dealt to the 8 XCDs round-robin: those of one XCD own neighbouring row tiles of one
     // (KV head, split), which walk the same keys
-    const int wg = (int)(wg_id_x() % kNumXCD) * a.per_xcd + (int)(wg_id_x() / kNumXCD);
+    const unsigned id = wg_id_y() * a.grid_x + wg_id_x();
+    const int wg = (int)(id % kNumXCD) * a.per_xcd + (int)(id / kNumXCD);
     if (wg >= a.W) return;
     const int rest = fast_div(wg, a.dMT), mt = wg - rest * a.MT;
     const int khv = fast_div(rest, a.dS), split = rest - khv * a.S;
@@ -532,7 +534,7 @@ static hipError_t launch(const Args& a, hipStream_t s)
         if (e != hipSuccess) return e;
         done.fetch_or(bit, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)(a.per_xcd * kNumXCD)), dim3(THREADS), F32Cfg<D>::LDS_BYTES, s, a);
+    hipLaunchKernelGGL(kern, f32_grid(a.W), dim3(THREADS), F32Cfg<D>::LDS_BYTES, s, a);
     return hipGetLastError();
 }
 
@@ -556,7 +558,9 @@ hipError_t launch_attn_f32(const fdd_attn_params& p, const AttnPlan& plan, float
     a.N = p.N; a.B = p.B; a.L = p.L; a.Hq = p.Hq; a.Hkv = p.Hkv;
     a.G = plan.G; a.R = plan.R; a.MT = plan.MT; a.S = plan.splits;
     a.W = p.Hkv * batch * plan.MT * plan.splits;
-    a.per_xcd = (a.W + kNumXCD - 1) / kNumXCD;
+    const dim3 grid = f32_grid(a.W);
+    a.grid_x = grid.x;
+    a.per_xcd = (int)(grid.x * grid.y / kNumXCD);
     a.c = scale * 1.4426950408889634f;
     a.causal = (p.flags & FDD_ATTN_CAUSAL_BLOCK) ? 1 : 0;
     a.qpos = p.n_q_positions > 0 ? p.q_positions : nullptr;

@@ -101,6 +101,15 @@ __host__ __device__ inline int key_cut(int n_tiles, int part, int parts, const F
     return base * part + fast_div(rem * part, by_parts);
 }
 
+// fp32 path: launch grid of `wgs` workgroups.  One dimension takes less than 2^32 work items, 2^23 workgroups of 512 (64 GiB
+// of queries at D = 64); larger calls get more rows, each of whole rounds of the XCDs.
+inline dim3 f32_grid(int wgs)
+{
+    constexpr int kMax = 1 << 22;
+    const int rows = (wgs + kMax - 1) / kMax, per_row = (wgs + rows - 1) / rows;
+    return dim3((unsigned)((per_row + kNumXCD - 1) / kNumXCD * kNumXCD), (unsigned)rows);
+}
+
 // Stream-K ranges: U units over W workgroups, base = U / W, rem = U % W; the
 // first `rem` workgroups own base + 1 units, the others base (>= 1).
 __host__ __device__ inline int unit_begin(int w, int base, int rem) { return w * base + (w < rem ? w : rem); }

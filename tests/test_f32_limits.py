@@ -24,3 +24,7 @@ def run_host(name, tmp_path):
 
 def test_key_tiles_are_cut_without_overflow(tmp_path):
     assert "key cut: ok" in run_host("key_cut_main", tmp_path)
+
+
+def test_launch_stays_below_2_to_the_32_work_items(tmp_path):
+    assert "launch grid: ok" in run_host("launch_grid_main", tmp_path)
