@@ -185,8 +185,9 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
     f32x4 kf[NJ], vf[NJ];
     auto k_off = [&](const Tile& t) { return (uint32_t)min(c16, t.valid - 1) * stride4 + (uint32_t)(16 * g4); };
     auto v_off = [&](const Tile& t, int v) { return (uint32_t)min(4 * g4 + v, t.valid - 1) * stride4 + (uint32_t)(16 * c16); };
+    // (offsets inside a tile stay below 2^32, as the whole block K does, but may pass 2^31 with very many KV heads)
     auto load = [&](const char* base, uint32_t off) {
-        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, 0x7fffffff, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, -1, 0x00020000);
         return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
     };
 
