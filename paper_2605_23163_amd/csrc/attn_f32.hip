@@ -181,7 +181,7 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
     };
 
     // Fragments of a tile.  K: row c16, channels 16 j + 4 g4 ..; V: row 4 g4 + v, channels 64 t + 4 c16 ..
-    // (rows beyond `valid` repeat the last valid one: finite values, masked below, nothing read out of bounds)
+    // (rows beyond `valid` repeat the last valid one: masked below, nothing read out of bounds)
     f32x4 kf[NJ], vf[NJ];
     auto k_off = [&](const Tile& t) { return (uint32_t)min(c16, t.valid - 1) * stride4 + (uint32_t)(16 * g4); };
     auto v_off = [&](const Tile& t, int v) { return (uint32_t)min(4 * g4 + v, t.valid - 1) * stride4 + (uint32_t)(16 * c16); };
@@ -279,6 +279,44 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
                 for (int v = 0; v < 4; ++v) p[qb][v] = __builtin_amdgcn_exp2f(fmaf(s[qb][v], a.c, -mc));
                 l_run[qb] += (p[qb][0] + p[qb][1]) + (p[qb][2] + p[qb][3]);
             }
+            // What a row does not see must not reach its sums through 0 x inf or 0 x NaN: keys that do not exist (the
+            // rows loaded in their place repeat the last one) ...
+            if (now.valid < KT) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int tt = 0; tt < NT; ++tt)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) vf[v * NT + tt][e] = 4 * g4 + v < now.valid ? vf[v * NT + tt][e] : 0.f;
+            }
+            // ... and, in a row tile of several rollouts, values of another one that are not finite.  A lane's outputs
+            // belong to one query: the tile's share is then summed by itself, added where the query sees it, and nothing
+            // is left for the sums below.
+            if (now.rollout >= 0 && n_lo != n_hi) {
+                float x0 = 0.f;      // NaN if any value is not finite
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x0 = fmaf(vf[j][e], 0.f, x0);
+                if (__any(x0 != 0.f)) {
+#pragma unroll
+                    for (int tt = 0; tt < NT; ++tt)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+#pragma unroll
+                            for (int qb = 0; qb < 2; ++qb) {
+                                f32x4 x = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                                for (int v = 0; v < 4; ++v)
+                                    x = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[v * NT + tt][e], p[qb][v], x, 0, 0, 0);
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) o[qb][tt][e][v] += now.rollout == my_rollout[qb] ? x[v] : 0.f;
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) vf[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const uint32_t next_v = v_off(next, v);
@@ -298,6 +336,9 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
     }
 
     // ---- merge of the wavefronts through LDS ----------------------------------------------------------
+    // (lane and thread index are worked out anew: the loop has no registers to keep them in)
+    const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), c16_e = lane_e & 15;
+    const int tid_e = wave * 64 + lane_e;
     float* const so = smem;                                  // [wave][qb][t][v][lane] x 4 channels
     float* const sm = smem + F32Cfg<D>::MERGE_FLOATS;        // [wave][row]: m, then the wavefront's weight
     float* const sl = sm + WAVES * RT;                       // [wave][row]: l
@@ -308,37 +349,37 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
         float l = l_run[qb];
         l += __shfl_xor(l, 16, 64);
         l += __shfl_xor(l, 32, 64);
-        if (g4 == 0) {
-            sm[wave * RT + qb * 16 + c16] = m_ref[qb];
-            sl[wave * RT + qb * 16 + c16] = l;
+        if (lane_e < 16) {
+            sm[wave * RT + qb * 16 + c16_e] = m_ref[qb];
+            sl[wave * RT + qb * 16 + c16_e] = l;
         }
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                *reinterpret_cast<f32x4*>(so + ((((wave * 2 + qb) * NT + tt) * 4 + v) * 64 + lane) * 4) =
+                *reinterpret_cast<f32x4*>(so + ((((wave * 2 + qb) * NT + tt) * 4 + v) * 64 + lane_e) * 4) =
                     f32x4{o[qb][tt][0][v], o[qb][tt][1][v], o[qb][tt][2][v], o[qb][tt][3][v]};
     }
     __syncthreads();
-    if (tid < RT) {
+    if (tid_e < RT) {
         float m = -INFINITY, l = 0.f;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) m = fmaxf(m, sm[w * RT + tid]);
+        for (int w = 0; w < WAVES; ++w) m = fmaxf(m, sm[w * RT + tid_e]);
         const float m_use = m == -INFINITY ? 0.f : m;
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) {
-            const float x = exp2f((sm[w * RT + tid] - m_use) * a.c);
-            l = fmaf(sl[w * RT + tid], x, l);
-            sm[w * RT + tid] = x;
+            const float x = exp2f((sm[w * RT + tid_e] - m_use) * a.c);
+            l = fmaf(sl[w * RT + tid_e], x, l);
+            sm[w * RT + tid_e] = x;
         }
-        row_l[tid] = l;
-        row_m[tid] = m;
+        row_l[tid_e] = l;
+        row_m[tid_e] = m;
     }
     __syncthreads();
     constexpr int CHUNKS = 2 * NT * 4 * 64;      // 16-byte pieces of the row tile
 #pragma unroll
     for (int i0 = 0; i0 < CHUNKS; i0 += THREADS) {
-        const int i = i0 + tid;
+        const int i = i0 + tid_e;
         if (CHUNKS % THREADS != 0 && i >= CHUNKS) break;
         const int ln = i & 63, v = (i >> 6) & 3, tt = (i >> 8) % NT, qb = (i >> 8) / NT;
         const int r = qb * 16 + (ln & 15), row = mt * RT + r;
