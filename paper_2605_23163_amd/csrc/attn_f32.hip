@@ -63,6 +63,7 @@ struct Args {
     unsigned grid_x;   // workgroups per row of the launch grid
     int causal;        // in-block keys are visible up to the query's own position only
     float c;           // scale * log2(e)
+    float slack;       // 8 / c: scores may pass their reference by this much
     const int32_t* qpos;   // stacked rows are the listed block positions only (ascending n*B + b), or nullptr: all of them
     int ext_per, per;      // private tiles per rollout: of its extension, in all (extension, then block)
     FastDiv dMT, dS, dHkv, dG, dB, dPer, dParts;   // divisions by launch constants
@@ -198,7 +199,8 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[qb][t][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_ref[2] = {-INFINITY, -INFINITY};   // reference the exponentials are taken against (raw score units)
+    float m_ref[2] = {0.f, 0.f};               // reference the exponentials are taken against (raw score units)
+    float limit[2] = {-INFINITY, -INFINITY};   // a score above it raises the reference; -inf: there is none yet
     float l_run[2] = {0.f, 0.f};               // this lane's share of the running sum
 
     if (t_lo < t_hi) {
@@ -249,21 +251,22 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
             }
             // The reference is raised when a score outgrows it by more than 2^8 (the same softmax; fp32 keeps its
             // relative precision), for a whole row at a time: its keys lie in the four lanes c16 + 16 i.
-            float mx[2];
             bool need = false;
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
-                mx[qb] = fmaxf(fmaxf(s[qb][0], s[qb][1]), fmaxf(s[qb][2], s[qb][3]));
-                need |= (mx[qb] > m_ref[qb]) & ((mx[qb] - m_ref[qb]) * a.c > 8.f);
-            }
+            for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) need |= s[qb][v] > limit[qb];
             if (__any(need)) {
 #pragma unroll
                 for (int qb = 0; qb < 2; ++qb) {
-                    float m = fmaxf(m_ref[qb], mx[qb]);
+                    const bool none = limit[qb] == -INFINITY;
+                    float m = fmaxf(fmaxf(s[qb][0], s[qb][1]), fmaxf(s[qb][2], s[qb][3]));
                     m = fmaxf(m, __shfl_xor(m, 16, 64));
                     m = fmaxf(m, __shfl_xor(m, 32, 64));
-                    const float alpha = m == -INFINITY ? 1.f : exp2f((m_ref[qb] - m) * a.c);
-                    m_ref[qb] = m;
+                    if (!none) m = fmaxf(m, m_ref[qb]);
+                    const float alpha = none ? 1.f : exp2f((m_ref[qb] - m) * a.c);
+                    m_ref[qb] = m == -INFINITY ? 0.f : m;
+                    limit[qb] = m == -INFINITY ? m : m + a.slack;
                     l_run[qb] *= alpha;
 #pragma unroll
                     for (int tt = 0; tt < NT; ++tt)
@@ -271,12 +274,13 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
                         for (int e = 0; e < 4; ++e) o[qb][tt][e] *= alpha;
                 }
             }
+            // (the difference first: rescales and merges weigh by differences of references, and a rounded product m c in
+            // place of m would set each wavefront off by up to half a unit of it)
             f32x4 p[2];
 #pragma unroll
             for (int qb = 0; qb < 2; ++qb) {
-                const float mc = (m_ref[qb] == -INFINITY ? 0.f : m_ref[qb]) * a.c;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) p[qb][v] = __builtin_amdgcn_exp2f(fmaf(s[qb][v], a.c, -mc));
+                for (int v = 0; v < 4; ++v) p[qb][v] = __builtin_amdgcn_exp2f((s[qb][v] - m_ref[qb]) * a.c);
                 l_run[qb] += (p[qb][0] + p[qb][1]) + (p[qb][2] + p[qb][3]);
             }
             // What a row does not see must not reach its sums through 0 x inf or 0 x NaN: keys that do not exist (the
@@ -350,7 +354,7 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
         l += __shfl_xor(l, 16, 64);
         l += __shfl_xor(l, 32, 64);
         if (lane_e < 16) {
-            sm[wave * RT + qb * 16 + c16_e] = m_ref[qb];
+            sm[wave * RT + qb * 16 + c16_e] = limit[qb] == -INFINITY ? -INFINITY : m_ref[qb];
             sl[wave * RT + qb * 16 + c16_e] = l;
         }
 #pragma unroll
@@ -604,6 +608,7 @@ hipError_t launch_attn_f32(const fdd_attn_params& p, const AttnPlan& plan, float
     a.grid_x = grid.x;
     a.per_xcd = (int)(grid.x * grid.y / kNumXCD);
     a.c = scale * 1.4426950408889634f;
+    a.slack = 8.f / a.c;
     a.causal = (p.flags & FDD_ATTN_CAUSAL_BLOCK) ? 1 : 0;
     a.qpos = p.n_q_positions > 0 ? p.q_positions : nullptr;
     a.ext_per = (p.E + KT - 1) / KT;
