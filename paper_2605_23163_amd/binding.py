@@ -9,11 +9,11 @@ from __future__ import annotations
 import ctypes as C
 import os
 
-import torch
-
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libfdd.so")
 _lib = None
+torch = None          # imported by the first call: building and importing the package need no torch
+_DTYPE_CODES = {}     # element type -> fdd_dtype, filled with it
 
 FDD_F32, FDD_BF16 = 0, 1
 FDD_ATTN_CAUSAL_BLOCK = 1
@@ -80,10 +80,18 @@ def library_path() -> str:
     return _LIB_PATH
 
 
+def _import_torch():
+    global torch
+    import torch as t
+    torch = t
+    _DTYPE_CODES.update({t.bfloat16: FDD_BF16, t.float32: FDD_F32})
+
+
 def load_library():
     """Load libfdd.so (after torch, which brings in the HIP runtime the library links against)."""
     global _lib
     if _lib is None:
+        _import_torch()
         if not os.path.exists(_LIB_PATH):
             raise FileNotFoundError(
                 f"{_LIB_PATH} is missing: build it with `python -m paper_2605_23163_amd.build` "
@@ -146,10 +154,9 @@ def _check(code):
         raise FddError(code, fdd_last_error())
 
 
-_DTYPE_CODES = {torch.bfloat16: FDD_BF16, torch.float32: FDD_F32}
-
-
 def _dtype_code(t):
+    if not _DTYPE_CODES:
+        _import_torch()
     code = _DTYPE_CODES.get(t.dtype)
     if code is None:
         raise TypeError(f"unsupported element type {t.dtype}")
