@@ -179,14 +179,39 @@ def _stream_ptr(stream):
     return stream.cuda_stream
 
 
-def _set_workspace(p, workspace, query, device):
+def _maker(stream, device, make, returned=True):
+    """``make`` (torch.empty, torch.empty_like) for memory of a call on the stream its caller named.
+
+    Torch hands freed memory to the next tensor of the stream it was allocated for.  Memory of a call on another
+    stream than the current one therefore comes from that stream's: not from tensors that work on the current stream
+    still uses, and, for scratch, not to be given away before the call has run.  Tensors that are ``returned`` are used
+    on the current stream as well, and are kept until what it holds when they are freed has run."""
+    if device.type != "cuda":
+        return make
+    current = torch.cuda.current_stream(device)
+    if stream.cuda_stream == current.cuda_stream:
+        return make
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+
+    def make_on_stream(*args, **kw):
+        with torch.cuda.stream(stream):
+            t = make(*args, **kw)
+        if returned:
+            t.record_stream(current)
+        return t
+    return make_on_stream
+
+
+def _set_workspace(p, workspace, query, device, stream):
     """The caller's workspace, whose size the library checks itself, or one of the size it asks for; returns the
     tensor, which has to live until the call has been made."""
     if workspace is None:
         need = query(C.byref(p))
         if need == 0:
             return None
-        workspace = torch.empty(need, dtype=torch.uint8, device=device)
+        new = torch.empty if stream is None else _maker(stream, device, torch.empty, returned=False)
+        workspace = new(need, dtype=torch.uint8, device=device)
     p.workspace = workspace.data_ptr()
     p.workspace_bytes = workspace.numel() * workspace.element_size()
     return workspace
@@ -233,7 +258,8 @@ def fdd_prefix_pack(prefix_v, packed=None, stream=None):
     if need == 0:
         return None
     if packed is None:
-        packed = torch.empty(need, dtype=torch.uint8, device=prefix_v.device)
+        new = torch.empty if stream is None else _maker(stream, prefix_v.device, torch.empty)
+        packed = new(need, dtype=torch.uint8, device=prefix_v.device)
     _check(lib.fdd_prefix_pack(_dev(prefix_v, "prefix_v"), L, Hkv, D, _dtype_code(prefix_v), _dev(packed, "packed"),
                                packed.numel() * packed.element_size(), _stream_ptr(stream)))
     return packed
@@ -260,7 +286,7 @@ def fdd_block_attn(q, prefix_k, prefix_v, block_k, block_v, scaffold_mask=None, 
     their rows of ``out`` are written (pass ``out`` then)."""
     lib = load_library()
     if out is None:
-        out = torch.empty_like(q)
+        out = (torch.empty_like if stream is None else _maker(stream, q.device, torch.empty_like))(q)
     p = _attn_params(q, prefix_k, prefix_v, block_k, block_v, scaffold_mask, out, scale, splits, prefix_v_packed,
                      causal_block, ext_k, ext_v, E)
     if q_positions is not None:
@@ -268,7 +294,7 @@ def fdd_block_attn(q, prefix_k, prefix_v, block_k, block_v, scaffold_mask=None, 
             raise ValueError("q_positions must be a contiguous 1-D int32 tensor")
         p.q_positions = _dev(q_positions, "q_positions")
         p.n_q_positions = q_positions.numel()
-    ws = _set_workspace(p, workspace, lib.fdd_block_attn_workspace, q.device)  # noqa: F841
+    ws = _set_workspace(p, workspace, lib.fdd_block_attn_workspace, q.device, stream)  # noqa: F841
     p.stream = _stream_ptr(stream)
     _check(lib.fdd_block_attn(C.byref(p)))
     return out
@@ -308,10 +334,10 @@ def fdd_block_attn_batched(q, prefix_k, prefix_v, block_k, block_v, out=None, sc
     prefix_v_packed [P, fdd_prefix_pack_bytes] if given.  Nothing is shared between the problems."""
     lib = load_library()
     if out is None:
-        out = torch.empty_like(q)
+        out = (torch.empty_like if stream is None else _maker(stream, q.device, torch.empty_like))(q)
     p = _batched_params(q, prefix_k, prefix_v, block_k, block_v, out, scale, splits, prefix_v_packed, causal_block,
                         ext_k, ext_v, E)
-    ws = _set_workspace(p, workspace, lib.fdd_block_attn_workspace, q.device)  # noqa: F841
+    ws = _set_workspace(p, workspace, lib.fdd_block_attn_workspace, q.device, stream)  # noqa: F841
     p.stream = _stream_ptr(stream)
     _check(lib.fdd_block_attn(C.byref(p)))
     return out
@@ -360,14 +386,15 @@ def fdd_unmask_step(logits, mask, scaffold_mask, tau, tokens, confidences=None, 
     if scaffold_mask is not None and (scaffold_mask.dtype != torch.uint8 or scaffold_mask.shape != (N, B)):
         raise TypeError("scaffold_mask must be uint8 [N,B]")
     dev = logits.device
+    new = torch.empty if stream is None else _maker(stream, dev, torch.empty)
     if confidences is None:
-        confidences = torch.empty((N, B), dtype=torch.float32, device=dev)
+        confidences = new((N, B), dtype=torch.float32, device=dev)
     if n_unmasked is None:
-        n_unmasked = torch.empty((N,), dtype=torch.int32, device=dev)
+        n_unmasked = new((N,), dtype=torch.int32, device=dev)
     if committed is None:
-        committed = torch.empty((N, B), dtype=torch.uint8, device=dev)
+        committed = new((N, B), dtype=torch.uint8, device=dev)
     p = _unmask_params(logits, mask, scaffold_mask, tokens, tau, confidences, n_unmasked, committed, refresh)
-    ws = _set_workspace(p, workspace, lib.fdd_unmask_workspace, dev)  # noqa: F841
+    ws = _set_workspace(p, workspace, lib.fdd_unmask_workspace, dev, stream)  # noqa: F841
     p.stream = _stream_ptr(stream)
     _check(lib.fdd_unmask_step(C.byref(p)))
     return tokens, confidences, n_unmasked, committed
@@ -407,10 +434,11 @@ def fdd_verify_step(ar_logits, mask, scaffold_mask, draft, tokens, n_accepted=No
         if t.dtype != dt or t.shape != (N, B):
             raise TypeError(f"{nm} must be {dt} [N,B]")
     dev = ar_logits.device
+    new = torch.empty if stream is None else _maker(stream, dev, torch.empty)
     if n_accepted is None:
-        n_accepted = torch.empty((N,), dtype=torch.int32, device=dev)
+        n_accepted = new((N,), dtype=torch.int32, device=dev)
     if accepted is None:
-        accepted = torch.empty((N, B), dtype=torch.uint8, device=dev)
+        accepted = new((N, B), dtype=torch.uint8, device=dev)
     p = VerifyParams()
     p.N, p.B, p.V, p.dtype = N, B, V, _dtype_code(ar_logits)
     p.temperature, p.seed = float(temperature), int(seed)
@@ -418,7 +446,7 @@ def fdd_verify_step(ar_logits, mask, scaffold_mask, draft, tokens, n_accepted=No
     p.scaffold_mask = _dev(scaffold_mask, "scaffold_mask")
     p.draft, p.mask, p.tokens = _dev(draft, "draft"), _dev(mask, "mask"), _dev(tokens, "tokens")
     p.n_accepted, p.accepted = _dev(n_accepted, "n_accepted"), _dev(accepted, "accepted")
-    ws = _set_workspace(p, workspace, lib.fdd_verify_workspace, dev)  # noqa: F841
+    ws = _set_workspace(p, workspace, lib.fdd_verify_workspace, dev, stream)  # noqa: F841
     p.stream = _stream_ptr(stream)
     _check(lib.fdd_verify_step(C.byref(p)))
     return tokens, n_accepted, accepted
@@ -428,7 +456,8 @@ def fdd_fork_block(src, N, dst=None, stream=None):
     """dst[n] = src for n < N: the private block state of N forked rollouts."""
     lib = load_library()
     if dst is None:
-        dst = torch.empty((N,) + tuple(src.shape), dtype=src.dtype, device=src.device)
+        new = torch.empty if stream is None else _maker(stream, src.device, torch.empty)
+        dst = new((N,) + tuple(src.shape), dtype=src.dtype, device=src.device)
     nbytes = src.numel() * src.element_size()
     if dst.numel() * dst.element_size() != N * nbytes:
         raise ValueError("dst must hold N copies of src")
@@ -471,6 +500,7 @@ def fdd_traj_mean(traj, out=None, stream=None):
     N = traj.shape[0]
     P = traj[0].numel()
     if out is None:
-        out = torch.empty(traj.shape[1:], dtype=torch.float32, device=traj.device)
+        new = torch.empty if stream is None else _maker(stream, traj.device, torch.empty)
+        out = new(traj.shape[1:], dtype=torch.float32, device=traj.device)
     _check(lib.fdd_traj_mean(N, P, _dev(traj, "traj"), _dev(out, "out"), _stream_ptr(stream)))
     return out
