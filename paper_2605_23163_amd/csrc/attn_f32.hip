@@ -17,20 +17,21 @@
 //     the rows of O^T) such that every operand is a 16-byte piece of a K or V row:
 //     the fragments come straight from global memory, no LDS, no barrier.
 //   * What bounds it: the matrix pipe (64 flop per cycle and SIMD; a 16-byte
-//     fragment load feeds 8 matrix instructions of 32 cycles, so 8 wavefronts that
-//     share nothing ask for 32 bytes per cycle and CU, half of what the vector
-//     cache delivers).  Splitting keys instead of rows over the wavefronts costs no
+//     fragment load feeds 8 matrix instructions of 32 cycles, so the four SIMDs
+//     ask for 16 bytes per cycle and CU, a quarter of what the vector cache
+//     delivers).  Splitting keys instead of rows over the wavefronts costs no
 //     time then, and makes the row tiles small: 32 rows fill the chip without (or
 //     with few) splits, whose partials would cost a pass over memory each.
 //   * A fragment register is requested again for the next tile as soon as it has
 //     been used: a whole step, 4096 cycles at D = 128, of latency is covered.
-//   * Measured at N = 8, B = 32, L = 4096, Hq = 28, Hkv = 4, D = 128 (15.1 GFLOP): 152 us,
-//     100 TFLOP/s of the 153 a large fp32 matrix product reaches here; 224 of 256 CUs
-//     are used, the matrix pipe of a used CU 78 % of its cycles, and the same loop
-//     without loads and exponentials takes 140 us.  (Scalar fused multiply-adds from
-//     LDS tiles: 687 us.)  No faster: K through a private LDS ring (157 us), the next
-//     tile's scores under this tile's exponentials (157 us), priorities that keep the
-//     two wavefronts of a SIMD level (157 us).
+//   * Measured at N = 8, B = 32, L = 4096, Hq = 28, Hkv = 4, D = 128 (15.1 GFLOP): 135 us
+//     in a loop of nothing else, 112 TFLOP/s of the 154 a large fp32 matrix product
+//     reaches here, and 149 us among the other kernels of a denoise step; 224 of 256
+//     CUs are used, the matrix pipe of a used CU 83 % of its cycles (loop of nothing
+//     else).  Scalar fused multiply-adds from LDS tiles: 687 us in a denoise step.  Not
+//     faster, when the kernel took 152 us there: K through a private LDS ring, the next
+//     tile's scores under this tile's exponentials, priorities that keep the two
+//     wavefronts of a SIMD level (157 us each).
 #include "fdd_internal.h"
 
 #include <atomic>
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[qb][t][e] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m_ref[2] = {0.f, 0.f};               // reference the exponentials are taken against (raw score units)
-    float limit[2] = {-INFINITY, -INFINITY};   // a score above it raises the reference; -inf: there is none yet
+    float limit[2] = {-INFINITY, -INFINITY};   // a score further above the reference raises it; -inf: there is none yet
     float l_run[2] = {0.f, 0.f};               // this lane's share of the running sum
 
     if (t_lo < t_hi) {
@@ -249,13 +250,18 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
                         s[qb][v] = hidden ? -INFINITY : s[qb][v];
                     }
             }
+            // Scores against the reference: the difference first, because rescales and merges weigh by differences of
+            // references, and a rounded product m c in place of m would set each wavefront off by up to half a unit of it.
             // The reference is raised when a score outgrows it by more than 2^8 (the same softmax; fp32 keeps its
             // relative precision), for a whole row at a time: its keys lie in the four lanes c16 + 16 i.
+            f32x4 p[2];
             bool need = false;
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb)
+            for (int qb = 0; qb < 2; ++qb) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) need |= s[qb][v] > limit[qb];
+                for (int v = 0; v < 4; ++v) p[qb][v] = s[qb][v] - m_ref[qb];
+                need |= fmaxf(fmaxf(p[qb][0], p[qb][1]), fmaxf(p[qb][2], p[qb][3])) > limit[qb];
+            }
             if (__any(need)) {
 #pragma unroll
                 for (int qb = 0; qb < 2; ++qb) {
@@ -266,21 +272,20 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
                     if (!none) m = fmaxf(m, m_ref[qb]);
                     const float alpha = none ? 1.f : exp2f((m_ref[qb] - m) * a.c);
                     m_ref[qb] = m == -INFINITY ? 0.f : m;
-                    limit[qb] = m == -INFINITY ? m : m + a.slack;
+                    limit[qb] = m == -INFINITY ? m : a.slack;
                     l_run[qb] *= alpha;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) p[qb][v] = s[qb][v] - m_ref[qb];
 #pragma unroll
                     for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) o[qb][tt][e] *= alpha;
                 }
             }
-            // (the difference first: rescales and merges weigh by differences of references, and a rounded product m c in
-            // place of m would set each wavefront off by up to half a unit of it)
-            f32x4 p[2];
 #pragma unroll
             for (int qb = 0; qb < 2; ++qb) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) p[qb][v] = __builtin_amdgcn_exp2f((s[qb][v] - m_ref[qb]) * a.c);
+                for (int v = 0; v < 4; ++v) p[qb][v] = __builtin_amdgcn_exp2f(p[qb][v] * a.c);
                 l_run[qb] += (p[qb][0] + p[qb][1]) + (p[qb][2] + p[qb][3]);
             }
             // What a row does not see must not reach its sums through 0 x inf or 0 x NaN: keys that do not exist (the
@@ -302,7 +307,7 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
                 for (int j = 0; j < NJ; ++j)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) x0 = fmaf(vf[j][e], 0.f, x0);
-                if (__any(x0 != 0.f)) {
+                if (__builtin_expect(__any(x0 != 0.f), 0)) {
 #pragma unroll
                     for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
