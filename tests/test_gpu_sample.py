@@ -23,7 +23,8 @@ def test_noise_bound_is_never_below_the_noise(oracle):
     w = ((~(k << np.uint32(9)) >> np.uint32(9)).astype(np.float32) + np.float32(0.5)).astype(np.float32)
     bound = (w.view(np.uint32).astype(np.float32).astype(np.float64) * -2.0 ** -23 + np.float64(np.float32(149.47223))).astype(np.float32)
     assert np.all(bound - noise > 5e-4) and bound.max() <= np.float32(23.47223)
-    assert np.all(bound[k >= 1 << 22] - noise[k >= 1 << 22] < 0.5)     # and close where an entry can win
+    for above, excess in ((0.5, 0.48), (0.875, 0.16), (0.99, 0.092)):   # and close where an entry can win
+        assert np.all(bound[u > above] - noise[u > above] < excess)
 
 
 # one position per block, so that the token of every row is seen.  V: one entry, less than a vector, rows that start at
