@@ -88,11 +88,12 @@ fdd_status check_attn_shape(const fdd_attn_params* p)
 }  // namespace
 
 // Workgroups per row tile of the fp32 path.  A round of workgroups takes ceil(tiles / (8 S)) tiles per wavefront, two
-// wavefronts per SIMD at 36 D/8 cycles of matrix pipe a tile (4.0 us per pair at D = 128), after about 4 us of start,
-// first loads and LDS merge; S > 1 adds the merge kernel (about 4 us, and the partials' way to memory and back).  The
-// smallest estimate wins, fewer splits on ties.  Measured on both sides of the choice, us per call at Hq = 28, Hkv = 4,
-// D = 128, B = 32 (choice in brackets): N = 1, L = 2048: S = 8 24.1, [9] 22.6, 12 33.7; N = 1, L = 16384: 8 78.8,
-// [9] 73.1, 12 106; N = 4, L = 4096: 1 138, [2] 80.0, 3 106; N = 8, L = 4096: [1] 139, 2 152.
+// wavefronts per SIMD at 36 D cycles a tile (32 D of them matrix pipe; 4.0 us per pair at D = 128 and 2.3 GHz), after
+// about 4 us of start, first loads and LDS merge; S > 1 adds the merge kernel (about 4 us, and the partials' way to memory
+// and back).  The smallest estimate wins, fewer splits on ties.  Measured on both sides of the choice, us per call in a loop
+// of nothing but these calls, Hq = 28, Hkv = 4, D = 128, B = 32 (choice in brackets): N = 1, L = 2048: S = 8 24.1, [9] 22.9,
+// 12 34.3; N = 1, L = 16384: 8 76.5, [9] 71.1, 12 104; N = 4, L = 4096: 1 134, [2] 77.3, 3 105; N = 8, L = 4096: [1] 135,
+// 2 149; N = 16, L = 4096: [1] 268, 2 292.
 static int f32_splits(long long row_tiles, long long tiles, int D)
 {
     const double tile_us = 2.0 * 36 * D / 2300.0;

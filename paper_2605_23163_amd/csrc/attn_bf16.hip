@@ -66,8 +66,8 @@
 //     M-tile and continue in the next one: each such segment keeps its own
 //     streaming-softmax state (m, l, o) per row.  An M-tile that was covered
 //     by a single segment is normalised and written as bf16 output directly;
-//     otherwise the segments leave fp32 partials that a second small kernel
-//     merges (log-sum-exp merge, fixed order).
+//     otherwise the segments leave their averages (bf16) and (m, l) (fp32),
+//     which a second small kernel merges (log-sum-exp merge, fixed order).
 //   * The ragged last prefix tile and the private tiles of every rollout the
 //     M-tile's rows belong to (the rows that rollout committed since the fork,
 //     then its live block: paper, "Shared prefix" and "Block-Causal

@@ -370,7 +370,7 @@ __device__ __forceinline__ void take(Best& a, float k, int idx)
 // u = 1 - w 2^-23, and -log2 u >= (1 - u) log2 e, so the noise -log2(-log2 u) is at most 23 - log2(log2 e) - log2 w;
 // log2 w in turn is at least exponent + mantissa fraction, i.e. the bits of the float w read as a fixed-point number.
 // The slack added to the constant (1e-3) is a hundred times what flog2_def and the roundings here are off by; the bound
-// exceeds the noise by 0.09 at most for u > 1/2 (the entries that can win), by more below.  fma is monotonic, so
+// exceeds the noise by less than 0.092 for u > 0.99, where most winners lie, by 0.16 above 7/8, 0.48 above 1/2 and more below.  fma is monotonic, so
 // fma(x, c, noise_bound(r)) is never below the entry's key.
 constexpr float NOISE_C = 149.47223f;          // 23 + 127 - log2(log2 e) + 1e-3
 constexpr float NOISE_MAX = 23.47223f;         // the bound at its largest (r >> 9 = 2^23 - 1)
@@ -827,8 +827,12 @@ hipError_t launch_verify(const fdd_verify_params& p, const UnmaskPlan& plan, hip
     a.seed_hi = (uint32_t)(p.seed >> 32);
     const dim3 grid((unsigned)a.units);
     if (p.temperature > 0.f) {
-        // 512 threads per piece while the pieces are so few that 256 leave SIMDs empty (1024 pieces, us: 512 threads 43, 256
-        // 42; 200 pieces of 100 KB: 26 and 33), 256 where there are more (4096 pieces: 512 threads 80, 256 71)
+        // 512 threads per piece while the pieces are so few that 256 leave SIMDs empty.  Measured, us per call with 512 / 256
+        // threads, 70 % of the rows live, V = 152064 bf16 in 4 pieces, rows with a clear winner and (without): 200 pieces
+        // 16.6/18.9 (17.9/20.3), 400 23.1/24.4 (27.2/28.2), 600 27.4/27.9 (36.0/35.7), 800 29.5/30.9 (37.4/43.4), 1024 32.4/36.3
+        // (44.6/44.3), 1280 36.9/38.5 (53.2/51.9), 1536 41.6/45.7 (56.1/59.8), 2048 49.6/50.5 (73.6/69.4), 3072 65.2/61.8
+        // (101/93).  Up to 1024 pieces 512 threads are faster or within 1 %; above, the two cross several times with the
+        // number of rounds; from 3072 on 256 are faster.  (V = 50001 in one piece: 200 28.5/36.0, 1000 63.0/62.4, 1200 66.0/66.9.)
         const bool wide = a.units <= 1024;
         if (p.dtype == FDD_BF16) {
             if (wide) hipLaunchKernelGGL((vocab_sample_kernel<uint16_t, 512>), grid, dim3(512), 0, s, a);
