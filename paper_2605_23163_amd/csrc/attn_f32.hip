@@ -27,7 +27,7 @@
 //   * Measured at N = 8, B = 32, L = 4096, Hq = 28, Hkv = 4, D = 128 (15.1 GFLOP): 135 us
 //     in a loop of nothing else, 112 TFLOP/s of the 154 a large fp32 matrix product
 //     reaches here, and 149 us among the other kernels of a denoise step; 224 of 256
-//     CUs are used, the matrix pipe of a used CU 83 % of its cycles (loop of nothing
+//     CUs are used, the matrix pipe of a used CU 84 % of its cycles (loop of nothing
 //     else).  Scalar fused multiply-adds from LDS tiles: 687 us in a denoise step.  Not
 //     faster, when the kernel took 152 us there: K through a private LDS ring, the next
 //     tile's scores under this tile's exponentials, priorities that keep the two
