@@ -832,9 +832,14 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
                 // (m, l) in fp32.  The averages lie in the order of the accumulator registers,
                 // [M-tile][segment][wavefront][register pair][lane] x 8 bf16, so every store instruction of a
                 // wavefront writes 1 KB in one piece and the merge kernel reads them the same way.
+                // The stores are written through to memory (aux 16 = device scope): the merge kernel's workgroups sit on
+                // other XCDs, and lines left dirty in the L2s go out only when the launch has ended (28 layers of N=1,
+                // L=16384: 723 -> 696 us; N=8, L=4096: 28.9 -> 27.7; plain, non-temporal and both measured).
                 const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-                const size_t pseg = (size_t)M * a.max_seg + seg;
-                u32x4* wo = reinterpret_cast<u32x4*>(a.ws_o) + (pseg * WAVES + wave) * (size_t)(2 * DB * 64) + lane;
+                const size_t pseg = (size_t)M * a.max_seg + __builtin_amdgcn_readfirstlane(seg);
+                const __amdgpu_buffer_rsrc_t o_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                    static_cast<unsigned char*>(a.ws_o) + pseg * (size_t)(MROWS * D * 2), 0, MROWS * D * 2, RSRC_FLAGS);
+                const uint32_t o_off = (uint32_t)(wave * (2 * DB * 64) + lane) * 16;
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -842,7 +847,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
                         bf16x8 w;
 #pragma unroll
                         for (int j = 0; j < 8; ++j) w[j] = (__bf16)(o[db][v2 * 8 + j] * inv);
-                        wo[(db * 2 + v2) * 64] = __builtin_bit_cast(u32x4, w);
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, w), o_rsrc, o_off + (db * 2 + v2) * 1024, 0, 16);
                     }
                 if (half == 0) {
                     const size_t prow = pseg * MROWS + (wave * 32 + l32);
@@ -909,12 +914,15 @@ __global__ __launch_bounds__(512) void vt_pack_kernel(const uint16_t* __restrict
 
 // ---------------------------------------------------------------------------
 // Merge of the segments of an M-tile (log-sum-exp merge, paper-independent arithmetic of the split):
-//   m* = max_s m_s,   W_s = l_s 2^((m_s - m*) c) / sum_t l_t 2^((m_t - m*) c),   out = sum_s W_s avg_s
+//   m* = max_s m_s,   W_s = l_s 2^((m_s - m*) c),   out = sum_s W_s avg_s / sum_s W_s
 // with avg_s the segment's own softmax average as the attention kernel left it (bf16, accumulator order).
-// The sum over s runs in a fixed order, so results are reproducible.
-// grid (M-tiles, 16 SG): a block of 256 threads = SG segment groups x 256/SG chunks of 8 channels of one
-// wavefront's 32 rows; thread (sg, chunk) sums segments sg, sg + SG, .., UX loads in flight, and the SG partial
-// sums are added in the order sg = 0, 1, .. through LDS.  SG grows when rows are few and segments many (N = 1).
+// The sums run in a fixed order, so results are reproducible.
+//
+// Bound by latency: a few MB through a launch of its own.  So a thread works alone as long as it can: it takes one
+// chunk (8 channels of a row) of every SG-th segment, requests UX averages and the (m, l) pairs that weigh them together,
+// and the SG threads of a chunk, which lie in one wavefront, meet in lane moves at the end.  No LDS, no barrier.  The
+// pairs of a row are read by the threads of all its chunks; that costs less than passing weights on.
+// grid (M-tiles, 2 DB SG x 8 / 4): 4 wavefronts of 64 / SG chunks each.
 struct MergeArgs {
     const u32x4* ws_o;
     const float* ws_ml;
@@ -922,154 +930,120 @@ struct MergeArgs {
     const int32_t* qpos;
     long long o_bs;
     int Hq, Hkv, G, R, MT, NB;
-    int max_seg, fixed_seg, TPU, base, rem;
-    int SG;
+    int max_seg, fixed_seg, TPU, rem, cut;   // cut = rem (base + 1): units of the longer ranges
+    FastDiv dMT, dHkv, dG, dBase, dBase1;
     float c;
 };
 
-// UX averages per thread and UY (m, l) pairs per thread are requested at once (what is left, if any, in loops)
-template <int D, int UX, int UY>
+// sum or maximum over the SG lanes lane % (64 / SG) + i 64 / SG, in every one of them
+template <int SG, typename Op>
+__device__ __forceinline__ float reduce_groups(float v, Op op)
+{
+    uint32_t x = __float_as_uint(v);
+    if (SG >= 8) x = __float_as_uint(op(v, __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, true))));   // row_ror:8
+    if (SG >= 4) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        x = __float_as_uint(op(__uint_as_float(r[0]), __uint_as_float(r[1])));
+    }
+    if (SG >= 2) {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        x = __float_as_uint(op(__uint_as_float(r[0]), __uint_as_float(r[1])));
+    }
+    return __uint_as_float(x);
+}
+
+template <int D, int SG, int UX>
 __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
 {
     constexpr int DB = D / 32;
     constexpr int CPW = 2 * DB * 64;          // 16-byte chunks per wavefront of the attention kernel
     constexpr int CH = 8 * CPW;               // chunks per M-tile and segment
-    extern __shared__ __align__(16) float smem[];
-    const int tid = (int)thread_id_x();
+    constexpr int CPL = 64 / SG;              // chunks per wavefront here
+    const int tid = thread_id_x();
     const int M = (int)wg_id_x();
     int n_seg = a.fixed_seg;
-    if (n_seg == 0)     // same arithmetic as the attention kernel: workgroups whose unit range meets this M-tile
-        n_seg = wg_of_unit((M + 1) * a.TPU - 1, a.base, a.rem) - wg_of_unit(M * a.TPU, a.base, a.rem) + 1;
+    if (n_seg == 0) {    // same arithmetic as the attention kernel: workgroups whose unit range meets this M-tile
+        auto owner = [&](int u) { return u < a.cut ? fast_div(u, a.dBase1) : a.rem + fast_div(u - a.cut, a.dBase); };
+        n_seg = owner((M + 1) * a.TPU - 1) - owner(M * a.TPU) + 1;
+    }
     if (n_seg == 1) return;     // written in final form by its only segment
-    const int khv = M / a.MT, mt = M - khv * a.MT;      // (problem of the batch, KV head), M-tile
-    const int pb = khv / a.Hkv, kh = khv - pb * a.Hkv;
-    const int CPB = 256 / a.SG;               // chunks per block: 32 .. 256, all of one wavefront (32 rows)
-    const int c0 = (int)wg_id_y() * CPB;
+    const int khv = fast_div(M, a.dMT), mt = M - khv * a.MT;      // (problem of the batch, KV head), M-tile
+    const int c0 = (int)wg_id_y() * (4 * CPL);                    // the block's first chunk: [wave][register pair][lane]
     const int wave = c0 / CPW;
     const int row0 = mt * 256 + wave * 32;    // first stacked row of the block's 32 rows
     if (row0 >= a.R) return;
-
-    // ---- everything is requested before anything is waited for: this thread's chunk of its first segments, and the
-    // (m, l) pairs of the block's rows, 8 threads per row
-    const int sg = tid / CPB, cl = tid - sg * CPB;
-    const int cidx = c0 + cl;                          // chunk inside the M-tile: [wave][register pair][lane]
-    const int lane = cidx & 63, i2 = (cidx >> 6) % (2 * DB);
-    const int r = lane & 31, half = lane >> 5;
+    const int lane = tid & 63, sg = lane / CPL;
+    const int cidx = c0 + (tid >> 6) * CPL + lane % CPL;
+    const int r = cidx & 31, half = (cidx >> 5) & 1, i2 = (cidx >> 6) % (2 * DB);
     const bool live = row0 + r < a.R;
-    const u32x4* src = a.ws_o + ((size_t)M * a.max_seg) * CH + cidx;
-    const int rr = tid >> 3, j8 = tid & 7;
-    const bool live_r = row0 + rr < a.R;
-    const float* ml = a.ws_ml + (((size_t)M * a.max_seg) * 256 + wave * 32 + rr) * 2;
-    float2 y[UY];
-    u32x4 x[UX];
-#pragma unroll
-    for (int u = 0; u < UY; ++u) {
-        const int s = j8 + 8 * u;
-        y[u] = make_float2(-INFINITY, 0.f);
-        if (live_r && s < n_seg) y[u] = *reinterpret_cast<const float2*>(ml + (size_t)s * 512);
-    }
-#pragma unroll
-    for (int u = 0; u < UX; ++u) {
-        const int s = sg + u * a.SG;
-        x[u] = u32x4{0u, 0u, 0u, 0u};
-        if (live && s < n_seg) x[u] = src[(size_t)s * CH];
-    }
-    __builtin_amdgcn_sched_barrier(0);
+    const u32x4* src = a.ws_o + (size_t)M * a.max_seg * CH + cidx;
+    const float* ml = a.ws_ml + ((size_t)M * a.max_seg * 256 + wave * 32 + r) * 2;
 
-    // ---- weights of the segments, per row ------------------------------------------------------
-    float* const W = smem;                            // [32][n_seg]
-    {
-        // (a segment that saw no key of this row has l = 0 and takes no part)
-        float mx = -INFINITY;
-#pragma unroll
-        for (int u = 0; u < UY; ++u) {
-            if (!(y[u].y > 0.f)) y[u].x = -INFINITY;
-            mx = fmaxf(mx, y[u].x);
-        }
-        for (int s = j8 + 8 * UY; s < n_seg; s += 8) {
-            float2 z = make_float2(-INFINITY, 0.f);
-            if (live_r) z = *reinterpret_cast<const float2*>(ml + (size_t)s * 512);
-            if (!(z.y > 0.f)) z.x = -INFINITY;
-            W[rr * n_seg + s] = z.x;
-            smem[32 * n_seg + rr * n_seg + s] = z.y;
-            mx = fmaxf(mx, z.x);
-        }
-        mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 4, 64));
-        const float mref = mx == -INFINITY ? 0.f : mx;
-        float sum = 0.f;
-#pragma unroll
-        for (int u = 0; u < UY; ++u) {
-            y[u].y *= exp2f((y[u].x - mref) * a.c);
-            sum += y[u].y;
-        }
-        for (int s = j8 + 8 * UY; s < n_seg; s += 8) {
-            const float w = smem[32 * n_seg + rr * n_seg + s] * exp2f((W[rr * n_seg + s] - mref) * a.c);
-            W[rr * n_seg + s] = w;
-            sum += w;
-        }
-        sum += __shfl_xor(sum, 1, 64);
-        sum += __shfl_xor(sum, 2, 64);
-        sum += __shfl_xor(sum, 4, 64);
-        const float inv = sum > 0.f ? 1.f / sum : 0.f;
-#pragma unroll
-        for (int u = 0; u < UY; ++u)
-            if (j8 + 8 * u < n_seg) W[rr * n_seg + j8 + 8 * u] = y[u].y * inv;
-        for (int s = j8 + 8 * UY; s < n_seg; s += 8) W[rr * n_seg + s] *= inv;
-    }
-    __syncthreads();
-
-    // ---- weighted sum of the segments' averages -------------------------------------------------
+    float m = -INFINITY, sum = 0.f;           // this thread's segments: largest m, sum of weights against it
     float acc[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-    if (live) {
-        for (int s0 = sg;;) {
+    for (int s0 = 0; s0 < n_seg; s0 += SG * UX) {
+        float2 y[UX];
+        u32x4 x[UX];
 #pragma unroll
-            for (int u = 0; u < UX; ++u) {
-                const int s = s0 + u * a.SG;
-                const float w = s < n_seg ? W[r * n_seg + s] : 0.f;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    // (a weight of 0 belongs to a segment without a key of this row: its average is 0 as well)
-                    acc[2 * j] = fmaf(__uint_as_float(x[u][j] << 16), w, acc[2 * j]);
-                    acc[2 * j + 1] = fmaf(__uint_as_float(x[u][j] & 0xffff0000u), w, acc[2 * j + 1]);
-                }
+        for (int u = 0; u < UX; ++u) {
+            const int s = s0 + sg + u * SG;
+            y[u] = make_float2(-INFINITY, 0.f);
+            x[u] = u32x4{0u, 0u, 0u, 0u};
+            if (live && s < n_seg) {
+                y[u] = *reinterpret_cast<const float2*>(ml + (size_t)s * 512);
+                x[u] = src[(size_t)s * CH];
             }
-            s0 += UX * a.SG;
-            if (s0 >= n_seg) break;
+        }
+        __builtin_amdgcn_sched_barrier(0);    // everything is requested before anything is waited for
+        float mx = m;
 #pragma unroll
-            for (int u = 0; u < UX; ++u) {
-                const int s = s0 + u * a.SG;
-                x[u] = u32x4{0u, 0u, 0u, 0u};
-                if (s < n_seg) x[u] = src[(size_t)s * CH];
+        for (int u = 0; u < UX; ++u) {
+            // (a segment that saw no key of this row has l = 0 and takes no part; its average is 0 as well)
+            if (!(y[u].y > 0.f)) y[u].x = -INFINITY;
+            mx = fmaxf(mx, y[u].x);
+        }
+        const float mref = mx == -INFINITY ? 0.f : mx;
+        if (s0 > 0) {
+            const float f = __builtin_amdgcn_exp2f((m - mref) * a.c);
+            sum *= f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] *= f;
+        }
+        m = mx;
+#pragma unroll
+        for (int u = 0; u < UX; ++u) {
+            const float w = y[u].y * __builtin_amdgcn_exp2f((y[u].x - mref) * a.c);
+            sum += w;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc[2 * j] = fmaf(__uint_as_float(x[u][j] << 16), w, acc[2 * j]);
+                acc[2 * j + 1] = fmaf(__uint_as_float(x[u][j] & 0xffff0000u), w, acc[2 * j + 1]);
             }
         }
     }
-    if (a.SG > 1) {
-        float* const red = smem + 2 * 32 * n_seg;     // [SG][CPB][8]
-        __syncthreads();
+    if (SG > 1) {
+        const float mx = reduce_groups<SG>(m, [](float p, float q) { return fmaxf(p, q); });
+        const float f = __builtin_amdgcn_exp2f((m - (mx == -INFINITY ? 0.f : mx)) * a.c);
+        auto add = [](float p, float q) { return p + q; };
+        sum = reduce_groups<SG>(sum * f, add);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) red[(sg * CPB + cl) * 8 + j] = acc[j];
-        __syncthreads();
-        if (sg != 0) return;
-        for (int k = 1; k < a.SG; ++k)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] += red[(k * CPB + cl) * 8 + j];
+        for (int j = 0; j < 8; ++j) acc[j] = reduce_groups<SG>(acc[j] * f, add);
     }
-    if (!live) return;
+    if (!live || sg != 0) return;
+    const float inv = sum > 0.f ? 1.f / sum : 0.f;
+    const int pb = fast_div(khv, a.dHkv), kh = khv - pb * a.Hkv;
     const int row = row0 + r;
-    const int sel = row / a.G, g = row - sel * a.G;
+    const int sel = fast_div(row, a.dG), g = row - sel * a.G;
     const int nb = a.qpos ? min(max(a.qpos[sel], 0), a.NB - 1) : sel;
-    const int db = i2 >> 1, v2 = i2 & 1;
-    uint16_t* op = a.out + pb * a.o_bs + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * D + db * 32 + v2 * 16 + half * 4;
+    uint16_t* op = a.out + pb * a.o_bs + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * D + (i2 >> 1) * 32 + (i2 & 1) * 16 + half * 4;
     typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
     bf16x4 lo, hi;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        lo[j] = (__bf16)acc[j];
-        hi[j] = (__bf16)acc[4 + j];
+        lo[j] = (__bf16)(acc[j] * inv);
+        hi[j] = (__bf16)(acc[4 + j] * inv);
     }
     *reinterpret_cast<bf16x4*>(op) = lo;
     *reinterpret_cast<bf16x4*>(op + 8) = hi;
@@ -1175,29 +1149,42 @@ hipError_t launch_attn_merge_bf16(const fdd_attn_params& p, const AttnPlan& plan
     const int batch = p.batch > 1 ? p.batch : 1;
     a.Hq = p.Hq; a.Hkv = p.Hkv; a.G = plan.G; a.R = plan.R; a.MT = plan.MT; a.NB = p.N * p.B;
     a.max_seg = plan.max_seg; a.fixed_seg = plan.uniform; a.TPU = plan.TPU;
-    a.base = (int)(plan.U / plan.W); a.rem = (int)(plan.U % plan.W);
+    const int base = (int)(plan.U / plan.W);
+    a.rem = (int)(plan.U % plan.W);
+    a.cut = a.rem * (base + 1);
+    a.dMT = make_fastdiv((uint32_t)a.MT);
+    a.dHkv = make_fastdiv((uint32_t)a.Hkv);
+    a.dG = make_fastdiv((uint32_t)a.G);
+    a.dBase = make_fastdiv((uint32_t)(base > 0 ? base : 1));
+    a.dBase1 = make_fastdiv((uint32_t)(base + 1));
     a.c = scale * 1.4426950408889634f;
-    // more threads per chunk when the rows are few and the segments many
-    const long long rows = (long long)p.Hkv * batch * plan.R;
-    const int seg_hint = plan.uniform > 0 ? plan.uniform : plan.max_seg;
+    if (plan.mtile_rows != 256) return hipErrorInvalidValue;
+    // SG threads per chunk: more of them while the chunks of a call leave most of the chip's lanes idle and each still has
+    // four segments or more to request.  us per call (replayed) with 1, 2, 4, 8 of them: N=1, L=16384 (52 segments, 14 k
+    // chunks) 28.3, 25.2, 23.8, 23.6; N=4, L=8192 (18, 57 k) 28.8, 28.5, 28.4, 29.0; N=8, L=4096 (9, 115 k) 27.3, 27.5,
+    // 27.7, 28.8; N=16, L=4096 (2, 459 k) 70.0, 71.5, 73.4, 81.6.
+    const long long chunks = (long long)p.Hkv * batch * plan.R * (p.D / 8);
+    const int n = plan.uniform > 0 ? plan.uniform : plan.max_seg;
     int sg = 1;
-    while (sg < 8 && sg * 2 <= seg_hint && rows * sg < 16384) sg *= 2;
-    a.SG = sg;
-    const int chunks = 8 * 2 * (p.D / 32) * 64;
-    const size_t smem = ((size_t)2 * 32 * plan.max_seg + (sg > 1 ? (size_t)256 * 8 : 0)) * sizeof(float);
-    if (smem > 60 * 1024 || plan.mtile_rows != 256) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(p.Hkv * batch * plan.MT), (unsigned)(chunks / (256 / sg)));
-    // A thread requests its share of the segments at once where registers allow: with 52 segments (N=1, L=16384) one
-    // latency instead of seven, 8.3 -> 6.4 us; but for 2..9 segments the loads that are not there cost more than they
-    // save (N=16, two segments: 8 + 8 9.7 us, 2 + 1 6.8, before 7.3; N=8, nine segments: 9.7, 4 + 2 6.6, before 8.2).
-    auto go = [&](auto d) {
-        constexpr int D = decltype(d)::value;
-        if (plan.max_seg <= 8 && plan.max_seg <= 2 * sg) hipLaunchKernelGGL((attn_merge_bf16_kernel<D, 2, 1>), grid, dim3(256), smem, s, a);
-        else if (plan.max_seg <= 16 && plan.max_seg <= 4 * sg) hipLaunchKernelGGL((attn_merge_bf16_kernel<D, 4, 2>), grid, dim3(256), smem, s, a);
-        else hipLaunchKernelGGL((attn_merge_bf16_kernel<D, 8, 8>), grid, dim3(256), smem, s, a);
+    while (sg < 8 && sg * 8 <= n && chunks * sg * 2 <= (1 << 17)) sg *= 2;
+    auto go = [&](auto d, auto sgc, auto ux) {
+        constexpr int D = decltype(d)::value, SG = decltype(sgc)::value, UX = decltype(ux)::value;
+        const dim3 grid((unsigned)(p.Hkv * batch * plan.MT), (unsigned)(8 * 2 * (D / 32) * SG / 4));
+        hipLaunchKernelGGL((attn_merge_bf16_kernel<D, SG, UX>), grid, dim3(256), 0, s, a);
     };
-    if (p.D == 128) go(std::integral_constant<int, 128>());
-    else go(std::integral_constant<int, 64>());
+    auto sized = [&](auto d) {
+        const std::integral_constant<int, 1> i1;
+        const std::integral_constant<int, 2> i2;
+        const std::integral_constant<int, 4> i4;
+        const std::integral_constant<int, 8> i8;
+        if (sg == 8) go(d, i8, i8);
+        else if (sg == 4) go(d, i4, i8);
+        else if (sg == 2) go(d, i2, i4);
+        else if (n > 2) go(d, i1, i4);
+        else go(d, i1, i2);
+    };
+    if (p.D == 128) sized(std::integral_constant<int, 128>());
+    else sized(std::integral_constant<int, 64>());
     return hipGetLastError();
 }
 
