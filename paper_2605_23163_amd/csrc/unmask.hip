@@ -35,9 +35,12 @@ namespace fdd {
 namespace {
 
 constexpr float LOG2E = 1.4426950408889634f;
-constexpr int RTHREADS = 256;
-constexpr int UNROLL = 6;            // 16-byte loads in flight per thread
 constexpr int PIECE_KB = 64;         // a row is cut into pieces of at least this size ...
+constexpr int PIECE_KB_FEW = 16;     // A call of few rows takes up to 8 pieces a row, of at least this size and up to
+constexpr int kFewPieces = 1024;     // this number in all.  us per call with a fork, replayed, unmask / sampled verifier:
+                                     // V = 152064 bf16, N=4, B=32, 4 pieces 13.5/28.0, 8 13.1/20.5, 16 14.9/25.9; N=1, 1 piece
+                                     // 19.4/43.8, 4 11.2/19.7, 8 11.2/14.8, 16 12.6/17.0; V = 50001, 200 rows, 1 piece 12.5/28.8,
+                                     // 5 11.5/21.5, 8 12.6/24.5; V = 32768, 128 rows, 1 10.4/17.4, 4 8.7/13.4, 8 9.8/12.7.
 constexpr int PIECE_KB_ARGMAX = 32;  // ... and of this size in the pass that takes no sums (measured: 8 pieces of a
                                      // 297 KB row are 1.5 us per call faster there than 4, and 1..2 us slower with the sums)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -67,6 +70,7 @@ struct Args {
     int rf_T, rf_row_vecs;  // table rows; 16-byte pieces per K/V row (0: no refresh)
     int N, B, vsplits;
     int units;              // workgroups of a vocabulary pass: N B vsplits
+    int compact;            // workgroups are dealt to eligible rows only
     int per;                // vocabulary entries per piece (the last pieces of a row may be shorter or empty)
     FastDiv dVs;            // division by vsplits
     long long V;
@@ -180,13 +184,62 @@ __device__ __forceinline__ Run settle(const ThreadRun& t)
 
 __device__ __forceinline__ float bf16_to_f32(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
 
-// Workgroups are dealt to the 8 XCDs round-robin by launch index, and a workgroup whose row is
-// not eligible leaves at once.  With (row, piece) = (index / vsplits, index % vsplits) an XCD
-// would always get rows of the same residue, and a scaffold pattern that repeats from rollout
-// to rollout (it does: the schema is shared) would load the XCDs unequally.  So each group of 8
-// consecutive indices is rotated, by an amount that changes from group to group, from 8 groups to the
-// next 8 and from 64 to the next 64 (a rotation by the group's number alone repeats with the pattern:
-// config 5's 720 eligible rows of 4 pieces then give the XCDs 304..416 workgroups instead of 360 each).
+// Which (row, piece) a workgroup of a vocabulary pass takes: workgroup u the piece u mod vsplits of the (u / vsplits)-th
+// ELIGIBLE row, so that the live workgroups come first and together, and the dispatcher deals them out evenly.  (With
+// row = u / vsplits, workgroups of rows that are not eligible left at once, but not before they had been dealt a place:
+// a scaffold pattern, which all rollouts share, left some compute units with several live workgroups and others with
+// none.  N=8, B=32, V=152064, half the rows eligible, with a fork, replayed: 18.7 -> 15.7 us,
+// the sampled verifier 30.8 -> 27.9.  Nothing is gained up to 512 pieces, which are two to a compute unit, and from about 3000
+// on, where so many even out: N=16, B=64 41.1 -> 42.1; those go by `unit_of_workgroup` below.)  Every wavefront counts for itself: a lane
+// looks at 16 positions, ballots give the counts before it, no LDS and no barrier; mask and scaffold are read in one
+// round trip.  Returns -1 past the last eligible row. Up to LIVE_ROWS rows,
+// which a wavefront reads at once.
+constexpr int LIVE_ROWS = 1024;
+__device__ __forceinline__ int eligible_row(const uint8_t* mask, const uint8_t* scaffold, int rows, int target)
+{
+    const int lane = thread_id_x() & 63;
+    const int at = lane * 16, p = min(at, rows - 16), drop = at - p;         // (drop: positions the lanes below have already)
+    const uint8_t* const sc = scaffold ? scaffold : mask;
+    const uint32_t use_sc = scaffold ? ~0u : 0u;
+    uint32_t m[4], s[4];
+    __builtin_memcpy(m, mask + p, 16);    // (positions start anywhere: the loads need no alignment)
+    __builtin_memcpy(s, sc + p, 16);
+    uint32_t z[4];                        // 0x80 in the bytes of eligible positions
+    int c = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const uint32_t t = (m[w] ^ 0x01010101u) | (s[w] & use_sc);                    // zero bytes: mask 1, no scaffold
+        const uint32_t e = ~(((t & 0x7f7f7f7fu) + 0x7f7f7f7fu) | t | 0x7f7f7f7fu);
+        z[w] = drop >= 4 * w + 4 ? 0u : drop <= 4 * w ? e : e & (~0u << (8 * (drop - 4 * w)));
+        c += __builtin_popcount(z[w]);
+    }
+    int before = 0;                       // eligible positions of the lanes below
+#pragma unroll
+    for (int b = 0; b < 5; ++b) {
+        const uint64_t has = __builtin_amdgcn_ballot_w64((c >> b) & 1);
+        before += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u)) << b;
+    }
+    const uint64_t here = __builtin_amdgcn_ballot_w64(before <= target && target < before + c);
+    if (here == 0) return -1;
+    const int l = __builtin_ctzll(here);
+    int left = target - __builtin_amdgcn_readlane(before, l);
+    const int first = __builtin_amdgcn_readlane(p, l);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)z[w], l);
+        const int n = __builtin_popcount(e);
+        if (left < n) {
+            for (; left > 0; --left) e &= e - 1;
+            return first + 4 * w + (__builtin_ctz(e) >> 3);
+        }
+        left -= n;
+    }
+    return -1;
+}
+
+// Other calls: each group of 8 consecutive launch indices (workgroups are dealt to the 8 XCDs round-robin) is
+// rotated, by an amount that changes from group to group, from 8 groups to the next 8 and from 64 to the next, so that a
+// scaffold pattern that repeats from rollout to rollout does not load the XCDs unequally.
 __device__ __forceinline__ unsigned unit_of_workgroup(unsigned n_units)
 {
     const unsigned u = wg_id_x(), g = u >> 3;
@@ -194,15 +247,29 @@ __device__ __forceinline__ unsigned unit_of_workgroup(unsigned n_units)
     return (g << 3) + ((u + g + (g >> 3) + (g >> 6) + (g >> 9)) & 7u);
 }
 
+// the row and the piece of this workgroup; false: nothing to do
+__device__ __forceinline__ bool unit_of(const Args& a, int* row, int* piece)
+{
+    if (a.compact) {
+        const int u = (int)wg_id_x(), t = fast_div(u, a.dVs);
+        *piece = u - t * a.vsplits;
+        *row = eligible_row(a.mask, a.scaffold, a.N * a.B, t);
+        return *row >= 0;
+    }
+    const int u = (int)unit_of_workgroup((unsigned)a.units);
+    *row = fast_div(u, a.dVs);
+    *piece = u - *row * a.vsplits;
+    return a.mask[*row] == 1 && !(a.scaffold && a.scaffold[*row]);
+}
+
 // T = uint16_t (bf16 bits) or float; SUM = false leaves (max, arg max) only and a sum of 0
-template <typename T, bool SUM>
-__global__ __launch_bounds__(RTHREADS) void vocab_reduce_kernel(Args a)
+template <typename T, bool SUM, int THREADS>
+__global__ __launch_bounds__(THREADS) void vocab_reduce_kernel(Args a)
 {
     constexpr int VEC = 16 / sizeof(T);
-    const unsigned unit = unit_of_workgroup((unsigned)a.units);
-    const int row = fast_div((int)unit, a.dVs);
-    if (a.mask[row] != 1 || (a.scaffold && a.scaffold[row])) return;
-    const int piece = (int)unit - row * a.vsplits;
+    constexpr int UNROLL = THREADS == 512 ? 5 : 6;      // 16-byte loads in flight per thread
+    int row, piece;
+    if (!unit_of(a, &row, &piece)) return;
     const long long v_lo = (long long)piece * a.per;
     const long long v_hi = min(a.V, v_lo + a.per);
     const T* base = static_cast<const T*>(a.logits) + (size_t)row * (size_t)a.V;
@@ -246,10 +313,10 @@ __global__ __launch_bounds__(RTHREADS) void vocab_reduce_kernel(Args a)
         };
         // UNROLL independent 16-byte loads in flight per thread, absorbed in ascending order
         long long i = tid;
-        for (; i + (UNROLL - 1) * RTHREADS < nvec; i += UNROLL * RTHREADS) {
+        for (; i + (UNROLL - 1) * THREADS < nvec; i += UNROLL * THREADS) {
             u32x4 raw[UNROLL];
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) raw[u] = __builtin_nontemporal_load(vp + i + u * RTHREADS);
+            for (int u = 0; u < UNROLL; ++u) raw[u] = __builtin_nontemporal_load(vp + i + u * THREADS);
             // all of them are requested before the first is waited for (left to itself the scheduler waits
             // for the first after two requests and only then issues the rest: two latencies per group)
             __builtin_amdgcn_sched_barrier(0);
@@ -257,7 +324,7 @@ __global__ __launch_bounds__(RTHREADS) void vocab_reduce_kernel(Args a)
             for (int u = 0; u < UNROLL; ++u) {
                 float x[VEC];
                 widen(raw[u], x);
-                absorb<VEC, SUM>(tr, x, (int)(body0 + (i + u * RTHREADS) * VEC));
+                absorb<VEC, SUM>(tr, x, (int)(body0 + (i + u * THREADS) * VEC));
             }
         }
         if (i < nvec) {
@@ -265,13 +332,13 @@ __global__ __launch_bounds__(RTHREADS) void vocab_reduce_kernel(Args a)
             u32x4 raw[UNROLL - 1];
 #pragma unroll
             for (int u = 0; u < UNROLL - 1; ++u)
-                if (i + u * RTHREADS < nvec) raw[u] = __builtin_nontemporal_load(vp + i + u * RTHREADS);
+                if (i + u * THREADS < nvec) raw[u] = __builtin_nontemporal_load(vp + i + u * THREADS);
 #pragma unroll
             for (int u = 0; u < UNROLL - 1; ++u) {
-                if (i + u * RTHREADS < nvec) {
+                if (i + u * THREADS < nvec) {
                     float x[VEC];
                     widen(raw[u], x);
-                    absorb<VEC, SUM>(tr, x, (int)(body0 + (i + u * RTHREADS) * VEC));
+                    absorb<VEC, SUM>(tr, x, (int)(body0 + (i + u * THREADS) * VEC));
                 }
             }
         }
@@ -283,19 +350,19 @@ __global__ __launch_bounds__(RTHREADS) void vocab_reduce_kernel(Args a)
         }
     }
 
-    // wavefront reduction, then across the 4 wavefronts through LDS
+    // wavefront reduction, then across the wavefronts through LDS
     Run r = SUM ? settle(tr) : tr.r;
     const float m_wave = wave_max(r.m);
     if (SUM) r.s = wave_sum(r.m == m_wave ? r.s : r.s * fast_exp2((r.m - m_wave) * LOG2E));
     r.idx = wave_min(r.m == m_wave ? r.idx : 0x7fffffff);
     r.m = m_wave;
-    __shared__ Run part[RTHREADS / 64];
+    __shared__ Run part[THREADS / 64];
     if ((tid & 63) == 0) part[tid >> 6] = r;
     __syncthreads();
     if (tid == 0) {
         Run t = part[0];
 #pragma unroll
-        for (int w = 1; w < RTHREADS / 64; ++w) merge(t, part[w]);
+        for (int w = 1; w < THREADS / 64; ++w) merge(t, part[w]);
         Partial p;
         p.m = t.m;
         p.arg = t.idx;
@@ -399,10 +466,8 @@ __global__ __launch_bounds__(VTHREADS) void vocab_sample_kernel(Args a)
 {
     constexpr int VEC = 16 / sizeof(T);
     constexpr int NW = VEC + 4;               // generator words that cover VEC entries starting anywhere
-    const unsigned unit = unit_of_workgroup((unsigned)a.units);
-    const int row = fast_div((int)unit, a.dVs);
-    if (a.mask[row] != 1 || (a.scaffold && a.scaffold[row])) return;
-    const int piece = (int)unit - row * a.vsplits;
+    int row, piece;
+    if (!unit_of(a, &row, &piece)) return;
     const long long v_lo = (long long)piece * a.per;
     const long long v_hi = min(a.V, v_lo + a.per);
     const T* base = static_cast<const T*>(a.logits) + (size_t)row * (size_t)a.V;
@@ -588,7 +653,7 @@ __global__ __launch_bounds__(STHREADS) void block_select_kernel(Args a)
         // The first pieces' records are requested together with the mask bytes, not after them: whether the
         // position is eligible is known one memory round trip later, and the records are then already there.
         // (records of positions that are not eligible hold whatever an earlier call left; they are not used)
-        constexpr int PRE = 4;
+        constexpr int PRE = 8;
         const u32x4* pr = reinterpret_cast<const u32x4*>(a.ws + i * a.vsplits);
         u32x4 rec[PRE];
 #pragma unroll
@@ -759,6 +824,8 @@ bool make_vocab_plan(int N, int B, long long V, int dtype, bool argmax_only, Unm
     long long want = (8192 + rows - 1) / rows;  // enough workgroups to fill 256 CUs several times
     if (want < 1) want = 1;
     long long vs = want < by_size ? want : by_size;
+    const long long small = std::min({(p.V * es) / (PIECE_KB_FEW * 1024), kFewPieces / rows, 8ll});
+    if (vs < small) vs = small;
     if (vs > 64) vs = 64;
     plan->vsplits = (int)vs;
     plan->ws_bytes = (size_t)rows * (size_t)vs * sizeof(Partial);
@@ -772,9 +839,28 @@ static void set_pieces(Args& a, int vsplits, long long V)
     a.vsplits = vsplits;
     a.units = a.N * a.B * vsplits;
     a.V = V;
+    a.compact = a.N * a.B >= 16 && a.N * a.B <= LIVE_ROWS && a.units > 512 && a.units <= 2560;
     const long long per = (V + vsplits - 1) / vsplits;
     a.per = (int)std::min<long long>((per + 63) / 64 * 64, V);
     a.dVs = make_fastdiv((uint32_t)vsplits);
+}
+
+// Threads per piece: 512 from 48 KB on (its loads in two groups instead of four, and twice the wavefronts for the few
+// workgroups of a small call), 256 below, where a group of 512 is mostly empty.  Measured, us per unmask call with a fork,
+// replayed, 256 / 512: pieces of 76 KB, 128 live rows 15.7/15.1, 720 43.2/41.1, 2867 137.7/134.5; 50 KB, 1024 rows (half of
+// them live) 18.4/17.1; 33 KB 17.8/19.8; 16 KB, 128 rows 11.1/12.0.
+template <bool SUM>
+static void launch_reduce(const Args& a, int dtype, hipStream_t s)
+{
+    const dim3 grid((unsigned)a.units);
+    const bool wide = (long long)a.per * (dtype == FDD_BF16 ? 2 : 4) >= 48 * 1024;
+    if (dtype == FDD_BF16) {
+        if (wide) hipLaunchKernelGGL((vocab_reduce_kernel<uint16_t, SUM, 512>), grid, dim3(512), 0, s, a);
+        else hipLaunchKernelGGL((vocab_reduce_kernel<uint16_t, SUM, 256>), grid, dim3(256), 0, s, a);
+    } else {
+        if (wide) hipLaunchKernelGGL((vocab_reduce_kernel<float, SUM, 512>), grid, dim3(512), 0, s, a);
+        else hipLaunchKernelGGL((vocab_reduce_kernel<float, SUM, 256>), grid, dim3(256), 0, s, a);
+    }
 }
 
 hipError_t launch_unmask(const fdd_unmask_params& p, const UnmaskPlan& plan, hipStream_t s)
@@ -798,9 +884,7 @@ hipError_t launch_unmask(const fdd_unmask_params& p, const UnmaskPlan& plan, hip
     a.N = p.N; a.B = p.B; a.tau = p.tau;
     set_pieces(a, plan.vsplits, p.V);
     a.c = 0.f; a.seed_lo = 0u; a.seed_hi = 0u;
-    const dim3 grid((unsigned)a.units);
-    if (p.dtype == FDD_BF16) hipLaunchKernelGGL((vocab_reduce_kernel<uint16_t, true>), grid, dim3(RTHREADS), 0, s, a);
-    else hipLaunchKernelGGL((vocab_reduce_kernel<float, true>), grid, dim3(RTHREADS), 0, s, a);
+    launch_reduce<true>(a, p.dtype, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(block_select_kernel, dim3(p.N), dim3(STHREADS), 0, s, a);
@@ -833,7 +917,8 @@ hipError_t launch_verify(const fdd_verify_params& p, const UnmaskPlan& plan, hip
         // (44.6/44.3), 1280 36.9/38.5 (53.2/51.9), 1536 41.6/45.7 (56.1/59.8), 2048 49.6/50.5 (73.6/69.4), 3072 65.2/61.8
         // (101/93).  Up to 1024 pieces 512 threads are faster or within 1 %; above, the two cross several times with the
         // number of rounds; from 3072 on 256 are faster.  (V = 50001 in one piece: 200 28.5/36.0, 1000 63.0/62.4, 1200 66.0/66.9.)
-        const bool wide = a.units <= 1024;
+        // (Pieces below 32 KB leave a group of 512 threads' loads mostly empty: V = 50001 in 5, 200 rows 23.3/21.5 with a fork.)
+        const bool wide = a.units <= 1024 && (long long)a.per * (p.dtype == FDD_BF16 ? 2 : 4) >= 32 * 1024;
         if (p.dtype == FDD_BF16) {
             if (wide) hipLaunchKernelGGL((vocab_sample_kernel<uint16_t, 512>), grid, dim3(512), 0, s, a);
             else hipLaunchKernelGGL((vocab_sample_kernel<uint16_t, 256>), grid, dim3(256), 0, s, a);
@@ -843,8 +928,7 @@ hipError_t launch_verify(const fdd_verify_params& p, const UnmaskPlan& plan, hip
         }
     } else {
         // greedy verifier: step 3 of scaffold speculative decoding compares arg maxima only, so no exponentials
-        if (p.dtype == FDD_BF16) hipLaunchKernelGGL((vocab_reduce_kernel<uint16_t, false>), grid, dim3(RTHREADS), 0, s, a);
-        else hipLaunchKernelGGL((vocab_reduce_kernel<float, false>), grid, dim3(RTHREADS), 0, s, a);
+        launch_reduce<false>(a, p.dtype, s);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
