@@ -115,19 +115,18 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
     AttnPlan pl;
     pl.G = p.Hq / p.Hkv;
     pl.R = (p.n_q_positions > 0 ? p.n_q_positions : p.N * p.B) * pl.G;
-    if (p.dtype == FDD_BF16) {
-        pl.mtile_rows = 256;
-        pl.key_tile = 64;
-    } else {
-        pl.mtile_rows = kF32RowTile;
-        pl.key_tile = 16;
-    }
-    pl.MT = (pl.R + pl.mtile_rows - 1) / pl.mtile_rows;
+    pl.key_tile = p.dtype == FDD_BF16 ? 64 : 16;
     pl.TP = (p.L + pl.key_tile - 1) / pl.key_tile;
     const int batch = p.batch > 1 ? p.batch : 1;
-    const long long NM = (long long)p.Hkv * batch * pl.MT;
+    long long NM;
+    auto set_rows = [&](int rows) {
+        pl.mtile_rows = rows;
+        pl.MT = (pl.R + rows - 1) / rows;
+        NM = (long long)p.Hkv * batch * pl.MT;
+    };
     bool partials;
-    if (p.dtype == FDD_BF16) {
+    auto cut_bf16 = [&](int rows) {
+        set_rows(rows);
         // The private tiles of an M-tile (extension and block of every rollout its rows belong to) are done
         // by the workgroup that ends the M-tile's key range, one after the other and at about 1.8 times the
         // cost of a pipelined prefix tile.  They are booked as `wt` extra units at the end of the M-tile's
@@ -142,9 +141,9 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
         if (wt < 1) wt = 1;
         if (wt > 64) wt = 64;
         auto pieces_for = [&](long long tpu) {
-            // equal pieces per M-tile, at least two units each; the fewest pieces that reach the shortest critical path
+            // equal pieces per M-tile, of two units or more (one of them may have less); the fewest pieces that reach the shortest critical path
             long long smax = NM > 0 ? kNumCU / NM : 0;
-            if (smax > tpu / 2) smax = tpu / 2;
+            if (smax > (tpu + 1) / 2) smax = (tpu + 1) / 2;
             if (smax < 1) return 0ll;
             const long long crit = (tpu + smax - 1) / smax;
             long long sbest = smax;
@@ -161,8 +160,10 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
         } else {
             // Equal pieces per M-tile when that fills at least 4/5 of the compute
             // units: the workgroups of an XCD then walk the same K/V tiles in step
-            // and the prefix is fetched from HBM once.  Otherwise equal contiguous
-            // unit ranges (stream-K), two units or more per workgroup.
+            // and the prefix is fetched from HBM once.  So are calls of fewer than two units per compute unit, which
+            // leave some idle either way: a range that crosses into the next M-tile does two set-ups and two partial
+            // results for its two units (us per call, ranges / pieces: N=1, L=64 13.5/9.3; N=8, L=64 17.3/11.7; N=1, L=700
+            // 13.5/12.6).  Otherwise equal contiguous unit ranges (stream-K).
             long long s = pieces_for(pl.TP + wt);
             if (s >= 1) {
                 const long long per = (pl.TP + wt) / s;       // a piece must not lie inside the booked units only
@@ -171,8 +172,8 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
             }
             pl.TPU = pl.TP + (int)wt;
             long long smax = NM > 0 ? kNumCU / NM : 0;
-            if (smax > pl.TPU / 2) smax = pl.TPU / 2;
-            if (s >= 1 && NM * smax * 5 >= (long long)kNumCU * 4) {
+            if (smax > (pl.TPU + 1) / 2) smax = (pl.TPU + 1) / 2;
+            if (s >= 1 && (NM * smax * 5 >= (long long)kNumCU * 4 || NM * pl.TPU < 2 * kNumCU)) {
                 w = NM * s;
                 pl.uniform = (int)s;
             } else {
@@ -194,7 +195,25 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
         const long long upw = pl.U / pl.W;
         pl.max_seg = pl.uniform > 0 ? pl.uniform : (int)((pl.TPU + upw - 1) / upw) + 1;
         partials = pl.W != NM;
+    };
+    if (p.dtype == FDD_BF16) {
+        cut_bf16(256);
+        // M-tiles of 128 rows (workgroups of 4 wavefronts, one per SIMD) while the call is short: a wavefront alone on its SIMD
+        // takes 0.86 us a tile where two take 1.33 (D = 128, few workgroups), a workgroup starts on three half tiles instead of
+        // seven, and the segments are half as large.  Two wavefronts per SIMD do more per second, so with many units per
+        // compute unit, or where only the larger tiles cut into equal pieces that fill the chip, those are faster.  us per call
+        // (replayed), 256 / 128 rows, Hq = 28, Hkv = 4, B = 32, with units per compute unit of the 256-row plan in brackets:
+        // D = 128: N=1, L=2048 [0.6] 14.0/10.5; N=12, L=3000 [8.5] 31.6/28.9; N=8, L=4096 [7.5] 29.4/27.4, L=6000 [10.8]
+        // 35.0/35.5; N=4, L=8192 [7.3] 28.2/26.7, L=12000 [10.5] 33.2/34.3; N=2, L=32768 [14] 40.4/43.3; N=24, L=1024 [6.9, no
+        // equal pieces of 128 rows] 27.4/29.4; Hq = Hkv = 8, N=20, L=2000 [3.5] 32.1/21.7.  D = 64 (half the matrix work per
+        // exponential): N=1, L=8192 [2] 13.4/11.2, N=8, L=4096 [7.5] 19.8/20.2, N=16, L=4096 [15] 27.9/32.7.
+        const int uniform256 = pl.uniform;
+        if (pl.U <= (p.D == 128 ? 9 : 5) * (long long)kNumCU) {
+            cut_bf16(128);
+            if (pl.uniform == 0 && (uniform256 > 0 || NM > kNumCU)) cut_bf16(256);
+        }
     } else {
+        set_rows(kF32RowTile);
         pl.TPU = pl.TP > 0 ? pl.TP : 1;
         pl.U = NM * pl.TPU;
         const long long rows_per_rollout = std::max(1ll, (long long)pl.R / p.N);

@@ -56,6 +56,10 @@
 //     exceed 1, which fp32 sums and bf16 relative precision do not mind, and
 //     the accumulator rescale becomes a rare wave-uniform branch.  The result
 //     is mathematically the same softmax.
+//   * A workgroup has 8 wavefronts (M-tiles of 256 rows, a ring of 4 slots per
+//     operand) or, where a call is short, 4 (128 rows, 2 slots, one wavefront
+//     per SIMD): the plan chooses (see make_attn_plan).  With 2 slots K of tile
+//     i+2 and V of tile i+1 are requested in step i and awaited at its end.
 //   * Work is dealt out in units of one 64-key prefix tile of one M-tile.
 //     Either every M-tile is cut into S equal pieces (workgroups numbered so
 //     that an XCD owns all M-tiles of one (KV head, piece): they walk the same
@@ -89,7 +93,6 @@ typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
 
 constexpr int ODD_XCD_WEIGHT = 97;   // share of a piece on an odd XCD, in per cent of one on an even XCD (measured: 96..98 alike)
 constexpr int KT = 64;           // keys per tile
-constexpr int NB = 4;            // ring slots per operand in LDS
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
 // Kernel arguments.  They are read from memory with scalar loads, a 64-byte line at a time, and every
@@ -138,6 +141,7 @@ struct Args {
 template <int D, int WAVES>
 struct Cfg {
     static constexpr int THREADS = WAVES * 64;
+    static constexpr int NB = WAVES == 8 ? 4 : 2;        // ring slots per operand in LDS (a power of two)
     // 64 x D tiles, unpadded, moved global -> LDS in 1 KB pieces, one per wavefront instruction
     static constexpr int T_BYTES = KT * D * 2;
     static constexpr int NI = T_BYTES / 1024 / WAVES;    // pieces per wavefront and tile
@@ -148,7 +152,7 @@ struct Cfg {
     static constexpr int V_RING = NB * T_BYTES;          // LDS offset of the V ring (the K ring starts at 0)
     static constexpr int LDS_BYTES = 2 * NB * T_BYTES;
     static_assert(NI >= 1 && T_BYTES % (1024 * WAVES) == 0, "tile must divide over the wavefronts");
-    static_assert(3 * IPT < 64, "outstanding loads must fit the counter");
+    static_assert((NB - 1) * IPT < 64, "outstanding loads must fit the counter");
 };
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -184,10 +188,11 @@ __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "mem
 #define FDD_PIN(x) asm volatile("" : "+v"(x))
 
 template <int D, int WAVES, bool PACKED>
-__global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
+__global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kernel(Args a)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
     using C = Cfg<D, WAVES>;
+    constexpr int NB = C::NB;
     constexpr int KS = D / 16;   // MFMA k-steps of Q K^T
     constexpr int DB = D / 32;   // 32-channel blocks of the output
     constexpr int MROWS = WAVES * 32;
@@ -328,14 +333,18 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
             const uint32_t soff = (uint32_t)((t0 + j) * KT) * stride2 + (uint32_t)(kh * D * 2);
             unsigned char* const kdst = lds + slot + wave_u * (C::NI * 1024);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(pk_rsrc, (lds_void*)kdst, 16, k_voff[0], soff, 0, 0);
-            if (C::NI > 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(pk_rsrc, (lds_void*)(kdst + 1024), 16, k_voff[C::NI - 1], soff, 0, 0);
+#pragma unroll
+            for (int jn = 1; jn < C::NI; ++jn)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(pk_rsrc, (lds_void*)(kdst + jn * 1024), 16, k_voff[jn], soff, 0, 0);
         };
         auto fetch_v = [&](int j, uint32_t slot) {
             unsigned char* const vdst = lds + slot + wave_u * (C::NI * 1024) + C::V_RING;
             if (PACKED) {
                 const uint32_t voff = (uint32_t)(kh * a.TPF + t0 + j) * C::T_BYTES;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(pv_rsrc, (lds_void*)vdst, 16, vp_voff, voff, 0, 0);
-                if (C::NI > 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(pv_rsrc, (lds_void*)(vdst + 1024), 16, vp_voff + 1024, voff, 0, 0);
+#pragma unroll
+                for (int jn = 1; jn < C::NI; ++jn)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(pv_rsrc, (lds_void*)(vdst + jn * 1024), 16, vp_voff + jn * 1024, voff, 0, 0);
             } else {
                 const uint32_t soff = (uint32_t)((t0 + j) * KT) * stride2 + (uint32_t)(kh * D * 2);
                 int tid_f = tid;
@@ -533,8 +542,8 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
         auto wait_landed = [&](int t) {
             landed = t;
             const int k = issued - 1 - t;
-            if (k >= 3) wait_vm<3 * C::IPT>();
-            else if (k == 2) wait_vm<2 * C::IPT>();
+            if (NB > 2 && k >= 3) wait_vm<(NB > 2 ? 3 : 0) * C::IPT>();
+            else if (NB > 2 && k == 2) wait_vm<(NB > 2 ? 2 : 0) * C::IPT>();
             else if (k == 1) wait_vm<C::IPT>();
             else wait_vm<0>();
             wg_barrier();
@@ -572,7 +581,8 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
         // end of step i of the pipelined loop: K of tile i+2 and V of tile i+1 must have landed (both requested two
         // steps ago); what this step and the previous one requested may still be on its way
         auto wait_step = [&](int i) {
-            if (i + 4 < F) wait_vm<4 * C::NI>();
+            if (NB == 2) wait_vm<0>();          // (two slots: both were requested in this step)
+            else if (i + 4 < F) wait_vm<4 * C::NI>();
             else if (i + 3 < F) wait_vm<3 * C::NI>();
             else if (i + 2 < F) wait_vm<C::NI>();
             else wait_vm<0>();
@@ -581,15 +591,19 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
         bf16x8 p[4];      // probabilities of a tile as MFMA B operands, one per 16-key step
 
         // ---- full prefix tiles, software pipelined ---------------------------------
-        // Issue order so far: Q, then K0 V0 K1 V1 K2 V2 K3.  The first step needs Q, K0, V0 and K1; with four
-        // full tiles or more nothing else has been requested, and the last four half tiles may stay in flight.
-        if (F >= NB) wait_vm<4 * C::NI>(); else wait_vm<0>();
+        // Issue order so far: Q, then K0 V0 K1 V1 K2 V2 K3 (or as far as there are slots).  The first step needs Q, K0, V0
+        // and K1; with four full tiles or more nothing else has been requested, and the last four half tiles may stay in
+        // flight.  With two slots the scores of tile 0 start on Q and K0 (nothing but K0 V0 K1 is on its way if F > 0).
+        if (NB == 2 && F > 0) wait_vm<2 * C::NI>();
+        else if (NB == 4 && F >= NB) wait_vm<4 * C::NI>();
+        else wait_vm<0>();
         wg_barrier();
         landed = issued - 1;
         if (F > 0 && !wave_has_rows) {
             // A wavefront without rows (the M-tile is not full) only moves its share of the tiles: the matrix pipe and
             // the power are left to the others (8 requests of N=1, 224 of 256 rows, L=16384: 84.0 -> 82.1 us; with 112
             // rows or fewer a SIMD has one wavefront to serve).  Same requests, waits and barriers as in the steps below.
+            if (NB == 2) wait_vm<0>();
             wg_barrier();
             for (int i = 0; i < F; ++i) {
                 if (i + NB < F) fetch_k(i + NB, (uint32_t)(i & (NB - 1)) * C::T_BYTES);
@@ -616,6 +630,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
             // there while another one is still reading.  (They can be far apart here: the first workgroups of a
             // launch fetch these instructions from memory.)
             FDD_SCHED_FENCE();
+            if (NB == 2) wait_vm<0>();
             wg_barrier();
 
             // One pipelined step: probabilities and P V of tile i from s_cur while
@@ -748,10 +763,12 @@ __global__ __launch_bounds__(WAVES * 64) void attn_bf16_kernel(Args a)
                 if (++i == F) break;
                 step(r1, i, sb, sa);
                 if (++i == F) break;
-                step(r2, i, sa, sb);
-                if (++i == F) break;
-                step(r3, i, sb, sa);
-                if (++i == F) break;
+                if constexpr (NB == 4) {
+                    step(r2, i, sa, sb);
+                    if (++i == F) break;
+                    step(r3, i, sb, sa);
+                    if (++i == F) break;
+                }
             }
             landed = issued - 1;     // the last step waits for everything requested
         }
@@ -922,7 +939,7 @@ __global__ __launch_bounds__(512) void vt_pack_kernel(const uint16_t* __restrict
 // chunk (8 channels of a row) of every SG-th segment, requests UX averages and the (m, l) pairs that weigh them together,
 // and the SG threads of a chunk, which lie in one wavefront, meet in lane moves at the end.  No LDS, no barrier.  The
 // pairs of a row are read by the threads of all its chunks; that costs less than passing weights on.
-// grid (M-tiles, 2 DB SG x 8 / 4): 4 wavefronts of 64 / SG chunks each.
+// grid (M-tiles, 2 DB SG WAVES / 4), WAVES as of the attention kernel: 4 wavefronts of 64 / SG chunks each.
 struct MergeArgs {
     const u32x4* ws_o;
     const float* ws_ml;
@@ -952,12 +969,13 @@ __device__ __forceinline__ float reduce_groups(float v, Op op)
     return __uint_as_float(x);
 }
 
-template <int D, int SG, int UX>
+template <int D, int WAVES, int SG, int UX>
 __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
 {
     constexpr int DB = D / 32;
     constexpr int CPW = 2 * DB * 64;          // 16-byte chunks per wavefront of the attention kernel
-    constexpr int CH = 8 * CPW;               // chunks per M-tile and segment
+    constexpr int CH = WAVES * CPW;           // chunks per M-tile and segment
+    constexpr int MROWS = WAVES * 32;
     constexpr int CPL = 64 / SG;              // chunks per wavefront here
     const int tid = thread_id_x();
     const int M = (int)wg_id_x();
@@ -970,14 +988,14 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
     const int khv = fast_div(M, a.dMT), mt = M - khv * a.MT;      // (problem of the batch, KV head), M-tile
     const int c0 = (int)wg_id_y() * (4 * CPL);                    // the block's first chunk: [wave][register pair][lane]
     const int wave = c0 / CPW;
-    const int row0 = mt * 256 + wave * 32;    // first stacked row of the block's 32 rows
+    const int row0 = mt * MROWS + wave * 32;  // first stacked row of the block's 32 rows
     if (row0 >= a.R) return;
     const int lane = tid & 63, sg = lane / CPL;
     const int cidx = c0 + (tid >> 6) * CPL + lane % CPL;
     const int r = cidx & 31, half = (cidx >> 5) & 1, i2 = (cidx >> 6) % (2 * DB);
     const bool live = row0 + r < a.R;
     const u32x4* src = a.ws_o + (size_t)M * a.max_seg * CH + cidx;
-    const float* ml = a.ws_ml + ((size_t)M * a.max_seg * 256 + wave * 32 + r) * 2;
+    const float* ml = a.ws_ml + ((size_t)M * a.max_seg * MROWS + wave * 32 + r) * 2;
 
     float m = -INFINITY, sum = 0.f;           // this thread's segments: largest m, sum of weights against it
     float acc[8];
@@ -992,7 +1010,7 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
             y[u] = make_float2(-INFINITY, 0.f);
             x[u] = u32x4{0u, 0u, 0u, 0u};
             if (live && s < n_seg) {
-                y[u] = *reinterpret_cast<const float2*>(ml + (size_t)s * 512);
+                y[u] = *reinterpret_cast<const float2*>(ml + (size_t)s * (2 * MROWS));
                 x[u] = src[(size_t)s * CH];
             }
         }
@@ -1132,10 +1150,15 @@ hipError_t launch_attn_bf16(const fdd_attn_params& p, const AttnPlan& plan, floa
     // (with 2..16 pieces of 32 units or more a shift of 3 % is at least one unit)
     a.w_even = 100;
     a.w_odd = (a.S >= 2 && a.S <= 16 && a.TPU >= 32 * a.S) ? ODD_XCD_WEIGHT : 100;
-    if (plan.mtile_rows != 256) return hipErrorInvalidValue;
-    if (plan.packed)
-        return p.D == 128 ? launch<128, 8, true>(a, pack_now, s, before_main) : launch<64, 8, true>(a, pack_now, s, before_main);
-    return p.D == 128 ? launch<128, 8, false>(a, false, s, before_main) : launch<64, 8, false>(a, false, s, before_main);
+    auto go = [&](auto waves) {
+        constexpr int WAVES = decltype(waves)::value;
+        if (plan.packed)
+            return p.D == 128 ? launch<128, WAVES, true>(a, pack_now, s, before_main) : launch<64, WAVES, true>(a, pack_now, s, before_main);
+        return p.D == 128 ? launch<128, WAVES, false>(a, false, s, before_main) : launch<64, WAVES, false>(a, false, s, before_main);
+    };
+    if (plan.mtile_rows == 256) return go(std::integral_constant<int, 8>());
+    if (plan.mtile_rows == 128) return go(std::integral_constant<int, 4>());
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_attn_merge_bf16(const fdd_attn_params& p, const AttnPlan& plan, float scale, hipStream_t s)
@@ -1158,7 +1181,6 @@ hipError_t launch_attn_merge_bf16(const fdd_attn_params& p, const AttnPlan& plan
     a.dBase = make_fastdiv((uint32_t)(base > 0 ? base : 1));
     a.dBase1 = make_fastdiv((uint32_t)(base + 1));
     a.c = scale * 1.4426950408889634f;
-    if (plan.mtile_rows != 256) return hipErrorInvalidValue;
     // SG threads per chunk: more of them while the chunks of a call leave most of the chip's lanes idle and each still has
     // four segments or more to request.  us per call (replayed) with 1, 2, 4, 8 of them: N=1, L=16384 (52 segments, 14 k
     // chunks) 28.3, 25.2, 23.8, 23.6; N=4, L=8192 (18, 57 k) 28.8, 28.5, 28.4, 29.0; N=8, L=4096 (9, 115 k) 27.3, 27.5,
@@ -1169,8 +1191,9 @@ hipError_t launch_attn_merge_bf16(const fdd_attn_params& p, const AttnPlan& plan
     while (sg < 8 && sg * 8 <= n && chunks * sg * 2 <= (1 << 17)) sg *= 2;
     auto go = [&](auto d, auto sgc, auto ux) {
         constexpr int D = decltype(d)::value, SG = decltype(sgc)::value, UX = decltype(ux)::value;
-        const dim3 grid((unsigned)(p.Hkv * batch * plan.MT), (unsigned)(8 * 2 * (D / 32) * SG / 4));
-        hipLaunchKernelGGL((attn_merge_bf16_kernel<D, SG, UX>), grid, dim3(256), 0, s, a);
+        const dim3 grid((unsigned)(p.Hkv * batch * plan.MT), (unsigned)(plan.mtile_rows / 32 * 2 * (D / 32) * SG / 4));
+        if (plan.mtile_rows == 256) hipLaunchKernelGGL((attn_merge_bf16_kernel<D, 8, SG, UX>), grid, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((attn_merge_bf16_kernel<D, 4, SG, UX>), grid, dim3(256), 0, s, a);
     };
     auto sized = [&](auto d) {
         const std::integral_constant<int, 1> i1;

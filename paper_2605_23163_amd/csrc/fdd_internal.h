@@ -35,7 +35,8 @@ constexpr int kNumXCD = 8;
 //   fp32 path : `splits` workgroups per M-tile, each of them kF32Waves
 //               wavefronts; the key tiles (prefix and private ones) are cut
 //               into splits * kF32Waves equal runs, one per wavefront.
-//   bf16 path : the unit is one key tile of one M-tile (TPU units per M-tile,
+//   bf16 path : M-tiles of 256 rows or, in short calls, 128 (mtile_rows / 32
+//               wavefronts per workgroup); the unit is one key tile of one M-tile (TPU units per M-tile,
 //               U in total).  Either every M-tile is cut into `uniform` equal
 //               pieces, piece s covering tiles [TPU s / S, TPU (s+1) / S), or
 //               (stream-K) workgroup w of W owns the contiguous unit range
