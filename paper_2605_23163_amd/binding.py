@@ -14,6 +14,7 @@ _LIB_PATH = os.path.join(_HERE, "libfdd.so")
 _lib = None
 torch = None          # imported by the first call: building and importing the package need no torch
 _DTYPE_CODES = {}     # element type -> fdd_dtype, filled with it
+_marshal = None       # native argument marshalling of the two calls of a denoise step (csrc/marshal.cpp), if it was built
 
 FDD_F32, FDD_BF16 = 0, 1
 FDD_ATTN_CAUSAL_BLOCK = 1
@@ -87,11 +88,22 @@ def _import_torch():
     _DTYPE_CODES.update({t.bfloat16: FDD_BF16, t.float32: FDD_F32})
 
 
+def _import_marshal():
+    """The module, or None where it was not built or was built for another torch: the functions below then do the same in Python."""
+    try:
+        from . import _marshal as m
+    except ImportError:
+        return None
+    fits = torch.__version__.split("+")[0] == m.torch_version and (m.attn_bytes, m.unmask_bytes) == (C.sizeof(AttnParams), C.sizeof(UnmaskParams))
+    return m if fits else None
+
+
 def load_library():
     """Load libfdd.so (after torch, which brings in the HIP runtime the library links against)."""
-    global _lib
+    global _lib, _marshal
     if _lib is None:
         _import_torch()
+        _marshal = _import_marshal()
         if not os.path.exists(_LIB_PATH):
             raise FileNotFoundError(
                 f"{_LIB_PATH} is missing: build it with `python -m paper_2605_23163_amd.build` "
@@ -289,9 +301,13 @@ def fdd_block_attn(q, prefix_k, prefix_v, block_k, block_v, scaffold_mask=None, 
     lib = load_library()
     if out is None:
         out = (torch.empty_like if stream is None else _maker(stream, q.device, torch.empty_like))(q)
-    p = _attn_params(q, prefix_k, prefix_v, block_k, block_v, scaffold_mask, out, scale, splits, prefix_v_packed,
-                     causal_block, ext_k, ext_v, E)
-    if q_positions is not None:
+    p = AttnParams()
+    filled = _marshal is not None and _marshal.attn(C.addressof(p), q, prefix_k, prefix_v, block_k, block_v, scaffold_mask, out,
+                                                    prefix_v_packed, ext_k, ext_v, q_positions, E, causal_block, splits, scale)
+    if not filled:
+        p = _attn_params(q, prefix_k, prefix_v, block_k, block_v, scaffold_mask, out, scale, splits, prefix_v_packed,
+                         causal_block, ext_k, ext_v, E)
+    if q_positions is not None and not filled:
         if q_positions.dtype != torch.int32 or q_positions.dim() != 1 or not q_positions.is_contiguous():
             raise ValueError("q_positions must be a contiguous 1-D int32 tensor")
         p.q_positions = _dev(q_positions, "q_positions")
@@ -381,21 +397,24 @@ def fdd_unmask_step(logits, mask, scaffold_mask, tau, tokens, confidences=None, 
     Returns (tokens, confidences, n_unmasked, committed).
     """
     lib = load_library()
-    N, B, V = logits.shape
-    for t, dt, nm in ((mask, torch.uint8, "mask"), (tokens, torch.int32, "tokens")):
-        if t.dtype != dt or t.shape != (N, B):
-            raise TypeError(f"{nm} must be {dt} [N,B]")
-    if scaffold_mask is not None and (scaffold_mask.dtype != torch.uint8 or scaffold_mask.shape != (N, B)):
-        raise TypeError("scaffold_mask must be uint8 [N,B]")
     dev = logits.device
-    new = torch.empty if stream is None else _maker(stream, dev, torch.empty)
-    if confidences is None:
-        confidences = new((N, B), dtype=torch.float32, device=dev)
-    if n_unmasked is None:
-        n_unmasked = new((N,), dtype=torch.int32, device=dev)
-    if committed is None:
-        committed = new((N, B), dtype=torch.uint8, device=dev)
-    p = _unmask_params(logits, mask, scaffold_mask, tokens, tau, confidences, n_unmasked, committed, refresh)
+    p = UnmaskParams()
+    if confidences is None or n_unmasked is None or committed is None or _marshal is None or not _marshal.unmask(
+            C.addressof(p), logits, mask, scaffold_mask, tokens, confidences, n_unmasked, committed, tau, refresh):
+        N, B, V = logits.shape
+        for t, dt, nm in ((mask, torch.uint8, "mask"), (tokens, torch.int32, "tokens")):
+            if t.dtype != dt or t.shape != (N, B):
+                raise TypeError(f"{nm} must be {dt} [N,B]")
+        if scaffold_mask is not None and (scaffold_mask.dtype != torch.uint8 or scaffold_mask.shape != (N, B)):
+            raise TypeError("scaffold_mask must be uint8 [N,B]")
+        new = torch.empty if stream is None else _maker(stream, dev, torch.empty)
+        if confidences is None:
+            confidences = new((N, B), dtype=torch.float32, device=dev)
+        if n_unmasked is None:
+            n_unmasked = new((N,), dtype=torch.int32, device=dev)
+        if committed is None:
+            committed = new((N, B), dtype=torch.uint8, device=dev)
+        p = _unmask_params(logits, mask, scaffold_mask, tokens, tau, confidences, n_unmasked, committed, refresh)
     ws = _set_workspace(p, workspace, lib.fdd_unmask_workspace, dev, stream)  # noqa: F841
     p.stream = _stream_ptr(stream)
     _check(lib.fdd_unmask_step(C.byref(p)))

@@ -7,15 +7,18 @@ file so that it travels with the source tree.
 """
 from __future__ import annotations
 
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libfdd.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"),
@@ -40,6 +43,23 @@ def _run(cmd):
         print(out)
 
 
+def marshal_command(out):
+    """The compiler call for the binding's native argument marshalling, or None where torch or the Python headers are
+    missing (the binding then does it in Python).  torch is looked up, not imported."""
+    try:
+        spec = importlib.util.find_spec("torch")
+    except (ImportError, ValueError):
+        spec = None
+    python = sysconfig.get_paths()["include"]
+    if spec is None or not spec.origin or not os.path.exists(os.path.join(python, "Python.h")):
+        return None
+    torch = os.path.dirname(spec.origin)
+    lib = os.path.join(torch, "lib")
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + os.path.join(ROOT, "include"), "-I" + python,
+            "-I" + os.path.join(torch, "include"), "-I" + os.path.join(torch, "include", "torch", "csrc", "api", "include"),
+            os.path.join(CSRC, "marshal.cpp"), "-o", out, "-L" + lib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build(asm: bool = False, jobs: int = 4) -> str:
     bdir = os.path.join(ROOT, "_build")
     os.makedirs(bdir, exist_ok=True)
@@ -53,11 +73,19 @@ def build(asm: bool = False, jobs: int = 4) -> str:
         if asm:   # device assembly next to the objects, for inspection
             cmds.append([HIPCC, *FLAGS, *EXTRA.get(os.path.basename(src), []), "-S", "--offload-device-only",
                          src, "-o", obj[:-2] + ".s"])
+    tmp_marshal = MARSHAL + f".{os.getpid()}.tmp"
+    marshal = marshal_command(tmp_marshal)
+    if marshal:
+        cmds.append(marshal)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         list(ex.map(_run, cmds))
     tmp = LIB + f".{os.getpid()}.tmp"
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp])
     os.replace(tmp, LIB)
+    if marshal:
+        os.replace(tmp_marshal, MARSHAL)
+    elif os.path.exists(MARSHAL):
+        os.remove(MARSHAL)
     return LIB
 
 
