@@ -69,10 +69,11 @@ struct Args {
     u32x4* rf_bv;
     int rf_T, rf_row_vecs;  // table rows; 16-byte pieces per K/V row (0: no refresh)
     int N, B, vsplits;
-    int units;              // workgroups of a vocabulary pass: N B vsplits
+    int units;              // workgroups of a vocabulary pass: N B pieces
+    int pieces;             // pieces per row: vsplits, or twice as many whose (key, id) pairs share a record
     int compact;            // workgroups are dealt to eligible rows only
     int per;                // vocabulary entries per piece (the last pieces of a row may be shorter or empty)
-    FastDiv dVs;            // division by vsplits
+    FastDiv dVs;            // division by pieces
     long long V;
     float tau;
     float c;                // sampled verifier: log2(e) / temperature
@@ -252,13 +253,13 @@ __device__ __forceinline__ bool unit_of(const Args& a, int* row, int* piece)
 {
     if (a.compact) {
         const int u = (int)wg_id_x(), t = fast_div(u, a.dVs);
-        *piece = u - t * a.vsplits;
+        *piece = u - t * a.pieces;
         *row = eligible_row(a.mask, a.scaffold, a.N * a.B, t);
         return *row >= 0;
     }
     const int u = (int)unit_of_workgroup((unsigned)a.units);
     *row = fast_div(u, a.dVs);
-    *piece = u - *row * a.vsplits;
+    *piece = u - *row * a.pieces;
     return a.mask[*row] == 1 && !(a.scaffold && a.scaffold[*row]);
 }
 
@@ -447,6 +448,7 @@ __device__ __forceinline__ float noise_bound(uint32_t r)
     return fmaf((float)__float_as_uint(w), -1.1920928955078125e-07f, NOISE_C);
 }
 
+constexpr int VTHREADS = 256;
 constexpr int VUNROLL = 5;       // sampled verifier: 16-byte loads in flight per thread
 
 // Same work split as vocab_reduce; leaves (largest key, lowest id attaining it) per piece.
@@ -457,11 +459,11 @@ constexpr int VUNROLL = 5;       // sampled verifier: 16-byte loads in flight pe
 // clear winner end here), then with the bound above in place of the logarithms.  What is left (a few entries per
 // wavefront) is worked out as defined, and the row's winner is never dropped, so the verifier's token is the same bit for
 // bit.
-// Measured, bf16, 70 % of the rows live, V = 152064 (in brackets every entry worked out in full): N=8, B=32 32 us (87) with
-// a clear winner in 4 of 5 rows, 42 (87) with none; N=16, B=64 70 (231) and 112 (230); N=5, B=40, V=50001 25 (211: rows
+// Measured, bf16, 70 % of the rows live, V = 152064 (in brackets every entry worked out in full): N=8, B=32 27 us (87) with
+// a clear winner in 4 of 5 rows, 36 (87) with none; N=16, B=64 63 (231) and 100 (230); N=5, B=40, V=50001 21 (211: rows
 // that start inside a generator block took a block per entry).  Without a winner the generator's 32 x 32 bit products
 // are what is left.
-template <typename T, int VTHREADS>
+template <typename T>
 __global__ __launch_bounds__(VTHREADS) void vocab_sample_kernel(Args a)
 {
     constexpr int VEC = 16 / sizeof(T);
@@ -600,12 +602,13 @@ __global__ __launch_bounds__(VTHREADS) void vocab_sample_kernel(Args a)
         Best t = part[0];
 #pragma unroll
         for (int w = 1; w < VTHREADS / 64; ++w) take(t, part[w].k, part[w].idx);
-        Partial p;
-        p.m = t.k;
-        p.arg = t.idx;
-        p.s = 0.f;
-        p.pad = 0;
-        a.ws[(size_t)row * a.vsplits + piece] = p;
+        Best* const ws = reinterpret_cast<Best*>(a.ws) + (size_t)row * a.vsplits * 2;     // two pairs per record
+        if (a.pieces > a.vsplits) {
+            ws[piece] = t;
+        } else {
+            ws[2 * piece] = t;
+            ws[2 * piece + 1] = Best{-INFINITY, 0};
+        }
     }
 }
 
@@ -755,6 +758,8 @@ __global__ __launch_bounds__(STHREADS) void block_select_kernel(Args a)
 // Draft positions are visited in ascending order; drafts equal to the AR arg
 // max are accepted up to the first mismatch, which takes the AR token; later
 // drafts are left masked.
+// PAIRS: a record holds the (key, id) pairs of two pieces (sampled verifier), else one piece's (max, id) and no second one.
+template <bool PAIRS>
 __global__ __launch_bounds__(STHREADS) void verify_scan_kernel(Args a)
 {
     const int n = wg_id_x();
@@ -777,12 +782,21 @@ __global__ __launch_bounds__(STHREADS) void verify_scan_kernel(Args a)
         // ascending pieces: strict '>' keeps the lowest id on ties
         float M = __uint_as_float(rec[0].x);
         int arg = (int)rec[0].y;
+        auto larger = [&](uint32_t m, uint32_t id) {
+            if (__uint_as_float(m) > M) { M = __uint_as_float(m); arg = (int)id; }
+        };
+        if (PAIRS) larger(rec[0].z, rec[0].w);
 #pragma unroll
-        for (int s = 1; s < PRE; ++s)
-            if (s < a.vsplits && __uint_as_float(rec[s].x) > M) { M = __uint_as_float(rec[s].x); arg = (int)rec[s].y; }
-        const Partial* p = a.ws + i * a.vsplits;
-        for (int s = PRE; s < a.vsplits; ++s)
-            if (p[s].m > M) { M = p[s].m; arg = p[s].arg; }
+        for (int s = 1; s < PRE; ++s) {
+            if (s >= a.vsplits) continue;
+            larger(rec[s].x, rec[s].y);
+            if (PAIRS) larger(rec[s].z, rec[s].w);
+        }
+        for (int s = PRE; s < a.vsplits; ++s) {
+            const u32x4 r = pr[s];
+            larger(r.x, r.y);
+            if (PAIRS) larger(r.z, r.w);
+        }
         if (arg != d && b < first_bad) { first_bad = b; bad_tok = arg; }
     }
     first_bad = wave_min(first_bad);
@@ -834,15 +848,16 @@ bool make_vocab_plan(int N, int B, long long V, int dtype, bool argmax_only, Unm
 
 // Entries per piece: a multiple of 64 (128 bytes of bf16), so that the pieces of an aligned row start on whole cache
 // lines and have no entries outside whole 16-byte vectors but the row's own last ones.
-static void set_pieces(Args& a, int vsplits, long long V)
+static void set_pieces(Args& a, int vsplits, long long V, int pieces)
 {
     a.vsplits = vsplits;
-    a.units = a.N * a.B * vsplits;
+    a.pieces = pieces;
+    a.units = a.N * a.B * pieces;
     a.V = V;
     a.compact = a.N * a.B >= 16 && a.N * a.B <= LIVE_ROWS && a.units > 512 && a.units <= 2560;
-    const long long per = (V + vsplits - 1) / vsplits;
+    const long long per = (V + pieces - 1) / pieces;
     a.per = (int)std::min<long long>((per + 63) / 64 * 64, V);
-    a.dVs = make_fastdiv((uint32_t)vsplits);
+    a.dVs = make_fastdiv((uint32_t)pieces);
 }
 
 // Threads per piece: 512 from 48 KB on (its loads in two groups instead of four, and twice the wavefronts for the few
@@ -882,7 +897,7 @@ hipError_t launch_unmask(const fdd_unmask_params& p, const UnmaskPlan& plan, hip
     a.rf_T = p.refresh_T;
     a.rf_row_vecs = p.refresh_block_k ? (int)((size_t)p.refresh_Hkv * p.refresh_D * (p.refresh_dtype == FDD_BF16 ? 2 : 4) / 16) : 0;
     a.N = p.N; a.B = p.B; a.tau = p.tau;
-    set_pieces(a, plan.vsplits, p.V);
+    set_pieces(a, plan.vsplits, p.V, plan.vsplits);
     a.c = 0.f; a.seed_lo = 0u; a.seed_hi = 0u;
     launch_reduce<true>(a, p.dtype, s);
     hipError_t e = hipGetLastError();
@@ -905,34 +920,27 @@ hipError_t launch_verify(const fdd_verify_params& p, const UnmaskPlan& plan, hip
     a.draft = p.draft;
     a.rf_tk = nullptr; a.rf_tv = nullptr; a.rf_bk = nullptr; a.rf_bv = nullptr; a.rf_T = 0; a.rf_row_vecs = 0;
     a.N = p.N; a.B = p.B; a.tau = 0.f;
-    set_pieces(a, plan.vsplits, p.V);
+    // The sampled verifier, bound by its arithmetic, takes twice the pieces while they are 16 KB or more and 2048 at most.
+    // us per call with a fork, replayed, plain / twice: V = 152064 bf16, 70 % of the rows live, a clear winner in 4 of 5 rows:
+    // N=1, B=32 16.8/15.6, N=4 21.5/21.3, N=8 30.4/27.3 (36.0/36.6 without winners; 512 threads per piece 30.9, 36.3); more
+    // pieces N=16, B=64 64.7/64.7 (99.9/115); smaller ones V = 50001, 200 rows in 5 21.5/24.3.
+    const long long bytes = p.V * (p.dtype == FDD_BF16 ? 2 : 4);
+    const bool twice = p.temperature > 0.f && (long long)p.N * p.B * plan.vsplits <= 1024 && bytes >= 32ll * 1024 * plan.vsplits;
+    set_pieces(a, plan.vsplits, p.V, twice ? 2 * plan.vsplits : plan.vsplits);
     a.c = p.temperature > 0.f ? (float)(1.4426950408889634 / (double)p.temperature) : 0.f;
     a.seed_lo = (uint32_t)p.seed;
     a.seed_hi = (uint32_t)(p.seed >> 32);
-    const dim3 grid((unsigned)a.units);
     if (p.temperature > 0.f) {
-        // 512 threads per piece while the pieces are so few that 256 leave SIMDs empty.  Measured, us per call with 512 / 256
-        // threads, 70 % of the rows live, V = 152064 bf16 in 4 pieces, rows with a clear winner and (without): 200 pieces
-        // 16.6/18.9 (17.9/20.3), 400 23.1/24.4 (27.2/28.2), 600 27.4/27.9 (36.0/35.7), 800 29.5/30.9 (37.4/43.4), 1024 32.4/36.3
-        // (44.6/44.3), 1280 36.9/38.5 (53.2/51.9), 1536 41.6/45.7 (56.1/59.8), 2048 49.6/50.5 (73.6/69.4), 3072 65.2/61.8
-        // (101/93).  Up to 1024 pieces 512 threads are faster or within 1 %; above, the two cross several times with the
-        // number of rounds; from 3072 on 256 are faster.  (V = 50001 in one piece: 200 28.5/36.0, 1000 63.0/62.4, 1200 66.0/66.9.)
-        // (Pieces below 32 KB leave a group of 512 threads' loads mostly empty: V = 50001 in 5, 200 rows 23.3/21.5 with a fork.)
-        const bool wide = a.units <= 1024 && (long long)a.per * (p.dtype == FDD_BF16 ? 2 : 4) >= 32 * 1024;
-        if (p.dtype == FDD_BF16) {
-            if (wide) hipLaunchKernelGGL((vocab_sample_kernel<uint16_t, 512>), grid, dim3(512), 0, s, a);
-            else hipLaunchKernelGGL((vocab_sample_kernel<uint16_t, 256>), grid, dim3(256), 0, s, a);
-        } else {
-            if (wide) hipLaunchKernelGGL((vocab_sample_kernel<float, 512>), grid, dim3(512), 0, s, a);
-            else hipLaunchKernelGGL((vocab_sample_kernel<float, 256>), grid, dim3(256), 0, s, a);
-        }
+        if (p.dtype == FDD_BF16) hipLaunchKernelGGL((vocab_sample_kernel<uint16_t>), dim3((unsigned)a.units), dim3(VTHREADS), 0, s, a);
+        else hipLaunchKernelGGL((vocab_sample_kernel<float>), dim3((unsigned)a.units), dim3(VTHREADS), 0, s, a);
     } else {
         // greedy verifier: step 3 of scaffold speculative decoding compares arg maxima only, so no exponentials
         launch_reduce<false>(a, p.dtype, s);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(verify_scan_kernel, dim3(p.N), dim3(STHREADS), 0, s, a);
+    if (p.temperature > 0.f) hipLaunchKernelGGL(verify_scan_kernel<true>, dim3(p.N), dim3(STHREADS), 0, s, a);
+    else hipLaunchKernelGGL(verify_scan_kernel<false>, dim3(p.N), dim3(STHREADS), 0, s, a);
     return hipGetLastError();
 }
 
