@@ -45,7 +45,7 @@
 //     and round them to bf16.  One wavefront can only issue a vector
 //     instruction every other issue slot, so two wavefronts per SIMD running
 //     this same mix are what fills both pipes.  V of tile i+3 and K of tile
-//     i+4 are requested at the start of step i (K is read one step before V,
+//     i+4 are requested in step i (K is read one step before V,
 //     so its slot is free one step earlier) and waits are counted (the loads
 //     of a wavefront complete in issue order), so four half tiles stay in
 //     flight across a step boundary; LDS
@@ -80,6 +80,7 @@
 //     speculative decoding the block keys after the query's own position too.
 #include <atomic>
 #include <type_traits>
+#include <utility>
 
 #include "fdd_internal.h"
 
@@ -187,6 +188,13 @@ __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "mem
 // the vector work of a slot is not sunk towards its first use.
 #define FDD_PIN(x) asm volatile("" : "+v"(x))
 
+// f(0), f(1), .. with compile-time arguments
+template <typename F, int... J>
+__device__ __forceinline__ void for_slots(F& f, std::integer_sequence<int, J...>)
+{
+    (f(std::integral_constant<int, J>()), ...);
+}
+
 template <int D, int WAVES, bool PACKED>
 __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kernel(Args a)
 {
@@ -196,6 +204,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
     constexpr int KS = D / 16;   // MFMA k-steps of Q K^T
     constexpr int DB = D / 32;   // 32-channel blocks of the output
     constexpr int MROWS = WAVES * 32;
+    constexpr bool SPREAD = WAVES == 8 && D == 128;   // order of a pipelined step, see there
     constexpr uint32_t RSRC_FLAGS = 0x00020000;
 
     extern __shared__ __align__(16) unsigned char lds[];
@@ -329,28 +338,27 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
         // ---- tile j: global memory -> ring slot j % NB, no registers in between ----
         int issued = 0;
         // full prefix tile (j < F): offsets were prepared once, only the scalar tile offset changes
-        auto fetch_k = [&](int j, uint32_t slot) {        // slot = (j % NB) * T_BYTES, a constant where it matters
+        // pieces [first, last) of this wavefront's share
+        auto fetch_k_pieces = [&](int j, uint32_t slot, int first, int last) {        // slot = (j % NB) * T_BYTES, a constant where it matters
             const uint32_t soff = (uint32_t)((t0 + j) * KT) * stride2 + (uint32_t)(kh * D * 2);
             unsigned char* const kdst = lds + slot + wave_u * (C::NI * 1024);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(pk_rsrc, (lds_void*)kdst, 16, k_voff[0], soff, 0, 0);
 #pragma unroll
-            for (int jn = 1; jn < C::NI; ++jn)
+            for (int jn = first; jn < last; ++jn)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(pk_rsrc, (lds_void*)(kdst + jn * 1024), 16, k_voff[jn], soff, 0, 0);
         };
-        auto fetch_v = [&](int j, uint32_t slot) {
+        auto fetch_v_pieces = [&](int j, uint32_t slot, int first, int last) {
             unsigned char* const vdst = lds + slot + wave_u * (C::NI * 1024) + C::V_RING;
             if (PACKED) {
                 const uint32_t voff = (uint32_t)(kh * a.TPF + t0 + j) * C::T_BYTES;
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(pv_rsrc, (lds_void*)vdst, 16, vp_voff, voff, 0, 0);
 #pragma unroll
-                for (int jn = 1; jn < C::NI; ++jn)
+                for (int jn = first; jn < last; ++jn)
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(pv_rsrc, (lds_void*)(vdst + jn * 1024), 16, vp_voff + jn * 1024, voff, 0, 0);
             } else {
                 const uint32_t soff = (uint32_t)((t0 + j) * KT) * stride2 + (uint32_t)(kh * D * 2);
                 int tid_f = tid;
                 FDD_PIN(tid_f);     // recomputed at every fetch rather than kept in registers
 #pragma unroll
-                for (int jn = 0; jn < C::NI; ++jn) {
+                for (int jn = first; jn < last; ++jn) {
                     const int r = ((tid_f >> 6) * C::NI + jn) * C::RPB + (tid_f & 63) / C::CH;
                     const uint32_t col16 = (uint32_t)((((tid_f & 63) % C::CH) ^ ((((r / C::RPL) & 3) << 2) & (C::CH - 1))) * 16);
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(pv_rsrc, (lds_void*)(vdst + jn * 1024), 16,
@@ -358,6 +366,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                 }
             }
         };
+        auto fetch_k = [&](int j, uint32_t slot) { fetch_k_pieces(j, slot, 0, C::NI); };
+        auto fetch_v = [&](int j, uint32_t slot) { fetch_v_pieces(j, slot, 0, C::NI); };
         auto fetch_full = [&](int j, uint32_t slot) {
             fetch_k(j, slot);
             fetch_v(j, slot);
@@ -635,7 +645,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
 
             // One pipelined step: probabilities and P V of tile i from s_cur while
             // the scores of tile i+1 go to s_nxt; K of tile i+4 and V of tile i+3 are requested.
-            //   slots  0- 7  S(i+1) first 32 keys   ||  row maximum of tile i
+            //   slots  0- 7  S(i+1) first 32 keys   ||  row maximum of tile i (and, with 8 wavefronts at D = 128, the requests)
             //   slots  8-15  S(i+1) second 32 keys  ||  exp of the first 32 keys
             //   slots 16-23  P V first 32 keys      ||  exp of the second 32 keys
             //   slots 24-31  P V second 32 keys
@@ -652,11 +662,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                 // computed ahead), V of tile i+NB-1 where V of tile i-1 was
                 // (masked tiles are requested after the loop: their request code is long, and inside the
                 // loop it costs registers the loop does not have: measured, 52..64 vector registers spilled)
-                if (i + NB < F) fetch_k(i + NB, (uint32_t)P * C::T_BYTES);
-                if (i + NB - 1 < F) {
-                    fetch_v(i + NB - 1, (uint32_t)((P + NB - 1) % NB) * C::T_BYTES);
-                    issued = i + NB;
-                }
+                const bool more_k = i + NB < F, more_v = i + NB - 1 < F;
+                constexpr uint32_t KNEW = (uint32_t)P * C::T_BYTES, VNEW = (uint32_t)((P + NB - 1) % NB) * C::T_BYTES;
+                if (more_v) issued = i + NB;
                 auto kfrag = [&](int kb, int ks) {
                     return *reinterpret_cast<const bf16x8*>(lds + k_fragoff[ks] + (KSLOT + kb * 32 * D * 2));
                 };
@@ -666,11 +674,113 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                     if (PACKED) return *reinterpret_cast<const bf16x8*>(lds + v_fragoff_ring + (VSLOT + t4 * (D * 32) + db * 512));
                     return v_frag_tr_at(vtr_off_ring + VSLOT, t4, db);
                 };
+                float mx = -INFINITY, mc = 0.f, acc = 0.f;
                 bf16x8 f[3];
+                u32x4 pw[4];     // the B operands of P V as packed words
+                typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+                const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+                auto reference = [&]() {
+                    mx = fmaxf(mx, other_half(mx));
+                    update_reference(mx);
+                    mc = ((m_ref == -INFINITY) ? 0.f : m_ref) * a.c;
+                };
+
+                if constexpr (SPREAD) {
+                    // What a wavefront does besides its matrix instructions is spread over the slots such that nothing in a slot
+                    // waits for the slot itself: the tile requests one at a time (issued in a row they held the matrix pipe up),
+                    // the fragments two slots ahead across the parts of a step, and an exponential in three stages (scale,
+                    // exponential, rounding and sum) a slot apart (a wavefront issues in order: a dependent instruction right
+                    // behind waits).  One workgroup alone 1.36 -> 1.27 us a tile; N=16, L=16384 227.5 -> 222.9 us a call, N=64,
+                    // L=32768 1679 -> 1645 (fragments 3 ahead 1.28, 4 ahead 1.32; requests from slot 0 on or in consecutive slots
+                    // 1.28, 1.29).  With one wavefront per SIMD and at D = 64, where a slot carries twice the exponentials,
+                    // the plain order below is 1 and 3 % faster.
+                    constexpr int NPV = 4 * DB, NSL = 2 * KS + NPV;        // slots of P V, of the step
+                    auto frag = [&](int j) -> bf16x8 {
+                        return j < 2 * KS ? kfrag(j / KS, j % KS) : vfrag((j - 2 * KS) / (2 * DB), (j - 2 * KS) % (2 * DB));
+                    };
+                    // two probabilities of the tile: registers 2k, 2k+1 of its 32
+                    auto scale_pair = [&](int k) {
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) {
+                            float x = fmaf(s_cur[k / 8][2 * (k % 8) + t], a.c, -mc);
+                            FDD_PIN(x);
+                            s_cur[k / 8][2 * (k % 8) + t] = x;
+                        }
+                    };
+                    auto exp_pair = [&](int k) {
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) {
+                            float x = fast_exp2(s_cur[k / 8][2 * (k % 8) + t]);
+                            FDD_PIN(x);
+                            s_cur[k / 8][2 * (k % 8) + t] = x;
+                        }
+                    };
+                    auto round_pair = [&](int k) {
+                        const bf16x2 pr = {(__bf16)s_cur[k / 8][2 * (k % 8)], (__bf16)s_cur[k / 8][2 * (k % 8) + 1]};
+                        uint32_t u = __builtin_bit_cast(uint32_t, pr);
+                        FDD_PIN(u);
+                        pw[k / 4][k % 4] = u;
+                    };
+                    // (the row sum is taken over the probabilities as they enter P V, see below)
+                    auto sum_pair = [&](int k) {
+                        acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)pw[k / 4][k % 4]), ones, acc, false);
+                        FDD_PIN(acc);
+                    };
+                    constexpr int NEXP = KS + 2 * DB;          // slots with exponentials, one pair each
+                    static_assert(!SPREAD || NEXP == 16, "16 pairs of probabilities");
+                    FDD_SCHED_FENCE();
+                    f[0] = frag(0);
+                    f[1] = frag(1);
+                    // (a compile-time slot number: what a slot carries is worked out by the compiler)
+                    auto slot = [&](auto jc) {
+                        constexpr int j = decltype(jc)::value;
+                        if constexpr (j == 0 || j == KS) {
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) s_nxt[j / KS][v] = 0.f;
+                        }
+                        if constexpr (j % 2 == 1 && j / 2 < C::NI) {
+                            if (more_k) fetch_k_pieces(i + NB, KNEW, j / 2, j / 2 + 1);
+                        } else if constexpr (j % 2 == 1 && j / 2 >= 2 && j / 2 - 2 < C::NI) {
+                            if (more_v) fetch_v_pieces(i + NB - 1, VNEW, j / 2 - 2, j / 2 - 1);
+                        }
+                        if constexpr (j + 2 < NSL) f[(j + 2) % 3] = frag(j + 2);
+                        if constexpr (j < 2 * KS) {
+                            s_nxt[j / KS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[j % 3], qf[j % KS], s_nxt[j / KS], 0, 0, 0);
+                        } else {
+                            constexpr int t4 = (j - 2 * KS) / DB, db = (j - 2 * KS) % DB;
+                            o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[j % 3], __builtin_bit_cast(bf16x8, pw[t4]), o[db], 0, 0, 0);
+                        }
+                        if constexpr (j < KS) {
+#pragma unroll
+                            for (int v = j * (16 / KS); v < (j + 1) * (16 / KS); ++v) mx = fmaxf(fmaxf(mx, s_cur[0][v]), s_cur[1][v]);
+                            FDD_PIN(mx);
+                            if constexpr (j == KS - 1) {
+                                FDD_SCHED_FENCE();
+                                reference();
+                                FDD_SCHED_FENCE();
+                                scale_pair(0);
+                            }
+                        } else if constexpr (j <= KS + NEXP) {
+                            constexpr int k = j - KS;          // exponentials of pair k, with the stages before and after beside it
+                            if constexpr (k < 16) exp_pair(k);
+                            FDD_SCHED_FENCE();
+                            if constexpr (k >= 1) round_pair(k - 1);
+                            FDD_SCHED_FENCE();
+                            if constexpr (k < 15) scale_pair(k + 1);
+                            FDD_SCHED_FENCE();
+                            if constexpr (k >= 1) sum_pair(k - 1);
+                        } else if constexpr (j == KS + NEXP + 1) {
+                            l_run += acc;
+                        }
+                        FDD_SCHED_FENCE();
+                    };
+                    for_slots(slot, std::make_integer_sequence<int, NSL>());
+                } else {
+                if (more_k) fetch_k(i + NB, KNEW);
+                if (more_v) fetch_v(i + NB - 1, VNEW);
                 FDD_SCHED_FENCE();
 
                 // ---- slots 0-7 ----
-                float mx = -INFINITY;
                 f[0] = kfrag(0, 0);
                 f[1] = kfrag(0, 1);
 #pragma unroll
@@ -686,21 +796,15 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                     FDD_PIN(mx);
                     FDD_SCHED_FENCE();
                 }
-                mx = fmaxf(mx, other_half(mx));
-                update_reference(mx);
-                const float mc = ((m_ref == -INFINITY) ? 0.f : m_ref) * a.c;
-                float acc = 0.f;
-                u32x4 pw[4];     // the B operands of P V as packed words
+                reference();
                 // four probabilities of block kb (registers 4e .. 4e+3), rounded into the B operands
                 auto exp_quad = [&](int kb, int e) {
                     float pr[4];
 #pragma unroll
                     for (int t = 0; t < 4; ++t) pr[t] = fast_exp2(fmaf(s_cur[kb][4 * e + t], a.c, -mc));
-                    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
                     bf16x2 lo = {(__bf16)pr[0], (__bf16)pr[1]}, hi = {(__bf16)pr[2], (__bf16)pr[3]};
                     // the row sum is taken over the probabilities as they enter P V (rounded to bf16):
                     // numerator and denominator then see the same values, and a pair costs one instruction
-                    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
                     acc = __builtin_amdgcn_fdot2_f32_bf16(lo, ones, acc, false);
                     acc = __builtin_amdgcn_fdot2_f32_bf16(hi, ones, acc, false);
                     uint32_t ulo = __builtin_bit_cast(uint32_t, lo), uhi = __builtin_bit_cast(uint32_t, hi);
@@ -750,6 +854,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                     if (j + 2 < PVS) f[(j + 2) % 3] = vfrag(1, j + 2);
                     o[j % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[j % 3], p[2 + j / DB], o[j % DB], 0, 0, 0);
                     FDD_SCHED_FENCE();
+                }
                 }
                 wait_step(i);
                 wg_barrier();
