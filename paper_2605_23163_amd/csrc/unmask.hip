@@ -7,7 +7,7 @@
 // commits when that probability reaches tau, and a block that would commit
 // nothing commits its most confident eligible position.
 //
-// Two kernels:
+// Two kernels, or in very small calls one (block_unmask_small):
 //   vocab_reduce  streams the logits rows of eligible positions once.  A row
 //                 is cut into `vsplits` pieces so that a few hundred rows
 //                 still fill 256 CUs; each piece is reduced by one workgroup
@@ -37,6 +37,7 @@ namespace {
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr int PIECE_KB = 64;         // a row is cut into pieces of at least this size ...
 constexpr int PIECE_KB_FEW = 16;     // A call of few rows takes up to 8 pieces a row, of at least this size and up to
+constexpr long long kSmallShare = 4 * 1024;   // bytes of logits per wavefront up to which a call is one launch
 constexpr int kFewPieces = 1024;     // this number in all.  us per call with a fork, replayed, unmask / sampled verifier:
                                      // V = 152064 bf16, N=4, B=32, 4 pieces 13.5/28.0, 8 13.1/20.5, 16 14.9/25.9; N=1, 1 piece
                                      // 19.4/43.8, 4 11.2/19.7, 8 11.2/14.8, 16 12.6/17.0; V = 50001, 200 rows, 1 piece 12.5/28.8,
@@ -613,11 +614,12 @@ __global__ __launch_bounds__(VTHREADS) void vocab_sample_kernel(Args a)
 }
 
 constexpr int STHREADS = 64;   // one wavefront per rollout: no LDS, no workgroup barrier
+constexpr int SMALL_THREADS = 512, SMALL_B = 128;   // small calls: threads per rollout, positions at most
 
-__global__ __launch_bounds__(STHREADS) void block_select_kernel(Args a)
+// The decisions for rollout n, by one wavefront (lane `tid`).  `own`: the records of the rollout's positions, one each, in LDS
+// (small calls, see below), or nullptr: vsplits per position in the workspace.
+__device__ __forceinline__ void select_block(const Args& a, int n, int tid, const Partial* own)
 {
-    const int n = wg_id_x();
-    const int tid = thread_id_x();
     const double tau = (double)a.tau;
 
     int count = 0;
@@ -660,7 +662,8 @@ __global__ __launch_bounds__(STHREADS) void block_select_kernel(Args a)
         const u32x4* pr = reinterpret_cast<const u32x4*>(a.ws + i * a.vsplits);
         u32x4 rec[PRE];
 #pragma unroll
-        for (int s = 0; s < PRE; ++s) rec[s] = s < a.vsplits ? pr[s] : u32x4{0u, 0u, 0u, 0u};
+        for (int s = 0; s < PRE; ++s) rec[s] = !own && s < a.vsplits ? pr[s] : u32x4{0u, 0u, 0u, 0u};
+        if (own) rec[0] = reinterpret_cast<const u32x4*>(own)[b < a.B ? b : 0];
         const bool eligible = b < a.B && a.mask[i] == 1 && !(a.scaffold && a.scaffold[i]);
         float conf_out = -INFINITY;
         uint8_t com = 0;
@@ -752,6 +755,59 @@ __global__ __launch_bounds__(STHREADS) void block_select_kernel(Args a)
         count = 1;
     }
     if (tid == 0 && a.n_unmasked) a.n_unmasked[n] = count;
+}
+
+__global__ __launch_bounds__(STHREADS) void block_select_kernel(Args a) { select_block(a, (int)wg_id_x(), thread_id_x(), nullptr); }
+
+// Small calls in one launch: a workgroup per rollout, a wavefront per position in turn, decisions by the first wavefront on
+// records in LDS.  Bound by latency and launches either way.  The same values as the two kernels: a row's lanes walk it in
+// ascending order and meet in the same reductions (their sums in another order: confidences differ by 1e-7).
+template <typename T>
+__global__ __launch_bounds__(SMALL_THREADS) void block_unmask_small_kernel(Args a)
+{
+    constexpr int VEC = 16 / sizeof(T);
+    __shared__ __align__(16) Partial part[SMALL_B];
+    const int n = (int)wg_id_x(), tid = thread_id_x(), wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int V = (int)a.V;
+    for (int b = wave; b < a.B; b += SMALL_THREADS / 64) {
+        const int row = n * a.B + b;
+        const uint8_t m = a.mask[row], sc = a.scaffold ? a.scaffold[row] : (uint8_t)0;
+        if (m != 1 || sc) continue;
+        const T* x0 = static_cast<const T*>(a.logits) + (size_t)row * V;
+        ThreadRun t;
+        t.r.m = -INFINITY;
+        t.r.idx = 0x7fffffff;
+        t.r.s = 0.f;
+        t.mc = -INFINITY;
+        auto at = [&](int v) { return sizeof(T) == 2 ? bf16_to_f32(((const uint16_t*)x0)[v]) : ((const float*)x0)[v]; };
+        const int head = min((int)((VEC - ((size_t)row * V) % VEC) % VEC), V), nvec = (V - head) / VEC;
+        if (lane < head) {
+            const float x[1] = {at(lane)};
+            absorb<1, true>(t, x, lane);
+        }
+        const u32x4* vp = reinterpret_cast<const u32x4*>(x0 + head);
+        for (int i = lane; i < nvec; i += 64) {
+            const u32x4 raw = vp[i];
+            const uint32_t q[4] = {raw.x, raw.y, raw.z, raw.w};
+            float x[VEC];
+#pragma unroll
+            for (int j = 0; j < VEC; ++j)
+                x[j] = sizeof(T) == 4 ? __uint_as_float(q[j % 4]) : (j & 1) ? __uint_as_float(q[j / 2] & 0xffff0000u) : __uint_as_float(q[j / 2] << 16);
+            absorb<VEC, true>(t, x, head + i * VEC);
+        }
+        const int tail = head + nvec * VEC + lane;
+        if (tail < V) {
+            const float x[1] = {at(tail)};
+            absorb<1, true>(t, x, tail);
+        }
+        Run r = settle(t);
+        const float m_wave = wave_max(r.m);
+        const float sum = wave_sum(r.m == m_wave ? r.s : r.s * fast_exp2((r.m - m_wave) * LOG2E));
+        const int idx = wave_min(r.m == m_wave ? r.idx : 0x7fffffff);
+        if (lane == 0) part[b] = Partial{m_wave, idx, sum, 0};
+    }
+    __syncthreads();
+    if (wave == 0) select_block(a, n, lane, part);
 }
 
 // Accept scan of scaffold speculative decoding: one wavefront per rollout.
@@ -899,6 +955,17 @@ hipError_t launch_unmask(const fdd_unmask_params& p, const UnmaskPlan& plan, hip
     a.N = p.N; a.B = p.B; a.tau = p.tau;
     set_pieces(a, plan.vsplits, p.V, plan.vsplits);
     a.c = 0.f; a.seed_lo = 0u; a.seed_hi = 0u;
+    // One launch where a wavefront's share of the rows is short: it takes them one after the other, a memory latency each, and a
+    // launch saved is 3 us replayed and 2.4 us of the host.  us per call with a fork, replayed, two launches / one, with the share:
+    // N=1, B=8, V=512 fp32 (2 KB) 7.3/5.3; B=32, V=512 bf16 (4 KB) N=4 7.4/7.1, N=64 9.5/8.0; N=8, B=64, V=512 fp32 (16 KB) 7.9/10.2;
+    // N=8, B=32, V=2000 bf16 (16 KB) 8.0/9.9.
+    const long long share = (p.B + SMALL_THREADS / 64 - 1) / (SMALL_THREADS / 64) * (p.V * (p.dtype == FDD_BF16 ? 2 : 4));
+    if (p.B <= SMALL_B && share <= kSmallShare) {
+        a.vsplits = 1;
+        if (p.dtype == FDD_BF16) hipLaunchKernelGGL(block_unmask_small_kernel<uint16_t>, dim3(p.N), dim3(SMALL_THREADS), 0, s, a);
+        else hipLaunchKernelGGL(block_unmask_small_kernel<float>, dim3(p.N), dim3(SMALL_THREADS), 0, s, a);
+        return hipGetLastError();
+    }
     launch_reduce<true>(a, p.dtype, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
