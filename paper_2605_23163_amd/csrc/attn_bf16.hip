@@ -1103,7 +1103,7 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
     const float* ml = a.ws_ml + ((size_t)M * a.max_seg * MROWS + wave * 32 + r) * 2;
 
     float m = -INFINITY, sum = 0.f;           // this thread's segments: largest m, sum of weights against it
-    float acc[8];
+    float acc[8];                             // and their weighted average
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
     for (int s0 = 0; s0 < n_seg; s0 += SG * UX) {
@@ -1128,17 +1128,23 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
             mx = fmaxf(mx, y[u].x);
         }
         const float mref = mx == -INFINITY ? 0.f : mx;
-        if (s0 > 0) {
-            const float f = __builtin_amdgcn_exp2f((m - mref) * a.c);
-            sum *= f;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] *= f;
-        }
+        const float old = s0 > 0 ? sum * __builtin_amdgcn_exp2f((m - mref) * a.c) : 0.f;
         m = mx;
+        sum = old;
 #pragma unroll
         for (int u = 0; u < UX; ++u) {
-            const float w = y[u].y * __builtin_amdgcn_exp2f((y[u].x - mref) * a.c);
-            sum += w;
+            y[u].y *= __builtin_amdgcn_exp2f((y[u].x - mref) * a.c);
+            sum += y[u].y;
+        }
+        // weights are divided before they meet the values: the sum of a few thousand keys' worth of large values would overflow
+        const float inv = sum > 0.f ? 1.f / sum : 0.f;
+        if (s0 > 0) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] *= old * inv;
+        }
+#pragma unroll
+        for (int u = 0; u < UX; ++u) {
+            const float w = y[u].y * inv;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 acc[2 * j] = fmaf(__uint_as_float(x[u][j] << 16), w, acc[2 * j]);
@@ -1150,12 +1156,12 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
         const float mx = reduce_groups<SG>(m, [](float p, float q) { return fmaxf(p, q); });
         const float f = __builtin_amdgcn_exp2f((m - (mx == -INFINITY ? 0.f : mx)) * a.c);
         auto add = [](float p, float q) { return p + q; };
-        sum = reduce_groups<SG>(sum * f, add);
+        sum *= f;
+        const float total = reduce_groups<SG>(sum, add), share = total > 0.f ? sum / total : 0.f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = reduce_groups<SG>(acc[j] * f, add);
+        for (int j = 0; j < 8; ++j) acc[j] = reduce_groups<SG>(acc[j] * share, add);
     }
     if (!live || sg != 0) return;
-    const float inv = sum > 0.f ? 1.f / sum : 0.f;
     const int pb = fast_div(khv, a.dHkv), kh = khv - pb * a.Hkv;
     const int row = row0 + r;
     const int sel = fast_div(row, a.dG), g = row - sel * a.G;
@@ -1165,8 +1171,8 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
     bf16x4 lo, hi;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        lo[j] = (__bf16)(acc[j] * inv);
-        hi[j] = (__bf16)(acc[4 + j] * inv);
+        lo[j] = (__bf16)acc[j];
+        hi[j] = (__bf16)acc[4 + j];
     }
     *reinterpret_cast<bf16x4*>(op) = lo;
     *reinterpret_cast<bf16x4*>(op + 8) = hi;

@@ -35,3 +35,23 @@ def test_segment_counts(oracle, shape, D):
     err = np.abs(to_f64(out) - ref).max()
     v_max = max(np.abs(to_f64(t[k])).max() for k in ("prefix_v", "block_v"))
     assert np.isfinite(err) and err <= 3 * 2.0**-9 * v_max
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("shape", [(1, 4, 1, 1, 20000, 0), (8, 40, 28, 4, 700, 9), (4, 64, 28, 4, 260, 2)])
+def test_large_values(oracle, shape, D):
+    """Values up to 2e36: a segment's sum of them still fits fp32, the sum over all keys does not; the average does.
+    Probabilities are 1; averages and outputs are each rounded to bf16, by 2^-8 of themselves at most."""
+    import paper_2605_23163_amd as F
+    N, B, Hq, Hkv, L, splits = shape
+    print_case(test="attn_merge_large", shape=shape, D=D)
+    rng = np.random.default_rng(L + D)
+    d = rand_attn(rng, N, B, L, Hq, Hkv, D, W.BF16)
+    d["q"] = np.zeros_like(d["q"])             # equal weights
+    for k in ("prefix_v", "block_v"):
+        d[k] = W.to_storage(rng.uniform(1e36, 2e36, d[k].shape).astype(np.float32), W.BF16)
+    t = {k: to_dev(v) for k, v in d.items()}
+    out = F.fdd_block_attn(t["q"], t["prefix_k"], t["prefix_v"], t["block_k"], t["block_v"], splits=splits)
+    torch.cuda.synchronize()
+    ref = oracle.block_attn(d["q"], d["prefix_k"], d["prefix_v"], d["block_k"], d["block_v"])
+    np.testing.assert_allclose(to_f64(out), ref, rtol=2 * 2.0**-8)
