@@ -204,7 +204,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
     constexpr int KS = D / 16;   // MFMA k-steps of Q K^T
     constexpr int DB = D / 32;   // 32-channel blocks of the output
     constexpr int MROWS = WAVES * 32;
-    constexpr bool SPREAD = WAVES == 8 && D == 128;   // order of a pipelined step, see there
+    constexpr bool SPREAD = WAVES == 8 && D == 128 && PACKED;   // order of a pipelined step, see there
     constexpr uint32_t RSRC_FLAGS = 0x00020000;
 
     extern __shared__ __align__(16) unsigned char lds[];
@@ -645,7 +645,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
 
             // One pipelined step: probabilities and P V of tile i from s_cur while
             // the scores of tile i+1 go to s_nxt; K of tile i+4 and V of tile i+3 are requested.
-            //   slots  0- 7  S(i+1) first 32 keys   ||  row maximum of tile i (and, with 8 wavefronts at D = 128, the requests)
+            //   slots  0- 7  S(i+1) first 32 keys   ||  row maximum of tile i (and, in the spread order, the requests)
             //   slots  8-15  S(i+1) second 32 keys  ||  exp of the first 32 keys
             //   slots 16-23  P V first 32 keys      ||  exp of the second 32 keys
             //   slots 24-31  P V second 32 keys
@@ -693,7 +693,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                     // behind waits).  One workgroup alone 1.36 -> 1.27 us a tile; N=16, L=16384 227.5 -> 222.9 us a call, N=64,
                     // L=32768 1679 -> 1645 (fragments 3 ahead 1.28, 4 ahead 1.32; requests from slot 0 on or in consecutive slots
                     // 1.28, 1.29).  With one wavefront per SIMD and at D = 64, where a slot carries twice the exponentials,
-                    // the plain order below is 1 and 3 % faster.
+                    // the plain order below is 1 and 3 % faster.  So it is where V is read as it lies, whose requests and fragments
+                    // take more vector instructions a slot: N=16, B=64, L=16384 246.3 spread, 239.8 plain, L=4096 75.4/72.3; N=32,
+                    // B=64, L=4096 128.0/124.3 (prefixes in rotation; 1 % the other way with free ranges, N=64, L=2048 142.5/144.3).
                     constexpr int NPV = 4 * DB, NSL = 2 * KS + NPV;        // slots of P V, of the step
                     auto frag = [&](int j) -> bf16x8 {
                         return j < 2 * KS ? kfrag(j / KS, j % KS) : vfrag((j - 2 * KS) / (2 * DB), (j - 2 * KS) % (2 * DB));
