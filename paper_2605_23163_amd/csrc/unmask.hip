@@ -616,8 +616,9 @@ __global__ __launch_bounds__(VTHREADS) void vocab_sample_kernel(Args a)
 constexpr int STHREADS = 64;   // one wavefront per rollout: no LDS, no workgroup barrier
 constexpr int SMALL_THREADS = 512, SMALL_B = 128;   // small calls: threads per rollout, positions at most
 
-// The decisions for rollout n, by one wavefront (lane `tid`).  `own`: the records of the rollout's positions, one each, in LDS
-// (small calls, see below), or nullptr: vsplits per position in the workspace.
+// The decisions for rollout n, by one wavefront (lane `tid`), on vsplits records per position in the workspace (the first PRE
+// of them requested together with the mask bytes), or, OWN, on one record each in LDS (small calls, see below).
+template <int PRE, bool OWN>
 __device__ __forceinline__ void select_block(const Args& a, int n, int tid, const Partial* own)
 {
     const double tau = (double)a.tau;
@@ -658,12 +659,11 @@ __device__ __forceinline__ void select_block(const Args& a, int n, int tid, cons
         // The first pieces' records are requested together with the mask bytes, not after them: whether the
         // position is eligible is known one memory round trip later, and the records are then already there.
         // (records of positions that are not eligible hold whatever an earlier call left; they are not used)
-        constexpr int PRE = 8;
-        const u32x4* pr = reinterpret_cast<const u32x4*>(a.ws + i * a.vsplits);
+        const int vsplits = OWN ? 1 : a.vsplits;
+        const Partial* const p = OWN ? own + (b < a.B ? b : 0) : a.ws + i * vsplits;
         u32x4 rec[PRE];
 #pragma unroll
-        for (int s = 0; s < PRE; ++s) rec[s] = !own && s < a.vsplits ? pr[s] : u32x4{0u, 0u, 0u, 0u};
-        if (own) rec[0] = reinterpret_cast<const u32x4*>(own)[b < a.B ? b : 0];
+        for (int s = 0; s < PRE; ++s) rec[s] = s < vsplits ? reinterpret_cast<const u32x4*>(p)[s] : u32x4{0u, 0u, 0u, 0u};
         const bool eligible = b < a.B && a.mask[i] == 1 && !(a.scaffold && a.scaffold[i]);
         float conf_out = -INFINITY;
         uint8_t com = 0;
@@ -674,25 +674,24 @@ __device__ __forceinline__ void select_block(const Args& a, int n, int tid, cons
                 q.m = __uint_as_float(r.x); q.arg = (int)r.y; q.s = __uint_as_float(r.z); q.pad = 0;
                 return q;
             };
-            const Partial* p = a.ws + i * a.vsplits;
             // pieces cover ascending index ranges: strict '>' keeps the lowest id
             float M = unpack(rec[0]).m;
             arg = unpack(rec[0]).arg;
 #pragma unroll
             for (int s = 1; s < PRE; ++s) {
                 const Partial q = unpack(rec[s]);
-                if (s < a.vsplits && q.m > M) { M = q.m; arg = q.arg; }
+                if (s < vsplits && q.m > M) { M = q.m; arg = q.arg; }
             }
-            for (int s = PRE; s < a.vsplits; ++s)
+            for (int s = PRE; s < vsplits; ++s)
                 if (p[s].m > M) { M = p[s].m; arg = p[s].arg; }
             // sum of the pieces' fp32 sums, rescaled to the row maximum, finished in fp64
             double z = 0.0;
 #pragma unroll
             for (int s = 0; s < PRE; ++s) {
                 const Partial q = unpack(rec[s]);
-                if (s < a.vsplits && q.s > 0.f) z += (double)(q.s * fast_exp2((q.m - M) * LOG2E));
+                if (s < vsplits && q.s > 0.f) z += (double)(q.s * fast_exp2((q.m - M) * LOG2E));
             }
-            for (int s = PRE; s < a.vsplits; ++s)
+            for (int s = PRE; s < vsplits; ++s)
                 if (p[s].s > 0.f) z += (double)(p[s].s * fast_exp2((p[s].m - M) * LOG2E));
             const double conf = 1.0 / z;
             conf_out = (float)conf;
@@ -757,7 +756,8 @@ __device__ __forceinline__ void select_block(const Args& a, int n, int tid, cons
     if (tid == 0 && a.n_unmasked) a.n_unmasked[n] = count;
 }
 
-__global__ __launch_bounds__(STHREADS) void block_select_kernel(Args a) { select_block(a, (int)wg_id_x(), thread_id_x(), nullptr); }
+template <int PRE>
+__global__ __launch_bounds__(STHREADS) void block_select_kernel(Args a) { select_block<PRE, false>(a, (int)wg_id_x(), thread_id_x(), nullptr); }
 
 // Small calls in one launch: a workgroup per rollout, a wavefront per position in turn, decisions by the first wavefront on
 // records in LDS.  Bound by latency and launches either way.  The same values as the two kernels: a row's lanes walk it in
@@ -807,7 +807,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void block_unmask_small_kernel(Args 
         if (lane == 0) part[b] = Partial{m_wave, idx, sum, 0};
     }
     __syncthreads();
-    if (wave == 0) select_block(a, n, lane, part);
+    if (wave == 0) select_block<1, true>(a, n, lane, part);
 }
 
 // Accept scan of scaffold speculative decoding: one wavefront per rollout.
@@ -961,7 +961,6 @@ hipError_t launch_unmask(const fdd_unmask_params& p, const UnmaskPlan& plan, hip
     // N=8, B=32, V=2000 bf16 (16 KB) 8.0/9.9.
     const long long share = (p.B + SMALL_THREADS / 64 - 1) / (SMALL_THREADS / 64) * (p.V * (p.dtype == FDD_BF16 ? 2 : 4));
     if (p.B <= SMALL_B && share <= kSmallShare) {
-        a.vsplits = 1;
         if (p.dtype == FDD_BF16) hipLaunchKernelGGL(block_unmask_small_kernel<uint16_t>, dim3(p.N), dim3(SMALL_THREADS), 0, s, a);
         else hipLaunchKernelGGL(block_unmask_small_kernel<float>, dim3(p.N), dim3(SMALL_THREADS), 0, s, a);
         return hipGetLastError();
@@ -969,7 +968,9 @@ hipError_t launch_unmask(const fdd_unmask_params& p, const UnmaskPlan& plan, hip
     launch_reduce<true>(a, p.dtype, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(block_select_kernel, dim3(p.N), dim3(STHREADS), 0, s, a);
+    // (eight records' requests where there are four or fewer cost 0.2 us for every 64 positions of a block)
+    if (a.vsplits <= 4) hipLaunchKernelGGL(block_select_kernel<4>, dim3(p.N), dim3(STHREADS), 0, s, a);
+    else hipLaunchKernelGGL(block_select_kernel<8>, dim3(p.N), dim3(STHREADS), 0, s, a);
     return hipGetLastError();
 }
 
