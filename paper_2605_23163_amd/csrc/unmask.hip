@@ -28,6 +28,7 @@
 //                 the tau test and the forced single commit, and writes
 //                 tokens / mask / confidences.
 #include <algorithm>
+#include <type_traits>
 
 #include "fdd_internal.h"
 
@@ -72,7 +73,6 @@ struct Args {
     int N, B, vsplits;
     int units;              // workgroups of a vocabulary pass: N B pieces
     int pieces;             // pieces per row: vsplits, or twice as many whose (key, id) pairs share a record
-    int compact;            // workgroups are dealt to eligible rows only
     int per;                // vocabulary entries per piece (the last pieces of a row may be shorter or empty)
     FastDiv dVs;            // division by pieces
     long long V;
@@ -249,10 +249,13 @@ __device__ __forceinline__ unsigned unit_of_workgroup(unsigned n_units)
     return (g << 3) + ((u + g + (g >> 3) + (g >> 6) + (g >> 9)) & 7u);
 }
 
-// the row and the piece of this workgroup; false: nothing to do
+// the row and the piece of this workgroup; false: nothing to do.  COMPACT: workgroups are dealt to eligible rows only (a
+// template argument: with the choice inside one kernel every workgroup waited for one more round of its arguments, 5 % of a
+// call of 131072 short rows)
+template <bool COMPACT>
 __device__ __forceinline__ bool unit_of(const Args& a, int* row, int* piece)
 {
-    if (a.compact) {
+    if (COMPACT) {
         const int u = (int)wg_id_x(), t = fast_div(u, a.dVs);
         *piece = u - t * a.pieces;
         *row = eligible_row(a.mask, a.scaffold, a.N * a.B, t);
@@ -265,13 +268,13 @@ __device__ __forceinline__ bool unit_of(const Args& a, int* row, int* piece)
 }
 
 // T = uint16_t (bf16 bits) or float; SUM = false leaves (max, arg max) only and a sum of 0
-template <typename T, bool SUM, int THREADS>
+template <typename T, bool SUM, int THREADS, bool COMPACT>
 __global__ __launch_bounds__(THREADS) void vocab_reduce_kernel(Args a)
 {
     constexpr int VEC = 16 / sizeof(T);
     constexpr int UNROLL = THREADS == 512 ? 5 : 6;      // 16-byte loads in flight per thread
     int row, piece;
-    if (!unit_of(a, &row, &piece)) return;
+    if (!unit_of<COMPACT>(a, &row, &piece)) return;
     const long long v_lo = (long long)piece * a.per;
     const long long v_hi = min(a.V, v_lo + a.per);
     const T* base = static_cast<const T*>(a.logits) + (size_t)row * (size_t)a.V;
@@ -464,13 +467,13 @@ constexpr int VUNROLL = 5;       // sampled verifier: 16-byte loads in flight pe
 // a clear winner in 4 of 5 rows, 36 (87) with none; N=16, B=64 63 (231) and 100 (230); N=5, B=40, V=50001 21 (211: rows
 // that start inside a generator block took a block per entry).  Without a winner the generator's 32 x 32 bit products
 // are what is left.
-template <typename T>
+template <typename T, bool COMPACT>
 __global__ __launch_bounds__(VTHREADS) void vocab_sample_kernel(Args a)
 {
     constexpr int VEC = 16 / sizeof(T);
     constexpr int NW = VEC + 4;               // generator words that cover VEC entries starting anywhere
     int row, piece;
-    if (!unit_of(a, &row, &piece)) return;
+    if (!unit_of<COMPACT>(a, &row, &piece)) return;
     const long long v_lo = (long long)piece * a.per;
     const long long v_hi = min(a.V, v_lo + a.per);
     const T* base = static_cast<const T*>(a.logits) + (size_t)row * (size_t)a.V;
@@ -910,11 +913,13 @@ static void set_pieces(Args& a, int vsplits, long long V, int pieces)
     a.pieces = pieces;
     a.units = a.N * a.B * pieces;
     a.V = V;
-    a.compact = a.N * a.B >= 16 && a.N * a.B <= LIVE_ROWS && a.units > 512 && a.units <= 2560;
     const long long per = (V + pieces - 1) / pieces;
     a.per = (int)std::min<long long>((per + 63) / 64 * 64, V);
     a.dVs = make_fastdiv((uint32_t)pieces);
 }
+
+// whether workgroups are dealt to eligible rows only (see eligible_row)
+static bool compact(const Args& a) { return a.N * a.B >= 16 && a.N * a.B <= LIVE_ROWS && a.units > 512 && a.units <= 2560; }
 
 // Threads per piece: 512 from 48 KB on (its loads in two groups instead of four, and twice the wavefronts for the few
 // workgroups of a small call), 256 below, where a group of 512 is mostly empty.  Measured, us per unmask call with a fork,
@@ -923,15 +928,28 @@ static void set_pieces(Args& a, int vsplits, long long V, int pieces)
 template <bool SUM>
 static void launch_reduce(const Args& a, int dtype, hipStream_t s)
 {
-    const dim3 grid((unsigned)a.units);
     const bool wide = (long long)a.per * (dtype == FDD_BF16 ? 2 : 4) >= 48 * 1024;
-    if (dtype == FDD_BF16) {
-        if (wide) hipLaunchKernelGGL((vocab_reduce_kernel<uint16_t, SUM, 512>), grid, dim3(512), 0, s, a);
-        else hipLaunchKernelGGL((vocab_reduce_kernel<uint16_t, SUM, 256>), grid, dim3(256), 0, s, a);
-    } else {
-        if (wide) hipLaunchKernelGGL((vocab_reduce_kernel<float, SUM, 512>), grid, dim3(512), 0, s, a);
-        else hipLaunchKernelGGL((vocab_reduce_kernel<float, SUM, 256>), grid, dim3(256), 0, s, a);
-    }
+    auto go = [&](auto t, auto threads, auto comp) {
+        constexpr int THREADS = decltype(threads)::value;
+        hipLaunchKernelGGL((vocab_reduce_kernel<decltype(t), SUM, THREADS, decltype(comp)::value>), dim3((unsigned)a.units), dim3(THREADS), 0, s, a);
+    };
+    auto sized = [&](auto t, auto comp) {
+        if (wide) go(t, std::integral_constant<int, 512>(), comp);
+        else go(t, std::integral_constant<int, 256>(), comp);
+    };
+    auto typed = [&](auto comp) {
+        if (dtype == FDD_BF16) sized(uint16_t(), comp);
+        else sized(float(), comp);
+    };
+    if (compact(a)) typed(std::true_type());
+    else typed(std::false_type());
+}
+
+template <typename T>
+static void launch_sample(const Args& a, hipStream_t s)
+{
+    if (compact(a)) hipLaunchKernelGGL((vocab_sample_kernel<T, true>), dim3((unsigned)a.units), dim3(VTHREADS), 0, s, a);
+    else hipLaunchKernelGGL((vocab_sample_kernel<T, false>), dim3((unsigned)a.units), dim3(VTHREADS), 0, s, a);
 }
 
 hipError_t launch_unmask(const fdd_unmask_params& p, const UnmaskPlan& plan, hipStream_t s)
@@ -999,8 +1017,8 @@ hipError_t launch_verify(const fdd_verify_params& p, const UnmaskPlan& plan, hip
     a.seed_lo = (uint32_t)p.seed;
     a.seed_hi = (uint32_t)(p.seed >> 32);
     if (p.temperature > 0.f) {
-        if (p.dtype == FDD_BF16) hipLaunchKernelGGL((vocab_sample_kernel<uint16_t>), dim3((unsigned)a.units), dim3(VTHREADS), 0, s, a);
-        else hipLaunchKernelGGL((vocab_sample_kernel<float>), dim3((unsigned)a.units), dim3(VTHREADS), 0, s, a);
+        if (p.dtype == FDD_BF16) launch_sample<uint16_t>(a, s);
+        else launch_sample<float>(a, s);
     } else {
         // greedy verifier: step 3 of scaffold speculative decoding compares arg maxima only, so no exponentials
         launch_reduce<false>(a, p.dtype, s);
