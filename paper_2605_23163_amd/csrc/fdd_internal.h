@@ -111,6 +111,25 @@ inline dim3 f32_grid(int wgs)
     return dim3((unsigned)((per_row + kNumXCD - 1) / kNumXCD * kNumXCD), (unsigned)rows);
 }
 
+// Unmask calls that take one launch, a workgroup of kOneLaunchWaves wavefronts per rollout, instead of a reduction over all
+// rows and the decisions behind it.  A wavefront takes its rows one after the other, a memory latency each.  us per call,
+// replayed, bf16, two launches / one:
+//   - short rows: N=1, B=8, V=512 7.3/4.9; B=16, V=1024 (4 KB a wavefront) 7.3/6.0, V=2048 (8 KB) 7.2/7.1; N=64, B=32, V=512
+//     8.7/6.8, V=1024 9.0/7.7 (fp32, N=8, B=64, V=512, 16 KB 7.9/10.2);
+//   - up to 4 rows a wavefront (B = 32), or as many rollouts as positions, whose rows would take several rounds of workgroups:
+//     B=64, V=128, N=1 7.3/8.5, N=16 7.9/8.8, N=64 9.7/8.9, N=256 18.1/9.1; B=128, V=128, N=1 8.2/13.7, N=64 13.3/14.3, N=256
+//     30.4/15.1;
+//   - up to one round of workgroups (four per compute unit); beyond it, where the rollouts keep the wavefronts busy: B=1, V=512,
+//     N=1024 8.7/6.3, N=4096 13.1/13.3, N=16384 30.8/42.3, V=2048, N=65536 118/401; B=4, N=16384, V=512 57/46, V=1024 61/73;
+//     B=8, N=16384, V=1024 107/83, V=2048 118/130; B=12, N=4096, V=1000 45/38; B=16, N=16384, V=1024 225/143.
+// (This also keeps the launch below 2^32 work items: N B <= 2^24.)
+constexpr int kOneLaunchWaves = 8, kOneLaunchB = 128;
+inline bool unmask_in_one_launch(int N, int B, long long row_bytes)
+{
+    const long long share = (B + kOneLaunchWaves - 1) / kOneLaunchWaves * row_bytes;      // bytes a wavefront reads
+    return B <= kOneLaunchB && share <= 4096 && (B <= 32 || N >= B) && (N <= 4 * kNumCU || (B >= 4 && 3 * share <= 1024 * B));
+}
+
 // Stream-K ranges: U units over W workgroups, base = U / W, rem = U % W; the
 // first `rem` workgroups own base + 1 units, the others base (>= 1).
 __host__ __device__ inline int unit_begin(int w, int base, int rem) { return w * base + (w < rem ? w : rem); }

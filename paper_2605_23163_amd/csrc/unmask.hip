@@ -38,7 +38,6 @@ namespace {
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr int PIECE_KB = 64;         // a row is cut into pieces of at least this size ...
 constexpr int PIECE_KB_FEW = 16;     // A call of few rows takes up to 8 pieces a row, of at least this size and up to
-constexpr long long kSmallShare = 4 * 1024;   // bytes of logits per wavefront up to which a call is one launch
 constexpr int kFewPieces = 1024;     // this number in all.  us per call with a fork, replayed, unmask / sampled verifier:
                                      // V = 152064 bf16, N=4, B=32, 4 pieces 13.5/28.0, 8 13.1/20.5, 16 14.9/25.9; N=1, 1 piece
                                      // 19.4/43.8, 4 11.2/19.7, 8 11.2/14.8, 16 12.6/17.0; V = 50001, 200 rows, 1 piece 12.5/28.8,
@@ -617,7 +616,7 @@ __global__ __launch_bounds__(VTHREADS) void vocab_sample_kernel(Args a)
 }
 
 constexpr int STHREADS = 64;   // one wavefront per rollout: no LDS, no workgroup barrier
-constexpr int SMALL_THREADS = 512, SMALL_B = 128;   // small calls: threads per rollout, positions at most
+constexpr int SMALL_THREADS = kOneLaunchWaves * 64;   // small calls: threads per rollout
 
 // The decisions for rollout n, by one wavefront (lane `tid`), on vsplits records per position in the workspace (the first PRE
 // of them requested together with the mask bytes), or, OWN, on one record each in LDS (small calls, see below).
@@ -769,7 +768,7 @@ template <typename T>
 __global__ __launch_bounds__(SMALL_THREADS) void block_unmask_small_kernel(Args a)
 {
     constexpr int VEC = 16 / sizeof(T);
-    __shared__ __align__(16) Partial part[SMALL_B];
+    __shared__ __align__(16) Partial part[kOneLaunchB];
     const int n = (int)wg_id_x(), tid = thread_id_x(), wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int V = (int)a.V;
     for (int b = wave; b < a.B; b += SMALL_THREADS / 64) {
@@ -973,12 +972,7 @@ hipError_t launch_unmask(const fdd_unmask_params& p, const UnmaskPlan& plan, hip
     a.N = p.N; a.B = p.B; a.tau = p.tau;
     set_pieces(a, plan.vsplits, p.V, plan.vsplits);
     a.c = 0.f; a.seed_lo = 0u; a.seed_hi = 0u;
-    // One launch where a wavefront's share of the rows is short: it takes them one after the other, a memory latency each, and a
-    // launch saved is 3 us replayed and 2.4 us of the host.  us per call with a fork, replayed, two launches / one, with the share:
-    // N=1, B=8, V=512 fp32 (2 KB) 7.3/5.3; B=32, V=512 bf16 (4 KB) N=4 7.4/7.1, N=64 9.5/8.0; N=8, B=64, V=512 fp32 (16 KB) 7.9/10.2;
-    // N=8, B=32, V=2000 bf16 (16 KB) 8.0/9.9.
-    const long long share = (p.B + SMALL_THREADS / 64 - 1) / (SMALL_THREADS / 64) * (p.V * (p.dtype == FDD_BF16 ? 2 : 4));
-    if (p.B <= SMALL_B && share <= kSmallShare) {
+    if (unmask_in_one_launch(p.N, p.B, p.V * (p.dtype == FDD_BF16 ? 2 : 4))) {
         if (p.dtype == FDD_BF16) hipLaunchKernelGGL(block_unmask_small_kernel<uint16_t>, dim3(p.N), dim3(SMALL_THREADS), 0, s, a);
         else hipLaunchKernelGGL(block_unmask_small_kernel<float>, dim3(p.N), dim3(SMALL_THREADS), 0, s, a);
         return hipGetLastError();
