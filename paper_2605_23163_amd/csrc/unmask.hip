@@ -920,14 +920,18 @@ static void set_pieces(Args& a, int vsplits, long long V, int pieces)
 // whether workgroups are dealt to eligible rows only (see eligible_row)
 static bool compact(const Args& a) { return a.N * a.B >= 16 && a.N * a.B <= LIVE_ROWS && a.units > 512 && a.units <= 2560; }
 
-// Threads per piece: 512 from 48 KB on (its loads in two groups instead of four, and twice the wavefronts for the few
-// workgroups of a small call), 256 below, where a group of 512 is mostly empty.  Measured, us per unmask call with a fork,
-// replayed, 256 / 512: pieces of 76 KB, 128 live rows 15.7/15.1, 720 43.2/41.1, 2867 137.7/134.5; 50 KB, 1024 rows (half of
-// them live) 18.4/17.1; 33 KB 17.8/19.8; 16 KB, 128 rows 11.1/12.0.
+// Threads per piece: 512 from 60 KB on (its loads in two groups instead of four), 256 below, where the second group of 512 is
+// nearly empty.  us per call, replayed, half of the rows live, 256 / 512 threads, and in brackets the mean of their ratio over
+// shares of live rows from 0.2 to 1 (a last round of workgroups that is nearly empty moves a single point by 10 %):
+//   with sums, pieces of 49 KB, 4096 rows 27.0/28.2 (0.97); 55 KB 29.1/29.6 (1.00); 61 KB 32.4/31.3 (1.02); 70 KB 36.3/34.2
+//   (1.09); 64 KB, two a row 51.0/52.0 (1.01), fp32, 2048 rows 32.1/29.8 (1.08); 74 KB, four a row 1024 rows 36.7/36.1 (1.04), 2048
+//   63.2/69.3 (0.97), 4096 105/101 (1.04);
+//   without, 49 KB, 4096 rows in two 42.0/48.7 (0.91), 2048 in four 38.8/40.5 (0.96); 54 KB 42.3/45.9 (0.97); 63 KB 46.5/46.4
+//   (1.01); 64 KB 48.7/46.9 (1.03); 74 KB 57.2/59.2 (1.00), 100/95.7 (1.04).
 template <bool SUM>
 static void launch_reduce(const Args& a, int dtype, hipStream_t s)
 {
-    const bool wide = (long long)a.per * (dtype == FDD_BF16 ? 2 : 4) >= 48 * 1024;
+    const bool wide = (long long)a.per * (dtype == FDD_BF16 ? 2 : 4) >= 60 * 1024;
     auto go = [&](auto t, auto threads, auto comp) {
         constexpr int THREADS = decltype(threads)::value;
         hipLaunchKernelGGL((vocab_reduce_kernel<decltype(t), SUM, THREADS, decltype(comp)::value>), dim3((unsigned)a.units), dim3(THREADS), 0, s, a);
