@@ -189,12 +189,9 @@ __device__ __forceinline__ float bf16_to_f32(uint32_t bits16) { return __uint_as
 // ELIGIBLE row, so that the live workgroups come first and together, and the dispatcher deals them out evenly.  (With
 // row = u / vsplits, workgroups of rows that are not eligible left at once, but not before they had been dealt a place:
 // a scaffold pattern, which all rollouts share, left some compute units with several live workgroups and others with
-// none.  N=8, B=32, V=152064, half the rows eligible, with a fork, replayed: 18.7 -> 15.7 us,
-// the sampled verifier 30.8 -> 27.9.  Nothing is gained up to 512 pieces, which are two to a compute unit, and from about 3000
-// on, where so many even out: N=16, B=64 41.1 -> 42.1; those go by `unit_of_workgroup` below.)  Every wavefront counts for itself: a lane
-// looks at 16 positions, ballots give the counts before it, no LDS and no barrier; mask and scaffold are read in one
-// round trip.  Returns -1 past the last eligible row. Up to LIVE_ROWS rows,
-// which a wavefront reads at once.
+// none.)  Every wavefront counts for itself: a lane looks at 16 positions, ballots give the counts before it, no LDS and no
+// barrier; mask and scaffold are read in one round trip.  Returns -1 past the last eligible row.  Up to LIVE_ROWS rows, which a
+// wavefront reads at once; `deal_to_eligible` has the calls it pays for, the others go by `unit_of_workgroup` below.
 constexpr int LIVE_ROWS = 1024;
 __device__ __forceinline__ int eligible_row(const uint8_t* mask, const uint8_t* scaffold, int rows, int target)
 {
@@ -917,8 +914,20 @@ static void set_pieces(Args& a, int vsplits, long long V, int pieces)
     a.dVs = make_fastdiv((uint32_t)pieces);
 }
 
-// whether workgroups are dealt to eligible rows only (see eligible_row)
-static bool compact(const Args& a) { return a.N * a.B >= 16 && a.N * a.B <= LIVE_ROWS && a.units > 512 && a.units <= 2560; }
+// Whether workgroups are dealt to eligible rows only (see eligible_row).  It costs each of them 0.3 us at its start, so not
+// where it has little to do, and nothing is gained up to 512 pieces, two to a compute unit, or from about 3000 on, where so
+// many even out.  us per call, replayed, row by row / dealt, at shares of 0.5 and 0.9 of the rows live:
+//   with sums N=8, B=32, V=152064 (pieces of 74 KB) 18.6/15.4, 20.0/20.5; N=16, B=64, V=50001 (98 KB) 21.4/17.6, 23.9/24.5, V=20000
+//   (39 KB) 13.8/12.7, 14.5/15.1, V=9973 (20 KB) 11.1/10.7, 11.7/12.1, V=2000 8.4/8.7, 8.4/9.4;
+//   without N=8, B=32, V=152064 (37 KB, 2048 pieces) 16.0/15.1, 18.4/19.0; N=16, B=64, V=20000 (39 KB, 1024 pieces) 12.4/11.7,
+//   13.4/14.0; N=4, B=40, V=50001 (16 KB) 9.8/10.1, 10.5/11.1;
+//   sampled verifier N=8, B=32, V=152064 39.1/29.4, 43.6/44.6; N=16, B=64, V=2000 12.9/11.6, 13.2/13.9.
+enum class Pass { SUMS, ARGMAX, SAMPLE };
+static bool deal_to_eligible(const Args& a, Pass pass, long long piece_bytes)
+{
+    if (a.N * a.B < 16 || a.N * a.B > LIVE_ROWS || a.units <= 512 || a.units > 2560) return false;
+    return pass == Pass::SAMPLE || (piece_bytes >= 32 * 1024 && (pass == Pass::SUMS || a.units > 1024));
+}
 
 // Threads per piece: 512 from 60 KB on (its loads in two groups instead of four), 256 below, where the second group of 512 is
 // nearly empty.  us per call, replayed, half of the rows live, 256 / 512 threads, and in brackets the mean of their ratio over
@@ -931,7 +940,8 @@ static bool compact(const Args& a) { return a.N * a.B >= 16 && a.N * a.B <= LIVE
 template <bool SUM>
 static void launch_reduce(const Args& a, int dtype, hipStream_t s)
 {
-    const bool wide = (long long)a.per * (dtype == FDD_BF16 ? 2 : 4) >= 60 * 1024;
+    const long long piece_bytes = (long long)a.per * (dtype == FDD_BF16 ? 2 : 4);
+    const bool wide = piece_bytes >= 60 * 1024;
     auto go = [&](auto t, auto threads, auto comp) {
         constexpr int THREADS = decltype(threads)::value;
         hipLaunchKernelGGL((vocab_reduce_kernel<decltype(t), SUM, THREADS, decltype(comp)::value>), dim3((unsigned)a.units), dim3(THREADS), 0, s, a);
@@ -944,14 +954,14 @@ static void launch_reduce(const Args& a, int dtype, hipStream_t s)
         if (dtype == FDD_BF16) sized(uint16_t(), comp);
         else sized(float(), comp);
     };
-    if (compact(a)) typed(std::true_type());
+    if (deal_to_eligible(a, SUM ? Pass::SUMS : Pass::ARGMAX, piece_bytes)) typed(std::true_type());
     else typed(std::false_type());
 }
 
 template <typename T>
 static void launch_sample(const Args& a, hipStream_t s)
 {
-    if (compact(a)) hipLaunchKernelGGL((vocab_sample_kernel<T, true>), dim3((unsigned)a.units), dim3(VTHREADS), 0, s, a);
+    if (deal_to_eligible(a, Pass::SAMPLE, 0)) hipLaunchKernelGGL((vocab_sample_kernel<T, true>), dim3((unsigned)a.units), dim3(VTHREADS), 0, s, a);
     else hipLaunchKernelGGL((vocab_sample_kernel<T, false>), dim3((unsigned)a.units), dim3(VTHREADS), 0, s, a);
 }
 
