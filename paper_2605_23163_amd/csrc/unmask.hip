@@ -1014,12 +1014,14 @@ hipError_t launch_verify(const fdd_verify_params& p, const UnmaskPlan& plan, hip
     a.draft = p.draft;
     a.rf_tk = nullptr; a.rf_tv = nullptr; a.rf_bk = nullptr; a.rf_bv = nullptr; a.rf_T = 0; a.rf_row_vecs = 0;
     a.N = p.N; a.B = p.B; a.tau = 0.f;
-    // The sampled verifier, bound by its arithmetic, takes twice the pieces while they are 16 KB or more and 2048 at most.
-    // us per call with a fork, replayed, plain / twice: V = 152064 bf16, 70 % of the rows live, a clear winner in 4 of 5 rows:
-    // N=1, B=32 16.8/15.6, N=4 21.5/21.3, N=8 30.4/27.3 (36.0/36.6 without winners; 512 threads per piece 30.9, 36.3); more
-    // pieces N=16, B=64 64.7/64.7 (99.9/115); smaller ones V = 50001, 200 rows in 5 21.5/24.3.
-    const long long bytes = p.V * (p.dtype == FDD_BF16 ? 2 : 4);
-    const bool twice = p.temperature > 0.f && (long long)p.N * p.B * plan.vsplits <= 1024 && bytes >= 32ll * 1024 * plan.vsplits;
+    // The sampled verifier, bound by its arithmetic, takes twice the pieces while those are 16 KB or more and 2048 at most, or, with
+    // no more than two of them to a compute unit, 8 KB.  us per call, replayed, plain / twice: V = 152064 bf16, 70 % of the rows
+    // live, a clear winner in 4 of 5 rows: N=1, B=32 16.8/15.6, N=4 21.5/21.3, N=8 30.4/27.3 (36.0/36.6 without winners; 512
+    // threads per piece 30.9, 36.3); more pieces N=16, B=64 64.7/64.7 (99.9/115); smaller ones V = 50001, 200 rows in 5 21.5/24.3.
+    // Smaller and few, half of the rows live: V = 9973, N=8, B=32 14.8/13.6, N=1 13.8/12.1; V = 16000, N=8 14.5/12.7; V = 50001, N=1
+    // 14.6/13.2; too small V = 5000, N=8 11.0/11.4.
+    const long long bytes = p.V * (p.dtype == FDD_BF16 ? 2 : 4), units = (long long)p.N * p.B * plan.vsplits;
+    const bool twice = p.temperature > 0.f && units <= 1024 && bytes >= (units <= kNumCU ? 16ll : 32ll) * 1024 * plan.vsplits;
     set_pieces(a, plan.vsplits, p.V, twice ? 2 * plan.vsplits : plan.vsplits);
     a.c = p.temperature > 0.f ? (float)(1.4426950408889634 / (double)p.temperature) : 0.f;
     a.seed_lo = (uint32_t)p.seed;

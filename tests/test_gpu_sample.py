@@ -28,10 +28,12 @@ def test_noise_bound_is_never_below_the_noise(oracle):
 
 
 # one position per block, so that the token of every row is seen.  V: one entry, less than a vector, rows that start at
-# every place of a vector and of a generator block, several pieces; more than 1024 pieces (narrow workgroups) and fewer
+# every place of a vector and of a generator block, several pieces; more than 1024 pieces and fewer, of 16 KB and less, around
+# 256 of them (where a row is cut twice as often)
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", [(1100, 1003, W.BF16, 0.7), (1100, 257, W.F32, 1.0), (30, 1, W.BF16, 1.0), (30, 7, W.BF16, 0.5),
-                                  (64, 20485, W.BF16, 1.0), (40, 70001, W.BF16, 0.7), (24, 33003, W.F32, 0.7), (16, 152064, W.BF16, 1.0)])
+                                  (64, 20485, W.BF16, 1.0), (40, 70001, W.BF16, 0.7), (24, 33003, W.F32, 0.7), (16, 152064, W.BF16, 1.0),
+                                  (200, 8192, W.BF16, 0.7), (256, 8191, W.BF16, 0.7), (257, 9973, W.BF16, 1.0), (31, 4099, W.F32, 1.0)])
 @pytest.mark.parametrize("spike", [0.0, 25.0])
 def test_sampled_tokens_with_and_without_a_clear_winner(F, oracle, case, spike):
     N, V, dtype, temperature = case
