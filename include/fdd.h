@@ -140,7 +140,9 @@ typedef struct fdd_attn_params {
 
 /* Bytes of scratch fdd_block_attn needs for these params (host-only
  * arithmetic, no device is touched).  Returns 0 if the params are invalid.
- * The figure is smaller when prefix_v_packed is set. */
+ * The figure serves the same call with and without prefix_v_packed, except
+ * that a very large call without it also needs room for the copy of V that
+ * it then makes. */
 size_t fdd_block_attn_workspace(const fdd_attn_params *p);
 fdd_status fdd_block_attn(const fdd_attn_params *p);
 

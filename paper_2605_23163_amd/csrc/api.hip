@@ -199,18 +199,31 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
     if (p.dtype == FDD_BF16) {
         cut_bf16(256);
         // M-tiles of 128 rows (workgroups of 4 wavefronts, one per SIMD) while the call is short: a wavefront alone on its SIMD
-        // takes 0.86 us a tile where two take 1.33 (D = 128, few workgroups), a workgroup starts on three half tiles instead of
-        // seven, and the segments are half as large.  Two wavefronts per SIMD do more per second, so with many units per
-        // compute unit, or where only the larger tiles cut into equal pieces that fill the chip, those are faster.  us per call
-        // (replayed), 256 / 128 rows, Hq = 28, Hkv = 4, B = 32, with units per compute unit of the 256-row plan in brackets:
-        // D = 128: N=1, L=2048 [0.6] 14.0/10.5; N=12, L=3000 [8.5] 31.6/28.9; N=8, L=4096 [7.5] 29.4/27.4, L=6000 [10.8]
-        // 35.0/35.5; N=4, L=8192 [7.3] 28.2/26.7, L=12000 [10.5] 33.2/34.3; N=2, L=32768 [14] 40.4/43.3; N=24, L=1024 [6.9, no
-        // equal pieces of 128 rows] 27.4/29.4; Hq = Hkv = 8, N=20, L=2000 [3.5] 32.1/21.7.  D = 64 (half the matrix work per
-        // exponential): N=1, L=8192 [2] 13.4/11.2, N=8, L=4096 [7.5] 19.8/20.2, N=16, L=4096 [15] 27.9/32.7.
+        // takes 0.86 us a tile where two take 1.33 (D = 128, few workgroups, tiles in the cache), a workgroup starts on three half
+        // tiles instead of seven, and the segments are half as large.  Two wavefronts per SIMD do more per second, and four ring
+        // slots hide more of the memory's latency than two, so with many units per compute unit those are faster: from 9 on, or 6
+        // where V is read as it lies, whose tiles of short rows take longer to come (but not if only the smaller M-tiles need no
+        // cutting), and always where only the larger tiles cut into equal pieces that fill the chip.  us per call, replayed,
+        // prefixes from memory (900 MB of them in rotation), 256 / 128 rows, Hq = 28, Hkv = 4, B = 32; in brackets the units per
+        // compute unit of the 256-row plan:
+        //   D = 128, V laid out: N=1, L=2048 [0.5] 15.0/11.3; N=8, L=2048 [3.9] 25.2/19.6; N=1, L=16384 [4.0] 22.6/20.1; N=8, L=4096 [7.7]
+        //   29.9/27.2; N=4, L=8192 [8.4] 29.0/27.0; N=2, L=18000 [8.9] 29.6/30.0; N=12, L=3000 [9.1] 31.4/28.9; N=4, L=9500 [9.7] 29.9/29.9;
+        //   N=8, L=6000 [10.9] 35.7/36.6; N=16, L=4096 [15] 41.4/44.2;
+        //   D = 128, plain V: N=8, L=2048 [3.9] 25.2/21.6; N=1, L=16384 [4.0] 23.2/22.4; N=8, L=2800 [5.4] 27.4/25.7; N=4, L=5500 [5.7]
+        //   25.3/24.4; N=2, L=10000 [5.0] 23.9/24.7, L=12000 [6.0] 25.2/26.7; N=16, L=1400 [6.1] 27.2/27.2; N=4, L=6500 [6.8] 26.6/27.3; N=8,
+        //   L=4096 [7.7] 30.3/32.5; N=16, L=2048 [8.3] 30.6/33.3; not cut: N=32, L=512 [6.1] 26.7/21.7, L=768 [7.9] 29.6/26.4; no equal
+        //   pieces of 128 rows: N=24, L=1024 [7.2] 27.6/29.0;
+        //   D = 64 (half the matrix work per exponential), V laid out: N=8, L=2048 [3.9] 16.9/14.9; N=4, L=4096 [4.3] 16.1/14.7; N=8, L=2400
+        //   [4.6] 17.3/18.3; N=1, L=20000 [4.9] 18.4/16.8; N=4, L=5000 [5.3] 17.1/17.1; N=8, L=4096 [7.7] 19.7/19.7;
+        //   D = 64, plain V: N=8, L=2048 [3.9] 16.9/16.4; N=2, L=8192 [4.1] 15.4/16.7; N=8, L=2400 [4.6] 17.3/18.9; N=4, L=4700 [4.9]
+        //   16.8/17.4; not cut: N=32, L=300 [4.4] 16.9/13.2.
+        // (plain V reads 2 to 5 % slower than V laid out with 256 rows, up to 18 % slower with 128)
         const int uniform256 = pl.uniform;
-        if (pl.U <= (p.D == 128 ? 9 : 5) * (long long)kNumCU) {
+        const long long u256 = pl.U, line = (p.D == 128 ? 9 : 5) * (long long)kNumCU, plain_line = (p.D == 128 ? 6 : 4) * (long long)kNumCU;
+        if (u256 <= line) {
             cut_bf16(128);
-            if (pl.uniform == 0 && (uniform256 > 0 || NM > kNumCU)) cut_bf16(256);
+            const bool plain = !p.prefix_v_packed && u256 > plain_line && !(pl.uniform == 1 && uniform256 > 1);
+            if (plain || (pl.uniform == 0 && (uniform256 > 0 || NM > kNumCU))) cut_bf16(256);
         }
     } else {
         set_rows(kF32RowTile);
@@ -239,7 +252,7 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
     }
     // The kernel reads V repacked when the caller brings it that way (fdd_prefix_pack, once per prefix).
     // Repacking inside the call is a launch and a pass over V of its own, and the kernel that reads V as it
-    // lies (transposing LDS reads) is only about 2.5 % slower: measured, the in-call pass pays from about
+    // lies (transposing LDS reads) is 2 to 5 % slower: measured, the in-call pass pays from about
     // the size of N=16, B=64, L=16384 on (28 M-tiles x 256 tiles per KV head), and costs 3..5 us below it.
     pl.ws_vt_bytes = 0;
     pl.packed = p.dtype == FDD_BF16 && p.L >= pl.key_tile && (p.prefix_v_packed || (long long)pl.MT * pl.TP >= 8192);
@@ -295,7 +308,15 @@ size_t fdd_block_attn_workspace(const fdd_attn_params* p)
     if (check_attn_shape(p) != FDD_OK) return 0;
     AttnPlan plan;
     make_attn_plan(*p, &plan);
-    return plan.ws_o_bytes + plan.ws_ml_bytes + plan.ws_vt_bytes;
+    size_t partials = plan.ws_o_bytes + plan.ws_ml_bytes;
+    if (p->dtype == FDD_BF16) {      // enough for the same call with V laid out and with V as it lies, which may be cut differently
+        fdd_attn_params other = *p;
+        other.prefix_v_packed = p->prefix_v_packed ? nullptr : p;      // (only whether it is set counts)
+        AttnPlan o;
+        make_attn_plan(other, &o);
+        partials = std::max(partials, o.ws_o_bytes + o.ws_ml_bytes);
+    }
+    return partials + plan.ws_vt_bytes;
 }
 
 fdd_status fdd_block_attn(const fdd_attn_params* p)

@@ -57,6 +57,10 @@ def test_attn_workspace_is_host_arithmetic(lib):
     # 4 KV heads x 1 M-tile x 4 segments x 256 rows x (128 bf16 averages + (m, l) in fp32)
     assert lib.fdd_block_attn_workspace(C.byref(p4)) == 4 * 4 * 256 * (128 * 2 + 2 * 4)
     assert lib.fdd_block_attn_workspace(C.byref(attn(Hq=30))) == 0     # invalid -> 0
+    # one figure for plain V and for V laid out, also where the two are cut into M-tiles of different sizes
+    for kw in (dict(N=8, L=4096), dict(N=4, L=8192), dict(N=2, L=18000), dict(N=1, L=28000), dict(N=8, L=2400, D=64), dict(N=32, L=768)):
+        plain, laid_out = attn(**kw), attn(prefix_v_packed=4096, **kw)
+        assert lib.fdd_block_attn_workspace(C.byref(plain)) == lib.fdd_block_attn_workspace(C.byref(laid_out))
 
 
 @pytest.mark.parametrize("kw,code", [
