@@ -18,7 +18,8 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libfdd.so")
-MARSHAL = os.path.join(PKG, "_marshal.so")
+# (named for this interpreter: another one does not load it)
+MARSHAL = os.path.join(PKG, "_marshal" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"),
@@ -44,8 +45,8 @@ def _run(cmd):
 
 
 def marshal_command(out):
-    """The compiler call for the binding's native argument marshalling, or None where torch or the Python headers are
-    missing (the binding then does it in Python).  torch is looked up, not imported."""
+    """The compiler call for the binding's native argument marshalling, or None where torch, its headers or Python's are
+    missing.  torch is looked up, not imported."""
     try:
         spec = importlib.util.find_spec("torch")
     except (ImportError, ValueError):
@@ -54,10 +55,36 @@ def marshal_command(out):
     if spec is None or not spec.origin or not os.path.exists(os.path.join(python, "Python.h")):
         return None
     torch = os.path.dirname(spec.origin)
+    if not os.path.isdir(os.path.join(torch, "include")):
+        return None
     lib = os.path.join(torch, "lib")
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + os.path.join(ROOT, "include"), "-I" + python,
             "-I" + os.path.join(torch, "include"), "-I" + os.path.join(torch, "include", "torch", "csrc", "api", "include"),
             os.path.join(CSRC, "marshal.cpp"), "-o", out, "-L" + lib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
+
+
+def build_marshal():
+    """Builds the marshalling module, which the library does not need: without it the binding does the same in Python.
+    Returns its path, or None if it could not be built; an older one does not stay."""
+    old = [f for f in os.listdir(os.path.dirname(MARSHAL)) if f.startswith("_marshal.") and f.endswith(".so")]
+    tmp = MARSHAL + f".{os.getpid()}.tmp"
+    cmd = marshal_command(tmp)
+    built = False
+    if cmd:
+        try:
+            _run(cmd)
+            built = True
+        except (OSError, RuntimeError) as e:
+            print(f"arguments will be marshalled in Python: {e}")
+    for f in old:
+        if not built or f != os.path.basename(MARSHAL):
+            os.remove(os.path.join(os.path.dirname(MARSHAL), f))
+    if not built:
+        if os.path.exists(tmp):
+            os.remove(tmp)
+        return None
+    os.replace(tmp, MARSHAL)
+    return MARSHAL
 
 
 def build(asm: bool = False, jobs: int = 4) -> str:
@@ -73,19 +100,13 @@ def build(asm: bool = False, jobs: int = 4) -> str:
         if asm:   # device assembly next to the objects, for inspection
             cmds.append([HIPCC, *FLAGS, *EXTRA.get(os.path.basename(src), []), "-S", "--offload-device-only",
                          src, "-o", obj[:-2] + ".s"])
-    tmp_marshal = MARSHAL + f".{os.getpid()}.tmp"
-    marshal = marshal_command(tmp_marshal)
-    if marshal:
-        cmds.append(marshal)
-    with ThreadPoolExecutor(max_workers=jobs) as ex:
+    with ThreadPoolExecutor(max_workers=jobs + 1) as ex:
+        marshal = ex.submit(build_marshal)
         list(ex.map(_run, cmds))
+        marshal.result()
     tmp = LIB + f".{os.getpid()}.tmp"
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp])
     os.replace(tmp, LIB)
-    if marshal:
-        os.replace(tmp_marshal, MARSHAL)
-    elif os.path.exists(MARSHAL):
-        os.remove(MARSHAL)
     return LIB
 
 
