@@ -125,6 +125,7 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
         NM = (long long)p.Hkv * batch * pl.MT;
     };
     bool partials;
+    long long private_tiles = 0;     // bf16 path: of an M-tile
     auto cut_bf16 = [&](int rows) {
         set_rows(rows);
         // The private tiles of an M-tile (extension and block of every rollout its rows belong to) are done
@@ -135,7 +136,7 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
         const long long BG = p.n_q_positions > 0 ? std::max(1ll, (long long)p.n_q_positions * pl.G / p.N) : (long long)p.B * pl.G;
         const long long span_lo = (pl.mtile_rows + BG - 1) / BG;                 // rollouts an M-tile spans at least
         const long long span = span_lo + ((pl.mtile_rows % BG) != 0 && BG < (long long)pl.R ? 1 : 0);
-        const long long private_tiles = (span < p.N ? span : p.N) *
+        private_tiles = (span < p.N ? span : p.N) *
                                         ((p.E + pl.key_tile - 1) / pl.key_tile + (p.B + pl.key_tile - 1) / pl.key_tile);
         long long wt = (private_tiles * 9 + 4) / 5;
         if (wt < 1) wt = 1;
@@ -203,16 +204,16 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
         // tiles instead of seven, and the segments are half as large.  Two wavefronts per SIMD do more per second, and four ring
         // slots hide more of the memory's latency than two, so with many units per compute unit those are faster: from 9 on, or 6
         // where V is read as it lies, whose tiles of short rows take longer to come (but not if only the smaller M-tiles need no
-        // cutting), and always where only the larger tiles cut into equal pieces that fill the chip.  us per call, replayed,
-        // prefixes from memory (900 MB of them in rotation), 256 / 128 rows, Hq = 28, Hkv = 4, B = 32; in brackets the units per
-        // compute unit of the 256-row plan:
+        // cutting, or with many private tiles, of which they have half), and always where only the larger tiles cut into equal
+        // pieces that fill the chip.  us per call, replayed, prefixes from memory (900 MB of them in rotation), 256 / 128 rows,
+        // Hq = 28, Hkv = 4, B = 32; in brackets the units per compute unit of the 256-row plan:
         //   D = 128, V laid out: N=1, L=2048 [0.5] 15.0/11.3; N=8, L=2048 [3.9] 25.2/19.6; N=1, L=16384 [4.0] 22.6/20.1; N=8, L=4096 [7.7]
         //   29.9/27.2; N=4, L=8192 [8.4] 29.0/27.0; N=2, L=18000 [8.9] 29.6/30.0; N=12, L=3000 [9.1] 31.4/28.9; N=4, L=9500 [9.7] 29.9/29.9;
         //   N=8, L=6000 [10.9] 35.7/36.6; N=16, L=4096 [15] 41.4/44.2;
         //   D = 128, plain V: N=8, L=2048 [3.9] 25.2/21.6; N=1, L=16384 [4.0] 23.2/22.4; N=8, L=2800 [5.4] 27.4/25.7; N=4, L=5500 [5.7]
         //   25.3/24.4; N=2, L=10000 [5.0] 23.9/24.7, L=12000 [6.0] 25.2/26.7; N=16, L=1400 [6.1] 27.2/27.2; N=4, L=6500 [6.8] 26.6/27.3; N=8,
-        //   L=4096 [7.7] 30.3/32.5; N=16, L=2048 [8.3] 30.6/33.3; not cut: N=32, L=512 [6.1] 26.7/21.7, L=768 [7.9] 29.6/26.4; no equal
-        //   pieces of 128 rows: N=24, L=1024 [7.2] 27.6/29.0;
+        //   L=4096 [7.7] 30.3/32.5, with E=64 31.0/33.7, E=128 31.2/34.8, E=256 41.0/36.8; N=16, L=2048 [8.3] 30.6/33.3; not cut: N=32,
+        //   L=512 [6.1] 26.7/21.7, L=768 [7.9] 29.6/26.4; no equal pieces of 128 rows: N=24, L=1024 [7.2] 27.6/29.0;
         //   D = 64 (half the matrix work per exponential), V laid out: N=8, L=2048 [3.9] 16.9/14.9; N=4, L=4096 [4.3] 16.1/14.7; N=8, L=2400
         //   [4.6] 17.3/18.3; N=1, L=20000 [4.9] 18.4/16.8; N=4, L=5000 [5.3] 17.1/17.1; N=8, L=4096 [7.7] 19.7/19.7;
         //   D = 64, plain V: N=8, L=2048 [3.9] 16.9/16.4; N=2, L=8192 [4.1] 15.4/16.7; N=8, L=2400 [4.6] 17.3/18.9; N=4, L=4700 [4.9]
@@ -221,8 +222,9 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
         const int uniform256 = pl.uniform;
         const long long u256 = pl.U, line = (p.D == 128 ? 9 : 5) * (long long)kNumCU, plain_line = (p.D == 128 ? 6 : 4) * (long long)kNumCU;
         if (u256 <= line) {
+            const bool few_private = 7 * private_tiles <= pl.TP;
             cut_bf16(128);
-            const bool plain = !p.prefix_v_packed && u256 > plain_line && !(pl.uniform == 1 && uniform256 > 1);
+            const bool plain = p.splits == 0 && !p.prefix_v_packed && u256 > plain_line && few_private && !(pl.uniform == 1 && uniform256 > 1);
             if (plain || (pl.uniform == 0 && (uniform256 > 0 || NM > kNumCU))) cut_bf16(256);
         }
     } else {
