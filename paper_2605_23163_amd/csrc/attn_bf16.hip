@@ -1295,9 +1295,11 @@ hipError_t launch_attn_merge_bf16(const fdd_attn_params& p, const AttnPlan& plan
     a.dBase1 = make_fastdiv((uint32_t)(base + 1));
     a.c = scale * 1.4426950408889634f;
     // SG threads per chunk: more of them while the chunks of a call leave most of the chip's lanes idle and each still has
-    // four segments or more to request.  us per call (replayed) with 1, 2, 4, 8 of them: N=1, L=16384 (52 segments, 14 k
-    // chunks) 28.3, 25.2, 23.8, 23.6; N=4, L=8192 (18, 57 k) 28.8, 28.5, 28.4, 29.0; N=8, L=4096 (9, 115 k) 27.3, 27.5,
-    // 27.7, 28.8; N=16, L=4096 (2, 459 k) 70.0, 71.5, 73.4, 81.6.
+    // four segments or more to request.  us per call (replayed) with 1, 2, 4, 8 of them, Hq = 28, Hkv = 4, D = 128, B = 32: N=1
+    // (14 k chunks), L=512 (5 segments) 10.8, 10.4, 10.5, 11.0, L=2048 (17) 13.1, 12.0, 11.0, 11.6, L=16384 (29) 24.1, 21.5, 20.1,
+    // 20.5; N=2 (29 k), L=8192 (15) 21.1, 19.9, 19.8, 20.4, L=32768 (31) 43.1, 40.9, 40.5, 40.8; N=4 (57 k), L=8192 (9) 27.5, 26.8, 27.4,
+    // 28.5; N=8 (115 k), L=4096 (4) 27.0, 27.3, 29.1, 31.9, L=6000 (9) 35.1, 36.3, 36.0, 39.1; N=16 (229 k), L=4096 (4) 41.1, 42.2, 44.9,
+    // 50.8; one head, N=1, B=4, L=20000 (64 chunks, 157 segments) 37.9, 26.1, 17.4, 14.9.
     const long long chunks = (long long)p.Hkv * batch * plan.R * (p.D / 8);
     const int n = plan.uniform > 0 ? plan.uniform : plan.max_seg;
     int sg = 1;

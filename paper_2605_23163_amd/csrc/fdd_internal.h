@@ -133,11 +133,6 @@ inline bool unmask_in_one_launch(int N, int B, long long row_bytes)
 // Stream-K ranges: U units over W workgroups, base = U / W, rem = U % W; the
 // first `rem` workgroups own base + 1 units, the others base (>= 1).
 __host__ __device__ inline int unit_begin(int w, int base, int rem) { return w * base + (w < rem ? w : rem); }
-__host__ __device__ inline int wg_of_unit(int u, int base, int rem)
-{
-    const int cut = rem * (base + 1);
-    return u < cut ? u / (base + 1) : rem + (u - cut) / base;
-}
 
 // `before_main`, if not null, is recorded on the stream right before the main kernel (after the V pre-pass).
 hipError_t launch_attn_bf16(const fdd_attn_params& p, const AttnPlan& plan, float scale, hipStream_t s, hipEvent_t before_main);

@@ -37,13 +37,13 @@ namespace {
 
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr int PIECE_KB = 64;         // a row is cut into pieces of at least this size ...
-constexpr int PIECE_KB_FEW = 16;     // A call of few rows takes up to 8 pieces a row, of at least this size and up to
+constexpr int PIECE_KB_ARGMAX = 32;  // ... and of this size in the pass that takes no sums (measured: 8 pieces of a
+                                     // 297 KB row are 1.5 us per call faster there than 4, and 1..2 us slower with the sums)
+constexpr int PIECE_KB_FEW = 16;     // a call of few rows takes up to 8 pieces a row, of at least this size and up to
 constexpr int kFewPieces = 1024;     // this number in all.  us per call with a fork, replayed, unmask / sampled verifier:
                                      // V = 152064 bf16, N=4, B=32, 4 pieces 13.5/28.0, 8 13.1/20.5, 16 14.9/25.9; N=1, 1 piece
                                      // 19.4/43.8, 4 11.2/19.7, 8 11.2/14.8, 16 12.6/17.0; V = 50001, 200 rows, 1 piece 12.5/28.8,
                                      // 5 11.5/21.5, 8 12.6/24.5; V = 32768, 128 rows, 1 10.4/17.4, 4 8.7/13.4, 8 9.8/12.7.
-constexpr int PIECE_KB_ARGMAX = 32;  // ... and of this size in the pass that takes no sums (measured: 8 pieces of a
-                                     // 297 KB row are 1.5 us per call faster there than 4, and 1..2 us slower with the sums)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 struct Partial {
@@ -460,7 +460,7 @@ constexpr int VUNROLL = 5;       // sampled verifier: 16-byte loads in flight pe
 // wavefront) is worked out as defined, and the row's winner is never dropped, so the verifier's token is the same bit for
 // bit.
 // Measured, bf16, 70 % of the rows live, V = 152064 (in brackets every entry worked out in full): N=8, B=32 27 us (87) with
-// a clear winner in 4 of 5 rows, 36 (87) with none; N=16, B=64 63 (231) and 100 (230); N=5, B=40, V=50001 21 (211: rows
+// a clear winner in 4 of 5 rows, 37 (87) with none; N=16, B=64 68 (231) and 115 (230); N=5, B=40, V=50001 21 (211: rows
 // that start inside a generator block took a block per entry).  Without a winner the generator's 32 x 32 bit products
 // are what is left.
 template <typename T, bool COMPACT>
