@@ -28,5 +28,15 @@ def rand_attn(rng, N, B, L, Hq, Hkv, D, dtype, std=1.0):
                 block_k=f(N, B, Hkv, D), block_v=f(N, B, Hkv, D))
 
 
+def row_error(out, ref):
+    """Largest error of an output row (last axis) in norm, relative to the row.  Three roundings to bf16 (probabilities, segments'
+    averages, outputs), each of 2^-9 to 2^-8 of a value, leave 3e-3 of it whatever the number of keys; ROW_TOL is five times
+    that, and less than what a tile of 64 keys too few leaves among 20000 (6e-2 and more)."""
+    return float((np.linalg.norm(out - ref, axis=-1) / np.linalg.norm(ref, axis=-1)).max())
+
+
+ROW_TOL = 1.5e-2
+
+
 def print_case(**kw):
     print("[case]", " ".join(f"{k}={v}" for k, v in kw.items()), flush=True)

@@ -1,7 +1,8 @@
 """M-tiles that are not full: wavefronts without a stacked row only move tiles (bf16 path).
 
-Row counts on both sides of a wavefront's 32 rows and of a tile's 256, key runs of 0..9 full tiles, with and without a
-ragged last one, in one piece and in several.  Tolerance: the task's 2e-2 for bf16 storage."""
+Row counts on both sides of a wavefront's 32 rows and of 256, key runs of 0..9 full tiles, with and without a ragged last
+one, in one piece and in several.  Calls this short take M-tiles of 128 rows; those of 256 with idle wavefronts are in
+test_gpu_attn_large_tiles.py.  Tolerance: 2e-2 for bf16 storage."""
 import numpy as np
 import pytest
 import torch

@@ -11,10 +11,12 @@ from tests.gpu_util import print_case, to_dev
 pytestmark = pytest.mark.gpu
 
 
-# N, B, V, dtype (8 wavefronts a rollout, 4 KB a wavefront, 128 positions: both sides of each line)
+# N, B, V, dtype (8 wavefronts a rollout, 4 KB a wavefront; more than 32 positions with as many rollouts, 128 at most; more than 1024
+# rollouts of 4 positions or more: both sides of each line)
 @pytest.mark.parametrize("case", [(1, 8, 512, W.F32), (3, 7, 1, W.F32), (2, 9, 3, W.BF16), (5, 33, 129, W.BF16), (4, 65, 227, W.BF16), (2, 128, 64, W.F32),
                                   (1, 128, 128, W.BF16), (2, 129, 100, W.BF16), (2, 32, 512, W.BF16), (1, 8, 1024, W.F32), (1, 8, 1025, W.F32),
-                                  (1, 1, 2048, W.BF16), (1, 1, 2049, W.BF16)])
+                                  (1, 1, 2048, W.BF16), (1, 1, 2049, W.BF16), (66, 65, 99, W.BF16), (128, 128, 31, W.F32), (1027, 5, 33, W.F32),
+                                  (1025, 3, 40, W.BF16)])
 @pytest.mark.parametrize("tau", [0.0, 0.5, 2.0])
 def test_one_launch(oracle, case, tau):
     import paper_2605_23163_amd as F
