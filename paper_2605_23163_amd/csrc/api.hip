@@ -87,27 +87,32 @@ fdd_status check_attn_shape(const fdd_attn_params* p)
 
 }  // namespace
 
-// Workgroups per row tile of the fp32 path.  A round of workgroups takes ceil(tiles / (8 S)) tiles per wavefront, two
-// wavefronts per SIMD at 36 D cycles a tile (32 D of them matrix pipe; 4.0 us per pair at D = 128 and 2.3 GHz), after
-// about 4 us of start, first loads and LDS merge; S > 1 adds the merge kernel (about 4 us, and the partials' way to memory
-// and back).  The smallest estimate wins, fewer splits on ties.  Measured on both sides of the choice, us per call in a loop
-// of nothing but these calls, Hq = 28, Hkv = 4, D = 128, B = 32 (choice in brackets): N = 1, L = 2048: S = 8 24.1, [9] 22.9,
-// 12 34.3; N = 1, L = 16384: 8 76.5, [9] 71.1, 12 104; N = 4, L = 4096: 1 134, [2] 77.3, 3 105; N = 8, L = 4096: [1] 135,
-// 2 149; N = 16, L = 4096: [1] 268, 2 292.
-static int f32_splits(long long row_tiles, long long tiles, int D)
+// Workgroups per row tile of the fp32 path, and the time that is expected of them.
+//   32-row tiles (attn_f32_kernel): a round of workgroups takes ceil(tiles / (8 S)) tiles per wavefront, two wavefronts per
+// SIMD at 36 D cycles a tile (32 D of them matrix pipe; 4.0 us per pair at D = 128 and 2.3 GHz), after about 4 us of start,
+// first loads and LDS merge; S > 1 adds the merge kernel (about 4 us, and the partials' way to memory and back).
+//   128-row tiles (attn_f32_wide_kernel): ceil(tiles / S) tiles of 32 keys a workgroup, 2.3 us each at D = 128 (2.0 with half of the
+// compute units, which clock higher), 1.3 at D = 64, after 8 us of start, queries and first tiles; S > 1 adds 3 us and the partials.
+// The smallest estimate wins, fewer splits on ties.
+struct F32Cut {
+    int splits;
+    double us;
+};
+static F32Cut f32_cut(bool wide, long long row_tiles, long long tiles, int D, int s_min)
 {
-    const double tile_us = 2.0 * 36 * D / 2300.0;
-    double best = 0.0;
-    int s_best = 1;
-    for (int s = 1; s <= 64 && (s == 1 || (s - 1) * kF32Waves < tiles); ++s) {
+    const double tile_us = wide ? (D == 128 ? 2.3 : 1.3) : 2.0 * 36 * D / 2300.0, start_us = wide ? 8.0 : 4.0, merge_us = wide ? 3.0 : 4.0;
+    const int sharers = wide ? 1 : kF32Waves;                    // of a workgroup's keys
+    const double partial_us = (wide ? (double)kF32WideRowTile * D * 4.0 / 4e6 : (double)kF32RowTile * D * 8.0 / 4e6);
+    F32Cut best = {1, 0.0};
+    for (int s = s_min; s <= 64 && (s == s_min || (long long)(s - 1) * sharers < tiles); ++s) {
         const long long rounds = (row_tiles * s + kNumCU - 1) / kNumCU;
-        const long long per_wave = (tiles + (long long)s * kF32Waves - 1) / ((long long)s * kF32Waves);
-        double us = (double)rounds * ((double)per_wave * tile_us + 4.0);
-        if (s > 1) us += 4.0 + (double)row_tiles * s * kF32RowTile * D * 8.0 / 4e6;
-        if (s == 1 || us < best) { best = us; s_best = s; }
+        const long long per = (tiles + (long long)s * sharers - 1) / ((long long)s * sharers);
+        double us = (double)rounds * ((double)per * tile_us + start_us);
+        if (s > 1) us += merge_us + (double)row_tiles * s * partial_us;
+        if (s == s_min || us < best.us) best = {s, us};
         if (row_tiles * s >= 4 * kNumCU) break;      // more rounds gain nothing
     }
-    return s_best;
+    return best;
 }
 
 bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
@@ -228,16 +233,40 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
             if (plain || (pl.uniform == 0 && (uniform256 > 0 || NM > kNumCU))) cut_bf16(256);
         }
     } else {
-        set_rows(kF32RowTile);
-        pl.TPU = pl.TP > 0 ? pl.TP : 1;
-        pl.U = NM * pl.TPU;
-        const long long rows_per_rollout = std::max(1ll, (long long)pl.R / p.N);
-        const long long span = std::min<long long>(p.N, (pl.mtile_rows + rows_per_rollout - 1) / rows_per_rollout + 1);
-        const long long tiles = pl.TP + span * ((p.E + pl.key_tile - 1) / pl.key_tile + (p.B + pl.key_tile - 1) / pl.key_tile);
+        auto cut_f32 = [&](int rows, int key_tile) {
+            set_rows(rows);
+            pl.key_tile = key_tile;
+            pl.TP = (p.L + key_tile - 1) / key_tile;
+            const long long rows_per_rollout = std::max(1ll, (long long)pl.R / p.N);
+            const long long span = std::min<long long>(p.N, (rows + rows_per_rollout - 1) / rows_per_rollout + 1);
+            return pl.TP + span * ((p.E + key_tile - 1) / key_tile + (p.B + key_tile - 1) / key_tile);
+        };
+        // Products on the bf16 pipe (128-row tiles) where they are expected to be faster and the keys are cut at least once more:
+        // a row's sum is rounded twice per 32 keys of a workgroup there, four times per 4 keys of a wavefront here, and with that
+        // many pieces the error against 64 bits was smaller in every one of 60 drawn calls (0.4 to 0.8 of it).  us per call, 32-row
+        // tiles / 128-row tiles (pieces): D = 128, Hq = 28, Hkv = 4, B = 32: N=1, L=2048 23.8 / 21.9 (32); N=1, L=16384 74.0 / 60.7 (32);
+        // N=2, L=1024 25.4 / 22.7 (16); N=4, L=4096 77.6 / 56.3 (8); N=8, L=4096 135.7 / 93.6 (4); N=16, L=4096 268 / 170 (2); D = 64: N=8,
+        // L=4096 74.7 / 55.3 (4); N=5, B=40, L=5003, Hq=14, Hkv=2, E=37 50.5 / 37.0 (8).
+        long long tiles = cut_f32(kF32RowTile, 16);
         int s = p.splits;
-        if (s == 0) s = f32_splits(NM, tiles, p.D);
+        if (s == 0) {
+            const F32Cut narrow = f32_cut(false, NM, tiles, p.D, 1);
+            s = narrow.splits;
+            const long long wide_tiles = cut_f32(kF32WideRowTile, kF32WideKeyTile);
+            const F32Cut wide = f32_cut(true, NM, wide_tiles, p.D, narrow.splits + 1);
+            // (up to a GiB of partials: beyond it the chip is full many times over, and the narrow tiles need none)
+            const bool fits = NM * wide.splits * (kF32WideRowTile * p.D * 4ll) <= (1ll << 30);
+            if (fits && wide_tiles >= 2 * wide.splits && wide.us < narrow.us) {
+                s = wide.splits;
+                tiles = wide_tiles;
+            } else {
+                tiles = cut_f32(kF32RowTile, 16);
+            }
+        }
         if (s > tiles) s = (int)tiles;
         if (s < 1) s = 1;
+        pl.TPU = pl.TP > 0 ? pl.TP : 1;
+        pl.U = NM * pl.TPU;
         pl.splits = s;
         pl.W = 0;
         pl.uniform = 0;

@@ -2,8 +2,10 @@
 // merge of its splits.
 //
 // The same thing as the bf16 kernel computes (paper, "Block-Causal Diffusion"
-// and "Shared prefix"), with fp32 products and sums on the matrix cores
-// (v_mfma_f32_16x16x4_f32).
+// and "Shared prefix").  Two kernels: attn_f32_kernel, with fp32 products and
+// sums on the matrix cores (v_mfma_f32_16x16x4_f32), for calls of few rows and
+// few keys, and attn_f32_wide_kernel further below, which takes each fp32
+// product apart into bf16 products.
 //
 // How the work is laid out
 //   * A workgroup owns 32 stacked query rows of one KV head (see AttnPlan); its
@@ -35,6 +37,8 @@
 #include "fdd_internal.h"
 
 #include <atomic>
+#include <type_traits>
+#include <utility>
 
 namespace fdd {
 namespace {
@@ -84,128 +88,97 @@ __device__ __forceinline__ const char* uniform(const char* p)
     return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
 }
 
+// Tile t of the keys of a row tile whose rollouts start at n_lo: TP prefix tiles of K keys, then for every rollout the tiles
+// of its extension and of its block.
+struct KeyTile {
+    const char* k;    // first key's row of this KV head
+    const char* v;
+    int valid;        // keys that exist
+    int rollout;      // whose rows may see it (-1: every row)
+    int key0;         // block position of the first key (block tiles under the causal mask), else hugely negative
+};
+template <int K, int D>
+__device__ __forceinline__ KeyTile key_tile(const Args& a, int pb, int kh, int n_lo, int TP, int t)
+{
+    KeyTile r;
+    long long row;
+    long long bs;
+    const float *kp, *vp;
+    r.key0 = -(1 << 30);
+    if (t < TP) {
+        kp = a.pk; vp = a.pv; bs = a.p_bs;
+        row = (long long)t * K;
+        r.valid = min(K, a.L - t * K);
+        r.rollout = -1;
+    } else {
+        const int j = t - TP, i = fast_div(j, a.dPer), w = j - i * a.per;
+        r.rollout = n_lo + i;
+        if (w < a.ext_per) {
+            kp = a.ek; vp = a.ev; bs = a.e_bs;
+            row = (long long)r.rollout * a.Ecap + w * K;
+            r.valid = min(K, a.E - w * K);
+        } else {
+            const int k0 = (w - a.ext_per) * K;
+            kp = a.bk; vp = a.bv; bs = a.b_bs;
+            row = (long long)r.rollout * a.B + k0;
+            r.valid = min(K, a.B - k0);
+            if (a.causal) r.key0 = k0;
+        }
+    }
+    const long long off = ((long long)pb * bs + row * a.Hkv * D + (long long)kh * D) * 4;
+    r.k = uniform(reinterpret_cast<const char*>(kp) + off);
+    r.v = uniform(reinterpret_cast<const char*>(vp) + off);
+    r.valid = __builtin_amdgcn_readfirstlane(r.valid);
+    r.rollout = __builtin_amdgcn_readfirstlane(r.rollout);
+    r.key0 = __builtin_amdgcn_readfirstlane(r.key0);
+    return r;
+}
+
+// Streaming softmax of a wavefront's 32 query rows in the layout of the 16x16x4 matrix instruction.
 template <int D>
-struct F32Cfg {
-    static constexpr int MERGE_FLOATS = WAVES * RT * D;   // outputs of all wavefronts, in register order
-    static constexpr int LDS_BYTES = (MERGE_FLOATS + 2 * WAVES * RT + 2 * RT) * 4;   // + (m, l) per wavefront and row, and per row
+struct WaveState {
+    f32x4 o[2][D / 64][4];   // [query block][64-channel block][e]: channels 64 t + 16 g4 + 4 v + e of query c16
+    float m_ref[2];          // reference the exponentials are taken against (raw score units)
+    float limit[2];          // a score further above the reference raises it; -inf: there is none yet
+    float l_run[2];          // this lane's share of the running sum
 };
 
-template <int D>
-__global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
+// One wavefront over tiles [t_lo, t_hi) of 16 keys.  `several`: the row tile's rows belong to more than one rollout.
+template <int D, typename TileAt>
+__device__ __forceinline__ void f32_wave_loop(const Args& a, const TileAt& tile_at, int t_lo, int t_hi, const f32x4 (&qf)[2][D / 16],
+                                              const int (&my_rollout)[2], const int (&my_b)[2], bool several, WaveState<D>& w)
 {
-#if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
     constexpr int NJ = D / 16;         // 16-byte fragment loads per tile and operand
     constexpr int NT = D / 64;         // 64-channel blocks of the output
-    extern __shared__ __align__(16) float smem[];
-
-    // workgroups are dealt to the 8 XCDs round-robin: those of one XCD own neighbouring row tiles of one
-    // (KV head, split), which walk the same keys
-    const unsigned id = wg_id_y() * a.grid_x + wg_id_x();
-    const int wg = (int)(id % kNumXCD) * a.per_xcd + (int)(id / kNumXCD);
-    if (wg >= a.W) return;
-    const int rest = fast_div(wg, a.dMT), mt = wg - rest * a.MT;
-    const int khv = fast_div(rest, a.dS), split = rest - khv * a.S;
-    const int pb = fast_div(khv, a.dHkv), kh = khv - pb * a.Hkv;     // problem of the batch, KV head
-
-    const int tid = thread_id_x(), lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c16 = lane & 15, g4 = lane >> 4;
-    const int NB = a.N * a.B;
+    const int lane = thread_id_x() & 63, c16 = lane & 15, g4 = lane >> 4;
     const uint32_t stride4 = (uint32_t)(a.Hkv * D * 4);     // bytes between consecutive keys
-
-    // ---- query rows of this lane: c16 of both 16-query blocks --------------------------------------
-    f32x4 qf[2][NJ];
-    int my_rollout[2], my_b[2];
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-        const int row = min(mt * RT + qb * 16 + c16, a.R - 1);
-        const int sel = fast_div(row, a.dG), g = row - sel * a.G;
-        const int nb = position_of(a.qpos, sel, NB);
-        my_rollout[qb] = fast_div(nb, a.dB);
-        my_b[qb] = nb - my_rollout[qb] * a.B;
-        const float* qp = a.q + pb * a.q_bs + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * D + 4 * g4;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) qf[qb][j] = *reinterpret_cast<const f32x4*>(qp + 16 * j);
-    }
-
-    // ---- key tiles of this wavefront ---------------------------------------------------------------
-    // prefix tiles, then for every rollout the rows belong to: extension tiles, block tiles
-    // (rows are in ascending order of position, hence of rollout)
-    const int row_hi = min(mt * RT + RT, a.R) - 1;
-    const int n_lo = __builtin_amdgcn_readfirstlane(fast_div(position_of(a.qpos, fast_div(mt * RT, a.dG), NB), a.dB));
-    const int n_hi = __builtin_amdgcn_readfirstlane(fast_div(position_of(a.qpos, fast_div(row_hi, a.dG), NB), a.dB));
-    const int TP = (a.L + KT - 1) / KT;
-    const int n_tiles = TP + (n_hi - n_lo + 1) * a.per;
-    const int part = split * WAVES + wave, parts = a.S * WAVES;
-    const int t_lo = __builtin_amdgcn_readfirstlane(key_cut(n_tiles, part, parts, a.dParts));
-    const int t_hi = __builtin_amdgcn_readfirstlane(key_cut(n_tiles, part + 1, parts, a.dParts));
-
-    struct Tile {
-        const char* k;    // first key's row of this KV head
-        const char* v;
-        int valid;        // keys that exist
-        int rollout;      // whose rows may see it (-1: every row)
-        int key0;         // block position of the first key (block tiles under the causal mask), else hugely negative
-    };
-    auto tile_at = [&](int t) {
-        Tile r;
-        long long row;
-        long long bs;
-        const float *kp, *vp;
-        r.key0 = -(1 << 30);
-        if (t < TP) {
-            kp = a.pk; vp = a.pv; bs = a.p_bs;
-            row = (long long)t * KT;
-            r.valid = min(KT, a.L - t * KT);
-            r.rollout = -1;
-        } else {
-            const int j = t - TP, i = fast_div(j, a.dPer), w = j - i * a.per;
-            r.rollout = n_lo + i;
-            if (w < a.ext_per) {
-                kp = a.ek; vp = a.ev; bs = a.e_bs;
-                row = (long long)r.rollout * a.Ecap + w * KT;
-                r.valid = min(KT, a.E - w * KT);
-            } else {
-                const int k0 = (w - a.ext_per) * KT;
-                kp = a.bk; vp = a.bv; bs = a.b_bs;
-                row = (long long)r.rollout * a.B + k0;
-                r.valid = min(KT, a.B - k0);
-                if (a.causal) r.key0 = k0;
-            }
-        }
-        const long long off = ((long long)pb * bs + row * a.Hkv * D + (long long)kh * D) * 4;
-        r.k = uniform(reinterpret_cast<const char*>(kp) + off);
-        r.v = uniform(reinterpret_cast<const char*>(vp) + off);
-        r.valid = __builtin_amdgcn_readfirstlane(r.valid);
-        r.rollout = __builtin_amdgcn_readfirstlane(r.rollout);
-        r.key0 = __builtin_amdgcn_readfirstlane(r.key0);
-        return r;
-    };
-
     // Fragments of a tile.  K: row c16, channels 16 j + 4 g4 ..; V: row 4 g4 + v, channels 64 t + 4 c16 ..
     // (rows beyond `valid` repeat the last valid one: masked below, nothing read out of bounds)
     f32x4 kf[NJ], vf[NJ];
-    auto k_off = [&](const Tile& t) { return (uint32_t)min(c16, t.valid - 1) * stride4 + (uint32_t)(16 * g4); };
-    auto v_off = [&](const Tile& t, int v) { return (uint32_t)min(4 * g4 + v, t.valid - 1) * stride4 + (uint32_t)(16 * c16); };
+    auto k_off = [&](const KeyTile& t) { return (uint32_t)min(c16, max(t.valid, 1) - 1) * stride4 + (uint32_t)(16 * g4); };
+    auto v_off = [&](const KeyTile& t, int v) { return (uint32_t)min(4 * g4 + v, max(t.valid, 1) - 1) * stride4 + (uint32_t)(16 * c16); };
     // (offsets inside a tile stay below 2^32, as the whole block K does, but may pass 2^31 with very many KV heads)
     auto load = [&](const char* base, uint32_t off) {
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, -1, 0x00020000);
         return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
     };
 
-    f32x4 o[2][NT][4];       // [query block][64-channel block][e]: channels 64 t + 16 g4 + 4 v + e of query c16
+    auto& o = w.o;
+    auto& m_ref = w.m_ref;
+    auto& limit = w.limit;
+    auto& l_run = w.l_run;
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
+    for (int qb = 0; qb < 2; ++qb) {
+        m_ref[qb] = l_run[qb] = 0.f;
+        limit[qb] = -INFINITY;
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[qb][t][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_ref[2] = {0.f, 0.f};               // reference the exponentials are taken against (raw score units)
-    float limit[2] = {-INFINITY, -INFINITY};   // a score further above the reference raises it; -inf: there is none yet
-    float l_run[2] = {0.f, 0.f};               // this lane's share of the running sum
+    }
 
     if (t_lo < t_hi) {
-        Tile now = tile_at(t_lo);
+        KeyTile now = tile_at(t_lo);
         {
             const uint32_t off = k_off(now);
 #pragma unroll
@@ -225,7 +198,7 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
             // A fragment of the next tile is requested as soon as the matrix instructions that read its
             // predecessor are issued: every request has a whole step to arrive.  (The last tile is requested
             // once more at the end, from the caches.)
-            const Tile next = tile_at(min(t + 1, t_hi - 1));
+            const KeyTile next = tile_at(min(t + 1, t_hi - 1));
             const uint32_t next_k = k_off(next);
             f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
@@ -301,7 +274,7 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
             // ... and, in a row tile of several rollouts, values of another one that are not finite.  A lane's outputs
             // belong to one query: the tile's share is then summed by itself, added where the query sees it, and nothing
             // is left for the sums below.
-            if (now.rollout >= 0 && n_lo != n_hi) {
+            if (now.rollout >= 0 && several) {
                 float x0 = 0.f;      // NaN if any value is not finite
 #pragma unroll
                 for (int j = 0; j < NJ; ++j)
@@ -343,6 +316,70 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
             now = next;
         }
     }
+}
+
+template <int D>
+struct F32Cfg {
+    static constexpr int MERGE_FLOATS = WAVES * RT * D;   // outputs of all wavefronts, in register order
+    static constexpr int LDS_BYTES = (MERGE_FLOATS + 2 * WAVES * RT + 2 * RT) * 4;   // + (m, l) per wavefront and row, and per row
+};
+
+template <int D>
+__global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
+{
+#if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
+    constexpr int NJ = D / 16;         // 16-byte fragment loads per tile and operand
+    constexpr int NT = D / 64;         // 64-channel blocks of the output
+    extern __shared__ __align__(16) float smem[];
+
+    // workgroups are dealt to the 8 XCDs round-robin: those of one XCD own neighbouring row tiles of one
+    // (KV head, split), which walk the same keys
+    const unsigned id = wg_id_y() * a.grid_x + wg_id_x();
+    const int wg = (int)(id % kNumXCD) * a.per_xcd + (int)(id / kNumXCD);
+    if (wg >= a.W) return;
+    const int rest = fast_div(wg, a.dMT), mt = wg - rest * a.MT;
+    const int khv = fast_div(rest, a.dS), split = rest - khv * a.S;
+    const int pb = fast_div(khv, a.dHkv), kh = khv - pb * a.Hkv;     // problem of the batch, KV head
+
+    const int tid = thread_id_x(), lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c16 = lane & 15, g4 = lane >> 4;
+    const int NB = a.N * a.B;
+
+    // ---- query rows of this lane: c16 of both 16-query blocks --------------------------------------
+    f32x4 qf[2][NJ];
+    int my_rollout[2], my_b[2];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+        const int row = min(mt * RT + qb * 16 + c16, a.R - 1);
+        const int sel = fast_div(row, a.dG), g = row - sel * a.G;
+        const int nb = position_of(a.qpos, sel, NB);
+        my_rollout[qb] = fast_div(nb, a.dB);
+        my_b[qb] = nb - my_rollout[qb] * a.B;
+        const float* qp = a.q + pb * a.q_bs + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * D + 4 * g4;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) qf[qb][j] = *reinterpret_cast<const f32x4*>(qp + 16 * j);
+    }
+
+    // ---- key tiles of this wavefront ---------------------------------------------------------------
+    // prefix tiles, then for every rollout the rows belong to: extension tiles, block tiles
+    // (rows are in ascending order of position, hence of rollout)
+    const int row_hi = min(mt * RT + RT, a.R) - 1;
+    const int n_lo = __builtin_amdgcn_readfirstlane(fast_div(position_of(a.qpos, fast_div(mt * RT, a.dG), NB), a.dB));
+    const int n_hi = __builtin_amdgcn_readfirstlane(fast_div(position_of(a.qpos, fast_div(row_hi, a.dG), NB), a.dB));
+    const int TP = (a.L + KT - 1) / KT;
+    const int n_tiles = TP + (n_hi - n_lo + 1) * a.per;
+    const int part = split * WAVES + wave, parts = a.S * WAVES;
+    const int t_lo = __builtin_amdgcn_readfirstlane(key_cut(n_tiles, part, parts, a.dParts));
+    const int t_hi = __builtin_amdgcn_readfirstlane(key_cut(n_tiles, part + 1, parts, a.dParts));
+
+    const auto tile_at = [&](int t) { return key_tile<KT, D>(a, pb, kh, n_lo, TP, t); };
+    WaveState<D> w;
+    f32_wave_loop<D>(a, tile_at, t_lo, t_hi, qf, my_rollout, my_b, n_lo != n_hi, w);
+    auto& o = w.o;
+    auto& m_ref = w.m_ref;
+    auto& limit = w.limit;
+    auto& l_run = w.l_run;
 
     // ---- merge of the wavefronts through LDS ----------------------------------------------------------
     // (lane and thread index are worked out anew: the loop has no registers to keep them in)
@@ -413,6 +450,543 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
             if (ch == 0) {
                 a.ws_ml[prow * 2 + 0] = row_m[r];
                 a.ws_ml[prow * 2 + 1] = row_l[r];
+            }
+        }
+    }
+#endif
+}
+
+// ---------------------------------------------------------------------------
+// The same attention with products on the bf16 matrix pipe, for calls with enough rows and keys (see make_attn_plan).
+//
+// A float is exactly the sum of three bf16 numbers, h + m + l with h the nearest bf16 number, m that of the rest and l what is
+// left (8 bits of mantissa each).  The product of two floats is then six products of bf16 numbers, exact in the matrix unit's
+// fp32 sums; what is dropped (m l', l m', l l') is below 2^-25 of the product, half a unit of an fp32 rounding.  Six
+// products at sixteen times the rate: 96 cycles of matrix pipe per 32 keys, 32 rows and 16 channels instead of 256.
+//
+// How the work is laid out
+//   * A workgroup has 4 wavefronts of 32 stacked rows each (one per SIMD, 512 registers) and takes tiles of 32 keys.  Each
+//     wavefront keeps its queries, split, in registers.  K and V are split once per workgroup, on their way from global memory
+//     through registers into LDS: 2 slots of K [part][key][channel] (16-byte pieces XOR-swizzled by the key), 2 slots of V
+//     [part][16-key step][half][channel][8 keys], the order of the probabilities in the transposed score accumulator.
+//   * One step: the scores of tile i+1 (48 matrix instructions at D = 128), beside them the parts of tile i's probabilities and
+//     the splitting of V of tile i+1; then P V of tile i (48), beside it the exponentials of tile i+1 and the splitting of K of
+//     tile i+2, whose floats were requested a step before.  Slots of one matrix instruction and a slice of vector work, fenced, as
+//     in the bf16 kernel.  A wavefront alone on its SIMD takes 5 cycles per vector instruction and 8 where one waits for the one
+//     before it, so a slot carries four or five that do not: pieces of ten in every other slot cost 12 % of the time.
+//   * What bounds it: N = 8, B = 32, L = 4096, Hq = 28, Hkv = 4, D = 128 takes 93.6 us a call (135.7 with fp32 products): 79 us of
+//     steps, 1 140 TFLOP/s of bf16 products, the rate the bf16 attention reaches at its largest sizes (the chip lowers its
+//     clock: 2.4 us a step with 224 workgroups, 2.0 with 56), 6 us until queries and first tiles are there, the merge.  Queries
+//     in LDS instead of registers and one slot each for K and V: 97.5; o and its small products in one sum: as fast, but the
+//     sum is rounded twelve times per tile (error against 64 bits 2.5 times as large).
+//   * Values that are not finite: a part of an infinity is a NaN, and one in a tile reaches every row of a wavefront.  A
+//     wavefront whose sums are not finite at the end does its keys again with fp32 products (f32_wave_loop), so such calls
+//     give what the kernel above gives, in twice the time and more.
+constexpr int WKT = kF32WideKeyTile, WRT = kF32WideRowTile;
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+
+template <int D>
+struct WideCfg {
+    static constexpr int CH = D / 8;                 // 16-byte pieces of a K row (bf16)
+    static constexpr int RPL = 256 / (D * 2);        // K rows per 256-byte bank line
+    static constexpr int PART = WKT * D * 2;         // bytes of one part of a tile
+    static constexpr int SLOT = 3 * PART;
+    static constexpr int V_RING = 2 * SLOT;          // K slots, then V slots
+    static constexpr int LDS_BYTES = 4 * SLOT;
+    static constexpr int KV = WKT * D / 8 / 256;     // groups of 8 floats per thread and operand
+    static_assert(KV >= 1, "a thread has work in every tile");
+};
+
+#define FDD_PIN(x) asm volatile("" : "+v"(x))
+#define FDD_FENCE() __builtin_amdgcn_sched_barrier(0)
+
+// The nearest bf16 numbers of two floats, packed.
+__device__ __forceinline__ uint32_t round_pair(float x0, float x1)
+{
+    const bf16x2 b = {(__bf16)x0, (__bf16)x1};
+    return __builtin_bit_cast(uint32_t, b);
+}
+// One part of four floats, in two pieces of about as many cycles as a matrix instruction takes: the nearest bf16 numbers, packed;
+// then what is left of the floats, which replaces them.
+struct SplitQuad {
+    uint32_t u, w;
+    float y0, y2;
+    __device__ __forceinline__ void first(const float* x)
+    {
+        u = round_pair(x[0], x[1]);
+        w = round_pair(x[2], x[3]);
+        // (u << 16 by another instruction: the compiler would round the float once more instead)
+        y0 = __uint_as_float(__builtin_amdgcn_perm(u, 0u, 0x05040c0cu));
+        y2 = __uint_as_float(__builtin_amdgcn_perm(w, 0u, 0x05040c0cu));
+        FDD_PIN(y0);
+        FDD_PIN(y2);
+    }
+    __device__ __forceinline__ void second(float* x)
+    {
+        const float y1 = __uint_as_float(u & 0xffff0000u), y3 = __uint_as_float(w & 0xffff0000u);
+        x[0] -= y0;
+        x[2] -= y2;
+        x[1] -= y1;
+        x[3] -= y3;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) FDD_PIN(x[i]);
+    }
+};
+
+template <typename F, int... J>
+__device__ __forceinline__ void for_each_int(F& f, std::integer_sequence<int, J...>)
+{
+    (f(std::integral_constant<int, J>()), ...);
+}
+
+template <int D>
+__global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
+{
+#if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
+    using C = WideCfg<D>;
+    constexpr int KS = D / 16, DB = D / 32, KV = C::KV;
+    extern __shared__ __align__(16) unsigned char lds[];
+
+    // workgroups are dealt to the 8 XCDs round-robin: those of one XCD own neighbouring row tiles of one
+    // (KV head, split), which walk the same keys
+    const unsigned id = wg_id_y() * a.grid_x + wg_id_x();
+    const int wg = (int)(id % kNumXCD) * a.per_xcd + (int)(id / kNumXCD);
+    if (wg >= a.W) return;
+    const int rest = fast_div(wg, a.dMT), mt = wg - rest * a.MT;
+    const int khv = fast_div(rest, a.dS), split = rest - khv * a.S;
+    const int pb = fast_div(khv, a.dHkv), kh = khv - pb * a.Hkv;     // problem of the batch, KV head
+
+    const int tid = thread_id_x(), lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int NB = a.N * a.B;
+    const uint32_t stride4 = (uint32_t)(a.Hkv * D * 4);     // bytes between consecutive keys
+
+    // ---- key tiles of this workgroup: prefix tiles, then the private tiles of every rollout its rows belong to ------
+    const int row_hi = min(mt * WRT + WRT, a.R) - 1;
+    const int n_lo = __builtin_amdgcn_readfirstlane(fast_div(position_of(a.qpos, fast_div(mt * WRT, a.dG), NB), a.dB));
+    const int n_hi = __builtin_amdgcn_readfirstlane(fast_div(position_of(a.qpos, fast_div(row_hi, a.dG), NB), a.dB));
+    const int TP = (a.L + WKT - 1) / WKT;
+    const int n_tiles = TP + (n_hi - n_lo + 1) * a.per;
+    const int t_lo = __builtin_amdgcn_readfirstlane(key_cut(n_tiles, split, a.S, a.dParts));
+    const int t_hi = __builtin_amdgcn_readfirstlane(key_cut(n_tiles, split + 1, a.S, a.dParts));
+    const auto tile_at = [&](int t) { return key_tile<WKT, D>(a, pb, kh, n_lo, TP, min(t, t_hi - 1)); };
+
+    // ---- this thread's share of a tile: KV groups of 8 channels of a key (K), of 8 keys of a channel (V) -------------
+    float raw[2 * KV][8];     // K groups, then V groups
+    const auto k_key = [&](int u) { return (tid + 256 * u) / C::CH; };
+    const auto v_th = [&](int u) { return (wave * 64 + 256 * u) / D; };     // 2 (16-key step) + half: the same for a wavefront
+    const uint32_t v_lane = (uint32_t)(tid % D) * 4;
+    // (in quarters: a K group is two loads, a V group eight)
+    const auto request_k = [&](const KeyTile& t, int u, int quarter) {
+        if (quarter % 2 != 0) return;
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(t.k), 0, -1, 0x00020000);
+        const uint32_t off = (uint32_t)min(k_key(u), t.valid - 1) * stride4 + (uint32_t)(tid % C::CH) * 32;
+        const f32x4 x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + 8 * quarter, 0, 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) raw[u][2 * quarter + e] = x[e];
+    };
+    const auto request_v = [&](const KeyTile& t, int u, int quarter) {
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(t.v), 0, -1, 0x00020000);
+        // (no branch: the compiler counts the loads in flight, and a path without these would make every wait a full one)
+        const int th = v_th(u);
+        const uint32_t first = (uint32_t)((th >> 1) * 16 + (th & 1) * 4) * stride4, last = (uint32_t)(t.valid - 1) * stride4;
+#pragma unroll
+        for (int e = 2 * quarter; e < 2 * quarter + 2; ++e) {
+            const uint32_t soff = min(first + (uint32_t)((e & 3) + (e >> 2) * 8) * stride4, last);
+            raw[KV + u][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, v_lane, soff, 0));
+        }
+    };
+    // where a group's parts go
+    uint32_t dst[2 * KV];
+#pragma unroll
+    for (int u = 0; u < KV; ++u) {
+        const int key = k_key(u);
+        dst[u] = (uint32_t)(key * D * 2 + (((tid % C::CH) ^ ((key / C::RPL) & (C::CH - 1))) << 4));
+        dst[KV + u] = (uint32_t)(C::V_RING + v_th(u) * (D * 16) + (tid % D) * 16);
+    }
+    // Splitting a group, in 14 pieces: first, second, third parts, four floats at a time; a part of the group is written to LDS
+    // when it is done.  At the end the group's floats are used up: its share of tile `next` is requested.
+    u32x4 part_w[3];
+    SplitQuad quad;
+    constexpr int NSP = 14;
+    const auto split_piece = [&](int g, int piece, uint32_t slot, const KeyTile& next) {
+        const int part = piece / 4, r = 4 * ((piece / 2) % 2);
+        if (part < 2) {
+            if (piece % 2 == 0) {
+                quad.first(&raw[g][r]);
+                part_w[part][r / 2] = quad.u;
+                part_w[part][r / 2 + 1] = quad.w;
+            } else {
+                quad.second(&raw[g][r]);
+            }
+        }
+        if (piece == 4 || piece == 8) *reinterpret_cast<u32x4*>(lds + (dst[g] + slot) + (part - 1) * C::PART) = part_w[part - 1];
+        if (piece == 8 || piece == 9) {
+            const int q = 4 * (piece - 8);
+            part_w[2][q / 2] = round_pair(raw[g][q], raw[g][q + 1]);
+            part_w[2][q / 2 + 1] = round_pair(raw[g][q + 2], raw[g][q + 3]);
+        }
+        if (piece == 10) *reinterpret_cast<u32x4*>(lds + (dst[g] + slot) + 2 * C::PART) = part_w[2];
+        if (piece >= 10) {
+            if (g < KV) request_k(next, g, piece - 10); else request_v(next, g - KV, piece - 10);
+        }
+    };
+    const auto split_groups = [&](int first, uint32_t slot, const KeyTile& next) {
+#pragma unroll
+        for (int g = first; g < first + KV; ++g)
+#pragma unroll
+            for (int piece = 0; piece < NSP; ++piece) split_piece(g, piece, slot, next);
+    };
+    const auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };     // orders LDS traffic only
+
+    KeyTile now = {nullptr, nullptr, 0, -1, 0}, next1 = now, next2 = now;
+    const int n = t_hi - t_lo;
+    if (n > 0) {
+        now = tile_at(t_lo);
+        next1 = tile_at(t_lo + 1);
+        next2 = tile_at(t_lo + 2);
+#pragma unroll
+        for (int u = 0; u < KV; ++u)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) request_k(now, u, x);
+#pragma unroll
+        for (int u = 0; u < KV; ++u)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) request_v(now, u, x);
+    }
+
+    // ---- the query row of this lane, split: B operand of S^T = K Q^T ---------------------------------------------------
+    const int row = min(mt * WRT + wave * 32 + l32, a.R - 1);
+    const bool row_ok = mt * WRT + wave * 32 + l32 < a.R;
+    const int sel = fast_div(row, a.dG);
+    const int nb = position_of(a.qpos, sel, NB);
+    const int my_rollout = fast_div(nb, a.dB), my_b = nb - my_rollout * a.B;
+    const size_t row_off = ((size_t)nb * a.Hq + (size_t)kh * a.G + (row - sel * a.G)) * D;      // of q and out
+    bf16x8 qf[3][KS];
+    {
+        const float* qp = a.q + pb * a.q_bs + row_off + 8 * half;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const f32x4 x0 = *reinterpret_cast<const f32x4*>(qp + 16 * ks), x1 = *reinterpret_cast<const f32x4*>(qp + 16 * ks + 4);
+            u32x4 w[3];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const f32x4 x = k == 0 ? x0 : x1;
+                float y[4] = {x[0], x[1], x[2], x[3]};
+                SplitQuad sq;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    sq.first(y);
+                    sq.second(y);
+                    w[i][2 * k] = sq.u;
+                    w[i][2 * k + 1] = sq.w;
+                }
+                w[2][2 * k] = round_pair(y[0], y[1]);
+                w[2][2 * k + 1] = round_pair(y[2], y[3]);
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) qf[i][ks] = __builtin_bit_cast(bf16x8, w[i]);
+        }
+    }
+
+    // channels 32 db + 8 (v / 4) + 4 half + v % 4 of the lane's row: sums of the products of first parts, and of all others
+    // (a sum of its own for the small ones: two roundings of the large sum per tile instead of twelve)
+    f32x16 o[DB], o_low[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[db][v] = o_low[db][v] = 0.f;
+    float m_ref = 0.f;             // reference the exponentials are taken against (raw score units)
+    float limit = -INFINITY;       // a score further above the reference raises it; -inf: there is none yet
+    float l_run = 0.f;             // this lane's share of the running sum
+
+    uint32_t k_frag0[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) k_frag0[ks] = (uint32_t)(l32 * D * 2 + ((((l32 / C::RPL) & (C::CH - 1)) ^ half ^ (ks << 1)) << 4));
+    const uint32_t v_frag0 = (uint32_t)(C::V_RING + half * (D * 16) + l32 * 16);
+    // products of two numbers, smallest first: part of K or V, part of Q or P
+    constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+
+    if (n > 0) {
+        f32x16 s;                  // scores of a tile, then its probabilities
+        u32x4 pw[3][2];            // the probabilities' parts, B operands of P V: [part][16-key step]
+        bf16x8 f[2][3];            // fragments of K or V, those of the next six products requested during the present ones
+        const auto k_frag = [&](int ks, int p, uint32_t slot) {
+            return *reinterpret_cast<const bf16x8*>(lds + (k_frag0[ks] + slot) + p * C::PART);
+        };
+        const auto v_frag = [&](int g, int p, uint32_t slot) {       // six products g: 16-key step g / DB, channel block g % DB
+            return *reinterpret_cast<const bf16x8*>(lds + (v_frag0 + slot) + p * C::PART + (g / DB) * (D * 32) + (g % DB) * 512);
+        };
+        // Scores of the tile in a K slot, 6 KS slots; `work(j)` is the vector work beside product j.
+        const auto scores = [&](f32x16& sum, uint32_t k_slot, uint32_t v_slot, auto work) {
+            constexpr int NQ = 6 * KS;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) f[0][p] = k_frag(0, p, k_slot);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[v] = 0.f;
+            FDD_FENCE();
+            const auto slot = [&](auto jc) {
+                constexpr int j = decltype(jc)::value, ks = j / 6, x = j % 6;
+                if constexpr (x < 3) {
+                    if constexpr (ks + 1 < KS) f[(ks + 1) & 1][x] = k_frag(ks + 1, x, k_slot);
+                    else f[0][x] = v_frag(0, x, v_slot);
+                }
+                sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[ks & 1][PA[x]], qf[PB[x]][ks], sum, 0, 0, 0);
+                work(jc);
+                FDD_FENCE();
+            };
+            for_each_int(slot, std::make_integer_sequence<int, NQ>());
+        };
+        // Softmax of tile t's scores, first half, in 25 pieces: the largest score; the reference raised if need be; the
+        // exponentials (of differences to the reference, see above) and their sum.  `alpha` weighs what was summed before.
+        float mx = -INFINITY, alpha = 1.f;
+        bool raised = false;
+        const auto mask = [&](const KeyTile& t) {
+            mx = -INFINITY;
+            raised = false;
+            if (t.valid < WKT || t.rollout >= 0) {
+                const bool sees = (t.rollout < 0) | (t.rollout == my_rollout);
+                const int seen = sees ? min(t.valid, my_b - t.key0 + 1) - 4 * half : -64;
+                // register v is key 8 (v / 4) + 4 half + v % 4
+#pragma unroll
+                for (int v = 0; v < 16; ++v) s[v] = 8 * (v >> 2) + (v & 3) >= seen ? -INFINITY : s[v];
+            }
+        };
+        constexpr int NS = 25;
+        const auto softmax_piece = [&](auto pc) {
+            constexpr int piece = decltype(pc)::value;
+            if constexpr (piece < 8) {
+                // (the larger of two numbers, in one instruction)
+                mx = __builtin_amdgcn_fmed3f(mx, s[2 * piece], 3.4028235e38f);
+                mx = __builtin_amdgcn_fmed3f(mx, s[2 * piece + 1], 3.4028235e38f);
+                FDD_PIN(mx);
+            } else if constexpr (piece == 8) {
+                raised = __any(mx - m_ref > limit);
+                if (raised) {
+                    const bool none = limit == -INFINITY;
+                    float m = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                    if (!none) m = fmaxf(m, m_ref);
+                    alpha = none ? 1.f : exp2f((m_ref - m) * a.c);
+                    m_ref = m == -INFINITY ? 0.f : m;
+                    limit = m == -INFINITY ? m : a.slack;
+                    l_run *= alpha;
+                }
+            } else {
+                float x = __builtin_amdgcn_exp2f((s[piece - 9] - m_ref) * a.c);
+                FDD_PIN(x);
+                s[piece - 9] = x;
+                if constexpr (piece % 2 == 0) l_run += s[piece - 10] + x;
+            }
+        };
+        // second half, in 20 pieces: the probabilities' parts, four at a time
+        SplitQuad prob;
+        const auto part_piece = [&](int piece) {
+            const int part = piece / 8, r = 4 * (part < 2 ? (piece / 2) % 4 : piece - 16);
+            float x[4] = {s[r], s[r + 1], s[r + 2], s[r + 3]};
+            if (part == 2) {
+                pw[2][r / 8][(r / 2) % 4] = round_pair(x[0], x[1]);
+                pw[2][r / 8][(r / 2) % 4 + 1] = round_pair(x[2], x[3]);
+            } else if (piece % 2 == 0) {
+                prob.first(x);
+                pw[part][r / 8][(r / 2) % 4] = prob.u;
+                pw[part][r / 8][(r / 2) % 4 + 1] = prob.w;
+            } else {
+                prob.second(x);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s[r + i] = x[i];
+            }
+        };
+
+        // ---- tile 0 into LDS, its scores, first half of its softmax; K of tile 1 into LDS ------------------------------------
+        split_groups(0, 0, next1);
+        split_groups(KV, 0, next1);
+        barrier();
+        scores(s, 0, 0, [](auto) {});
+        if (n > 1) split_groups(0, C::SLOT, next2);
+        mask(now);
+        for_each_int(softmax_piece, std::make_integer_sequence<int, NS>());
+        barrier();
+
+        // ---- one step ------------------------------------------------------------------------------------------------------
+        //   scores of tile i+1   ||  parts of tile i's probabilities, V of tile i+1 split into LDS
+        //   P V of tile i        ||  first half of the softmax of tile i+1, K of tile i+2 split into LDS
+        // (the last step has no tile i+1)
+        const auto step = [&](auto more, int i) {
+            constexpr bool MORE = decltype(more)::value;
+            const uint32_t even = (i & 1) ? (uint32_t)C::SLOT : 0u, odd = (uint32_t)C::SLOT - even;    // slots of tile i, of tile i+1
+            f32x16 s_next;
+            KeyTile next3 = next2;
+            if constexpr (MORE) next3 = tile_at(t_lo + i + 3);
+            const auto beside_scores = [&](auto jc) {
+                // (splitting in the odd slots, softmax in the even ones: what a slot carries must not outlast its matrix instruction)
+                constexpr int j = decltype(jc)::value, h = j / 2, NQ = 3 * KS, NV = NSP * KV, NX = 20;
+                if constexpr (j % 2 == 1) {
+                    if constexpr (MORE) {
+#pragma unroll
+                        for (int w = h * NV / NQ; w < (h + 1) * NV / NQ; ++w) split_piece(KV + w / NSP, w % NSP, odd, next2);
+                    }
+                } else {
+#pragma unroll
+                    for (int w = h * NX / NQ; w < (h + 1) * NX / NQ; ++w) part_piece(w);
+                }
+            };
+            if constexpr (MORE) {
+                scores(s_next, odd, even, beside_scores);
+                s = s_next;
+                mask(next1);
+            } else {
+#pragma unroll
+                for (int p = 0; p < 3; ++p) f[0][p] = v_frag(0, p, even);
+                for_each_int(beside_scores, std::make_integer_sequence<int, 6 * KS>());
+            }
+            FDD_FENCE();
+            constexpr int NP = 12 * DB;
+            const auto slot = [&](auto jc) {
+                constexpr int j = decltype(jc)::value, g = j / 6, x = j % 6;
+                if constexpr (x < 3 && g + 1 < 2 * DB) f[(g + 1) & 1][x] = v_frag(g + 1, x, even);
+                f32x16& sum = x == 5 ? o[g % DB] : o_low[g % DB];
+                sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[g & 1][PA[x]], __builtin_bit_cast(bf16x8, pw[PB[x]][g / DB]), sum, 0, 0, 0);
+                if constexpr (MORE) {
+                    constexpr int h = j / 2, NH = NP / 2, NK = NSP * KV;
+                    if constexpr (j % 2 == 1) {
+#pragma unroll
+                        for (int w = h * NK / NH; w < (h + 1) * NK / NH; ++w) split_piece(w / NSP, w % NSP, even, next3);
+                    } else {
+                        const auto piece = [&](auto wc) { softmax_piece(std::integral_constant<int, h * NS / NH + decltype(wc)::value>()); };
+                        for_each_int(piece, std::make_integer_sequence<int, (h + 1) * NS / NH - h * NS / NH>());
+                    }
+                }
+                FDD_FENCE();
+            };
+            for_each_int(slot, std::make_integer_sequence<int, NP>());
+            if constexpr (MORE) {
+                barrier();
+                next1 = next2;
+                next2 = next3;
+            }
+        };
+        // (a loop of its own around the steps that raise no reference: the sums stay where the matrix instructions keep them)
+        for (int i = 0; i + 1 < n;) {
+            do {
+                step(std::true_type(), i);
+                ++i;
+            } while (i + 1 < n && !raised);
+            if (raised) {
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        o[db][v] *= alpha;
+                        o_low[db][v] *= alpha;
+                    }
+            }
+        }
+        step(std::false_type(), n - 1);
+    }
+
+    // ---- epilogue --------------------------------------------------------------------------------------------------------
+    const size_t pseg = (((size_t)khv * a.MT + mt) * a.S + split) * WRT;      // first row of this workgroup's partial results
+    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    float x0 = l_tot * 0.f;      // NaN if any sum is not finite
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            o[db][v] += o_low[db][v];
+            x0 = fmaf(o[db][v], 0.f, x0);
+        }
+    // Partial results lie in the order of the accumulator registers, [wavefront][db][v / 4][lane] x 4 floats, so that a store
+    // writes 1 KB in one piece, and are written through to memory (aux 16 = device scope): the merge kernel's workgroups sit
+    // on other XCDs, and lines left dirty in the L2s go out only when the launch has ended.
+    const __amdgpu_buffer_rsrc_t part_rsrc = __builtin_amdgcn_make_buffer_rsrc(a.ws_o + pseg * D, 0, WRT * D * 4, 0x00020000);
+    const uint32_t part0 = (uint32_t)(wave * 32 * D * 4);
+    if (__builtin_expect(!__any(x0 != 0.f), 1)) {
+        if (!row_ok) return;
+        if (a.S == 1) {
+            const float inv = 1.f / l_tot;
+            float* const op = a.out + pb * a.o_bs + row_off;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int v4 = 0; v4 < 4; ++v4)
+                    *reinterpret_cast<f32x4*>(op + db * 32 + v4 * 8 + half * 4) =
+                        f32x4{o[db][4 * v4], o[db][4 * v4 + 1], o[db][4 * v4 + 2], o[db][4 * v4 + 3]} * inv;
+            return;
+        }
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int v4 = 0; v4 < 4; ++v4) {
+                const f32x4 x = f32x4{o[db][4 * v4], o[db][4 * v4 + 1], o[db][4 * v4 + 2], o[db][4 * v4 + 3]};
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), part_rsrc, part0 + (db * 4 + v4) * 1024 + lane * 16, 0, 16);
+            }
+        if (half == 0) {
+            float* const ml = a.ws_ml + (pseg + wave * 32 + l32) * 2;
+            ml[0] = limit == -INFINITY ? -INFINITY : m_ref;
+            ml[1] = l_tot;
+        }
+        return;
+    }
+    // ---- the wavefront's keys again, with fp32 products --------------------------------------------------------------------
+    {
+        constexpr int NT = D / 64;
+        const int c16 = lane & 15, g4 = lane >> 4;
+        f32x4 q16[2][D / 16];
+        int rollout16[2], b16[2];
+        size_t off16[2];
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            const int r = min(mt * WRT + wave * 32 + qb * 16 + c16, a.R - 1);
+            const int e = fast_div(r, a.dG), pos = position_of(a.qpos, e, NB);
+            rollout16[qb] = fast_div(pos, a.dB);
+            b16[qb] = pos - rollout16[qb] * a.B;
+            off16[qb] = ((size_t)pos * a.Hq + (size_t)kh * a.G + (r - e * a.G)) * D;
+            const float* qp = a.q + pb * a.q_bs + off16[qb] + 4 * g4;
+#pragma unroll
+            for (int j = 0; j < D / 16; ++j) q16[qb][j] = *reinterpret_cast<const f32x4*>(qp + 16 * j);
+        }
+        const auto half_tile = [&](int t) {       // 16 keys of a tile; none of them may exist
+            KeyTile r = tile_at(t >> 1);
+            if (t & 1) {
+                const bool any = r.valid > 16;
+                if (any) {
+                    r.k += 16 * (size_t)stride4;
+                    r.v += 16 * (size_t)stride4;
+                }
+                r.valid = any ? r.valid - 16 : 0;
+                r.key0 += 16;
+            }
+            r.valid = min(r.valid, 16);
+            return r;
+        };
+        WaveState<D> w;
+        f32_wave_loop<D>(a, half_tile, 2 * t_lo, 2 * t_hi, q16, rollout16, b16, n_lo != n_hi, w);
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            float l = w.l_run[qb];
+            l += __shfl_xor(l, 16, 64);
+            l += __shfl_xor(l, 32, 64);
+            const int r = wave * 32 + qb * 16 + c16;
+            if (mt * WRT + r >= a.R) continue;
+            const float inv = a.S == 1 ? 1.f / l : 1.f;
+            float* const op = a.out + pb * a.o_bs + off16[qb];
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const f32x4 x = f32x4{w.o[qb][t][0][v], w.o[qb][t][1][v], w.o[qb][t][2][v], w.o[qb][t][3][v]} * inv;
+                    const int ch = 64 * t + 16 * g4 + 4 * v;
+                    if (a.S == 1) *reinterpret_cast<f32x4*>(op + ch) = x;
+                    else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), part_rsrc,
+                                                                part0 + (ch / 8) * 1024 + ((ch / 4) % 2 * 32 + qb * 16 + c16) * 16, 0, 16);
+                }
+            if (a.S > 1 && g4 == 0) {
+                a.ws_ml[(pseg + r) * 2 + 0] = w.limit[qb] == -INFINITY ? -INFINITY : w.m_ref[qb];
+                a.ws_ml[(pseg + r) * 2 + 1] = l;
             }
         }
     }
@@ -568,25 +1142,113 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a)
         make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
 }
 
+// The same merge for the partials of attn_f32_wide_kernel, which lie in accumulator order.  A thread takes one 16-byte chunk
+// (4 channels of a row) of every SG-th segment, and the SG threads of a chunk, lanes of one wavefront, meet in lane moves.
+// grid (Hkv*MT, chunks of a row tile * SG / 256)
+struct WideMergeArgs {
+    const float* ws_o;
+    const float* ws_ml;
+    float* out;
+    const int32_t* qpos;
+    long long o_bs;
+    int Hq, G, R, NB, S;
+    FastDiv dMT, dHkv, dG;
+    int MT, Hkv;
+    float c;
+};
+
+template <int D, int SG>
+__global__ __launch_bounds__(256) void attn_wide_merge_kernel(WideMergeArgs a)
+{
+    constexpr int CPL = 64 / SG, UX = 4;             // chunks per wavefront, segments requested together
+    const int tid = (int)thread_id_x(), lane = tid & 63, sg = lane / CPL;
+    const int M = (int)wg_id_x();
+    const int khv = fast_div(M, a.dMT), mt = M - khv * a.MT;      // (problem of the batch, KV head), M-tile
+    const int pb = fast_div(khv, a.dHkv), kh = khv - pb * a.Hkv;
+    // chunk: [wavefront of 32 rows][channel / 8][channel / 4 % 2][row]
+    const int chunk = ((int)wg_id_y() * 4 + (tid >> 6)) * CPL + lane % CPL;
+    const int r = chunk / (8 * D) * 32 + (chunk & 31), ch = (chunk / 32) % (D / 4) * 4;
+    const int row = mt * WRT + r;
+    const bool live = row < a.R;
+    const f32x4* src = reinterpret_cast<const f32x4*>(a.ws_o) + (size_t)M * a.S * (WRT * D / 4) + chunk;
+    const float* ml = a.ws_ml + ((size_t)M * a.S * WRT + r) * 2;
+    float m = -INFINITY, l = 0.f;
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (live)
+        for (int s0 = sg; s0 < a.S; s0 += SG * UX) {
+            float2 y[UX];
+            f32x4 x[UX];
+#pragma unroll
+            for (int u = 0; u < UX; ++u) {
+                const int s = s0 + u * SG;
+                y[u] = make_float2(-INFINITY, 0.f);
+                x[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (s < a.S) {
+                    y[u] = *reinterpret_cast<const float2*>(ml + (size_t)s * (2 * WRT));
+                    x[u] = src[(size_t)s * (WRT * D / 4)];
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);    // everything is requested before anything is waited for
+            float mx = m;
+#pragma unroll
+            for (int u = 0; u < UX; ++u) mx = fmaxf(mx, y[u].x);
+            if (mx == -INFINITY) continue;        // (no key so far, sums are zero)
+            const float old = exp2f((m - mx) * a.c);
+            m = mx;
+            l *= old;
+            acc *= old;
+#pragma unroll
+            for (int u = 0; u < UX; ++u) {
+                const float w = exp2f((y[u].x - mx) * a.c);
+                l = fmaf(y[u].y, w, l);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] = fmaf(x[u][e], w, acc[e]);
+            }
+        }
+    if (SG > 1) {
+        float mx = m;
+#pragma unroll
+        for (int d = CPL; d < 64; d *= 2) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
+        const float w = m == -INFINITY ? 0.f : exp2f((m - mx) * a.c);
+        l *= w;
+        acc *= w;
+#pragma unroll
+        for (int d = CPL; d < 64; d *= 2) {
+            l += __shfl_xor(l, d, 64);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], d, 64);
+        }
+    }
+    if (!live || sg != 0) return;
+    const int sel = fast_div(row, a.dG), g = row - sel * a.G;
+    const int nb = position_of(a.qpos, sel, a.NB);
+    *reinterpret_cast<f32x4*>(a.out + pb * a.o_bs + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * D + ch) = acc * (1.f / l);
+}
+
 }  // namespace
 
-template <int D>
-static hipError_t launch(const Args& a, hipStream_t s)
+template <typename Kernel>
+static hipError_t launch(Kernel kern, int threads, int lds_bytes, std::atomic<uint64_t>& done, const Args& a, hipStream_t s)
 {
-    const auto kern = &attn_f32_kernel<D>;
     // the LDS limit of this instantiation is raised once per device (bit d of `done`: device d)
-    static std::atomic<uint64_t> done{0};
     int dev = 0;
     if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
     const uint64_t bit = 1ull << (dev & 63);
     if (!(done.load(std::memory_order_acquire) & bit)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           F32Cfg<D>::LDS_BYTES);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
         if (e != hipSuccess) return e;
         done.fetch_or(bit, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, f32_grid(a.W), dim3(THREADS), F32Cfg<D>::LDS_BYTES, s, a);
+    hipLaunchKernelGGL(kern, f32_grid(a.W), dim3(threads), lds_bytes, s, a);
     return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch(const Args& a, bool wide, hipStream_t s)
+{
+    static std::atomic<uint64_t> done{0}, done_wide{0};
+    if (wide) return launch(&attn_f32_wide_kernel<D>, 256, WideCfg<D>::LDS_BYTES, done_wide, a, s);
+    return launch(&attn_f32_kernel<D>, THREADS, F32Cfg<D>::LDS_BYTES, done, a, s);
 }
 
 hipError_t launch_attn_f32(const fdd_attn_params& p, const AttnPlan& plan, float scale, hipStream_t s)
@@ -616,21 +1278,43 @@ hipError_t launch_attn_f32(const fdd_attn_params& p, const AttnPlan& plan, float
     a.slack = 8.f / a.c;
     a.causal = (p.flags & FDD_ATTN_CAUSAL_BLOCK) ? 1 : 0;
     a.qpos = p.n_q_positions > 0 ? p.q_positions : nullptr;
-    a.ext_per = (p.E + KT - 1) / KT;
-    a.per = a.ext_per + (p.B + KT - 1) / KT;
+    const bool wide = plan.mtile_rows == WRT;
+    if (!wide && plan.mtile_rows != RT) return hipErrorInvalidValue;
+    if (plan.key_tile != (wide ? WKT : KT)) return hipErrorInvalidValue;
+    a.ext_per = (p.E + plan.key_tile - 1) / plan.key_tile;
+    a.per = a.ext_per + (p.B + plan.key_tile - 1) / plan.key_tile;
     a.dMT = make_fastdiv((uint32_t)a.MT);
     a.dS = make_fastdiv((uint32_t)a.S);
     a.dHkv = make_fastdiv((uint32_t)a.Hkv);
     a.dG = make_fastdiv((uint32_t)a.G);
     a.dB = make_fastdiv((uint32_t)a.B);
     a.dPer = make_fastdiv((uint32_t)a.per);
-    a.dParts = make_fastdiv((uint32_t)(a.S * WAVES));
-    if (plan.mtile_rows != RT || plan.key_tile != KT) return hipErrorInvalidValue;
-    return p.D == 128 ? launch<128>(a, s) : launch<64>(a, s);
+    a.dParts = make_fastdiv((uint32_t)(a.S * (wide ? 1 : WAVES)));     // wavefronts or workgroups that share the keys
+    return p.D == 128 ? launch<128>(a, wide, s) : launch<64>(a, wide, s);
 }
 
 hipError_t launch_attn_combine(const fdd_attn_params& p, const AttnPlan& plan, float scale, hipStream_t s)
 {
+    if (plan.mtile_rows == WRT) {
+        WideMergeArgs a;
+        a.ws_o = static_cast<const float*>(p.workspace);
+        a.ws_ml = reinterpret_cast<const float*>(static_cast<const char*>(p.workspace) + plan.ws_o_bytes);
+        a.out = static_cast<float*>(p.out);
+        a.qpos = p.n_q_positions > 0 ? p.q_positions : nullptr;
+        a.o_bs = p.out_batch_stride;
+        a.Hq = p.Hq; a.G = plan.G; a.R = plan.R; a.NB = p.N * p.B; a.S = plan.splits; a.MT = plan.MT; a.Hkv = p.Hkv;
+        a.dMT = make_fastdiv((uint32_t)a.MT);
+        a.dHkv = make_fastdiv((uint32_t)a.Hkv);
+        a.dG = make_fastdiv((uint32_t)a.G);
+        a.c = scale * 1.4426950408889634f;
+        const unsigned tiles = (unsigned)(p.Hkv * (p.batch > 1 ? p.batch : 1) * plan.MT);
+        // (several threads per chunk where each would take more than two rounds of loads)
+        const int sg = a.S > 16 ? 4 : a.S > 8 ? 2 : 1;
+        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(tiles, (unsigned)(WRT * p.D / 4 * sg / 256)), dim3(256), 0, s, a); };
+        if (p.D == 128) sg == 4 ? go(&attn_wide_merge_kernel<128, 4>) : sg == 2 ? go(&attn_wide_merge_kernel<128, 2>) : go(&attn_wide_merge_kernel<128, 1>);
+        else sg == 4 ? go(&attn_wide_merge_kernel<64, 4>) : sg == 2 ? go(&attn_wide_merge_kernel<64, 2>) : go(&attn_wide_merge_kernel<64, 1>);
+        return hipGetLastError();
+    }
     CombineArgs a;
     a.ws_o = static_cast<const float*>(p.workspace);
     a.ws_ml = reinterpret_cast<const float*>(static_cast<const char*>(p.workspace) + plan.ws_o_bytes);

@@ -43,6 +43,7 @@ constexpr int kNumXCD = 8;
 //               [unit_begin(w), unit_begin(w+1)), which may cross M-tiles.
 constexpr int kF32RowTile = 32;    // fp32 path: stacked rows per workgroup
 constexpr int kF32Waves = 8;       // fp32 path: wavefronts per workgroup
+constexpr int kF32WideRowTile = 128, kF32WideKeyTile = 32;   // fp32 path, products on the bf16 pipe: rows per workgroup, keys per tile
 
 struct AttnPlan {
     int G;            // query heads per KV head

@@ -1,0 +1,148 @@
+"""GPU parity of fp32 attention on the bf16 matrix pipe (128-row tiles, every fp32 product as six bf16 products) at the edges
+of its tiles, and what values that are not finite do there.
+
+Tolerance: products are kept to 2^-25 and sums are rounded to fp32, so results agree with the oracle as fp32 arithmetic does:
+a score of D products of size 1 is off by a few 2^-24 sqrt(D), scaled by 1/sqrt(D), a probability by as much, and the average
+of values up to 5 by 5 * 2^-24 times a few: 1e-5 is 30 times 2^-24 * 5."""
+import numpy as np
+import pytest
+import torch
+
+import fdd_workloads as W
+from tests.gpu_util import print_case, rand_attn, to_dev, to_f64
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5
+
+# (N, B, L, Hq, Hkv, E, D): row tiles of several rollouts, a part of one row tile over a full one, the last tile of 32 keys
+# nearly empty and nearly full, extensions and blocks of less and more than a tile, fewer tiles than pieces would like
+SHAPES = [(12, 20, 1025, 14, 2, 0, 128), (5, 39, 2527, 28, 4, 37, 64), (3, 33, 5000, 16, 4, 1, 128), (9, 65, 2200, 8, 2, 96, 64),
+          (40, 7, 2311, 28, 4, 0, 64), (3, 70, 3009, 8, 8, 31, 128)]
+
+
+@pytest.fixture(scope="module")
+def F():
+    import paper_2605_23163_amd as F
+    F.load_library()
+    return F
+
+
+def make(shape, seed=0):
+    N, B, L, Hq, Hkv, E, D = shape
+    rng = np.random.default_rng(seed + L)
+    d = rand_attn(rng, N, B, L, Hq, Hkv, D, W.F32)
+    if E:
+        d["ext_k"], d["ext_v"] = (rng.standard_normal((N, E + 2, Hkv, D)).astype(np.float32) for _ in range(2))
+    return d
+
+
+def run(F, d, E, check_wide=True, **kw):
+    t = {k: to_dev(v) for k, v in d.items()}
+    args = (t["q"], t["prefix_k"], t["prefix_v"], t["block_k"], t["block_v"])
+    ext = dict(ext_k=t["ext_k"], ext_v=t["ext_v"], E=E) if E else {}
+    if check_wide:      # the partial results of 128-row tiles, and not of 32-row tiles
+        N, B, Hq, D = d["q"].shape
+        Hkv = d["block_k"].shape[2]
+        rows, per = N * B * (Hq // Hkv), 4 * D + 8
+        need = F.fdd_block_attn_workspace(*args, **ext)
+        assert need > 0 and need % (Hkv * ((rows + 127) // 128) * 128 * per) == 0, need
+        assert need % (Hkv * ((rows + 31) // 32) * 32 * per) != 0, need
+    out = F.fdd_block_attn(*args, **ext, **kw)
+    torch.cuda.synchronize()
+    return out
+
+
+def reference(oracle, d, E, **kw):
+    ext = dict(ext_k=d["ext_k"], ext_v=d["ext_v"], E=E) if E else {}
+    return oracle.block_attn(d["q"], d["prefix_k"], d["prefix_v"], d["block_k"], d["block_v"], **ext, **kw)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("causal", [False, True])
+def test_tile_edges(F, oracle, shape, causal):
+    print_case(test="f32_wide_edges", shape=shape, causal=causal)
+    d, E = make(shape), shape[5]
+    got = to_f64(run(F, d, E, causal_block=causal))
+    assert np.abs(got - reference(oracle, d, E, causal_block=causal)).max() <= TOL
+
+
+def test_scores_that_grow_along_the_keys(F, oracle):
+    # exponents of up to +-40 that rise with the key: the reference is raised again and again, in every piece
+    shape = SHAPES[1]
+    print_case(test="f32_wide_growing", shape=shape)
+    d, E, D = make(shape), shape[5], shape[6]
+    d["q"][..., 0] = 1.0
+    d["prefix_k"][..., 0] = np.linspace(0, 40 * np.sqrt(D), shape[2], dtype=np.float32)[:, None]
+    got, ref = to_f64(run(F, d, E)), reference(oracle, d, E)
+    # (scores up to 40 sqrt(D), rounded to 2^-24 of that, are exponents off by 40 * 2^-24)
+    assert np.abs(got - ref).max() <= 8 * TOL
+
+
+def test_listed_positions_and_a_batch(F, oracle):
+    shape = (5, 39, 2527, 28, 4, 0, 64)
+    print_case(test="f32_wide_list_batch", shape=shape)
+    d = make(shape)
+    N, B, L, Hq, Hkv, E, D = shape
+    pos = np.sort(np.random.default_rng(1).permutation(N * B)[:149])
+    full = to_f64(run(F, d, 0)).reshape(N * B, Hq, D)
+    out = torch.full((N, B, Hq, D), 7.0, device="cuda")
+    t = {k: to_dev(v) for k, v in d.items()}
+    args = [t[k] for k in ("q", "prefix_k", "prefix_v", "block_k", "block_v")]
+    F.fdd_block_attn(*args, out=out, q_positions=torch.from_numpy(pos.astype(np.int32)).cuda())
+    torch.cuda.synchronize()
+    got = to_f64(out).reshape(N * B, Hq, D)
+    rest = np.ones(N * B, dtype=bool)
+    rest[pos] = False
+    assert np.all(got[rest] == 7.0) and np.abs(got[pos] - full[pos]).max() <= TOL
+    e = make(shape, seed=1)
+    both = [torch.stack([to_dev(d[k]), to_dev(e[k])]) for k in ("q", "prefix_k", "prefix_v", "block_k", "block_v")]
+    out = F.fdd_block_attn_batched(*both)
+    torch.cuda.synchronize()
+    for i, x in enumerate((d, e)):
+        assert np.abs(to_f64(out[i]) - reference(oracle, x, 0)).max() <= TOL
+
+
+@pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[0]])
+@pytest.mark.parametrize("bad", [np.inf, np.nan, -np.inf])
+def test_values_that_are_not_finite_reach_only_who_sees_them(F, oracle, shape, bad):
+    # (rows that share a wavefront with a sick one are computed with fp32 products instead: the same up to rounding)
+    print_case(test="f32_wide_not_finite", shape=shape, bad=bad)
+    d, E = make(shape), shape[5]
+    clean = to_f64(run(F, d, E))
+    sick, others = 1, [n for n in range(shape[0]) if n != 1]
+    for name in ("block_v", "block_k") + (("ext_v", "ext_k") if E else ()):
+        x = dict(d, **{name: d[name].copy()})
+        x[name][sick, 0, :, ::3] = bad
+        got = to_f64(run(F, x, E))
+        assert np.abs(got[others] - clean[others]).max() <= TOL, name
+        assert not np.isfinite(got[sick]).all(), name
+
+
+def test_an_infinite_value_stays_infinite(F, oracle):
+    shape = SHAPES[0]
+    print_case(test="f32_wide_infinite", shape=shape)
+    d = make(shape)
+    d["prefix_v"][-1, :, 5] = np.inf          # the last key, alone in its tile
+    got, ref = to_f64(run(F, d, 0)), reference(oracle, d, 0)
+    assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and not np.isnan(got).any()
+    fin = np.isfinite(ref)
+    assert np.abs(got[fin] - ref[fin]).max() <= TOL
+
+
+def test_values_at_both_ends_of_the_range(F, oracle):
+    # the parts of 1e-34 and less are below the smallest normal number; 3.4e38 has no nearest bf16 number
+    shape = SHAPES[0]
+    print_case(test="f32_wide_range", shape=shape)
+    for scale in (1e34, 1e-34):
+        d = make(shape)
+        for k in ("prefix_v", "block_v"):
+            d[k] = (d[k] * np.float32(scale)).astype(np.float32)
+        got, ref = to_f64(run(F, d, 0)) / scale, reference(oracle, d, 0) / scale
+        print(f"scale {scale:.0e}: max-abs error {np.abs(got - ref).max():.2e}")
+        assert np.isfinite(got).all() and np.abs(got - ref).max() <= TOL
+    d = make(shape)
+    d["prefix_k"][700], d["prefix_v"][700, :, 3] = 0.0, np.float32(3.4e38)
+    got, ref = to_f64(run(F, d, 0)), reference(oracle, d, 0)
+    size = np.maximum(np.abs(ref), 1.0)
+    assert np.isfinite(got).all() and (np.abs(got - ref) / size).max() <= TOL
