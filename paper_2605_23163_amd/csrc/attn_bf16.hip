@@ -135,6 +135,7 @@ struct Args {
     int max_seg;    // partial slots per M-tile
     int causal;     // in-block keys are visible up to the query's own position only
     float c;        // scale * log2(e)
+    float slack;    // 8 / c: scores may pass their reference by this much
     int ttpr;       // private tiles per rollout: extension tiles, then block tiles
     FastDiv dB, dBG, dTTPR, dBase, dBase1;
 };
@@ -568,23 +569,27 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
         for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
-        float m_ref = -INFINITY;   // reference value the exponentials are taken against (raw score units)
+        float m_ref = 0.f;         // reference value the exponentials are taken against (raw score units)
+        float limit = -INFINITY;   // a score above it raises the reference: 2^8 above it, or -inf: there is none yet
         float l_run = 0.f;         // this lane's share of the running sum
 
-        // raise the reference when the tile maximum outgrew it by more than 2^8
+        // Raise the reference when a row outgrew it by more than 2^8 (always on the first tile).  `mx` is the largest score of
+        // this lane's half of the keys: whether any lane passes its limit needs no exchange, only the rare raise does.  (A
+        // compare and a branch between the row maximum and the exponentials instead of a chain of ten instructions that wait for
+        // one another.)
         auto update_reference = [&](float mx) {
-            // also true for the first tile (m_ref = -inf); never evaluates inf - inf
-            const bool need = (mx > m_ref) && ((mx - m_ref) * a.c > 8.f);
-            if (__any(need)) {
-                const float m_new = fmaxf(m_ref, mx);
-                const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-                const float alpha = fast_exp2((m_ref - m_use) * a.c);
+            if (__any(mx > limit)) {
+                const bool none = limit == -INFINITY;       // (nothing summed so far, or only keys the row does not see)
+                float m = fmaxf(mx, other_half(mx));
+                if (!none) m = fmaxf(m, m_ref);
+                const float alpha = none ? 0.f : fast_exp2((m_ref - m) * a.c);
                 l_run *= alpha;
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
-                m_ref = m_new;
+                m_ref = (m == -INFINITY) ? 0.f : m;
+                limit = (m == -INFINITY) ? m : m + a.slack;
             }
         };
 
@@ -679,11 +684,6 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                 u32x4 pw[4];     // the B operands of P V as packed words
                 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
                 const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-                auto reference = [&]() {
-                    mx = fmaxf(mx, other_half(mx));
-                    update_reference(mx);
-                    mc = ((m_ref == -INFINITY) ? 0.f : m_ref) * a.c;
-                };
 
                 if constexpr (SPREAD) {
                     // What a wavefront does besides its matrix instructions is spread over the slots such that nothing in a slot
@@ -758,7 +758,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                             FDD_PIN(mx);
                             if constexpr (j == KS - 1) {
                                 FDD_SCHED_FENCE();
-                                reference();
+                                update_reference(mx);
+                                mc = m_ref * a.c;
                                 FDD_SCHED_FENCE();
                                 scale_pair(0);
                             }
@@ -798,7 +799,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                     FDD_PIN(mx);
                     FDD_SCHED_FENCE();
                 }
-                reference();
+                update_reference(mx);
+                mc = m_ref * a.c;
                 // four probabilities of block kb (registers 4e .. 4e+3), rounded into the B operands
                 auto exp_quad = [&](int kb, int e) {
                     float pr[4];
@@ -912,8 +914,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                         if (!row_sees || key >= t.valid || later) s[kb][v] = -INFINITY;
                         mx = fmaxf(mx, s[kb][v]);
                     }
-                update_reference(fmaxf(mx, other_half(mx)));
-                const float mc = ((m_ref == -INFINITY) ? 0.f : m_ref) * a.c;
+                update_reference(mx);
+                const float mc = m_ref * a.c;
                 float acc = 0.f;
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
@@ -932,7 +934,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
             }
             if (j + 1 < n_tiles) wait_landed(j + 1); else wg_barrier();
         }
-        const float m_run = m_ref;
+        const float m_run = limit == -INFINITY ? limit : m_ref;
 
         // ---- epilogue of the segment ------------------------------------------------
         const float l_tot = l_run + other_half(l_run);
@@ -1246,6 +1248,7 @@ hipError_t launch_attn_bf16(const fdd_attn_params& p, const AttnPlan& plan, floa
     a.base = (int)(plan.U / plan.W); a.rem = (int)(plan.U % plan.W);
     a.causal = (p.flags & FDD_ATTN_CAUSAL_BLOCK) ? 1 : 0;
     a.c = scale * 1.4426950408889634f;
+    a.slack = 8.f / a.c;
     a.ttpr = (p.E + 63) / 64 + (p.B + 63) / 64;
     a.qpos = p.n_q_positions > 0 ? p.q_positions : nullptr;
     a.NB = p.N * p.B;
