@@ -196,6 +196,24 @@ __device__ __forceinline__ void for_slots(F& f, std::integer_sequence<int, J...>
     (f(std::integral_constant<int, J>()), ...);
 }
 
+// use(j, read(j)) for j in [0, N), every fragment requested AHEAD matrix instructions before its own: left to itself the
+// compiler, short of registers elsewhere, reads each one right before its use, and a wavefront that has nothing else to do
+// (before the pipelined loop, in masked tiles) waits for LDS 16 times a tile.
+template <int N, int AHEAD, typename Read, typename Use>
+__device__ __forceinline__ void read_ahead(const Read& read, const Use& use)
+{
+    bf16x8 f[AHEAD + 1];
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) f[j] = read(j);
+    FDD_SCHED_FENCE();
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        if (j + AHEAD < N) f[(j + AHEAD) % (AHEAD + 1)] = read(j + AHEAD);
+        use(j, f[j % (AHEAD + 1)]);
+        FDD_SCHED_FENCE();
+    }
+}
+
 template <int D, int WAVES, bool PACKED>
 __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kernel(Args a)
 {
@@ -205,11 +223,21 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
     constexpr int KS = D / 16;   // MFMA k-steps of Q K^T
     constexpr int DB = D / 32;   // 32-channel blocks of the output
     constexpr int MROWS = WAVES * 32;
+    constexpr int RA = 4;        // fragments requested ahead outside the pipelined loop
     constexpr bool SPREAD = WAVES == 8 && D == 128 && PACKED;   // order of a pipelined step, see there
     constexpr uint32_t RSRC_FLAGS = 0x00020000;
 
     extern __shared__ __align__(16) unsigned char lds[];
     typedef __attribute__((address_space(3))) void lds_void;
+    // Arguments that only masked tiles and the end of a segment need are read again where they are used, through a pointer the
+    // compiler cannot follow back: kept from the first read on, they and what is computed from them do not fit the scalar
+    // registers, and each register that is put aside costs two instructions before the first tile.
+    typedef const __attribute__((address_space(4))) Args LateArgs;
+    auto late_args = [&]() {
+        LateArgs* z = (LateArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(z));
+        return z;
+    };
 
     const int tid = thread_id_x();
     const int wave = tid >> 6;
@@ -379,17 +407,17 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
         const int row = row0 + l32;
         const bool row_ok = row < a.R;
         // a stacked row is (entry of the list of query positions, query head of the group)
-        const int sel = row_ok ? fast_div(row, a.dG) : 0;
-        const int g = row_ok ? row - sel * a.G : 0;
+        // (lanes beyond the last row compute it once more and store nothing: the loads need no branch)
+        const int row_c = min(row, a.R - 1);
+        const int sel = fast_div(row_c, a.dG);
+        const int g = row_c - sel * a.G;
         const int nb = a.qpos ? min(max(a.qpos[sel], 0), a.NB - 1) : sel;   // n*B + b
         bf16x8 qf[KS];
         {
             const uint16_t* qp = a.q + pb * a.q_bs + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * D + half * 8;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                u32x4 raw = {0u, 0u, 0u, 0u};
-                if (row_ok) raw = *reinterpret_cast<const u32x4*>(qp + ks * 16);
-                qf[ks] = __builtin_bit_cast(bf16x8, raw);
+                qf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + ks * 16));
             }
         }
         FDD_SCHED_FENCE();
@@ -447,30 +475,40 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
             seg = piece;
         } else {
             // owner of a unit: the first `rem` workgroups hold base + 1 units each, the others base
+            LateArgs* const z = late_args();
+            const FastDiv by1 = {z->dBase1.mul, z->dBase1.shift}, by = {z->dBase.mul, z->dBase.shift};
             const int cut = a.rem * (a.base + 1);
-            auto owner = [&](int u) { return u < cut ? fast_div(u, a.dBase1) : a.rem + fast_div(u - cut, a.dBase); };
+            auto owner = [&](int u) { return u < cut ? fast_div(u, by1) : a.rem + fast_div(u - cut, by); };
             const int first = owner(M * a.TPU);
             n_seg = owner((M + 1) * a.TPU - 1) - first + 1;
             seg = wg - first;
         }
-        const int my_rollout = row_ok ? fast_div(nb, a.dB) : -1;
-        const int my_b = row_ok ? nb - my_rollout * a.B : 0;   // position inside the block
-        // rollouts spanned by this wave's rows and by the whole M-tile
+        // What masked tiles need (the ragged last tile of the prefix, private tiles), in the segments that have any: rollout and
+        // block position of the lane's row, the rollouts that this wavefront's rows and the whole M-tile span
         // (rows are in ascending order of position, hence of rollout; `r` is clamped to the rows that exist)
-        auto rollout_of_row = [&](int r) {
-            r = min(r, a.R - 1);
-            if (!a.qpos) return fast_div(r, a.dBG);
-            const int e = __builtin_amdgcn_readfirstlane(fast_div(r, a.dG));
-            return fast_div(min(max(a.qpos[e], 0), a.NB - 1), a.dB);
-        };
-        const int wave_n_lo = rollout_of_row(row0);
-        const int wave_n_hi = rollout_of_row(row0 + 31);
         const bool wave_has_rows = row0_wg + wave_u * 32 < a.R;
-        const int wg_n_lo = __builtin_amdgcn_readfirstlane(rollout_of_row(row0_wg));
-        const int wg_n_hi = __builtin_amdgcn_readfirstlane(rollout_of_row(row0_wg + MROWS - 1));
-        const int tte = (a.E + KT - 1) >> 6;             // tiles of a rollout's extension
-        const int ttpr = a.ttpr;                         // private tiles per rollout: extension, then block
-        const int n_tail = (t_end == a.TPU) ? (wg_n_hi - wg_n_lo + 1) * ttpr : 0;
+        int my_rollout = -1, my_b = 0, wave_n_lo = 0, wave_n_hi = 0, wg_n_lo = 0, tte = 0, ttpr = 1, n_tail = 0;
+        if (t_end == a.TPU || F < n_prefix) {
+            LateArgs* const z = late_args();
+            const FastDiv by_b = a.dB, by_bg = a.dBG;
+            if (row_ok) {
+                my_rollout = fast_div(nb, by_b);
+                my_b = nb - my_rollout * a.B;
+            }
+            auto rollout_of_row = [&](int r) {
+                r = min(r, a.R - 1);
+                if (!a.qpos) return fast_div(r, by_bg);
+                const int e = __builtin_amdgcn_readfirstlane(fast_div(r, a.dG));
+                return fast_div(min(max(a.qpos[e], 0), a.NB - 1), by_b);
+            };
+            wave_n_lo = rollout_of_row(row0);
+            wave_n_hi = rollout_of_row(row0 + 31);
+            wg_n_lo = __builtin_amdgcn_readfirstlane(rollout_of_row(row0_wg));
+            const int wg_n_hi = __builtin_amdgcn_readfirstlane(rollout_of_row(row0_wg + MROWS - 1));
+            tte = (a.E + KT - 1) >> 6;             // tiles of a rollout's extension
+            ttpr = a.ttpr;                         // private tiles per rollout: extension, then block
+            if (t_end == a.TPU) n_tail = (wg_n_hi - wg_n_lo + 1) * ttpr;
+        }
         const int n_tiles = n_prefix + n_tail;
 
         struct Tile {
@@ -564,11 +602,13 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
         while (issued < min(NB - 1, n_tiles)) fetch(issued);
 
         // ---- streaming-softmax state: one query row per lane --------------------
+        float zero = 0.f;       // (a vector of constants would be built in 16 scalar registers)
+        FDD_PIN(zero);
         f32x16 o[DB];
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
+            for (int v = 0; v < 16; ++v) o[db][v] = zero;
         float m_ref = 0.f;         // reference value the exponentials are taken against (raw score units)
         float limit = -INFINITY;   // a score above it raises the reference: 2^8 above it, or -inf: there is none yet
         float l_run = 0.f;         // this lane's share of the running sum
@@ -634,13 +674,12 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
             // prologue: scores of tile 0
             f32x16 sa[2], sb[2];
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
+            for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) sa[kb][v] = 0.f;
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-                    sa[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(0, kb, ks), qf[ks], sa[kb], 0, 0, 0);
-            }
+            read_ahead<2 * KS, RA>([&](int j) { return k_frag(0, j / KS, j % KS); }, [&](int j, const bf16x8& f) {
+                sa[j / KS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[j % KS], sa[j / KS], 0, 0, 0);
+            });
             // Step 0 requests K of tile 4 into the slot that the scores above were read from: no wavefront may get
             // there while another one is still reading.  (They can be far apart here: the first workgroups of a
             // launch fetch these instructions from memory.)
@@ -893,47 +932,51 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
             const bool wave_active = wave_has_rows &&
                 (t.rollout < 0 || (t.rollout >= wave_n_lo && t.rollout <= wave_n_hi));
             if (wave_active) {
+                // A tile of 32 keys or fewer (a block of 32, the last rows of an extension) takes half of the products and
+                // exponentials.  us per call, all of both blocks / as here: N=1, L=2048 10.98/10.75; N=8, L=2048 19.3/18.8, L=4096 with E=64
+                // 28.4/27.5; N=5, B=40, L=5003, D=64, E=37 18.0/16.5 (most of it from one bound per row in place of four conditions a key).
+                const int n_kb = t.valid > 32 ? 2 : 1;
                 f32x16 s[2];
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) s[kb][v] = 0.f;
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks)
-                        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(kbase, kb, ks), qf[ks], s[kb], 0, 0, 0);
-                }
-                // register v of block kb is key kb*32 + (v/4)*8 + half*4 + v%4
-                const bool row_sees = (t.rollout < 0) || (t.rollout == my_rollout);
+                // register v of block kb is key kb*32 + (v/4)*8 + half*4 + v%4; in the verify pass later keys of the block are hidden
+                const int upto = a.causal && t.src == 2 ? min(t.valid, my_b + 1 - t.key0) : t.valid;
+                const int seen = (t.rollout < 0 || t.rollout == my_rollout ? upto : 0) - half * 4;
                 float mx = -INFINITY;
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
+                for (int kb = 0; kb < 2; ++kb) {
+                    if (kb >= n_kb) break;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) s[kb][v] = 0.f;
+                    read_ahead<KS, RA>([&](int x) { return k_frag(kbase, kb, x); }, [&](int x, const bf16x8& f) {
+                        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[x], s[kb], 0, 0, 0);
+                    });
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
-                        const int key = kb * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
-                        const bool later = a.causal && t.src == 2 && t.key0 + key > my_b;   // verify pass: causal inside the block
-                        if (!row_sees || key >= t.valid || later) s[kb][v] = -INFINITY;
+                        if (kb * 32 + (v >> 2) * 8 + (v & 3) >= seen) s[kb][v] = -INFINITY;
                         mx = fmaxf(mx, s[kb][v]);
                     }
+                }
                 update_reference(mx);
                 const float mc = m_ref * a.c;
                 float acc = 0.f;
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
+                for (int kb = 0; kb < 2; ++kb) {
+                    if (kb >= n_kb) break;
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
                         const float pr = fast_exp2(fmaf(s[kb][v], a.c, -mc));
                         acc += pr;
                         p[kb * 2 + v / 8][v % 8] = (__bf16)pr;
                     }
+                    read_ahead<2 * DB, RA>([&](int x) { return v_frag_tr_at(vtr_off_ring + kbase, 2 * kb + x / DB, x % DB); },
+                                           [&](int x, const bf16x8& f) {
+                                               o[x % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, p[2 * kb + x / DB], o[x % DB], 0, 0, 0);
+                                           });
+                }
                 l_run += acc;
-#pragma unroll
-                for (int t4 = 0; t4 < 4; ++t4)
-#pragma unroll
-                    for (int db = 0; db < DB; ++db)
-                        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag_tr_at(vtr_off_ring + kbase, t4, db), p[t4], o[db], 0, 0, 0);
             }
             if (j + 1 < n_tiles) wait_landed(j + 1); else wg_barrier();
         }
+        LateArgs* const z = late_args();
         const float m_run = limit == -INFINITY ? limit : m_ref;
 
         // ---- epilogue of the segment ------------------------------------------------
@@ -941,7 +984,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
         if (row_ok) {
             if (n_seg == 1) {
                 const float inv = 1.f / l_tot;
-                uint16_t* op = a.out + pb * a.o_bs + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * D;
+                uint16_t* op = z->out + pb * z->o_bs + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * D;
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -962,9 +1005,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                 // other XCDs, and lines left dirty in the L2s go out only when the launch has ended (28 layers of N=1,
                 // L=16384: 723 -> 696 us; N=8, L=4096: 28.9 -> 27.7; plain, non-temporal and both measured).
                 const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-                const size_t pseg = (size_t)M * a.max_seg + __builtin_amdgcn_readfirstlane(seg);
+                const size_t pseg = (size_t)M * z->max_seg + __builtin_amdgcn_readfirstlane(seg);
                 const __amdgpu_buffer_rsrc_t o_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                    static_cast<unsigned char*>(a.ws_o) + pseg * (size_t)(MROWS * D * 2), 0, MROWS * D * 2, RSRC_FLAGS);
+                    static_cast<unsigned char*>(z->ws_o) + pseg * (size_t)(MROWS * D * 2), 0, MROWS * D * 2, RSRC_FLAGS);
                 const uint32_t o_off = (uint32_t)(wave * (2 * DB * 64) + lane) * 16;
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
@@ -977,8 +1020,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                     }
                 if (half == 0) {
                     const size_t prow = pseg * MROWS + (wave * 32 + l32);
-                    a.ws_ml[prow * 2 + 0] = m_run;
-                    a.ws_ml[prow * 2 + 1] = l_tot;
+                    float* const ml = z->ws_ml + prow * 2;
+                    ml[0] = m_run;
+                    ml[1] = l_tot;
                 }
             }
         }
