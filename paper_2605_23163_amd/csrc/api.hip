@@ -243,10 +243,10 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
         };
         // Products on the bf16 pipe (128-row tiles) where they are expected to be faster and the keys are cut at least once more:
         // a row's sum is rounded twice per 32 keys of a workgroup there, four times per 4 keys of a wavefront here, and with that
-        // many pieces the error against 64 bits was smaller in every one of 60 drawn calls (0.4 to 0.8 of it).  us per call, 32-row
-        // tiles / 128-row tiles (pieces): D = 128, Hq = 28, Hkv = 4, B = 32: N=1, L=2048 23.8 / 21.9 (32); N=1, L=16384 74.0 / 60.7 (32);
-        // N=2, L=1024 25.4 / 22.7 (16); N=4, L=4096 77.6 / 56.3 (8); N=8, L=4096 135.7 / 93.6 (4); N=16, L=4096 268 / 170 (2); D = 64: N=8,
-        // L=4096 74.7 / 55.3 (4); N=5, B=40, L=5003, Hq=14, Hkv=2, E=37 50.5 / 37.0 (8).
+        // many pieces the error against 64 bits was smaller in every one of 130 drawn calls (0.3 to 0.8 of it).  us per call, 32-row
+        // tiles / 128-row tiles (pieces): D = 128, Hq = 28, Hkv = 4, B = 32: N=1, L=2048 23.8 / 20.6 (22); N=1, L=16384 74.0 / 53.3 (31);
+        // N=2, L=1024 25.4 / 20.6 (12); N=4, L=4096 77.6 / 50.0 (9); N=8, L=4096 135.7 / 84.5 (4); N=16, L=4096 268 / 152 (2); D = 64: N=8,
+        // L=4096 74.7 / 52.5 (4); N=5, B=40, L=5003, Hq=14, Hkv=2, E=37 50.5 / 31.2 (11).
         long long tiles = cut_f32(kF32RowTile, 16);
         int s = p.splits;
         if (s == 0) {
@@ -254,9 +254,10 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
             s = narrow.splits;
             const long long wide_tiles = cut_f32(kF32WideRowTile, kF32WideKeyTile);
             const F32Cut wide = f32_cut(true, NM, wide_tiles, p.D, narrow.splits + 1);
+            // (short calls that are cut take 2 to 5 us more than the estimate for 32-row tiles says)
             // (up to a GiB of partials: beyond it the chip is full many times over, and the narrow tiles need none)
             const bool fits = NM * wide.splits * (kF32WideRowTile * p.D * 4ll) <= (1ll << 30);
-            if (fits && wide_tiles >= 2 * wide.splits && wide.us < narrow.us) {
+            if (fits && wide_tiles >= 2 * wide.splits && wide.us < narrow.us + (narrow.splits > 1 ? 3.0 : 0.0)) {
                 s = wide.splits;
                 tiles = wide_tiles;
             } else {

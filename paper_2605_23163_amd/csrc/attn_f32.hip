@@ -474,11 +474,12 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
 //     tile i+2, whose floats were requested a step before.  Slots of one matrix instruction and a slice of vector work, fenced, as
 //     in the bf16 kernel.  A wavefront alone on its SIMD takes 5 cycles per vector instruction and 8 where one waits for the one
 //     before it, so a slot carries four or five that do not: pieces of ten in every other slot cost 12 % of the time.
-//   * What bounds it: N = 8, B = 32, L = 4096, Hq = 28, Hkv = 4, D = 128 takes 93.6 us a call (135.7 with fp32 products): 79 us of
-//     steps, 1 140 TFLOP/s of bf16 products, the rate the bf16 attention reaches at its largest sizes (the chip lowers its
-//     clock: 2.4 us a step with 224 workgroups, 2.0 with 56), 6 us until queries and first tiles are there, the merge.  Queries
-//     in LDS instead of registers and one slot each for K and V: 97.5; o and its small products in one sum: as fast, but the
-//     sum is rounded twelve times per tile (error against 64 bits 2.5 times as large).
+//   * What bounds it: N = 8, B = 32, L = 4096, Hq = 28, Hkv = 4, D = 128 takes 84.5 us a call (135.7 with fp32 products): 70 us of
+//     steps, 1 290 TFLOP/s of bf16 products beside the 1 420 that a loop of nothing but this mix reaches (the chip lowers its
+//     clock: 2.1 us a step with 224 workgroups, 1.8 with 56), 6 us until queries and first tiles are there, the merge.
+//     Measured on the way, us for that call: queries in LDS and one slot each for K and V 97.5; in registers, where the compiler
+//     copied them for every use 93.6; kept in the accumulation registers 89; and no address worked out per tile 86.5.  One sum for
+//     all products is as fast, but rounded twelve times per tile (error against 64 bits 2.5 times as large).
 //   * Values that are not finite: a part of an infinity is a NaN, and one in a tile reaches every row of a wavefront.  A
 //     wavefront whose sums are not finite at the end does its keys again with fp32 products (f32_wave_loop), so such calls
 //     give what the kernel above gives, in twice the time and more.
@@ -579,26 +580,29 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
     float raw[2 * KV][8];     // K groups, then V groups
     const auto k_key = [&](int u) { return (tid + 256 * u) / C::CH; };
     const auto v_th = [&](int u) { return (wave * 64 + 256 * u) / D; };     // 2 (16-key step) + half: the same for a wavefront
-    const uint32_t v_lane = (uint32_t)(tid % D) * 4;
+    uint32_t k_lane[KV], v_lane[KV];
+#pragma unroll
+    for (int u = 0; u < KV; ++u) {
+        k_lane[u] = (uint32_t)k_key(u) * stride4 + (uint32_t)(tid % C::CH) * 32;
+        v_lane[u] = (uint32_t)((v_th(u) >> 1) * 16 + (v_th(u) & 1) * 4) * stride4 + (uint32_t)(tid % D) * 4;
+    }
+    // Keys that do not exist lie beyond the buffer's end and read as zeros (their scores are masked): no address depends on the
+    // tile, and no branch is needed, without which the compiler can count the loads in flight.
+    const auto tile_buffer = [&](const char* base, int valid) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, (uint32_t)(valid - 1) * stride4 + (uint32_t)(D * 4), 0x00020000);
+    };
     // (in quarters: a K group is two loads, a V group eight)
     const auto request_k = [&](const KeyTile& t, int u, int quarter) {
         if (quarter % 2 != 0) return;
-        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(t.k), 0, -1, 0x00020000);
-        const uint32_t off = (uint32_t)min(k_key(u), t.valid - 1) * stride4 + (uint32_t)(tid % C::CH) * 32;
-        const f32x4 x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + 8 * quarter, 0, 0));
+        const f32x4 x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(tile_buffer(t.k, t.valid), k_lane[u] + 8 * quarter, 0, 0));
 #pragma unroll
         for (int e = 0; e < 4; ++e) raw[u][2 * quarter + e] = x[e];
     };
     const auto request_v = [&](const KeyTile& t, int u, int quarter) {
-        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(t.v), 0, -1, 0x00020000);
-        // (no branch: the compiler counts the loads in flight, and a path without these would make every wait a full one)
-        const int th = v_th(u);
-        const uint32_t first = (uint32_t)((th >> 1) * 16 + (th & 1) * 4) * stride4, last = (uint32_t)(t.valid - 1) * stride4;
 #pragma unroll
-        for (int e = 2 * quarter; e < 2 * quarter + 2; ++e) {
-            const uint32_t soff = min(first + (uint32_t)((e & 3) + (e >> 2) * 8) * stride4, last);
-            raw[KV + u][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, v_lane, soff, 0));
-        }
+        for (int e = 2 * quarter; e < 2 * quarter + 2; ++e)
+            raw[KV + u][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(tile_buffer(t.v, t.valid), v_lane[u],
+                                                                                  (uint32_t)((e & 3) + (e >> 2) * 8) * stride4, 0));
     };
     // where a group's parts go
     uint32_t dst[2 * KV];
@@ -647,8 +651,6 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
     const int n = t_hi - t_lo;
     if (n > 0) {
         now = tile_at(t_lo);
-        next1 = tile_at(t_lo + 1);
-        next2 = tile_at(t_lo + 2);
 #pragma unroll
         for (int u = 0; u < KV; ++u)
 #pragma unroll
@@ -657,6 +659,9 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
         for (int u = 0; u < KV; ++u)
 #pragma unroll
             for (int x = 0; x < 4; ++x) request_v(now, u, x);
+        FDD_FENCE();
+        next1 = tile_at(t_lo + 1);
+        next2 = tile_at(t_lo + 2);
     }
 
     // ---- the query row of this lane, split: B operand of S^T = K Q^T ---------------------------------------------------
@@ -689,7 +694,10 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
                 w[2][2 * k + 1] = round_pair(y[2], y[3]);
             }
 #pragma unroll
-            for (int i = 0; i < 3; ++i) qf[i][ks] = __builtin_bit_cast(bf16x8, w[i]);
+            for (int i = 0; i < 3; ++i) {
+                qf[i][ks] = __builtin_bit_cast(bf16x8, w[i]);
+                asm volatile("" : "+a"(qf[i][ks]));      // (kept where the matrix instructions read it, not copied for each)
+            }
         }
     }
 
