@@ -103,13 +103,13 @@ static F32Cut f32_cut(bool wide, long long row_tiles, long long tiles, int D, in
     const double tile_us = wide ? (D == 128 ? 2.3 : 1.3) : 2.0 * 36 * D / 2300.0, start_us = wide ? 8.0 : 4.0, merge_us = wide ? 3.0 : 4.0;
     const int sharers = wide ? 1 : kF32Waves;                    // of a workgroup's keys
     const double partial_us = (wide ? (double)kF32WideRowTile * D * 4.0 / 4e6 : (double)kF32RowTile * D * 8.0 / 4e6);
-    F32Cut best = {1, 0.0};
+    F32Cut best = {1, HUGE_VAL};                                 // (kept where s_min is above the most splits)
     for (int s = s_min; s <= 64 && (s == s_min || (long long)(s - 1) * sharers < tiles); ++s) {
         const long long rounds = (row_tiles * s + kNumCU - 1) / kNumCU;
         const long long per = (tiles + (long long)s * sharers - 1) / ((long long)s * sharers);
         double us = (double)rounds * ((double)per * tile_us + start_us);
         if (s > 1) us += merge_us + (double)row_tiles * s * partial_us;
-        if (s == s_min || us < best.us) best = {s, us};
+        if (us < best.us) best = {s, us};
         if (row_tiles * s >= 4 * kNumCU) break;      // more rounds gain nothing
     }
     return best;

@@ -28,3 +28,17 @@ def test_key_tiles_are_cut_without_overflow(tmp_path):
 
 def test_launch_stays_below_2_to_the_32_work_items(tmp_path):
     assert "launch grid: ok" in run_host("launch_grid_main", tmp_path)
+
+
+def test_long_calls_of_one_row_tile_are_cut():
+    # one or two row tiles and keys for up to 64 pieces, the most there are (L = 8100: exactly 64): such a call is never left whole
+    import ctypes as C
+
+    import paper_2605_23163_amd.binding as b
+    lib = b.load_library()
+    for Hq, Hkv, D in ((4, 1, 64), (2, 2, 128)):
+        for L in list(range(4000, 17000, 57)) + [8100, 16200]:
+            p = b.AttnParams()
+            p.N, p.B, p.L, p.Hq, p.Hkv, p.D, p.dtype = 1, 8, L, Hq, Hkv, D, b.FDD_F32
+            need = lib.fdd_block_attn_workspace(C.byref(p))
+            assert need > 0, (L, Hq, Hkv, D)
