@@ -266,6 +266,12 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
         }
         if (s > tiles) s = (int)tiles;
         if (s < 1) s = 1;
+        // Tiles of 16 rows, cut alike, where twice the workgroups still find a compute unit each: half of the matrix work for
+        // every wavefront, the same sums per row.  us per call, replayed, 32 rows / 16 rows (workgroups of 32 rows): D = 64, Hq = 4,
+        // Hkv = 1, N=1, B=8, L=256 10.4 / 7.1 (1), L=20000 16.4 / 12.6 (53); D = 64, Hq = 28, Hkv = 4, N=1, B=64, L=100 8.8 / 6.5 (56); D = 128,
+        // Hq = 28, Hkv = 4, N=1, B=32, L=256 15.3 / 11.9 (84), N=2, B=32, L=128 16.3 / 11.0 (56); Hq = 8, Hkv = 8, B=8, L=1000 13.0 / 11.0 (64).
+        // (With more workgroups than compute units the second round costs what the halves save.)
+        if (pl.mtile_rows == kF32RowTile && 2 * NM * s <= kNumCU) cut_f32(kF32FewRowTile, 16);
         pl.TPU = pl.TP > 0 ? pl.TP : 1;
         pl.U = NM * pl.TPU;
         pl.splits = s;

@@ -8,12 +8,13 @@
 // product apart into bf16 products.
 //
 // How the work is laid out
-//   * A workgroup owns 32 stacked query rows of one KV head (see AttnPlan); its
+//   * A workgroup owns 32 stacked query rows of one KV head (see AttnPlan), or 16
+//     where the call leaves half of the compute units idle; its
 //     8 wavefronts share the KEYS out among themselves, 16 at a time, each with
 //     a streaming-softmax state (m, l, o) of its own, and merge through LDS at
 //     the end.  `splits` workgroups share one row tile when the row tiles alone
 //     leave the chip idle; then a second small kernel merges their partials.
-//   * S^T = K Q^T: a lane owns query lane % 16 of each of two 16-query blocks and
+//   * S^T = K Q^T: a lane owns query lane % 16 of each 16-query block and
 //     keys 4 (lane / 16) .. + 3, so the probabilities are the B operand of
 //     O^T += V^T P^T as they lie.  The channels are dealt to the k-steps (and to
 //     the rows of O^T) such that every operand is a 16-byte piece of a K or V row:
@@ -26,6 +27,10 @@
 //     with few) splits, whose partials would cost a pass over memory each.
 //   * A fragment register is requested again for the next tile as soon as it has
 //     been used: a whole step, 4096 cycles at D = 128, of latency is covered.
+//   * A short call is start, first loads, a few tiles and the LDS merge.  With 16 rows a
+//     wavefront has half of the matrix work per tile and half of the merge: N = 1, B = 8,
+//     L = 256, Hq = 4, Hkv = 1, D = 64 10.4 -> 7.1 us, N = 2, B = 32, L = 128, Hq = 28, Hkv = 4,
+//     D = 128 16.3 -> 11.0 (replayed).
 //   * Measured at N = 8, B = 32, L = 4096, Hq = 28, Hkv = 4, D = 128 (15.1 GFLOP): 135 us
 //     in a loop of nothing else, 112 TFLOP/s of the 154 a large fp32 matrix product
 //     reaches here, and 149 us among the other kernels of a denoise step; 224 of 256
@@ -46,7 +51,6 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int KT = 16;                 // keys per tile
-constexpr int RT = kF32RowTile;        // rows per workgroup: two 16-query blocks
 constexpr int WAVES = kF32Waves;       // wavefronts of a workgroup, sharing the keys
 constexpr int THREADS = WAVES * 64;
 
@@ -134,19 +138,19 @@ __device__ __forceinline__ KeyTile key_tile(const Args& a, int pb, int kh, int n
     return r;
 }
 
-// Streaming softmax of a wavefront's 32 query rows in the layout of the 16x16x4 matrix instruction.
-template <int D>
+// Streaming softmax of a wavefront's QB blocks of 16 query rows in the layout of the 16x16x4 matrix instruction.
+template <int D, int QB>
 struct WaveState {
-    f32x4 o[2][D / 64][4];   // [query block][64-channel block][e]: channels 64 t + 16 g4 + 4 v + e of query c16
-    float m_ref[2];          // reference the exponentials are taken against (raw score units)
-    float limit[2];          // a score further above the reference raises it; -inf: there is none yet
-    float l_run[2];          // this lane's share of the running sum
+    f32x4 o[QB][D / 64][4];   // [query block][64-channel block][e]: channels 64 t + 16 g4 + 4 v + e of query c16
+    float m_ref[QB];          // reference the exponentials are taken against (raw score units)
+    float limit[QB];          // a score further above the reference raises it; -inf: there is none yet
+    float l_run[QB];          // this lane's share of the running sum
 };
 
 // One wavefront over tiles [t_lo, t_hi) of 16 keys.  `several`: the row tile's rows belong to more than one rollout.
-template <int D, typename TileAt>
-__device__ __forceinline__ void f32_wave_loop(const Args& a, const TileAt& tile_at, int t_lo, int t_hi, const f32x4 (&qf)[2][D / 16],
-                                              const int (&my_rollout)[2], const int (&my_b)[2], bool several, WaveState<D>& w)
+template <int D, int QB, typename TileAt>
+__device__ __forceinline__ void f32_wave_loop(const Args& a, const TileAt& tile_at, int t_lo, int t_hi, const f32x4 (&qf)[QB][D / 16],
+                                              const int (&my_rollout)[QB], const int (&my_b)[QB], bool several, WaveState<D, QB>& w)
 {
     constexpr int NJ = D / 16;         // 16-byte fragment loads per tile and operand
     constexpr int NT = D / 64;         // 64-channel blocks of the output
@@ -168,7 +172,7 @@ __device__ __forceinline__ void f32_wave_loop(const Args& a, const TileAt& tile_
     auto& limit = w.limit;
     auto& l_run = w.l_run;
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int qb = 0; qb < QB; ++qb) {
         m_ref[qb] = l_run[qb] = 0.f;
         limit[qb] = -INFINITY;
 #pragma unroll
@@ -200,13 +204,15 @@ __device__ __forceinline__ void f32_wave_loop(const Args& a, const TileAt& tile_
             // once more at the end, from the caches.)
             const KeyTile next = tile_at(min(t + 1, t_hi - 1));
             const uint32_t next_k = k_off(next);
-            f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+            f32x4 s[QB];
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) s[qb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int qb = 0; qb < 2; ++qb)
+                    for (int qb = 0; qb < QB; ++qb)
                         s[qb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][i], qf[qb][j][i], s[qb], 0, 0, 0);
                 kf[j] = load(next.k, next_k + 64 * j);
                 __builtin_amdgcn_sched_barrier(0);
@@ -214,7 +220,7 @@ __device__ __forceinline__ void f32_wave_loop(const Args& a, const TileAt& tile_
             // register v of a query block is key 4 g4 + v
             if (now.valid < KT || now.rollout >= 0) {
 #pragma unroll
-                for (int qb = 0; qb < 2; ++qb)
+                for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const int key = 4 * g4 + v;
@@ -227,17 +233,17 @@ __device__ __forceinline__ void f32_wave_loop(const Args& a, const TileAt& tile_
             // references, and a rounded product m c in place of m would set each wavefront off by up to half a unit of it.
             // The reference is raised when a score outgrows it by more than 2^8 (the same softmax; fp32 keeps its
             // relative precision), for a whole row at a time: its keys lie in the four lanes c16 + 16 i.
-            f32x4 p[2];
+            f32x4 p[QB];
             bool need = false;
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
+            for (int qb = 0; qb < QB; ++qb) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) p[qb][v] = s[qb][v] - m_ref[qb];
                 need |= fmaxf(fmaxf(p[qb][0], p[qb][1]), fmaxf(p[qb][2], p[qb][3])) > limit[qb];
             }
             if (__any(need)) {
 #pragma unroll
-                for (int qb = 0; qb < 2; ++qb) {
+                for (int qb = 0; qb < QB; ++qb) {
                     const bool none = limit[qb] == -INFINITY;
                     float m = fmaxf(fmaxf(s[qb][0], s[qb][1]), fmaxf(s[qb][2], s[qb][3]));
                     m = fmaxf(m, __shfl_xor(m, 16, 64));
@@ -256,7 +262,7 @@ __device__ __forceinline__ void f32_wave_loop(const Args& a, const TileAt& tile_
                 }
             }
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
+            for (int qb = 0; qb < QB; ++qb) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) p[qb][v] = __builtin_amdgcn_exp2f(p[qb][v] * a.c);
                 l_run[qb] += (p[qb][0] + p[qb][1]) + (p[qb][2] + p[qb][3]);
@@ -286,7 +292,7 @@ __device__ __forceinline__ void f32_wave_loop(const Args& a, const TileAt& tile_
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
 #pragma unroll
-                            for (int qb = 0; qb < 2; ++qb) {
+                            for (int qb = 0; qb < QB; ++qb) {
                                 f32x4 x = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                                 for (int v = 0; v < 4; ++v)
@@ -307,7 +313,7 @@ __device__ __forceinline__ void f32_wave_loop(const Args& a, const TileAt& tile_
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
 #pragma unroll
-                        for (int qb = 0; qb < 2; ++qb)
+                        for (int qb = 0; qb < QB; ++qb)
                             o[qb][tt][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[v * NT + tt][e], p[qb][v], o[qb][tt][e], 0, 0, 0);
                     vf[v * NT + tt] = load(next.v, next_v + 256 * tt);
                     __builtin_amdgcn_sched_barrier(0);
@@ -318,16 +324,18 @@ __device__ __forceinline__ void f32_wave_loop(const Args& a, const TileAt& tile_
     }
 }
 
-template <int D>
+template <int D, int QB>
 struct F32Cfg {
+    static constexpr int RT = 16 * QB;                    // rows per workgroup
     static constexpr int MERGE_FLOATS = WAVES * RT * D;   // outputs of all wavefronts, in register order
     static constexpr int LDS_BYTES = (MERGE_FLOATS + 2 * WAVES * RT + 2 * RT) * 4;   // + (m, l) per wavefront and row, and per row
 };
 
-template <int D>
+template <int D, int QB>
 __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
+    constexpr int RT = F32Cfg<D, QB>::RT;
     constexpr int NJ = D / 16;         // 16-byte fragment loads per tile and operand
     constexpr int NT = D / 64;         // 64-channel blocks of the output
     extern __shared__ __align__(16) float smem[];
@@ -346,11 +354,11 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
     const int c16 = lane & 15, g4 = lane >> 4;
     const int NB = a.N * a.B;
 
-    // ---- query rows of this lane: c16 of both 16-query blocks --------------------------------------
-    f32x4 qf[2][NJ];
-    int my_rollout[2], my_b[2];
+    // ---- query rows of this lane: c16 of every 16-query block --------------------------------------
+    f32x4 qf[QB][NJ];
+    int my_rollout[QB], my_b[QB];
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int qb = 0; qb < QB; ++qb) {
         const int row = min(mt * RT + qb * 16 + c16, a.R - 1);
         const int sel = fast_div(row, a.dG), g = row - sel * a.G;
         const int nb = position_of(a.qpos, sel, NB);
@@ -374,8 +382,8 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
     const int t_hi = __builtin_amdgcn_readfirstlane(key_cut(n_tiles, part + 1, parts, a.dParts));
 
     const auto tile_at = [&](int t) { return key_tile<KT, D>(a, pb, kh, n_lo, TP, t); };
-    WaveState<D> w;
-    f32_wave_loop<D>(a, tile_at, t_lo, t_hi, qf, my_rollout, my_b, n_lo != n_hi, w);
+    WaveState<D, QB> w;
+    f32_wave_loop<D, QB>(a, tile_at, t_lo, t_hi, qf, my_rollout, my_b, n_lo != n_hi, w);
     auto& o = w.o;
     auto& m_ref = w.m_ref;
     auto& limit = w.limit;
@@ -386,12 +394,12 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
     const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), c16_e = lane_e & 15;
     const int tid_e = wave * 64 + lane_e;
     float* const so = smem;                                  // [wave][qb][t][v][lane] x 4 channels
-    float* const sm = smem + F32Cfg<D>::MERGE_FLOATS;        // [wave][row]: m, then the wavefront's weight
+    float* const sm = smem + F32Cfg<D, QB>::MERGE_FLOATS;        // [wave][row]: m, then the wavefront's weight
     float* const sl = sm + WAVES * RT;                       // [wave][row]: l
     float* const row_l = sl + WAVES * RT;                    // [row]: l of the workgroup
     float* const row_m = row_l + RT;                         // [row]: m of the workgroup
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int qb = 0; qb < QB; ++qb) {
         float l = l_run[qb];
         l += __shfl_xor(l, 16, 64);
         l += __shfl_xor(l, 32, 64);
@@ -403,7 +411,7 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
         for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                *reinterpret_cast<f32x4*>(so + ((((wave * 2 + qb) * NT + tt) * 4 + v) * 64 + lane_e) * 4) =
+                *reinterpret_cast<f32x4*>(so + ((((wave * QB + qb) * NT + tt) * 4 + v) * 64 + lane_e) * 4) =
                     f32x4{o[qb][tt][0][v], o[qb][tt][1][v], o[qb][tt][2][v], o[qb][tt][3][v]};
     }
     __syncthreads();
@@ -422,7 +430,7 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
         row_m[tid_e] = m;
     }
     __syncthreads();
-    constexpr int CHUNKS = 2 * NT * 4 * 64;      // 16-byte pieces of the row tile
+    constexpr int CHUNKS = QB * NT * 4 * 64;      // 16-byte pieces of the row tile
 #pragma unroll
     for (int i0 = 0; i0 < CHUNKS; i0 += THREADS) {
         const int i = i0 + tid_e;
@@ -971,8 +979,8 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
             r.valid = min(r.valid, 16);
             return r;
         };
-        WaveState<D> w;
-        f32_wave_loop<D>(a, half_tile, 2 * t_lo, 2 * t_hi, q16, rollout16, b16, n_lo != n_hi, w);
+        WaveState<D, 2> w;
+        f32_wave_loop<D, 2>(a, half_tile, 2 * t_lo, 2 * t_hi, q16, rollout16, b16, n_lo != n_hi, w);
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
             float l = w.l_run[qb];
@@ -1252,11 +1260,12 @@ static hipError_t launch(Kernel kern, int threads, int lds_bytes, std::atomic<ui
 }
 
 template <int D>
-static hipError_t launch(const Args& a, bool wide, hipStream_t s)
+static hipError_t launch(const Args& a, int rows, hipStream_t s)
 {
-    static std::atomic<uint64_t> done{0}, done_wide{0};
-    if (wide) return launch(&attn_f32_wide_kernel<D>, 256, WideCfg<D>::LDS_BYTES, done_wide, a, s);
-    return launch(&attn_f32_kernel<D>, THREADS, F32Cfg<D>::LDS_BYTES, done, a, s);
+    static std::atomic<uint64_t> done{0}, done_few{0}, done_wide{0};
+    if (rows == WRT) return launch(&attn_f32_wide_kernel<D>, 256, WideCfg<D>::LDS_BYTES, done_wide, a, s);
+    if (rows == kF32FewRowTile) return launch(&attn_f32_kernel<D, 1>, THREADS, F32Cfg<D, 1>::LDS_BYTES, done_few, a, s);
+    return launch(&attn_f32_kernel<D, 2>, THREADS, F32Cfg<D, 2>::LDS_BYTES, done, a, s);
 }
 
 hipError_t launch_attn_f32(const fdd_attn_params& p, const AttnPlan& plan, float scale, hipStream_t s)
@@ -1287,7 +1296,7 @@ hipError_t launch_attn_f32(const fdd_attn_params& p, const AttnPlan& plan, float
     a.causal = (p.flags & FDD_ATTN_CAUSAL_BLOCK) ? 1 : 0;
     a.qpos = p.n_q_positions > 0 ? p.q_positions : nullptr;
     const bool wide = plan.mtile_rows == WRT;
-    if (!wide && plan.mtile_rows != RT) return hipErrorInvalidValue;
+    if (!wide && plan.mtile_rows != kF32RowTile && plan.mtile_rows != kF32FewRowTile) return hipErrorInvalidValue;
     if (plan.key_tile != (wide ? WKT : KT)) return hipErrorInvalidValue;
     a.ext_per = (p.E + plan.key_tile - 1) / plan.key_tile;
     a.per = a.ext_per + (p.B + plan.key_tile - 1) / plan.key_tile;
@@ -1298,7 +1307,7 @@ hipError_t launch_attn_f32(const fdd_attn_params& p, const AttnPlan& plan, float
     a.dB = make_fastdiv((uint32_t)a.B);
     a.dPer = make_fastdiv((uint32_t)a.per);
     a.dParts = make_fastdiv((uint32_t)(a.S * (wide ? 1 : WAVES)));     // wavefronts or workgroups that share the keys
-    return p.D == 128 ? launch<128>(a, wide, s) : launch<64>(a, wide, s);
+    return p.D == 128 ? launch<128>(a, plan.mtile_rows, s) : launch<64>(a, plan.mtile_rows, s);
 }
 
 hipError_t launch_attn_combine(const fdd_attn_params& p, const AttnPlan& plan, float scale, hipStream_t s)

@@ -42,6 +42,7 @@ constexpr int kNumXCD = 8;
 //               (stream-K) workgroup w of W owns the contiguous unit range
 //               [unit_begin(w), unit_begin(w+1)), which may cross M-tiles.
 constexpr int kF32RowTile = 32;    // fp32 path: stacked rows per workgroup
+constexpr int kF32FewRowTile = 16; // fp32 path: the same in calls that leave half of the compute units idle
 constexpr int kF32Waves = 8;       // fp32 path: wavefronts per workgroup
 constexpr int kF32WideRowTile = 128, kF32WideKeyTile = 32;   // fp32 path, products on the bf16 pipe: rows per workgroup, keys per tile
 
