@@ -115,7 +115,7 @@ static F32Cut f32_cut(bool wide, long long row_tiles, long long tiles, int D, in
     return best;
 }
 
-bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
+bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
 {
     AttnPlan pl;
     pl.G = p.Hq / p.Hkv;
@@ -257,7 +257,7 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
             // (short calls that are cut take 2 to 5 us more than the estimate for 32-row tiles says)
             // (up to a GiB of partials: beyond it the chip is full many times over, and the narrow tiles need none)
             const bool fits = NM * wide.splits * (kF32WideRowTile * p.D * 4ll) <= (1ll << 30);
-            if (f32_wide && fits && wide_tiles >= 2 * wide.splits && wide.us < narrow.us + (narrow.splits > 1 ? 3.0 : 0.0)) {
+            if (fits && wide_tiles >= 2 * wide.splits && wide.us < narrow.us + (narrow.splits > 1 ? 3.0 : 0.0)) {
                 s = wide.splits;
                 tiles = wide_tiles;
             } else {
@@ -373,18 +373,7 @@ fdd_status fdd_block_attn(const fdd_attn_params* p)
     if (p->out == p->q) return fail(FDD_ERR_UNSUPPORTED, "fdd_block_attn: out must not alias q");
     AttnPlan plan;
     make_attn_plan(*p, &plan);
-    size_t need = plan.ws_o_bytes + plan.ws_ml_bytes + plan.ws_vt_bytes;
-    const size_t given = p->workspace ? p->workspace_bytes : 0;
-    if (need > given && plan.mtile_rows == kF32WideRowTile && p->dtype == FDD_F32) {
-        // the 32-row tiles need less scratch than the 128-row tiles, often none: a call that brings enough for them runs on them
-        AttnPlan narrow;
-        make_attn_plan(*p, &narrow, false);
-        const size_t narrow_need = narrow.ws_o_bytes + narrow.ws_ml_bytes;
-        if (narrow_need <= given) {
-            plan = narrow;
-            need = narrow_need;
-        }
-    }
+    const size_t need = plan.ws_o_bytes + plan.ws_ml_bytes + plan.ws_vt_bytes;
     if (need > 0) {
         if (!p->workspace) return fail(FDD_ERR_WORKSPACE, "fdd_block_attn: workspace is NULL, %zu bytes needed", need);
         if (reinterpret_cast<uintptr_t>(p->workspace) & 255u) return fail(FDD_ERR_WORKSPACE, "fdd_block_attn: workspace must be 256-byte aligned");

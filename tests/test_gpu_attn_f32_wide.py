@@ -146,33 +146,3 @@ def test_values_at_both_ends_of_the_range(F, oracle):
     got, ref = to_f64(run(F, d, 0)), reference(oracle, d, 0)
     size = np.maximum(np.abs(ref), 1.0)
     assert np.isfinite(got).all() and (np.abs(got - ref) / size).max() <= TOL
-
-
-def test_a_call_without_the_scratch_runs_on_32_row_tiles(F, oracle):
-    # (32-row tiles that are not cut need no scratch: such a call may bring none)
-    import ctypes as C
-
-    import paper_2605_23163_amd.binding as b
-    shape = (7, 64, 190, 28, 4, 0, 64)
-    print_case(test="f32_wide_no_scratch", shape=shape)
-    d = make(shape)
-    t = {k: to_dev(v) for k, v in d.items()}
-    args = [t[k] for k in ("q", "prefix_k", "prefix_v", "block_k", "block_v")]
-    need = F.fdd_block_attn_workspace(*args)
-    assert need > 0
-    ref = reference(oracle, d, 0)
-    lib, out, ws = F.load_library(), torch.empty_like(t["q"]), torch.empty(need, dtype=torch.uint8, device="cuda")
-    for given in (None, ws[:need - 256], ws):
-        p = b._attn_params(*args, None, out.fill_(7.0), None, 0)
-        if given is not None:
-            p.workspace, p.workspace_bytes = given.data_ptr(), given.numel()
-        p.stream = torch.cuda.current_stream().cuda_stream
-        assert lib.fdd_block_attn(C.byref(p)) == 0
-        torch.cuda.synchronize()
-        assert np.abs(to_f64(out) - ref).max() <= TOL
-    # (where the 32-row tiles are cut, what they need is still asked for)
-    d = make((1, 32, 3000, 28, 4, 0, 128))
-    t = {k: to_dev(v) for k, v in d.items()}
-    args = [t[k] for k in ("q", "prefix_k", "prefix_v", "block_k", "block_v")]
-    p = b._attn_params(*args, None, torch.empty_like(t["q"]), None, 0)
-    assert lib.fdd_block_attn(C.byref(p)) == 5
