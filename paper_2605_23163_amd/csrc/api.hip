@@ -270,7 +270,8 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
         // every wavefront, the same sums per row.  us per call, replayed, 32 rows / 16 rows (workgroups of 32 rows): D = 64, Hq = 4,
         // Hkv = 1, N=1, B=8, L=256 10.4 / 7.1 (1), L=20000 16.4 / 12.6 (53); D = 64, Hq = 28, Hkv = 4, N=1, B=64, L=100 8.8 / 6.5 (56); D = 128,
         // Hq = 28, Hkv = 4, N=1, B=32, L=256 15.3 / 11.9 (84), N=2, B=32, L=128 16.3 / 11.0 (56); Hq = 8, Hkv = 8, B=8, L=1000 13.0 / 11.0 (64).
-        // (With more workgroups than compute units the second round costs what the halves save.)
+        // With more workgroups a second round costs more than the halves save: D = 128, Hq = 28, Hkv = 4, N=8, B=32, L=40 12.5 / 15.5
+        // (224), N=9, L=64 12.8 / 16.3 (252), Hq = 4, Hkv = 1, N=2, B=31, L=10559 25.6 / 30.7 (208); at D = 64 it is 10 % either way.
         if (pl.mtile_rows == kF32RowTile && 2 * NM * s <= kNumCU) cut_f32(kF32FewRowTile, 16);
         pl.TPU = pl.TP > 0 ? pl.TP : 1;
         pl.U = NM * pl.TPU;

@@ -678,10 +678,9 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
     const int sel = fast_div(row, a.dG);
     const int nb = position_of(a.qpos, sel, NB);
     const int my_rollout = fast_div(nb, a.dB), my_b = nb - my_rollout * a.B;
-    const size_t row_off = ((size_t)nb * a.Hq + (size_t)kh * a.G + (row - sel * a.G)) * D;      // of q and out
     bf16x8 qf[3][KS];
     {
-        const float* qp = a.q + pb * a.q_bs + row_off + 8 * half;
+        const float* qp = a.q + pb * a.q_bs + ((size_t)nb * a.Hq + (size_t)kh * a.G + (row - sel * a.G)) * D + 8 * half;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const f32x4 x0 = *reinterpret_cast<const f32x4*>(qp + 16 * ks), x1 = *reinterpret_cast<const f32x4*>(qp + 16 * ks + 4);
@@ -922,17 +921,6 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
     const uint32_t part0 = (uint32_t)(wave * 32 * D * 4);
     if (__builtin_expect(!__any(x0 != 0.f), 1)) {
         if (!row_ok) return;
-        if (a.S == 1) {
-            const float inv = 1.f / l_tot;
-            float* const op = a.out + pb * a.o_bs + row_off;
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int v4 = 0; v4 < 4; ++v4)
-                    *reinterpret_cast<f32x4*>(op + db * 32 + v4 * 8 + half * 4) =
-                        f32x4{o[db][4 * v4], o[db][4 * v4 + 1], o[db][4 * v4 + 2], o[db][4 * v4 + 3]} * inv;
-            return;
-        }
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -953,15 +941,13 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
         const int c16 = lane & 15, g4 = lane >> 4;
         f32x4 q16[2][D / 16];
         int rollout16[2], b16[2];
-        size_t off16[2];
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
             const int r = min(mt * WRT + wave * 32 + qb * 16 + c16, a.R - 1);
             const int e = fast_div(r, a.dG), pos = position_of(a.qpos, e, NB);
             rollout16[qb] = fast_div(pos, a.dB);
             b16[qb] = pos - rollout16[qb] * a.B;
-            off16[qb] = ((size_t)pos * a.Hq + (size_t)kh * a.G + (r - e * a.G)) * D;
-            const float* qp = a.q + pb * a.q_bs + off16[qb] + 4 * g4;
+            const float* qp = a.q + pb * a.q_bs + ((size_t)pos * a.Hq + (size_t)kh * a.G + (r - e * a.G)) * D + 4 * g4;
 #pragma unroll
             for (int j = 0; j < D / 16; ++j) q16[qb][j] = *reinterpret_cast<const f32x4*>(qp + 16 * j);
         }
@@ -988,19 +974,16 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
             l += __shfl_xor(l, 32, 64);
             const int r = wave * 32 + qb * 16 + c16;
             if (mt * WRT + r >= a.R) continue;
-            const float inv = a.S == 1 ? 1.f / l : 1.f;
-            float* const op = a.out + pb * a.o_bs + off16[qb];
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const f32x4 x = f32x4{w.o[qb][t][0][v], w.o[qb][t][1][v], w.o[qb][t][2][v], w.o[qb][t][3][v]} * inv;
+                    const f32x4 x = f32x4{w.o[qb][t][0][v], w.o[qb][t][1][v], w.o[qb][t][2][v], w.o[qb][t][3][v]};
                     const int ch = 64 * t + 16 * g4 + 4 * v;
-                    if (a.S == 1) *reinterpret_cast<f32x4*>(op + ch) = x;
-                    else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), part_rsrc,
-                                                                part0 + (ch / 8) * 1024 + ((ch / 4) % 2 * 32 + qb * 16 + c16) * 16, 0, 16);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), part_rsrc,
+                                                           part0 + (ch / 8) * 1024 + ((ch / 4) % 2 * 32 + qb * 16 + c16) * 16, 0, 16);
                 }
-            if (a.S > 1 && g4 == 0) {
+            if (g4 == 0) {
                 a.ws_ml[(pseg + r) * 2 + 0] = w.limit[qb] == -INFINITY ? -INFINITY : w.m_ref[qb];
                 a.ws_ml[(pseg + r) * 2 + 1] = l;
             }
@@ -1297,6 +1280,7 @@ hipError_t launch_attn_f32(const fdd_attn_params& p, const AttnPlan& plan, float
     a.qpos = p.n_q_positions > 0 ? p.q_positions : nullptr;
     const bool wide = plan.mtile_rows == WRT;
     if (!wide && plan.mtile_rows != kF32RowTile && plan.mtile_rows != kF32FewRowTile) return hipErrorInvalidValue;
+    if (wide && plan.splits < 2) return hipErrorInvalidValue;      // (it leaves partial results)
     if (plan.key_tile != (wide ? WKT : KT)) return hipErrorInvalidValue;
     a.ext_per = (p.E + plan.key_tile - 1) / plan.key_tile;
     a.per = a.ext_per + (p.B + plan.key_tile - 1) / plan.key_tile;
