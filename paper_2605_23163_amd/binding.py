@@ -476,6 +476,10 @@ def fdd_verify_step(ar_logits, mask, scaffold_mask, draft, tokens, n_accepted=No
 def fdd_fork_block(src, N, dst=None, stream=None):
     """dst[n] = src for n < N: the private block state of N forked rollouts."""
     lib = load_library()
+    args = _marshal.fork(src, N, dst) if dst is not None and _marshal is not None else None
+    if args is not None:
+        _check(lib.fdd_fork_block(N, *args, _stream_ptr(stream)))
+        return dst
     if dst is None:
         new = torch.empty if stream is None else _maker(stream, src.device, torch.empty)
         dst = new((N,) + tuple(src.shape), dtype=src.dtype, device=src.device)

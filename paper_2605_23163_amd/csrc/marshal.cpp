@@ -1,4 +1,4 @@
-// Arguments of the two calls of a denoise step, from tensors to the C structs of fdd.h.
+// Arguments of the two calls of a denoise step, and of a fork, from tensors to the C structs of fdd.h.
 //
 // Host code, a CPython module: `attn` and `unmask` check shapes, types and placement as binding.py does and fill the
 // struct at the given address.  They return True, or False (and set no exception) for anything that is not the ordinary
@@ -170,7 +170,30 @@ PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t n)
     return PyBool_FromLong(ok);
 }
 
+// src, N, dst of a fork into a tensor of the caller's: (bytes, address of src, address of dst), or None
+PyObject* fork(PyObject*, PyObject* const* args, Py_ssize_t n)
+{
+    if (n != 3) {
+        PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
+        return nullptr;
+    }
+    if (!at::impl::torch_function_mode_enabled()) {
+        try {
+            const at::Tensor &src = tensor(args[0]), &dst = tensor(args[2]);
+            const int64_t N = int32_of(args[1]);
+            need(N > 0 && dst.numel() % N == 0 && dst.numel() / N * (int64_t)dst.element_size() == src.numel() * (int64_t)src.element_size());
+            void *const from = pointer(src), *const to = pointer(dst);
+            return Py_BuildValue("(nKK)", (Py_ssize_t)(src.numel() * src.element_size()), (unsigned long long)reinterpret_cast<uintptr_t>(from),
+                                 (unsigned long long)reinterpret_cast<uintptr_t>(to));
+        } catch (...) {       // (NotOrdinary, or an exception of torch's own)
+            PyErr_Clear();
+        }
+    }
+    Py_RETURN_NONE;
+}
+
 PyMethodDef methods[] = {
+    {"fork", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(&fork)), METH_FASTCALL, "arguments of fdd_fork_block"},
     {"attn", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(&call<fdd_attn_params, 15, fill_attn>)), METH_FASTCALL, "fill an fdd_attn_params"},
     {"unmask", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(&call<fdd_unmask_params, 9, fill_unmask>)), METH_FASTCALL, "fill an fdd_unmask_params"},
     {nullptr, nullptr, 0, nullptr}};

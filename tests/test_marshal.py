@@ -105,3 +105,27 @@ def test_other_cases_are_left_to_python(M):
         Bd.fdd_unmask_step(**dict(u, mask=u["mask"].int()))
     with pytest.raises(ValueError):
         Bd.fdd_block_attn(**dict(a, q_positions=torch.zeros(3, device="cuda")))
+
+
+def test_forks_of_cpu_tensors_are_left_to_python(M):
+    assert M.fork(torch.zeros(4), 2, torch.zeros(2, 4)) is None
+    with pytest.raises(ValueError, match="GPU memory"):
+        Bd.fdd_fork_block(torch.zeros(4), 2, dst=torch.zeros(2, 4))
+    with pytest.raises(TypeError):
+        M.fork(torch.zeros(4), 2)
+
+
+@pytest.mark.gpu
+def test_fork_arguments(M):
+    src = torch.zeros(3, 8, dtype=torch.bfloat16, device="cuda")
+    for dst in (src.new_zeros(5, 3, 8), src.new_zeros(120), torch.zeros(5, 12, dtype=torch.int32, device="cuda")):
+        assert M.fork(src, 5, dst) == (48, src.data_ptr(), dst.data_ptr())
+    dst = src.new_zeros(5, 3, 8)
+    others = [(src, 4, dst), (src, 0, dst), (src, -5, dst), (src, 5.0, dst), (src, 5, dst.cpu()), (src.t(), 5, dst), (src, 5, dst.transpose(0, 1)),
+              (src, 5, None), (src.half()[:2], 5, dst), (src, 2**40, dst)]
+    for a in others:
+        assert M.fork(*a) is None, a[1]
+    with torch.overrides.TorchFunctionMode():
+        assert M.fork(src, 5, dst) is None
+    with pytest.raises(ValueError):
+        Bd.fdd_fork_block(src, 4, dst=dst)
