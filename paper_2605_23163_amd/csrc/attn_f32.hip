@@ -596,6 +596,9 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
     }
     // Keys that do not exist lie beyond the buffer's end and read as zeros (their scores are masked): no address depends on the
     // tile, and no branch is needed, without which the compiler can count the loads in flight.
+    // (The range check counts the scalar offset, also one that is past the end by itself: all 105 pairs tried of lane offset and
+    // scalar offset, up to 256 KB past ends of 512 bytes to 64 KB, read data inside and zeros outside.  A plan's partials, a GiB
+    // at most, keep 32 rows of keys far below 2^32 bytes, so no sum of offsets wraps.)
     const auto tile_buffer = [&](const char* base, int valid) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, (uint32_t)(valid - 1) * stride4 + (uint32_t)(D * 4), 0x00020000);
     };
