@@ -1194,14 +1194,16 @@ __global__ __launch_bounds__(256) void attn_wide_merge_kernel(WideMergeArgs a)
             float mx = m;
 #pragma unroll
             for (int u = 0; u < UX; ++u) mx = fmaxf(mx, y[u].x);
-            if (mx == -INFINITY) continue;        // (no key so far, sums are zero)
-            const float old = exp2f((m - mx) * a.c);
+            // (Where no segment so far has a reference, its sums are zero, or NaN, for no score that is NaN raises a reference:
+            // weights of zero keep both.)
+            const float m_use = mx == -INFINITY ? 0.f : mx;
+            const float old = exp2f((m - m_use) * a.c);
             m = mx;
             l *= old;
             acc *= old;
 #pragma unroll
             for (int u = 0; u < UX; ++u) {
-                const float w = exp2f((y[u].x - mx) * a.c);
+                const float w = exp2f((y[u].x - m_use) * a.c);
                 l = fmaf(y[u].y, w, l);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[e] = fmaf(x[u][e], w, acc[e]);

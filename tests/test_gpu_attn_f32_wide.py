@@ -103,6 +103,23 @@ def test_listed_positions_and_a_batch(F, oracle):
         assert np.abs(to_f64(out[i]) - reference(oracle, x, 0)).max() <= TOL
 
 
+# All variants of the merge: 5 pieces (a thread sums them all), 11 (two threads) and 22 to 26 (four), the last of which hold
+# private keys only, for every row tile or all but one
+PIECES = [(3, 64, 334, 28, 4, 32, 128), (3, 64, 732, 28, 4, 128, 64), (1, 64, 498, 28, 4, 128, 128), (1, 64, 505, 28, 4, 128, 64),
+          (4, 20, 1005, 8, 8, 128, 128), (4, 20, 1006, 8, 8, 64, 64)]
+
+
+@pytest.mark.parametrize("shape", PIECES)
+def test_nan_keys_in_all_pieces_but_the_last(F, oracle, shape):
+    # every score of a piece is NaN, so that nothing ever raises its reference: what it leaves is NaN all the same
+    print_case(test="f32_wide_nan_pieces", shape=shape)
+    d, E = make(shape), shape[5]
+    got = to_f64(run(F, d, E))
+    assert np.abs(got - reference(oracle, d, E)).max() <= TOL
+    d["prefix_k"][..., 3] = np.nan
+    assert np.isnan(to_f64(run(F, d, E))).all()
+
+
 @pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[0]])
 @pytest.mark.parametrize("bad", [np.inf, np.nan, -np.inf])
 def test_values_that_are_not_finite_reach_only_who_sees_them(F, oracle, shape, bad):
