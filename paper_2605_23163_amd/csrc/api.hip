@@ -257,7 +257,10 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
             // (short calls that are cut take 2 to 5 us more than the estimate for 32-row tiles says)
             // (up to a GiB of partials: beyond it the chip is full many times over, and the narrow tiles need none)
             const bool fits = NM * wide.splits * (kF32WideRowTile * p.D * 4ll) <= (1ll << 30);
-            if (fits && wide_tiles >= 2 * wide.splits && wide.us < narrow.us + (narrow.splits > 1 ? 3.0 : 0.0)) {
+            // (a larger scale multiplies what those products lose of keys below 2^-110; a smaller one gives weight to scores that
+            // overflow with their factor on Q)
+            const bool usual_scale = !(p.scale > 0.f) || (p.scale >= 0x1p-30f && p.scale <= 0x1p10f);
+            if (usual_scale && fits && wide_tiles >= 2 * wide.splits && wide.us < narrow.us + (narrow.splits > 1 ? 3.0 : 0.0)) {
                 s = wide.splits;
                 tiles = wide_tiles;
             } else {

@@ -467,10 +467,16 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
 // ---------------------------------------------------------------------------
 // The same attention with products on the bf16 matrix pipe, for calls with enough rows and keys (see make_attn_plan).
 //
-// A float is exactly the sum of three bf16 numbers, h + m + l with h the nearest bf16 number, m that of the rest and l what is
-// left (8 bits of mantissa each).  The product of two floats is then six products of bf16 numbers, exact in the matrix unit's
-// fp32 sums; what is dropped (m l', l m', l l') is below 2^-25 of the product, half a unit of an fp32 rounding.  Six
-// products at sixteen times the rate: 96 cycles of matrix pipe per 32 keys, 32 rows and 16 channels instead of 256.
+// A float of 2^-110 and more is exactly the sum of three bf16 numbers, h + m + l with h the nearest bf16 number, m that of the
+// rest and l what is left (8 bits of mantissa each).  The product of two floats is then six products of bf16 numbers, exact in the
+// matrix unit's fp32 sums; what is dropped (m l', l m', l l') is at most 2^-24 (1 + 2^-10) of 2^(e + e'), the powers of two below
+// the factors, where |m| reaches 2^-8 and |l| 2^-17 of theirs.  Six products at sixteen times the rate: 96 cycles of matrix
+// pipe per 32 keys, 32 rows and 16 channels instead of 256.
+//   Of a smaller float the last parts would lie below bf16's smallest number, 2^-133, so V is split times 2^32 and Q times 2^44:
+// every part of any float is then a normal bf16 number, and results carry the inverse factor.  K is split as it is: |q| stays below
+// 2^84, or its parts are infinite, and so what a product with k loses below 2^-42, even if the matrix unit took subnormal parts for
+// zeros; make_attn_plan sends calls with unusual scales to the 32-row tiles.  A probability of less than 2^-110 loses up to
+// 2^-126 of the row's largest, no more than the exponential itself, which is flushed to zero there.
 //
 // How the work is laid out
 //   * A workgroup has 4 wavefronts of 32 stacked rows each (one per SIMD, 512 registers) and takes tiles of 32 keys.  Each
@@ -488,10 +494,13 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
 //     Measured on the way, us for that call: queries in LDS and one slot each for K and V 97.5; in registers, where the compiler
 //     copied them for every use 93.6; kept in the accumulation registers 89; and no address worked out per tile 86.5.  One sum for
 //     all products is as fast, but rounded twelve times per tile (error against 64 bits 2.5 times as large).
-//   * Values that are not finite: a part of an infinity is a NaN, and one in a tile reaches every row of a wavefront.  A
-//     wavefront whose sums are not finite at the end does its keys again with fp32 products (f32_wave_loop), so such calls
-//     give what the kernel above gives, in twice the time and more.
+//   * Values that are not finite, or become so here (|q| and scores from 2^84 on, |v| from 2^96 on): a part of an
+//     infinity is a NaN, and one in a tile reaches every row of a wavefront.  A wavefront whose sums are not finite at the end does
+//     its keys again with fp32 products (f32_wave_loop), so such calls give what the kernel above gives, in 1.2 to 1.9 times the
+//     time of its 32-row tiles (us, 32-row tiles / these, one NaN in a prefix key: N = 8, L = 4096 148 / 240; N = 1, L = 16384 72 / 125;
+//     N = 1, L = 2048 23 / 27; one infinity in a value: 144 / 244, 71 / 132, 23 / 35).
 constexpr int WKT = kF32WideKeyTile, WRT = kF32WideRowTile;
+constexpr float V_UP = 0x1p32f, Q_UP = 0x1p44f;      // (powers of two: no rounding but a result's own below 2^-126)
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
@@ -650,11 +659,24 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
             if (g < KV) request_k(next, g, piece - 10); else request_v(next, g - KV, piece - 10);
         }
     };
+    // four floats of a V group get their factor, before the group is split
+    const auto scale_piece = [&](int u, int quad) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            raw[KV + u][4 * quad + e] *= V_UP;
+            FDD_PIN(raw[KV + u][4 * quad + e]);
+        }
+    };
     const auto split_groups = [&](int first, uint32_t slot, const KeyTile& next) {
 #pragma unroll
-        for (int g = first; g < first + KV; ++g)
+        for (int g = first; g < first + KV; ++g) {
+            if (g >= KV) {
+                scale_piece(g - KV, 0);
+                scale_piece(g - KV, 1);
+            }
 #pragma unroll
             for (int piece = 0; piece < NSP; ++piece) split_piece(g, piece, slot, next);
+        }
     };
     const auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };     // orders LDS traffic only
 
@@ -691,7 +713,7 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const f32x4 x = k == 0 ? x0 : x1;
-                float y[4] = {x[0], x[1], x[2], x[3]};
+                float y[4] = {x[0] * Q_UP, x[1] * Q_UP, x[2] * Q_UP, x[3] * Q_UP};
                 SplitQuad sq;
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
@@ -718,7 +740,8 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
     for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[db][v] = o_low[db][v] = 0.f;
-    float m_ref = 0.f;             // reference the exponentials are taken against (raw score units)
+    const float c = a.c / Q_UP, slack = a.slack * Q_UP;
+    float m_ref = 0.f;             // reference the exponentials are taken against (raw score units, times Q_UP)
     float limit = -INFINITY;       // a score further above the reference raises it; -inf: there is none yet
     float l_run = 0.f;             // this lane's share of the running sum
 
@@ -788,13 +811,13 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
                     const bool none = limit == -INFINITY;
                     float m = fmaxf(mx, __shfl_xor(mx, 32, 64));
                     if (!none) m = fmaxf(m, m_ref);
-                    alpha = none ? 1.f : exp2f((m_ref - m) * a.c);
+                    alpha = none ? 1.f : exp2f((m_ref - m) * c);
                     m_ref = m == -INFINITY ? 0.f : m;
-                    limit = m == -INFINITY ? m : a.slack;
+                    limit = m == -INFINITY ? m : slack;
                     l_run *= alpha;
                 }
             } else {
-                float x = __builtin_amdgcn_exp2f((s[piece - 9] - m_ref) * a.c);
+                float x = __builtin_amdgcn_exp2f((s[piece - 9] - m_ref) * c);
                 FDD_PIN(x);
                 s[piece - 9] = x;
                 if constexpr (piece % 2 == 0) l_run += s[piece - 10] + x;
@@ -841,7 +864,8 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
             if constexpr (MORE) next3 = tile_at(t_lo + i + 3);
             const auto beside_scores = [&](auto jc) {
                 // (splitting in the odd slots, softmax in the even ones: what a slot carries must not outlast its matrix instruction)
-                constexpr int j = decltype(jc)::value, h = j / 2, NQ = 3 * KS, NV = NSP * KV, NX = 20;
+                // (and the factors of V: of a group's two quads right before its first and third piece)
+                constexpr int j = decltype(jc)::value, h = j / 2, NQ = 3 * KS, NV = NSP * KV, NX = 20 + 2 * KV, XG = NX / KV;
                 if constexpr (j % 2 == 1) {
                     if constexpr (MORE) {
 #pragma unroll
@@ -849,7 +873,10 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
                     }
                 } else {
 #pragma unroll
-                    for (int w = h * NX / NQ; w < (h + 1) * NX / NQ; ++w) part_piece(w);
+                    for (int w = h * NX / NQ; w < (h + 1) * NX / NQ; ++w) {
+                        if (w % XG >= 2) part_piece(w - 2 * (w / XG + 1));
+                        else if constexpr (MORE) scale_piece(w / XG, w % XG);
+                    }
                 }
             };
             if constexpr (MORE) {
@@ -922,18 +949,22 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
     // on other XCDs, and lines left dirty in the L2s go out only when the launch has ended.
     const __amdgpu_buffer_rsrc_t part_rsrc = __builtin_amdgcn_make_buffer_rsrc(a.ws_o + pseg * D, 0, WRT * D * 4, 0x00020000);
     const uint32_t part0 = (uint32_t)(wave * 32 * D * 4);
+    // A row that sees a key (prefix keys, or those of its own rollout up to where the causal mask ends) and has no reference: all
+    // of its scores were -2^84 and less.  (Fewer such scores weigh nothing: they are 2^60 and more below the others.)
+    const int own = TP + (my_rollout - n_lo) * a.per, own_end = own + (a.causal ? a.ext_per + my_b / WKT + 1 : a.per);
+    if ((t_lo < t_hi && t_lo < TP || max(t_lo, own) < min(t_hi, own_end)) && limit == -INFINITY) x0 = NAN;
     if (__builtin_expect(!__any(x0 != 0.f), 1)) {
         if (!row_ok) return;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int v4 = 0; v4 < 4; ++v4) {
-                const f32x4 x = f32x4{o[db][4 * v4], o[db][4 * v4 + 1], o[db][4 * v4 + 2], o[db][4 * v4 + 3]};
+                const f32x4 x = f32x4{o[db][4 * v4], o[db][4 * v4 + 1], o[db][4 * v4 + 2], o[db][4 * v4 + 3]} / V_UP;
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), part_rsrc, part0 + (db * 4 + v4) * 1024 + lane * 16, 0, 16);
             }
         if (half == 0) {
             float* const ml = a.ws_ml + (pseg + wave * 32 + l32) * 2;
-            ml[0] = limit == -INFINITY ? -INFINITY : m_ref;
+            ml[0] = limit == -INFINITY ? -INFINITY : m_ref / Q_UP;
             ml[1] = l_tot;
         }
         return;

@@ -42,3 +42,22 @@ def test_long_calls_of_one_row_tile_are_cut():
             p.N, p.B, p.L, p.Hq, p.Hkv, p.D, p.dtype = 1, 8, L, Hq, Hkv, D, b.FDD_F32
             need = lib.fdd_block_attn_workspace(C.byref(p))
             assert need > 0, (L, Hq, Hkv, D)
+
+
+def test_unusual_scales_take_the_32_row_tiles():
+    # (which need less scratch; 0 is the usual scale)
+    import ctypes as C
+
+    import paper_2605_23163_amd.binding as b
+    lib = b.load_library()
+    p = b.AttnParams()
+    p.N, p.B, p.L, p.Hq, p.Hkv, p.D, p.dtype = 8, 32, 4096, 28, 4, 128, b.FDD_F32
+
+    def need(scale):
+        p.scale = scale
+        return lib.fdd_block_attn_workspace(C.byref(p))
+    assert need(0.0) > 0
+    for scale in (-1.0, 2.0 ** -30, 0.1, 1.0, 2.0 ** 10):
+        assert need(scale) == need(0.0), scale
+    for scale in (2.0 ** -31, 1e-40, 1025.0, 3e38, float("inf")):
+        assert need(scale) == 0, scale

@@ -1,7 +1,7 @@
 """GPU parity of fp32 attention on the bf16 matrix pipe (128-row tiles, every fp32 product as six bf16 products) at the edges
 of its tiles, and what values that are not finite do there.
 
-Tolerance: products are kept to 2^-25 and sums are rounded to fp32, so results agree with the oracle as fp32 arithmetic does:
+Tolerance: products are kept to 2^-24 and sums are rounded to fp32, so results agree with the oracle as fp32 arithmetic does:
 a score of D products of size 1 is off by a few 2^-24 sqrt(D), scaled by 1/sqrt(D), a probability by as much, and the average
 of values up to 5 by 5 * 2^-24 times a few: 1e-5 is 30 times 2^-24 * 5."""
 import numpy as np
@@ -147,19 +147,56 @@ def test_an_infinite_value_stays_infinite(F, oracle):
     assert np.abs(got[fin] - ref[fin]).max() <= TOL
 
 
-def test_values_at_both_ends_of_the_range(F, oracle):
-    # the parts of 1e-34 and less are below the smallest normal number; 3.4e38 has no nearest bf16 number
+# factors of V, Q and K (and of the scale, where the scores would not be those of the default one)
+RANGES = [(1.0, 1.0, 1.0, 1.0), (1e-36, 1.0, 1.0, 1.0), (1e-37, 1.0, 1.0, 1.0), (1e-41, 1.0, 1.0, 1.0), (1e28, 1.0, 1.0, 1.0),
+          (1e34, 1.0, 1.0, 1.0), (1.0, 1e-37, 1e37, 1.0), (1.0, 1e37, 1e-37, 1.0), (1.0, 1e-40, 1e37, 1e3), (1.0, 1e37, 1e-40, 1e3),
+          (1.0, 2.0 ** -40, 1.0, 2.0 ** 40), (1.0, 1.0, 2.0 ** 40, 2.0 ** -40), (1.0, 1e22, 1e-34, 1e12)]
+
+
+@pytest.mark.parametrize("factors", RANGES)
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[1]])
+def test_small_and_large_values_keep_their_bits(F, oracle, shape, factors):
+    # Positive values, so nothing cancels: an average is off by 2^-24 for each of its weights' and its own few roundings, with
+    # scores up to 5 off by 5 * 2^-24 a few times over, 2e-6 in all; below 2^-126 also by 2^-149 for the partial results and the
+    # result.  The third part of 1e-36 would be below the smallest bf16 number, 3.4e38 has no nearest one.
+    print_case(test="f32_wide_range", shape=shape, factors=factors)
+    fv, fq, fk, fs = factors
+    d, E, D = make(shape), shape[5], shape[6]
+    with np.errstate(under="ignore"):
+        for k in d:
+            if k.endswith("_v"):
+                d[k] = ((np.abs(d[k]) * 0.3 + 0.5) * np.float64(fv)).astype(np.float32)
+            else:
+                d[k] = (d[k] * np.float64(fq if k == "q" else fk)).astype(np.float32)
+    scale = fs / np.sqrt(D)
+    got = to_f64(run(F, d, E, scale=scale))
+    ref = reference(oracle, d, E, scale=scale)
+    err = np.abs(got - ref)
+    print(f"relative error {(err / ref).max():.2e}, in norm {np.linalg.norm(err) / np.linalg.norm(ref):.2e}")
+    assert (err <= 2e-6 * ref + 2 * 2.0 ** -149).all()
+
+
+def test_a_value_without_a_nearest_bf16_number(F, oracle):
     shape = SHAPES[0]
-    print_case(test="f32_wide_range", shape=shape)
-    for scale in (1e34, 1e-34):
-        d = make(shape)
-        for k in ("prefix_v", "block_v"):
-            d[k] = (d[k] * np.float32(scale)).astype(np.float32)
-        got, ref = to_f64(run(F, d, 0)) / scale, reference(oracle, d, 0) / scale
-        print(f"scale {scale:.0e}: max-abs error {np.abs(got - ref).max():.2e}")
-        assert np.isfinite(got).all() and np.abs(got - ref).max() <= TOL
+    print_case(test="f32_wide_largest", shape=shape)
     d = make(shape)
     d["prefix_k"][700], d["prefix_v"][700, :, 3] = 0.0, np.float32(3.4e38)
     got, ref = to_f64(run(F, d, 0)), reference(oracle, d, 0)
     size = np.maximum(np.abs(ref), 1.0)
     assert np.isfinite(got).all() and (np.abs(got - ref) / size).max() <= TOL
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[5]])
+def test_scores_far_below_zero(F, oracle, shape, causal):
+    # every score a row sees is -2^86 and less, so that it overflows with the factor on the queries: the last prefix key is the
+    # largest by 2^74, 2^44 after the scale, and holds the row
+    print_case(test="f32_wide_far_below", shape=shape, causal=causal)
+    d, E, L = make(shape), shape[5], shape[2]
+    for k in ("q", "prefix_k", "block_k") + (("ext_k",) if E else ()):
+        d[k][...] = 0.0
+        d[k][..., 0] = 2.0 ** 44 if k == "q" else -2.0 ** 43
+    d["prefix_k"][..., 0] = (-2.0 ** 42 - 2.0 ** 30 * np.arange(L)[::-1])[:, None]
+    got = to_f64(run(F, d, E, scale=2.0 ** -30, causal_block=causal))
+    ref = reference(oracle, d, E, scale=2.0 ** -30, causal_block=causal)
+    assert np.array_equal(got, ref)
