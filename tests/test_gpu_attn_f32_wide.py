@@ -67,6 +67,26 @@ def test_tile_edges(F, oracle, shape, causal):
     assert np.abs(got - reference(oracle, d, E, causal_block=causal)).max() <= TOL
 
 
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[1], SHAPES[5]])
+def test_rows_behind_the_last_key_are_not_read(F, shape):
+    # The rows that follow a run of keys in memory are NaN.  Had a tile read one, its wavefront would have done its keys
+    # again with fp32 products, whose sums differ in their last bits.
+    print_case(test="f32_wide_behind", shape=shape)
+    d, E, L = make(shape), shape[5], shape[2]
+    clean = run(F, d, E)
+    t = {k: to_dev(v) for k, v in d.items()}
+    for k in ("prefix_k", "prefix_v", "block_k", "block_v"):
+        flat = t[k].reshape(-1, *t[k].shape[-2:])
+        t[k] = torch.cat([flat, torch.full_like(flat[:40], float("nan"))])[:flat.shape[0]].reshape(t[k].shape)
+    ext = {}
+    if E:
+        t["ext_k"][:, E:] = t["ext_v"][:, E:] = float("nan")
+        ext = dict(ext_k=t["ext_k"], ext_v=t["ext_v"], E=E)
+    got = F.fdd_block_attn(*(t[k] for k in ("q", "prefix_k", "prefix_v", "block_k", "block_v")), **ext)
+    torch.cuda.synchronize()
+    assert torch.equal(got, clean)
+
+
 def test_scores_that_grow_along_the_keys(F, oracle):
     # exponents of up to +-40 that rise with the key: the reference is raised again and again, in every piece
     shape = SHAPES[1]
