@@ -115,7 +115,7 @@ static F32Cut f32_cut(bool wide, long long row_tiles, long long tiles, int D, in
     return best;
 }
 
-bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
+bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
 {
     AttnPlan pl;
     pl.G = p.Hq / p.Hkv;
@@ -260,7 +260,7 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan)
             // (a larger scale multiplies what those products lose of keys below 2^-110; a smaller one gives weight to scores that
             // overflow with their factor on Q)
             const bool usual_scale = !(p.scale > 0.f) || (p.scale >= 0x1p-30f && p.scale <= 0x1p10f);
-            if (usual_scale && fits && wide_tiles >= 2 * wide.splits && wide.us < narrow.us + (narrow.splits > 1 ? 3.0 : 0.0)) {
+            if (f32_wide && usual_scale && fits && wide_tiles >= 2 * wide.splits && wide.us < narrow.us + (narrow.splits > 1 ? 3.0 : 0.0)) {
                 s = wide.splits;
                 tiles = wide_tiles;
             } else {
@@ -377,7 +377,19 @@ fdd_status fdd_block_attn(const fdd_attn_params* p)
     if (p->out == p->q) return fail(FDD_ERR_UNSUPPORTED, "fdd_block_attn: out must not alias q");
     AttnPlan plan;
     make_attn_plan(*p, &plan);
-    const size_t need = plan.ws_o_bytes + plan.ws_ml_bytes + plan.ws_vt_bytes;
+    size_t need = plan.ws_o_bytes + plan.ws_ml_bytes + plan.ws_vt_bytes;
+    const size_t given = p->workspace && (reinterpret_cast<uintptr_t>(p->workspace) & 255u) == 0 ? p->workspace_bytes : 0;
+    if (need > given && p->dtype == FDD_F32 && plan.mtile_rows == kF32WideRowTile) {
+        // 128-row tiles always leave partial results, the smaller ones fewer and often none: a call that brings what those need
+        // (less than the query says, which asks for the faster ones) runs on them
+        AttnPlan narrow;
+        make_attn_plan(*p, &narrow, false);
+        const size_t narrow_need = narrow.ws_o_bytes + narrow.ws_ml_bytes;
+        if (narrow_need <= given) {
+            plan = narrow;
+            need = narrow_need;
+        }
+    }
     if (need > 0) {
         if (!p->workspace) return fail(FDD_ERR_WORKSPACE, "fdd_block_attn: workspace is NULL, %zu bytes needed", need);
         if (reinterpret_cast<uintptr_t>(p->workspace) & 255u) return fail(FDD_ERR_WORKSPACE, "fdd_block_attn: workspace must be 256-byte aligned");

@@ -65,7 +65,8 @@ struct AttnPlan {
     bool packed;         // bf16 path: the kernel reads repacked V (from the workspace or from the caller)
 };
 
-bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan);
+// `f32_wide`: fp32 calls may take 128-row tiles
+bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide = true);
 
 // Records the message fdd_last_error() returns on this thread; returns `code`.
 fdd_status set_error(fdd_status code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));

@@ -220,3 +220,61 @@ def test_scores_far_below_zero(F, oracle, shape, causal):
     got = to_f64(run(F, d, E, scale=2.0 ** -30, causal_block=causal))
     ref = reference(oracle, d, E, scale=2.0 ** -30, causal_block=causal)
     assert np.array_equal(got, ref)
+
+
+def test_calls_with_less_scratch_run_on_smaller_tiles(F, oracle):
+    # 32-row tiles that are not cut need no scratch: such a call may bring none, too little or a misaligned one
+    import ctypes as C
+
+    import paper_2605_23163_amd.binding as b
+    lib, ok, refused = F.load_library(), 0, 5
+
+    def call(shape, splits=0):
+        d = make(shape)
+        t = {k: to_dev(v) for k, v in d.items()}
+        args = [t[k] for k in ("q", "prefix_k", "prefix_v", "block_k", "block_v")]
+        out = torch.empty_like(t["q"])
+        p = b._attn_params(*args, None, out, None, splits)
+        p.stream = torch.cuda.current_stream().cuda_stream
+        return p, out, (d, t)
+
+    def run_with(p, ptr, size):
+        p.workspace, p.workspace_bytes = ptr, size
+        return lib.fdd_block_attn(C.byref(p))
+
+    shape = (7, 64, 190, 28, 4, 0, 64)
+    print_case(test="f32_wide_less_scratch", shape=shape)
+    p, out, keep = call(shape)
+    need, ref = lib.fdd_block_attn_workspace(C.byref(p)), reference(oracle, keep[0], 0)
+    ws = torch.empty(need + 256, dtype=torch.uint8, device="cuda")
+    assert need > 0 and ws.data_ptr() % 256 == 0
+    got = {}
+    for name, ptr, size in (("none", None, 0), ("none, a size", None, need), ("short", ws.data_ptr(), need - 256),
+                            ("misaligned", ws.data_ptr() + 16, need), ("enough", ws.data_ptr(), need)):
+        out.fill_(7.0)
+        assert run_with(p, ptr, size) == ok, name
+        torch.cuda.synchronize()
+        got[name] = out.clone()
+        assert np.abs(to_f64(out) - ref).max() <= TOL, name
+    assert torch.equal(got["none"], got["short"]) and torch.equal(got["none"], got["misaligned"])
+    assert torch.equal(got["none"], got["none, a size"]) and not torch.equal(got["none"], got["enough"])
+
+    # where the 32-row tiles are cut, what they need is still asked for
+    shape = (2, 40, 3000, 28, 4, 0, 128)
+    print_case(test="f32_wide_less_scratch", shape=shape)
+    p, out, keep = call(shape)
+    ref = reference(oracle, keep[0], 0)
+    ws = torch.empty(lib.fdd_block_attn_workspace(C.byref(p)), dtype=torch.uint8, device="cuda")
+    assert run_with(p, None, 0) == refused
+    for splits in range(2, 12):
+        forced, forced_out, keep2 = call(shape, splits)
+        size = lib.fdd_block_attn_workspace(C.byref(forced))
+        assert size < ws.numel()
+        assert run_with(p, ws.data_ptr(), size - 256) == refused
+        if run_with(p, ws.data_ptr(), size) == ok:
+            break
+    else:
+        assert False, "no cut of 32-row tiles was enough"
+    assert run_with(forced, ws.data_ptr(), size) == ok
+    torch.cuda.synchronize()
+    assert torch.equal(out, forced_out) and np.abs(to_f64(out) - ref).max() <= TOL
