@@ -229,16 +229,6 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
 
     extern __shared__ __align__(16) unsigned char lds[];
     typedef __attribute__((address_space(3))) void lds_void;
-    // Arguments that only masked tiles and the end of a segment need are read again where they are used, through a pointer the
-    // compiler cannot follow back: kept from the first read on, they and what is computed from them do not fit the scalar
-    // registers, and each register that is put aside costs two instructions before the first tile.
-    typedef const __attribute__((address_space(4))) Args LateArgs;
-    auto late_args = [&]() {
-        LateArgs* z = (LateArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-        asm volatile("" : "+s"(z));
-        return z;
-    };
-
     const int tid = thread_id_x();
     const int wave = tid >> 6;
     const int lane = tid & 63;
@@ -475,9 +465,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
             seg = piece;
         } else {
             // owner of a unit: the first `rem` workgroups hold base + 1 units each, the others base
-            LateArgs* const z = late_args();
-            const FastDiv by1 = {z->dBase1.mul, z->dBase1.shift}, by = {z->dBase.mul, z->dBase.shift};
             const int cut = a.rem * (a.base + 1);
+            const FastDiv by1 = a.dBase1, by = a.dBase;     // (copies, here and below: 4 to 8 scalar registers fewer are put aside)
             auto owner = [&](int u) { return u < cut ? fast_div(u, by1) : a.rem + fast_div(u - cut, by); };
             const int first = owner(M * a.TPU);
             n_seg = owner((M + 1) * a.TPU - 1) - first + 1;
@@ -489,7 +478,6 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
         const bool wave_has_rows = row0_wg + wave_u * 32 < a.R;
         int my_rollout = -1, my_b = 0, wave_n_lo = 0, wave_n_hi = 0, wg_n_lo = 0, tte = 0, ttpr = 1, n_tail = 0;
         if (t_end == a.TPU || F < n_prefix) {
-            LateArgs* const z = late_args();
             const FastDiv by_b = a.dB, by_bg = a.dBG;
             if (row_ok) {
                 my_rollout = fast_div(nb, by_b);
@@ -976,7 +964,6 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
             }
             if (j + 1 < n_tiles) wait_landed(j + 1); else wg_barrier();
         }
-        LateArgs* const z = late_args();
         const float m_run = limit == -INFINITY ? limit : m_ref;
 
         // ---- epilogue of the segment ------------------------------------------------
@@ -984,7 +971,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
         if (row_ok) {
             if (n_seg == 1) {
                 const float inv = 1.f / l_tot;
-                uint16_t* op = z->out + pb * z->o_bs + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * D;
+                uint16_t* op = a.out + pb * a.o_bs + ((size_t)nb * a.Hq + (size_t)kh * a.G + g) * D;
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -1005,9 +992,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                 // other XCDs, and lines left dirty in the L2s go out only when the launch has ended (28 layers of N=1,
                 // L=16384: 723 -> 696 us; N=8, L=4096: 28.9 -> 27.7; plain, non-temporal and both measured).
                 const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-                const size_t pseg = (size_t)M * z->max_seg + __builtin_amdgcn_readfirstlane(seg);
+                const size_t pseg = (size_t)M * a.max_seg + __builtin_amdgcn_readfirstlane(seg);
                 const __amdgpu_buffer_rsrc_t o_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                    static_cast<unsigned char*>(z->ws_o) + pseg * (size_t)(MROWS * D * 2), 0, MROWS * D * 2, RSRC_FLAGS);
+                    static_cast<unsigned char*>(a.ws_o) + pseg * (size_t)(MROWS * D * 2), 0, MROWS * D * 2, RSRC_FLAGS);
                 const uint32_t o_off = (uint32_t)(wave * (2 * DB * 64) + lane) * 16;
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
@@ -1020,7 +1007,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                     }
                 if (half == 0) {
                     const size_t prow = pseg * MROWS + (wave * 32 + l32);
-                    float* const ml = z->ws_ml + prow * 2;
+                    float* const ml = a.ws_ml + prow * 2;
                     ml[0] = m_run;
                     ml[1] = l_tot;
                 }
