@@ -61,3 +61,18 @@ def test_unusual_scales_take_the_32_row_tiles():
         assert need(scale) == need(0.0), scale
     for scale in (2.0 ** -31, 1e-40, 1025.0, 3e38, float("inf")):
         assert need(scale) == 0, scale
+
+
+def test_tiles_of_16_rows_are_taken_up_to_128_workgroups_of_32():
+    # (the partial results say which: 5 rows beyond whole tiles of 32 are padded to 16 or to 32)
+    import ctypes as C
+
+    import paper_2605_23163_amd.binding as b
+    lib = b.load_library()
+    up = lambda n: (n + 255) // 256 * 256
+    for D in (64, 128):
+        for tiles, splits in ((1, 2), (1, 64), (2, 64), (32, 4), (33, 4), (43, 3), (42, 3), (64, 2), (65, 2), (200, 2)):
+            p = b.AttnParams()
+            p.N, p.B, p.L, p.Hq, p.Hkv, p.D, p.dtype, p.splits = 1, 32 * (tiles - 1) + 5, 20000, 1, 1, D, b.FDD_F32, splits
+            rows = tiles * 32 - (16 if tiles * splits <= 128 else 0)
+            assert lib.fdd_block_attn_workspace(C.byref(p)) == up(rows * splits * D * 4) + up(rows * splits * 8), (tiles, splits, D)

@@ -14,9 +14,10 @@ pytestmark = pytest.mark.gpu
 TOL = 1e-5
 
 # (N, B, L, Hq, Hkv, E, D): one row, a full tile, one row more; tiles of several rollouts; rollouts that cross tiles; keys of a
-# single tile and of none; key ranges shared by workgroups; 128 workgroups of 32 rows (the most) and 132
+# single tile and of none; key ranges shared by workgroups; 448 workgroups of 32 rows, 96, 132 (32-row tiles, beyond 128) and 128
 SHAPES = [(1, 1, 0, 1, 1, 0, 64), (1, 4, 15, 4, 1, 0, 64), (1, 17, 33, 4, 4, 0, 128), (7, 3, 100, 2, 1, 5, 64), (3, 11, 64, 6, 2, 17, 128),
-          (1, 8, 5000, 4, 1, 0, 64), (5, 5, 900, 14, 2, 9, 128), (16, 32, 31, 28, 4, 0, 64), (2, 33, 48, 32, 32, 0, 128), (33, 32, 20, 4, 1, 0, 64)]
+          (1, 8, 5000, 4, 1, 0, 64), (5, 5, 900, 14, 2, 9, 128), (16, 32, 31, 28, 4, 0, 64), (2, 33, 48, 32, 32, 0, 128), (33, 32, 20, 4, 1, 0, 64),
+          (32, 32, 20, 4, 1, 0, 64)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)

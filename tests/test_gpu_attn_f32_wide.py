@@ -10,6 +10,7 @@ import torch
 
 import fdd_workloads as W
 from tests.gpu_util import print_case, rand_attn, to_dev, to_f64
+from tests.test_gpu_attn_f32_values import levels
 
 pytestmark = pytest.mark.gpu
 
@@ -99,6 +100,50 @@ def test_scores_that_grow_along_the_keys(F, oracle):
     assert np.abs(got - ref).max() <= 8 * TOL
 
 
+@pytest.mark.parametrize("N,D", [(16, 64), (6, 128)])        # 3 and 7 or 8 pieces
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("kind", ["plateau", "ramp", "fall", "peaks"])
+def test_exact_scores_of_large_magnitude(F, oracle, kind, causal, N, D):
+    # scores, values and bounds of the test of this name for the other tiles, on which see there; pieces chosen by the library
+    B, L, Hq, Hkv, E, scale = 20, 600, 28, 4, 21, 0.25
+    print_case(test="f32_wide_exact_scores", kind=kind, causal=causal, D=D)
+    rng = np.random.default_rng(D + len(kind))
+    raw_per_bit = 1.0 / (scale * np.log2(np.e))
+    if kind in ("ramp", "fall"):
+        L = 16 * 28 + 5
+
+    def kv(*shape):
+        n = int(np.prod(shape))
+        s = levels(rng, n, kind, raw_per_bit)
+        k = np.zeros((n, Hkv, D), dtype=np.float32)
+        k[:, :, 0] = s[:, None]
+        v = rng.standard_normal((n, Hkv, D))
+        if kind in ("ramp", "fall"):
+            v *= np.exp2(-np.round(s / raw_per_bit))[:, None, None]
+        return k.reshape(*shape, Hkv, D), v.astype(np.float32).reshape(*shape, Hkv, D)
+
+    d = {}
+    d["prefix_k"], d["prefix_v"] = kv(L)
+    d["block_k"], d["block_v"] = kv(N, B)
+    d["ext_k"], d["ext_v"] = kv(N, E)
+    d["q"] = np.zeros((N, B, Hq, D), dtype=np.float32)
+    d["q"][..., 0] = 1.0
+    if kind not in ("ramp", "fall"):
+        d["q"][:, 1::2, :, 0] = 0.5
+    got = to_f64(run(F, d, E, scale=scale, causal_block=causal))
+    ref = reference(oracle, d, E, scale=scale, causal_block=causal)
+    size = reference(oracle, {k: np.abs(v) if k.endswith("_v") else v for k, v in d.items()}, E, scale=scale, causal_block=causal)
+    rel = (np.abs(got - ref) / size).max()
+    print(f"error over sum of absolute terms: {rel:.2e}")
+    assert np.isfinite(got).all() and rel <= (1e-6 if kind in ("plateau", "peaks") else 1e-5), rel
+
+
+def wide_size(rows, Hkv, D, pieces):
+    """Scratch of 128-row tiles in so many pieces."""
+    up = lambda n: (n + 255) // 256 * 256
+    return up(Hkv * -(-rows // 128) * 128 * pieces * D * 4) + up(Hkv * -(-rows // 128) * 128 * pieces * 8)
+
+
 def test_listed_positions_and_a_batch(F, oracle):
     shape = (5, 39, 2527, 28, 4, 0, 64)
     print_case(test="f32_wide_list_batch", shape=shape)
@@ -109,6 +154,9 @@ def test_listed_positions_and_a_batch(F, oracle):
     out = torch.full((N, B, Hq, D), 7.0, device="cuda")
     t = {k: to_dev(v) for k, v in d.items()}
     args = [t[k] for k in ("q", "prefix_k", "prefix_v", "block_k", "block_v")]
+    # (scratch of 128-row tiles and of no others: the rows of a list and of a batch are not multiples of 32)
+    need = F.fdd_block_attn_workspace(*args, n_q_positions=149)
+    assert need in [wide_size(149 * 7, Hkv, D, s) for s in range(2, 65)] and need % (Hkv * 33 * 32 * (4 * D + 8)) != 0
     F.fdd_block_attn(*args, out=out, q_positions=torch.from_numpy(pos.astype(np.int32)).cuda())
     torch.cuda.synchronize()
     got = to_f64(out).reshape(N * B, Hq, D)
@@ -117,6 +165,8 @@ def test_listed_positions_and_a_batch(F, oracle):
     assert np.all(got[rest] == 7.0) and np.abs(got[pos] - full[pos]).max() <= TOL
     e = make(shape, seed=1)
     both = [torch.stack([to_dev(d[k]), to_dev(e[k])]) for k in ("q", "prefix_k", "prefix_v", "block_k", "block_v")]
+    need = F.fdd_block_attn_batched_workspace(*both)
+    assert need in [wide_size(N * B * 7, 2 * Hkv, D, s) for s in range(2, 65)] and need % (2 * Hkv * 43 * 32 * (4 * D + 8)) != 0
     out = F.fdd_block_attn_batched(*both)
     torch.cuda.synchronize()
     for i, x in enumerate((d, e)):
