@@ -376,7 +376,7 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
     const int n_lo = __builtin_amdgcn_readfirstlane(fast_div(position_of(a.qpos, fast_div(mt * RT, a.dG), NB), a.dB));
     const int n_hi = __builtin_amdgcn_readfirstlane(fast_div(position_of(a.qpos, fast_div(row_hi, a.dG), NB), a.dB));
     const int TP = (a.L + KT - 1) / KT;
-    const int n_tiles = TP + (n_hi - n_lo + 1) * a.per;
+    const int n_tiles = key_tiles(TP, a.per, n_lo, n_hi);
     const int part = split * WAVES + wave, parts = a.S * WAVES;
     const int t_lo = __builtin_amdgcn_readfirstlane(key_cut(n_tiles, part, parts, a.dParts));
     const int t_hi = __builtin_amdgcn_readfirstlane(key_cut(n_tiles, part + 1, parts, a.dParts));
@@ -588,7 +588,7 @@ __global__ __launch_bounds__(256, 1) void attn_f32_wide_kernel(Args a)
     const int n_lo = __builtin_amdgcn_readfirstlane(fast_div(position_of(a.qpos, fast_div(mt * WRT, a.dG), NB), a.dB));
     const int n_hi = __builtin_amdgcn_readfirstlane(fast_div(position_of(a.qpos, fast_div(row_hi, a.dG), NB), a.dB));
     const int TP = (a.L + WKT - 1) / WKT;
-    const int n_tiles = TP + (n_hi - n_lo + 1) * a.per;
+    const int n_tiles = key_tiles(TP, a.per, n_lo, n_hi);
     const int t_lo = __builtin_amdgcn_readfirstlane(key_cut(n_tiles, split, a.S, a.dParts));
     const int t_hi = __builtin_amdgcn_readfirstlane(key_cut(n_tiles, split + 1, a.S, a.dParts));
     const auto tile_at = [&](int t) { return key_tile<WKT, D>(a, pb, kh, n_lo, TP, min(t, t_hi - 1)); };

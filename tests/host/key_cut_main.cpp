@@ -1,5 +1,5 @@
-// Checks the cut of an fp32 row tile's key tiles among its wavefronts (key_cut in fdd_internal.h, which the kernel
-// calls) against 64-bit arithmetic, up to the most tiles a call can have.  Host code only; built and run by
+// Checks the cut of an fp32 row tile's key tiles among its wavefronts (key_tiles and key_cut in fdd_internal.h, which the
+// kernels call) against 64-bit arithmetic, up to the most tiles a call can have, and for lists of positions in any order.  Host code only; built and run by
 // tests/test_f32_limits.py.
 #include <cstdio>
 
@@ -23,6 +23,22 @@ int main()
                 if (got != want && bad++ < 5) std::printf("tiles %d part %d of %d: %d, should be %lld\n", n, part, parts, got, want);
             }
         }
+    // lists in any order: the parts of a row tile's keys are its prefix tiles and private tiles of rollouts that exist
+    const int N = 50;
+    for (int prefix : {0, 1, 5, 40})
+        for (int per : {1, 3})
+            for (int n_lo : {0, 1, 20, N - 1})
+                for (int n_hi : {0, 1, 19, 20, N - 1})
+                    for (int parts : {2, 8, 9, 24}) {
+                        const int n = key_tiles(prefix, per, n_lo, n_hi);
+                        const FastDiv d = make_fastdiv((uint32_t)parts);
+                        for (int part = 0; part <= parts; ++part) {
+                            const int t = key_cut(n, part, parts, d);
+                            if ((t < 0 || t > prefix + (N - n_lo) * per) && bad++ < 5)
+                                std::printf("rollouts %d to %d, part %d of %d: tile %d\n", n_lo, n_hi, part, parts, t);
+                        }
+                        if (n_hi >= n_lo && n != prefix + (n_hi - n_lo + 1) * per && bad++ < 5) std::printf("%d tiles\n", n);
+                    }
     if (bad) return 1;
     std::puts("key cut: ok");
     return 0;

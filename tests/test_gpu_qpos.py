@@ -89,6 +89,26 @@ def test_degenerate_lists(F, oracle, dtype):
     assert torch.equal(out, full)
 
 
+@pytest.mark.parametrize("shape", [(9, 40, 33, 4, 2, 64), (9, 40, 2200, 14, 2, 128)])     # tiles of 16 or 32 rows, of 128
+def test_descending_lists_stay_within_the_arrays(F, shape):
+    # (undefined values, fp32: the number of a row tile's keys came out negative, and where to cut it far outside)
+    N, B, L, Hq, Hkv, D = shape
+    print_case(test="qpos_descending", shape=shape)
+    rng = np.random.default_rng(8)
+    d = rand_attn(rng, N, B, L, Hq, Hkv, D, W.F32)
+    t = {k: to_dev(v) for k, v in d.items()}
+    pos = np.arange(N * B)[::-3].astype(np.int32).copy()
+    rest = np.ones(N * B, dtype=bool)
+    rest[pos] = False
+    for splits in (0, 3):
+        out = torch.full_like(t["q"], 7.0)
+        F.fdd_block_attn(t["q"], t["prefix_k"], t["prefix_v"], t["block_k"], t["block_v"], out=out, splits=splits,
+                         q_positions=torch.from_numpy(pos).cuda())
+        torch.cuda.synchronize()
+        got = to_f64(out).reshape(N * B, Hq, D)
+        assert np.all(got[rest] == 7.0) and np.isfinite(got).all()
+
+
 @pytest.mark.parametrize("dtype", [W.BF16, W.F32])
 def test_list_with_extension_and_causal_block(F, oracle, dtype):
     N, B, L, Hq, Hkv, D, E, Ecap = 6, 24, 300, 14, 2, 128, 40, 48
