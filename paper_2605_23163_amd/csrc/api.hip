@@ -379,9 +379,10 @@ fdd_status fdd_block_attn(const fdd_attn_params* p)
     make_attn_plan(*p, &plan);
     size_t need = plan.ws_o_bytes + plan.ws_ml_bytes + plan.ws_vt_bytes;
     const size_t given = p->workspace && (reinterpret_cast<uintptr_t>(p->workspace) & 255u) == 0 ? p->workspace_bytes : 0;
-    if (need > given && p->dtype == FDD_F32 && plan.mtile_rows == kF32WideRowTile) {
+    if (need >= given + 256 && p->dtype == FDD_F32 && plan.mtile_rows == kF32WideRowTile) {
         // 128-row tiles always leave partial results, the smaller ones fewer and often none: a call that brings what those need
-        // (less than the query says, which asks for the faster ones) runs on them
+        // (less than the query says, which asks for the faster ones) runs on them.  (Sizes come in steps of 256 bytes: one that misses the
+        // query's by less is a slip of the caller's and refused, as it always was.)
         AttnPlan narrow;
         make_attn_plan(*p, &narrow, false);
         const size_t narrow_need = narrow.ws_o_bytes + narrow.ws_ml_bytes;
