@@ -71,15 +71,18 @@ typedef enum { FDD_F32 = 0, FDD_BF16 = 1 } fdd_dtype;
  *
  * dtype FDD_BF16: q/k/v/out are bfloat16, products on the matrix cores with
  * fp32 accumulation, softmax in fp32.  dtype FDD_F32: fp32 storage and
- * arithmetic.  D must be 64 or 128.  L may be 0.  `out` must not alias an
- * input.  splits: number of pieces the prefix is cut into along L, with
- * FDD_F32 all keys of a query row (0 = chosen by the library); the result
- * does not depend on it beyond fp32 rounding.
+ * arithmetic (calls of many rows and keys take each product as six exact
+ * products of bf16 parts: to 2^-24 of its factors' powers of two, fp32 sums).
+ * D must be 64 or 128.  L may be 0.  `out` must not alias an input.  splits:
+ * number of pieces the prefix is cut into along L, with FDD_F32 all keys of a
+ * query row (0 = chosen by the library); the result does not depend on it
+ * beyond fp32 rounding.
  *
  * Values: q, k and v finite, scores within fp32's range.  For others nothing
  * is read or written out of bounds.  FDD_F32 passes a NaN or an infinity on
  * as arithmetic gives it, to the rows that see it (with
- * FDD_ATTN_CAUSAL_BLOCK also to earlier rows of its block).  FDD_BF16: the
+ * FDD_ATTN_CAUSAL_BLOCK also to earlier rows of its block), and such a
+ * call may take up to three times as long.  FDD_BF16: the
  * rows that see one, and up to 31 rows stacked next to them, which may
  * belong to another rollout, are undefined.
  */

@@ -243,10 +243,11 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
         };
         // Products on the bf16 pipe (128-row tiles) where they are expected to be faster and the keys are cut at least once more:
         // a row's sum is rounded twice per 32 keys of a workgroup there, four times per 4 keys of a wavefront here, and with that
-        // many pieces the error against 64 bits was smaller in every one of 130 drawn calls (0.3 to 0.8 of it).  us per call, 32-row
-        // tiles / 128-row tiles (pieces): D = 128, Hq = 28, Hkv = 4, B = 32: N=1, L=2048 23.8 / 20.6 (22); N=1, L=16384 74.0 / 53.3 (31);
-        // N=2, L=1024 25.4 / 20.6 (12); N=4, L=4096 77.6 / 50.0 (9); N=8, L=4096 135.7 / 84.5 (4); N=16, L=4096 268 / 152 (2); D = 64: N=8,
-        // L=4096 74.7 / 52.5 (4); N=5, B=40, L=5003, Hq=14, Hkv=2, E=37 50.5 / 31.2 (11).
+        // many pieces the error against 64 bits in norm was 0.53 to 0.86 of that of 32-row tiles in the 33 of 60 drawn calls that
+        // take them (N to 33, L = 200 to 16384, six head counts, both D, deviations 0.09 to 2).  us per call, replayed, 32-row tiles / 128-row
+        // tiles (pieces): D = 128, Hq = 28, Hkv = 4, B = 32: N=1, L=2048 22.1 / 19.3 (22); N=1, L=16384 71.0 / 51.5 (31); N=2, L=1024
+        // 24.2 / 20.6 (12); N=4, L=4096 76.5 / 49.2 (9); N=8, L=4096 135.1 / 85.5 (4); N=16, L=4096 268 / 157 (2); D = 64: N=8, L=4096
+        // 73.7 / 51.5 (4); N=5, B=40, L=5003, Hq=14, Hkv=2 47.8 / 29.9 (11).
         long long tiles = cut_f32(kF32RowTile, 16);
         int s = p.splits;
         if (s == 0) {

@@ -31,13 +31,13 @@
 //     wavefront has half of the matrix work per tile and half of the merge: N = 1, B = 8,
 //     L = 256, Hq = 4, Hkv = 1, D = 64 10.4 -> 7.1 us, N = 2, B = 32, L = 128, Hq = 28, Hkv = 4,
 //     D = 128 16.3 -> 11.0 (replayed).
-//   * Measured at N = 8, B = 32, L = 4096, Hq = 28, Hkv = 4, D = 128 (15.1 GFLOP): 135 us
-//     in a loop of nothing else, 112 TFLOP/s of the 154 a large fp32 matrix product
-//     reaches here, and 149 us among the other kernels of a denoise step; 224 of 256
-//     CUs are used, the matrix pipe of a used CU 84 % of its cycles (loop of nothing
-//     else).  Scalar fused multiply-adds from LDS tiles: 687 us in a denoise step.  Not
-//     faster, when the kernel took 152 us there: K through a private LDS ring, the next
-//     tile's scores under this tile's exponentials, priorities that keep the two
+//   * Measured at N = 8, B = 32, L = 4096, Hq = 28, Hkv = 4, D = 128 (15.1 GFLOP), a call that
+//     comes here with a forced cut, an unusual scale or too little scratch only and takes the
+//     128-row tiles otherwise: 135 us in a loop of nothing else, 112 TFLOP/s of the 154 a large
+//     fp32 matrix product reaches here; 224 of 256 CUs are used, the matrix pipe of a used CU 84 %
+//     of its cycles.  Scalar fused multiply-adds from LDS tiles: 687 us in a denoise step, where
+//     this kernel took 149.  Not faster, when it took 152 there: K through a private LDS ring,
+//     the next tile's scores under this tile's exponentials, priorities that keep the two
 //     wavefronts of a SIMD level (157 us each).
 #include "fdd_internal.h"
 
@@ -471,7 +471,8 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
 // rest and l what is left (8 bits of mantissa each).  The product of two floats is then six products of bf16 numbers, exact in the
 // matrix unit's fp32 sums; what is dropped (m l', l m', l l') is at most 2^-24 (1 + 2^-10) of 2^(e + e'), the powers of two below
 // the factors, where |m| reaches 2^-8 and |l| 2^-17 of theirs.  Six products at sixteen times the rate: 96 cycles of matrix
-// pipe per 32 keys, 32 rows and 16 channels instead of 256.
+// pipe per 32 keys, 32 rows and 16 channels instead of 256.  (The method is that of Henry, Tang and Heinecke, "Leveraging the
+// bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", 2019.)
 //   Of a smaller float the last parts would lie below bf16's smallest number, 2^-133, so V is split times 2^32 and Q times 2^44:
 // every part of any float is then a normal bf16 number, and results carry the inverse factor.  K is split as it is: |q| stays below
 // 2^84, or its parts are infinite, and so what a product with k loses below 2^-42, even if the matrix unit took subnormal parts for
@@ -488,11 +489,12 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(Args a)
 //     tile i+2, whose floats were requested a step before.  Slots of one matrix instruction and a slice of vector work, fenced, as
 //     in the bf16 kernel.  A wavefront alone on its SIMD takes 5 cycles per vector instruction and 8 where one waits for the one
 //     before it, so a slot carries four or five that do not: pieces of ten in every other slot cost 12 % of the time.
-//   * What bounds it: N = 8, B = 32, L = 4096, Hq = 28, Hkv = 4, D = 128 takes 84.5 us a call (135.7 with fp32 products): 70 us of
+//   * What bounds it: N = 8, B = 32, L = 4096, Hq = 28, Hkv = 4, D = 128 takes 85.5 us a call (135.1 with fp32 products, replayed): 70 us of
 //     steps, 1 290 TFLOP/s of bf16 products beside the 1 420 that a loop of nothing but this mix reaches (the chip lowers its
 //     clock: 2.1 us a step with 224 workgroups, 1.8 with 56), 6 us until queries and first tiles are there, the merge.
 //     Measured on the way, us for that call: queries in LDS and one slot each for K and V 97.5; in registers, where the compiler
-//     copied them for every use 93.6; kept in the accumulation registers 89; and no address worked out per tile 86.5.  One sum for
+//     copied them for every use 93.6; kept in the accumulation registers 89; and no address worked out per tile 86.5.  The factors of V and Q cost 1.5 us, as much as the
+//     row of a V load in the lane's offset instead of the scalar one gave (85.9 -> 84.7, one box).  One sum for
 //     all products is as fast, but rounded twelve times per tile (error against 64 bits 2.5 times as large).
 //   * Values that are not finite, or become so here (|q| and scores from 2^84 on, |v| from 2^96 on): a part of an
 //     infinity is a NaN, and one in a tile reaches every row of a wavefront.  A wavefront whose sums are not finite at the end does
