@@ -214,6 +214,15 @@ __device__ __forceinline__ void read_ahead(const Read& read, const Use& use)
     }
 }
 
+// Transposing LDS read.  `restrict` is for the compiler's wait insertion: before an LDS read that carries no alias
+// information it waits for every tile that is still on its way into LDS (vmcnt(0)), which ordinary reads are spared by their
+// type.  The plain-V loop stood still for the tiles requested in the same step, and masked tiles for the next ones.
+typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
+__device__ __forceinline__ i16x4 read_tr(const lds_i16x4* __restrict__ p)
+{
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(const_cast<lds_i16x4*>(p));
+}
+
 template <int D, int WAVES, bool PACKED>
 __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kernel(Args a)
 {
@@ -316,10 +325,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
     };
     // `vaddr` = slot base + vtr_off0
     auto v_frag_tr_at = [&](uint32_t vaddr, int t4, int db) -> bf16x8 {
-        typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
         const unsigned char* p0 = lds + (vaddr ^ (uint32_t)(db << 6)) + t4 * 16 * (D * 2);
-        const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p0));
-        const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p0 + 8 * (D * 2)));
+        const i16x4 lo = read_tr((const lds_i16x4*)(p0));
+        const i16x4 hi = read_tr((const lds_i16x4*)(p0 + 8 * (D * 2)));
         typedef short i16x8 __attribute__((ext_vector_type(8)));
         const i16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         return __builtin_bit_cast(bf16x8, both);
