@@ -118,6 +118,7 @@ static F32Cut f32_cut(bool wide, long long row_tiles, long long tiles, int D, in
 bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
 {
     AttnPlan pl;
+    pl.slots = 0;
     pl.G = p.Hq / p.Hkv;
     pl.R = (p.n_q_positions > 0 ? p.n_q_positions : p.N * p.B) * pl.G;
     pl.key_tile = p.dtype == FDD_BF16 ? 64 : 16;
@@ -130,7 +131,6 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
         NM = (long long)p.Hkv * batch * pl.MT;
     };
     bool partials;
-    long long private_tiles = 0;     // bf16 path: of an M-tile
     auto cut_bf16 = [&](int rows) {
         set_rows(rows);
         // The private tiles of an M-tile (extension and block of every rollout its rows belong to) are done
@@ -141,7 +141,7 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
         const long long BG = p.n_q_positions > 0 ? std::max(1ll, (long long)p.n_q_positions * pl.G / p.N) : (long long)p.B * pl.G;
         const long long span_lo = (pl.mtile_rows + BG - 1) / BG;                 // rollouts an M-tile spans at least
         const long long span = span_lo + ((pl.mtile_rows % BG) != 0 && BG < (long long)pl.R ? 1 : 0);
-        private_tiles = (span < p.N ? span : p.N) *
+        const long long private_tiles = (span < p.N ? span : p.N) *
                                         ((p.E + pl.key_tile - 1) / pl.key_tile + (p.B + pl.key_tile - 1) / pl.key_tile);
         long long wt = (private_tiles * 9 + 4) / 5;
         if (wt < 1) wt = 1;
@@ -204,34 +204,31 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
     };
     if (p.dtype == FDD_BF16) {
         cut_bf16(256);
-        // M-tiles of 128 rows (workgroups of 4 wavefronts, one per SIMD) while the call is short: a wavefront alone on its SIMD
-        // takes 0.86 us a tile where two take 1.33 (D = 128, few workgroups, tiles in the cache), a workgroup starts on three half
-        // tiles instead of seven, and the segments are half as large.  Two wavefronts per SIMD do more per second, and four ring
-        // slots hide more of the memory's latency than two, so with many units per compute unit those are faster: from 9 on, or 6
-        // where V is read as it lies, whose tiles of short rows take longer to come (but not if only the smaller M-tiles need no
-        // cutting, or with many private tiles, of which they have half), and always where only the larger tiles cut into equal
-        // pieces that fill the chip.  us per call, replayed, prefixes from memory (900 MB of them in rotation), 256 / 128 rows,
-        // Hq = 28, Hkv = 4, B = 32; in brackets the units per compute unit of the 256-row plan:
-        //   D = 128, V laid out: N=1, L=2048 [0.5] 15.0/11.3; N=8, L=2048 [3.9] 25.2/19.6; N=1, L=16384 [4.0] 22.6/20.1; N=8, L=4096 [7.7]
-        //   29.9/27.2; N=4, L=8192 [8.4] 29.0/27.0; N=2, L=18000 [8.9] 29.6/30.0; N=12, L=3000 [9.1] 31.4/28.9; N=4, L=9500 [9.7] 29.9/29.9;
-        //   N=8, L=6000 [10.9] 35.7/36.6; N=16, L=4096 [15] 41.4/44.2;
-        //   D = 128, plain V: N=8, L=2048 [3.9] 25.2/21.6; N=1, L=16384 [4.0] 23.2/22.4; N=8, L=2800 [5.4] 27.4/25.7; N=4, L=5500 [5.7]
-        //   25.3/24.4; N=2, L=10000 [5.0] 23.9/24.7, L=12000 [6.0] 25.2/26.7; N=16, L=1400 [6.1] 27.2/27.2; N=4, L=6500 [6.8] 26.6/27.3; N=8,
-        //   L=4096 [7.7] 30.3/32.5, with E=64 31.0/33.7, E=128 31.2/34.8, E=256 41.0/36.8; N=16, L=2048 [8.3] 30.6/33.3; not cut: N=32,
-        //   L=512 [6.1] 26.7/21.7, L=768 [7.9] 29.6/26.4; no equal pieces of 128 rows: N=24, L=1024 [7.2] 27.6/29.0;
-        //   D = 64 (half the matrix work per exponential), V laid out: N=8, L=2048 [3.9] 16.9/14.9; N=4, L=4096 [4.3] 16.1/14.7; N=8, L=2400
-        //   [4.6] 17.3/18.3; N=1, L=20000 [4.9] 18.4/16.8; N=4, L=5000 [5.3] 17.1/17.1; N=8, L=4096 [7.7] 19.7/19.7;
-        //   D = 64, plain V: N=8, L=2048 [3.9] 16.9/16.4; N=2, L=8192 [4.1] 15.4/16.7; N=8, L=2400 [4.6] 17.3/18.9; N=4, L=4700 [4.9]
-        //   16.8/17.4; not cut: N=32, L=300 [4.4] 16.9/13.2.
-        // (plain V reads 2 to 5 % slower than V laid out with 256 rows, up to 18 % slower with 128)
+        // M-tiles of 128 rows (workgroups of 4 wavefronts, one per SIMD) while the call is short: alone in a compute unit such a
+        // workgroup takes 0.68 us a tile where one of 8 takes 1.09 (D = 128), starts on fewer tiles, and its segments are half as
+        // large; long calls fetch K and V twice as often.  Up to 9 units per compute unit of the 256-row plan, D = 64 5 (either is within a
+        // few per cent of the other up to 11 and 8); not where only the larger tiles cut into equal pieces that fill the chip.  us per call,
+        // prefixes from memory (30 calls in rotation), 256 / 128 rows, Hq = 28, Hkv = 4, B = 32, in brackets the units per compute unit:
+        //   D = 128, V laid out: N=8, L=2048 [3.9] 19.8/17.1; L=4096 [7.7] 25.6/23.6; N=4, L=8192 [8.4] 25.8/24.2; N=2, L=18000 [8.9]
+        //   27.3/26.2; N=12, L=3000 [9.1] 27.4/25.8; N=4, L=9500 [9.7] 27.6/26.3; N=8, L=6000 [10.9] 31.0/30.8; N=16, L=4096 [15]
+        //   37.2/38.0;
+        //   D = 128, plain V: N=1, L=2048 12.5/10.4; N=8, L=512 14.6/12.4; N=8, L=4096 25.7/23.8; N=12, L=3000 27.6/25.9; N=16, L=2048
+        //   [8.3] 26.2/24.8; no equal pieces of 128 rows: N=24, L=1024 [7.2] 24.8/26.7;
+        //   D = 64: N=1, L=2048 9.5/8.3; N=8, L=2048 [3.9] 13.8/12.5, plain 13.9/12.8; N=1, L=20000 [4.9] 15.3/14.4; N=8, L=4096 [7.7]
+        //   17.2/16.7, plain 17.3/17.5; N=8, L=6000 [10.9] 20.3/22.2; N=16, L=4096 [15], plain 24.9/27.5.
         const int uniform256 = pl.uniform;
-        const long long u256 = pl.U, line = (p.D == 128 ? 9 : 5) * (long long)kNumCU, plain_line = (p.D == 128 ? 6 : 4) * (long long)kNumCU;
-        if (u256 <= line) {
-            const bool few_private = 7 * private_tiles <= pl.TP;
+        if (pl.U <= (p.D == 128 ? 9 : 5) * (long long)kNumCU) {
             cut_bf16(128);
-            const bool plain = p.splits == 0 && !p.prefix_v_packed && u256 > plain_line && few_private && !(pl.uniform == 1 && uniform256 > 1);
-            if (plain || (pl.uniform == 0 && (uniform256 > 0 || NM > kNumCU))) cut_bf16(256);
+            if (pl.uniform == 0 && (uniform256 > 0 || NM > kNumCU)) cut_bf16(256);
         }
+        // Ring slots per operand: four hide more of the memory's latency, two start earlier, with fewer requests in flight, and do
+        // better where nearly every request goes to memory (one M-tile per KV head).  us per call, prefixes from memory, 4 / 2 slots, in
+        // brackets the units per workgroup: several M-tiles, D = 128, N=1, L=2048 [2] 10.4/10.1; N=3, L=1279, Hq=32, Hkv=8 [2]
+        // 12.9/12.5; N=1, L=6518 [3.2] 13.6/13.1; B=70, L=3008, Hq=32, Hkv=8 [4.4] 16.1/15.7; N=2, L=6239 [6.1] 16.3/16.1; B=40, L=14464,
+        // Hq=16 [7.1] 17.2/18.2; N=2, L=18304, Hq=16 [8.9] 20.6/21.9; N=3, B=8, L=24960 [12] 21.3/24.4; N=8, L=4096, V laid out [16]
+        // 23.6/28.7; D = 64, N=8, L=1024 [4] 10.2/10.1, L=2048 [8] 12.5/13.2, N=1, L=20000 [10] 14.4/16.1; one M-tile, D = 128, Hkv=8, N=2,
+        // B=8, L=14976, Hq=8 [7.3] 16.9/16.4, N=2, B=64, L=13888, E=64, Hq=8 [6.9] 22.6/21.0.
+        pl.slots = pl.mtile_rows == 128 && (pl.MT == 1 || pl.U < 6ll * pl.W) ? 2 : 4;
     } else {
         auto cut_f32 = [&](int rows, int key_tile) {
             set_rows(rows);

@@ -41,25 +41,24 @@
 //     slots per tile, one per MFMA.  Each slot also carries a slice of vector
 //     ALU work that does not depend on that MFMA: while the matrix pipe
 //     produces the scores of tile i+1 and then the P V products of tile i,
-//     the vector ALUs reduce the row maximum of tile i, take its exponentials
-//     and round them to bf16.  One wavefront can only issue a vector
-//     instruction every other issue slot, so two wavefronts per SIMD running
-//     this same mix are what fills both pipes.  V of tile i+3 and K of tile
+//     the vector ALUs take the exponentials of tile i, round them to bf16 and
+//     find the row maximum of tile i+1.  V of tile i+3 and K of tile
 //     i+4 are requested in step i (K is read one step before V,
 //     so its slot is free one step earlier) and waits are counted (the loads
 //     of a wavefront complete in issue order), so four half tiles stay in
 //     flight across a step boundary; LDS
-//     fragments are requested two MFMAs before their use.  The loop is
+//     fragments are requested three MFMAs before their use.  The loop is
 //     unrolled four times so that ring slots are immediate offsets.
 //   * The softmax reference value of a row is only raised when the running
 //     maximum outgrows it by more than 2^8; in between probabilities may
 //     exceed 1, which fp32 sums and bf16 relative precision do not mind, and
 //     the accumulator rescale becomes a rare wave-uniform branch.  The result
 //     is mathematically the same softmax.
-//   * A workgroup has 8 wavefronts (M-tiles of 256 rows, a ring of 4 slots per
-//     operand) or, where a call is short, 4 (128 rows, 2 slots, one wavefront
-//     per SIMD): the plan chooses (see make_attn_plan).  With 2 slots K of tile
-//     i+2 and V of tile i+1 are requested in step i and awaited at its end.
+//   * A workgroup has 8 wavefronts (M-tiles of 256 rows) or, where a call is
+//     short, 4 (128 rows, one wavefront per SIMD), and 4 ring slots per operand
+//     or, where it is very short, 2: the plan chooses (see make_attn_plan).
+//     With 2 slots K of tile i+2 and V of tile i+1 are requested in step i and
+//     awaited at its end.
 //   * Work is dealt out in units of one 64-key prefix tile of one M-tile.
 //     Either every M-tile is cut into S equal pieces (workgroups numbered so
 //     that an XCD owns all M-tiles of one (KV head, piece): they walk the same
@@ -140,10 +139,10 @@ struct Args {
     FastDiv dB, dBG, dTTPR, dBase, dBase1;
 };
 
-template <int D, int WAVES>
+template <int D, int WAVES, int SLOTS>
 struct Cfg {
     static constexpr int THREADS = WAVES * 64;
-    static constexpr int NB = WAVES == 8 ? 4 : 2;        // ring slots per operand in LDS (a power of two)
+    static constexpr int NB = SLOTS;                     // ring slots per operand in LDS (2 or 4)
     // 64 x D tiles, unpadded, moved global -> LDS in 1 KB pieces, one per wavefront instruction
     static constexpr int T_BYTES = KT * D * 2;
     static constexpr int NI = T_BYTES / 1024 / WAVES;    // pieces per wavefront and tile
@@ -152,7 +151,8 @@ struct Cfg {
     static constexpr int RPB = 1024 / (D * 2);           // rows per 1 KB piece
     static constexpr int RPL = 256 / (D * 2);            // rows per 256-byte bank line
     static constexpr int V_RING = NB * T_BYTES;          // LDS offset of the V ring (the K ring starts at 0)
-    static constexpr int LDS_BYTES = 2 * NB * T_BYTES;
+    static constexpr int DUMP = 2 * NB * T_BYTES;        // where requests that have no tile go
+    static constexpr int LDS_BYTES = DUMP + T_BYTES;
     static_assert(NI >= 1 && T_BYTES % (1024 * WAVES) == 0, "tile must divide over the wavefronts");
     static_assert((NB - 1) * IPT < 64, "outstanding loads must fit the counter");
 };
@@ -223,17 +223,16 @@ __device__ __forceinline__ i16x4 read_tr(const lds_i16x4* __restrict__ p)
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16(const_cast<lds_i16x4*>(p));
 }
 
-template <int D, int WAVES, bool PACKED>
+template <int D, int WAVES, int SLOTS, bool PACKED>
 __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kernel(Args a)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
-    using C = Cfg<D, WAVES>;
+    using C = Cfg<D, WAVES, SLOTS>;
     constexpr int NB = C::NB;
     constexpr int KS = D / 16;   // MFMA k-steps of Q K^T
     constexpr int DB = D / 32;   // 32-channel blocks of the output
     constexpr int MROWS = WAVES * 32;
     constexpr int RA = 4;        // fragments requested ahead outside the pipelined loop
-    constexpr bool SPREAD = WAVES == 8 && D == 128 && PACKED;   // order of a pipelined step, see there
     constexpr uint32_t RSRC_FLAGS = 0x00020000;
 
     extern __shared__ __align__(16) unsigned char lds[];
@@ -307,7 +306,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
     const uint32_t stride2 = (uint32_t)(a.Hkv * D * 2);       // bytes between consecutive keys
     // LDS offsets of this lane's fragments (set while the first tiles of a segment are on their way)
     uint32_t k_fragoff[KS];
-    uint32_t v_fragoff_ring, vtr_off0, vtr_off_ring;
+    uint32_t v_fragoff_ring, vtr_off[DB];
     // Tile movement: piece jn of this wavefront covers rows (wave NI + jn) RPB .. of
     // a tile; this lane moves the 16 bytes that land at LDS piece (lane % CH) of
     // its row.  K: the pieces of a row are XOR-swizzled by the row's bank line.
@@ -317,15 +316,24 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
 #pragma unroll
     for (int jn = 0; jn < C::NI; ++jn) {
         const int r = (wave * C::NI + jn) * C::RPB + lane / C::CH;
-        k_voff[jn] = (uint32_t)r * stride2 + (uint32_t)(((lane % C::CH) ^ ((r / C::RPL) & (C::CH - 1))) * 16);
+        // (less the instruction's offset, which moves the place in LDS and the address alike; a piece is 1 KB or more from the last)
+        k_voff[jn] = (uint32_t)r * stride2 + (uint32_t)(((lane % C::CH) ^ ((r / C::RPL) & (C::CH - 1))) * 16) - jn * 1024u;
     }
-    const uint32_t vp_voff = (uint32_t)(wave * C::NI * 1024 + lane * 16);
+    // V: one offset for all pieces of a wavefront (its column swizzle repeats every piece; the pieces' rows are in the scalar offset)
+    uint32_t v_voff;
+    if (PACKED) {
+        v_voff = (uint32_t)(wave * C::NI * 1024 + lane * 16);
+    } else {
+        static_assert(C::RPB / C::RPL == 4, "the column swizzle of V repeats every piece");
+        const int r = wave * C::NI * C::RPB + lane / C::CH;
+        v_voff = (uint32_t)r * stride2 + (uint32_t)(((lane % C::CH) ^ ((((r / C::RPL) & 3) << 2) & (C::CH - 1))) * 16);
+    }
+    const uint32_t v_piece = PACKED ? 0u : C::RPB * stride2 - 1024u;      // between pieces, beyond the 1 KB of the instruction's offset
     auto k_frag = [&](uint32_t kbase, int kb, int ks) -> bf16x8 {
         return *reinterpret_cast<const bf16x8*>(lds + (kbase + k_fragoff[ks]) + kb * 32 * D * 2);
     };
-    // `vaddr` = slot base + vtr_off0
-    auto v_frag_tr_at = [&](uint32_t vaddr, int t4, int db) -> bf16x8 {
-        const unsigned char* p0 = lds + (vaddr ^ (uint32_t)(db << 6)) + t4 * 16 * (D * 2);
+    auto v_frag_tr = [&](uint32_t slot, int t4, int db) -> bf16x8 {
+        const unsigned char* p0 = lds + vtr_off[db] + (slot + t4 * 16 * (D * 2));
         const i16x4 lo = read_tr((const lds_i16x4*)(p0));
         const i16x4 hi = read_tr((const lds_i16x4*)(p0 + 8 * (D * 2)));
         typedef short i16x8 __attribute__((ext_vector_type(8)));
@@ -346,11 +354,10 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
         const int pb = a.batch > 1 ? fast_div(khv, a.dHkv) : 0;
         const int kh = khv - pb * a.Hkv;
         // (the arrays of problem pb are addressed where they are used: few of these pointers are live at a time)
-        const __amdgpu_buffer_rsrc_t pk_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint16_t*>(a.pk + pb * a.p_bs), 0, (uint32_t)a.L * stride2, RSRC_FLAGS);
-        const __amdgpu_buffer_rsrc_t pv_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint16_t*>((PACKED ? a.vt + pb * a.vt_bs : a.pv + pb * a.p_bs)), 0,
-            PACKED ? (uint32_t)(a.Hkv * a.TPF) * C::T_BYTES : (uint32_t)a.L * stride2, RSRC_FLAGS);
+        const uint16_t* const pk = a.pk + pb * a.p_bs;
+        const uint16_t* const pv = PACKED ? a.vt + pb * a.vt_bs : a.pv + pb * a.p_bs;
+        const uint32_t pk_bytes = (uint32_t)a.L * stride2;
+        const uint32_t pv_bytes = PACKED ? (uint32_t)(a.Hkv * a.TPF) * C::T_BYTES : pk_bytes;
         // stores of the previous segment are out of the way of the load counting below
         wait_vm<0>();
 
@@ -364,41 +371,29 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
 
         // ---- tile j: global memory -> ring slot j % NB, no registers in between ----
         int issued = 0;
-        // full prefix tile (j < F): offsets were prepared once, only the scalar tile offset changes
-        // pieces [first, last) of this wavefront's share
-        auto fetch_k_pieces = [&](int j, uint32_t slot, int first, int last) {        // slot = (j % NB) * T_BYTES, a constant where it matters
-            const uint32_t soff = (uint32_t)((t0 + j) * KT) * stride2 + (uint32_t)(kh * D * 2);
-            unsigned char* const kdst = lds + slot + wave_u * (C::NI * 1024);
-#pragma unroll
-            for (int jn = first; jn < last; ++jn)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(pk_rsrc, (lds_void*)(kdst + jn * 1024), 16, k_voff[jn], soff, 0, 0);
+        // Full prefix tile (j < F).  A request for a tile that there is not goes to the dump slot and reads nothing (a
+        // buffer of no bytes): so every step issues the same loads without a branch, and its wait counts a constant.
+        auto request = [&](auto is_v, int j, uint32_t slot, auto first, auto last) {
+            constexpr bool V = decltype(is_v)::value;
+            constexpr int P0 = decltype(first)::value, P1 = decltype(last)::value;
+            const bool live = j < F;
+            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint16_t*>(V ? pv : pk), 0, live ? (V ? pv_bytes : pk_bytes) : 0u, RSRC_FLAGS);
+            unsigned char* const dst = lds + (live ? slot + (V ? C::V_RING : 0) : C::DUMP) + wave_u * (C::NI * 1024);
+            const uint32_t soff = V && PACKED ? (uint32_t)(kh * a.TPF + t0 + j) * C::T_BYTES : (uint32_t)((t0 + j) * KT) * stride2 + (uint32_t)(kh * D * 2);
+            auto piece = [&](auto jc) {
+                constexpr int jn = decltype(jc)::value + P0;
+                if constexpr (jn < P1)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)dst, 16, V ? v_voff : k_voff[jn], V ? soff + jn * v_piece : soff, jn * 1024, 0);
+            };
+            for_slots(piece, std::make_integer_sequence<int, P1 - P0>());
         };
-        auto fetch_v_pieces = [&](int j, uint32_t slot, int first, int last) {
-            unsigned char* const vdst = lds + slot + wave_u * (C::NI * 1024) + C::V_RING;
-            if (PACKED) {
-                const uint32_t voff = (uint32_t)(kh * a.TPF + t0 + j) * C::T_BYTES;
-#pragma unroll
-                for (int jn = first; jn < last; ++jn)
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(pv_rsrc, (lds_void*)(vdst + jn * 1024), 16, vp_voff + jn * 1024, voff, 0, 0);
-            } else {
-                const uint32_t soff = (uint32_t)((t0 + j) * KT) * stride2 + (uint32_t)(kh * D * 2);
-                int tid_f = tid;
-                FDD_PIN(tid_f);     // recomputed at every fetch rather than kept in registers
-#pragma unroll
-                for (int jn = first; jn < last; ++jn) {
-                    const int r = ((tid_f >> 6) * C::NI + jn) * C::RPB + (tid_f & 63) / C::CH;
-                    const uint32_t col16 = (uint32_t)((((tid_f & 63) % C::CH) ^ ((((r / C::RPL) & 3) << 2) & (C::CH - 1))) * 16);
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(pv_rsrc, (lds_void*)(vdst + jn * 1024), 16,
-                                                             (uint32_t)r * stride2 + col16, soff, 0, 0);
-                }
-            }
-        };
-        auto fetch_k = [&](int j, uint32_t slot) { fetch_k_pieces(j, slot, 0, C::NI); };
-        auto fetch_v = [&](int j, uint32_t slot) { fetch_v_pieces(j, slot, 0, C::NI); };
-        auto fetch_full = [&](int j, uint32_t slot) {
-            fetch_k(j, slot);
-            fetch_v(j, slot);
-        };
+        const std::integral_constant<int, 0> p_0;
+        const std::integral_constant<int, C::NI> p_all;
+        const std::true_type is_v;
+        const std::false_type is_k;
+        auto fetch_k = [&](int j, uint32_t slot) { request(is_k, j, slot, p_0, p_all); };
+        auto fetch_v = [&](int j, uint32_t slot) { request(is_v, j, slot, p_0, p_all); };
         // ---- Q fragments: B operand of S^T = K Q^T ------------------------------
         const int row0_wg = mt * MROWS;
         const int row0 = row0_wg + wave * 32;
@@ -426,18 +421,11 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
         // there, while the later ones are still on their way.
         // (K runs one tile ahead of V: K of tile j is read one step before V of tile j, so its slot is free
         // one step earlier, and one more half tile per workgroup is on its way at any time)
-        // The seven requests are issued without a branch, whatever F is: a segment with fewer than four full
-        // tiles requests its last full tile again (same addresses, served by the caches; a segment with none
-        // requests the last full tile of the prefix, and a prefix shorter than a tile is cut off by the buffer bounds),
-        // into slots whose later contents arrive later.  Only so does the compiler know that these requests
-        // follow the Q loads on every path and lets the wait for Q pass while they are in flight.
-        {
-            const int jmax = max(F - 1, 0);
-            const int jcap = max(a.TPF - 1, 0) - t0;     // keeps t0 + j inside the full tiles (it may be negative)
-#pragma unroll
-            for (int j = 0; j < NB - 1; ++j) fetch_full(min(min(j, jmax), jcap), (uint32_t)j * C::T_BYTES);
-            fetch_k(min(min(NB - 1, jmax), jcap), (uint32_t)(NB - 1) * C::T_BYTES);
-        }
+        // Only what the first step needs is requested here; the rest of the ring follows in the shadow of its first scores (all at
+        // once, every workgroup's first tile waited behind the others' fourth: first barrier 4.5 -> 4.0 us after the start at N=8, L=4096).
+        fetch_k(0, 0);
+        fetch_v(0, 0);
+        fetch_k(1, C::T_BYTES);
         issued = min(NB - 1, F);
         FDD_SCHED_FENCE();
 
@@ -463,9 +451,11 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
             const int row_l = half * 4 + ((lane_f & 15) >> 2);
             const int x = ((lane_f >> 4) & 1) * 2 + ((lane_f & 3) >> 1);
             const int sw = (((row_l / C::RPL) & 3) << 2) & (C::CH - 1);
-            vtr_off0 = (uint32_t)(row_l * D * 2 + ((x ^ sw) << 4) + (lane_f & 1) * 8);
-            vtr_off_ring = C::V_RING + vtr_off0;
-            FDD_PIN(vtr_off_ring);
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                vtr_off[db] = (uint32_t)(C::V_RING + ((row_l * D * 2 + ((x ^ sw) << 4) + (lane_f & 1) * 8) ^ (db << 6)));
+                FDD_PIN(vtr_off[db]);
+            }
         }
         int n_seg, seg;
         if (a.S > 0) {
@@ -578,7 +568,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
         // tile j: global memory -> ring slot j % NB, no registers in between
         auto fetch = [&](int j_) {
             const int j = __builtin_amdgcn_readfirstlane(j_);
-            if (j < F) fetch_full(j, (uint32_t)(j & (NB - 1)) * C::T_BYTES); else fetch_masked(j);
+            fetch_masked(j);
             issued = j + 1;
         };
         // block until tile t has landed in LDS for the whole workgroup; tiles are
@@ -596,6 +586,14 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
 
         // masked tiles that fit the ring ahead of time
         while (issued < min(NB - 1, n_tiles)) fetch(issued);
+        const int ahead = F > 0 ? issued - min(NB - 1, F) : 0;       // such tiles of a segment with full ones: fewer than NB - 1
+        // all but the newest n loads and these tiles must have landed
+        auto wait_but = [&](auto n) {
+            constexpr int N = decltype(n)::value;
+            if (NB == 2 || ahead == 0) wait_vm<N>();
+            else if (ahead == 1) wait_vm<N + (NB > 2 ? 1 : 0) * C::IPT>();
+            else wait_vm<N + (NB > 2 ? 2 : 0) * C::IPT>();
+        };
 
         // ---- streaming-softmax state: one query row per lane --------------------
         float zero = 0.f;       // (a vector of constants would be built in 16 scalar registers)
@@ -629,128 +627,123 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
             }
         };
 
-        // end of step i of the pipelined loop: K of tile i+2 and V of tile i+1 must have landed (both requested two
-        // steps ago); what this step and the previous one requested may still be on its way
-        auto wait_step = [&](int i) {
-            if (NB == 2) wait_vm<0>();          // (two slots: both were requested in this step)
-            else if (i + 4 < F) wait_vm<4 * C::NI>();
-            else if (i + 3 < F) wait_vm<3 * C::NI>();
-            else if (i + 2 < F) wait_vm<C::NI>();
-            else wait_vm<0>();
-        };
+        // What step i requests: K of tile i+NB, V of tile i+NB-1 (into the slots of K of tile i, read last in step i-1, and V
+        // of tile i-1).  At its end K of tile i+2 and V of tile i+1 must have landed.
+        auto wait_step = [&] { wait_vm<(NB - 2) * 2 * C::NI>(); };
 
         bf16x8 p[4];      // probabilities of a tile as MFMA B operands, one per 16-key step
 
         // ---- full prefix tiles, software pipelined ---------------------------------
-        // Issue order so far: Q, then K0 V0 K1 V1 K2 V2 K3 (or as far as there are slots).  The first step needs Q, K0, V0
-        // and K1; with four full tiles or more nothing else has been requested, and the last four half tiles may stay in
-        // flight.  With two slots the scores of tile 0 start on Q and K0 (nothing but K0 V0 K1 is on its way if F > 0).
-        if (NB == 2 && F > 0) wait_vm<2 * C::NI>();
-        else if (NB == 4 && F >= NB) wait_vm<4 * C::NI>();
-        else wait_vm<0>();
-        wg_barrier();
-        landed = issued - 1;
-        if (F > 0 && !wave_has_rows) {
-            // A wavefront without rows (the M-tile is not full) only moves its share of the tiles: the matrix pipe and
-            // the power are left to the others (8 requests of N=1, 224 of 256 rows, L=16384: 84.0 -> 82.1 us; with 112
-            // rows or fewer a SIMD has one wavefront to serve).  Same requests, waits and barriers as in the steps below.
-            if (NB == 2) wait_vm<0>();
+        // Issue order so far: Q, K0 V0 K1 (and masked tiles of a short segment).
+        if (F > 0) {
+            const std::integral_constant<int, 2 * C::NI> first;
+            const std::integral_constant<int, (NB - 2) * 2 * C::NI> rest;
+            wait_but(first);       // Q, K0
             wg_barrier();
-            for (int i = 0; i < F; ++i) {
-                if (i + NB < F) fetch_k(i + NB, (uint32_t)(i & (NB - 1)) * C::T_BYTES);
-                if (i + NB - 1 < F) {
-                    fetch_v(i + NB - 1, (uint32_t)((i + NB - 1) & (NB - 1)) * C::T_BYTES);
-                    issued = i + NB;
-                }
-                wait_step(i);
+            // what the ring still has room for: V1 K2 V2 K3
+            auto request_rest = [&](auto c) {        // half tile c
+                constexpr int h = decltype(c)::value;
+                if constexpr (h % 2 == 0) fetch_v(1 + h / 2, (uint32_t)(1 + h / 2) * C::T_BYTES);
+                else fetch_k(2 + h / 2, (uint32_t)(2 + h / 2) * C::T_BYTES);
+            };
+            if (!wave_has_rows) {
+                // A wavefront without rows (the M-tile is not full) only moves its share of the tiles: the matrix pipe and
+                // the power are left to the others (8 requests of N=1, 224 of 256 rows, L=16384: 84.0 -> 82.1 us; with 112
+                // rows or fewer a SIMD has one wavefront to serve).  Same requests, waits and barriers as in the steps below.
+                for_slots(request_rest, std::make_integer_sequence<int, 2 * (NB - 2)>());
+                wait_but(rest);
                 wg_barrier();
-            }
-            landed = issued - 1;
-        } else if (F > 0) {
-            // prologue: scores of tile 0
-            f32x16 sa[2], sb[2];
+                for (int i = 0; i < F; ++i) {
+                    fetch_k(i + NB, (uint32_t)(i & (NB - 1)) * C::T_BYTES);
+                    fetch_v(i + NB - 1, (uint32_t)((i + NB - 1) & (NB - 1)) * C::T_BYTES);
+                    wait_step();
+                    wg_barrier();
+                }
+            } else {
+                // prologue: scores of tile 0, the other requests of the ring spread over them
+                f32x16 sa[2], sb[2];
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+                for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) sa[kb][v] = 0.f;
-            read_ahead<2 * KS, RA>([&](int j) { return k_frag(0, j / KS, j % KS); }, [&](int j, const bf16x8& f) {
-                sa[j / KS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[j % KS], sa[j / KS], 0, 0, 0);
-            });
-            // Step 0 requests K of tile 4 into the slot that the scores above were read from: no wavefront may get
-            // there while another one is still reading.  (They can be far apart here: the first workgroups of a
-            // launch fetch these instructions from memory.)
-            FDD_SCHED_FENCE();
-            if (NB == 2) wait_vm<0>();
-            wg_barrier();
+                    for (int v = 0; v < 16; ++v) sa[kb][v] = 0.f;
+                {
+                    bf16x8 f[RA + 1];
+#pragma unroll
+                    for (int j = 0; j < RA; ++j) f[j] = k_frag(0, j / KS, j % KS);
+                    FDD_SCHED_FENCE();
+                    auto slot = [&](auto jc) {
+                        constexpr int j = decltype(jc)::value, NREQ = 2 * (NB - 2) * C::NI;        // pieces to request
+                        if constexpr (j + RA < 2 * KS) f[(j + RA) % (RA + 1)] = k_frag(0, (j + RA) / KS, (j + RA) % KS);
+                        sa[j / KS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[j % (RA + 1)], qf[j % KS], sa[j / KS], 0, 0, 0);
+                        auto req = [&](auto rc) {
+                            constexpr int r = j * NREQ / (2 * KS) + decltype(rc)::value;
+                            if constexpr (r < (j + 1) * NREQ / (2 * KS)) {
+                                constexpr int h = r / C::NI, pc = r % C::NI;
+                                const std::integral_constant<int, pc> p0;
+                                const std::integral_constant<int, pc + 1> p1;
+                                if constexpr (h % 2 == 0) request(is_v, 1 + h / 2, (uint32_t)(1 + h / 2) * C::T_BYTES, p0, p1);
+                                else request(is_k, 2 + h / 2, (uint32_t)(2 + h / 2) * C::T_BYTES, p0, p1);
+                            }
+                        };
+                        for_slots(req, std::make_integer_sequence<int, 4>());
+                        FDD_SCHED_FENCE();
+                    };
+                    static_assert(2 * (NB - 2) * C::NI <= 4 * 2 * KS, "four requests a slot");
+                    for_slots(slot, std::make_integer_sequence<int, 2 * KS>());
+                }
+                // largest score of the tile whose probabilities are next, over this lane's half of the keys
+                float mx = -INFINITY;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) mx = fmaxf(fmaxf(mx, sa[0][v]), sa[1][v]);
+                // Step 0 requests K of tile 4 into the slot that the scores above were read from: no wavefront may get
+                // there while another one is still reading.  (They can be far apart here: the first workgroups of a
+                // launch fetch these instructions from memory.)
+                FDD_SCHED_FENCE();
+                wait_but(rest);        // V0, K1
+                wg_barrier();
 
-            // One pipelined step: probabilities and P V of tile i from s_cur while
-            // the scores of tile i+1 go to s_nxt; K of tile i+4 and V of tile i+3 are requested.
-            //   slots  0- 7  S(i+1) first 32 keys   ||  row maximum of tile i (and, in the spread order, the requests)
-            //   slots  8-15  S(i+1) second 32 keys  ||  exp of the first 32 keys
-            //   slots 16-23  P V first 32 keys      ||  exp of the second 32 keys
-            //   slots 24-31  P V second 32 keys
-            // `par` is i % NB as a compile-time constant: ring slots become
-            // immediate offsets of the LDS reads.  The scores of tile i+1 are
-            // computed whether or not it is a full tile (from whatever its slot
-            // holds); they are only used if it is.  On entry K up to tile i+1 and V up
-            // to tile i have landed; on exit K up to tile i+2 and V up to tile i+1.
-            auto step = [&](auto par, int i, f32x16 (&s_cur)[2], f32x16 (&s_nxt)[2]) {
-                constexpr int P = decltype(par)::value;
-                constexpr uint32_t KSLOT = (uint32_t)((P + 1) % NB) * C::T_BYTES;
-                constexpr uint32_t VSLOT = (uint32_t)P * C::T_BYTES;
-                // K of tile i+NB goes where K of tile i was (last read in the previous step, by the scores
-                // computed ahead), V of tile i+NB-1 where V of tile i-1 was
-                // (masked tiles are requested after the loop: their request code is long, and inside the
-                // loop it costs registers the loop does not have: measured, 52..64 vector registers spilled)
-                const bool more_k = i + NB < F, more_v = i + NB - 1 < F;
-                constexpr uint32_t KNEW = (uint32_t)P * C::T_BYTES, VNEW = (uint32_t)((P + NB - 1) % NB) * C::T_BYTES;
-                if (more_v) issued = i + NB;
-                auto kfrag = [&](int kb, int ks) {
-                    return *reinterpret_cast<const bf16x8*>(lds + k_fragoff[ks] + (KSLOT + kb * 32 * D * 2));
-                };
-                // P V slot j of block kb: 16-key step j / DB, channel block j % DB
-                auto vfrag = [&](int kb, int j) -> bf16x8 {
-                    const int t4 = kb * 2 + j / DB, db = j % DB;
-                    if (PACKED) return *reinterpret_cast<const bf16x8*>(lds + v_fragoff_ring + (VSLOT + t4 * (D * 32) + db * 512));
-                    return v_frag_tr_at(vtr_off_ring + VSLOT, t4, db);
-                };
-                float mx = -INFINITY, mc = 0.f, acc = 0.f;
-                bf16x8 f[3];
-                u32x4 pw[4];     // the B operands of P V as packed words
-                typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-                const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-
-                if constexpr (SPREAD) {
-                    // What a wavefront does besides its matrix instructions is spread over the slots such that nothing in a slot
-                    // waits for the slot itself: the tile requests one at a time (issued in a row they held the matrix pipe up),
-                    // the fragments two slots ahead across the parts of a step, and an exponential in three stages (scale,
-                    // exponential, rounding and sum) a slot apart (a wavefront issues in order: a dependent instruction right
-                    // behind waits).  One workgroup alone 1.36 -> 1.27 us a tile; N=16, L=16384 227.5 -> 222.9 us a call, N=64,
-                    // L=32768 1679 -> 1645 (fragments 3 ahead 1.28, 4 ahead 1.32; requests from slot 0 on or in consecutive slots
-                    // 1.28, 1.29).  With one wavefront per SIMD and at D = 64, where a slot carries twice the exponentials,
-                    // the plain order below is 1 and 3 % faster.  So it is where V is read as it lies, whose requests and fragments
-                    // take more vector instructions a slot: N=16, B=64, L=16384 246.3 spread, 239.8 plain, L=4096 75.4/72.3; N=32,
-                    // B=64, L=4096 128.0/124.3 (prefixes in rotation; 1 % the other way with free ranges, N=64, L=2048 142.5/144.3).
-                    constexpr int NPV = 4 * DB, NSL = 2 * KS + NPV;        // slots of P V, of the step
+                // One pipelined step: probabilities and P V of tile i from s_cur while the scores of tile i+1 go to s_nxt.
+                //   slots  0-15  S(i+1), first and second 32 keys  ||  exponentials of tile i
+                //   slots 16-31  P V                               ||  the last exponentials, row maximum of tile i+1
+                // `par` is i % NB as a compile-time constant: ring slots become immediate offsets of the LDS reads.  The scores of
+                // tile i+1 are computed whether or not it is a full tile (from whatever its slot holds); they are only used if it is.
+                // On entry K up to tile i+1 and V up to tile i have landed; on exit K up to tile i+2 and V up to tile i+1.
+                //
+                // What a wavefront issues beside its matrix instructions (32 cycles each) has to fit into their shadow: 6 cycles a
+                // vector instruction, 10 an exponential, for a wavefront alone on its SIMD (measured).  So exponentials are spread
+                // evenly, one "tick" (exponential, scaling of the one after next, rounding of the last pair) every 0.85 slots, each
+                // stage behind the next tick's so that nothing waits for its predecessor; requests are single instructions without
+                // branches, spread over the slots as well; and the row sum is taken in one run at the end: v_dot2 shares the matrix pipe
+                // and costs 16 of its cycles between two matrix instructions, 4 behind another v_dot2.
+                // Cycles a step, few workgroups: D = 128, V laid out, 8 wavefronts 3036 -> 2559 (64 matrix instructions a SIMD), 4
+                // wavefronts 2240 -> 1610 (32); D = 64 2240 -> 1896 and 1788 -> 1287.  With the chip full its power sets the clock:
+                // N=64, B=64, L=8192 413 -> 398 us a call; N=8, B=32, L=4096, 128 rows 27.2 -> 24.3; N=1, L=16384 20.7 -> 19.6.
+                auto step = [&](auto par, int i, f32x16 (&s_cur)[2], f32x16 (&s_nxt)[2]) {
+                    constexpr int P = decltype(par)::value;
+                    constexpr uint32_t KSLOT = (uint32_t)((P + 1) % NB) * C::T_BYTES;
+                    constexpr uint32_t VSLOT = (uint32_t)P * C::T_BYTES;
+                    constexpr uint32_t KNEW = (uint32_t)P * C::T_BYTES, VNEW = (uint32_t)((P + NB - 1) % NB) * C::T_BYTES;
+                    constexpr int AH = 3;                                         // fragments requested ahead
+                    constexpr int NS = 2 * KS, NPV = 4 * DB, NSL = NS + NPV;      // slots of the scores, of P V, of the step
+                    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+                    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+                    u32x4 pw[4];     // the B operands of P V as packed words
                     auto frag = [&](int j) -> bf16x8 {
-                        return j < 2 * KS ? kfrag(j / KS, j % KS) : vfrag((j - 2 * KS) / (2 * DB), (j - 2 * KS) % (2 * DB));
+                        if (j < NS) return *reinterpret_cast<const bf16x8*>(lds + k_fragoff[j % KS] + (KSLOT + j / KS * 32 * D * 2));
+                        const int t4 = (j - NS) / DB, db = (j - NS) % DB;
+                        if (PACKED) return *reinterpret_cast<const bf16x8*>(lds + v_fragoff_ring + (VSLOT + t4 * (D * 32) + db * 512));
+                        return v_frag_tr(VSLOT, t4, db);
                     };
-                    // two probabilities of the tile: registers 2k, 2k+1 of its 32
-                    auto scale_pair = [&](int k) {
-#pragma unroll
-                        for (int t = 0; t < 2; ++t) {
-                            float x = fmaf(s_cur[k / 8][2 * (k % 8) + t], a.c, -mc);
-                            FDD_PIN(x);
-                            s_cur[k / 8][2 * (k % 8) + t] = x;
-                        }
+                    float mc = 0.f;
+                    auto scale = [&](int e) {
+                        float x = fmaf(s_cur[e / 16][e % 16], a.c, -mc);
+                        FDD_PIN(x);
+                        s_cur[e / 16][e % 16] = x;
                     };
-                    auto exp_pair = [&](int k) {
-#pragma unroll
-                        for (int t = 0; t < 2; ++t) {
-                            float x = fast_exp2(s_cur[k / 8][2 * (k % 8) + t]);
-                            FDD_PIN(x);
-                            s_cur[k / 8][2 * (k % 8) + t] = x;
-                        }
+                    auto expo = [&](int e) {
+                        float x = fast_exp2(s_cur[e / 16][e % 16]);
+                        FDD_PIN(x);
+                        s_cur[e / 16][e % 16] = x;
                     };
                     auto round_pair = [&](int k) {
                         const bf16x2 pr = {(__bf16)s_cur[k / 8][2 * (k % 8)], (__bf16)s_cur[k / 8][2 * (k % 8) + 1]};
@@ -758,164 +751,100 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                         FDD_PIN(u);
                         pw[k / 4][k % 4] = u;
                     };
-                    // (the row sum is taken over the probabilities as they enter P V, see below)
-                    auto sum_pair = [&](int k) {
-                        acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)pw[k / 4][k % 4]), ones, acc, false);
-                        FDD_PIN(acc);
-                    };
-                    constexpr int NEXP = KS + 2 * DB;          // slots with exponentials, one pair each
-                    static_assert(!SPREAD || NEXP == 16, "16 pairs of probabilities");
+                    bf16x8 f[AH + 1];
                     FDD_SCHED_FENCE();
-                    f[0] = frag(0);
-                    f[1] = frag(1);
-                    // (a compile-time slot number: what a slot carries is worked out by the compiler)
+#pragma unroll
+                    for (int j = 0; j < AH; ++j) f[j] = frag(j);
+                    FDD_SCHED_FENCE();
+                    update_reference(mx);
+                    mc = m_ref * a.c;
+                    mx = -INFINITY;
+                    FDD_SCHED_FENCE();
+                    scale(0);
+                    scale(1);
+                    FDD_SCHED_FENCE();
+                    constexpr int NT = 33, SPAN = NSL - DB;      // ticks, the slots they are spread over
+                    static_assert(8 * SPAN / NT < NS && 16 * SPAN / NT < NS + DB && 24 * SPAN / NT < NS + 2 * DB && 32 * SPAN / NT < NS + 3 * DB, "probabilities before their use");
                     auto slot = [&](auto jc) {
                         constexpr int j = decltype(jc)::value;
+                        if constexpr (j + AH < NSL) f[(j + AH) % (AH + 1)] = frag(j + AH);
                         if constexpr (j == 0 || j == KS) {
 #pragma unroll
                             for (int v = 0; v < 16; ++v) s_nxt[j / KS][v] = 0.f;
                         }
-                        if constexpr (j % 2 == 1 && j / 2 < C::NI) {
-                            if (more_k) fetch_k_pieces(i + NB, KNEW, j / 2, j / 2 + 1);
-                        } else if constexpr (j % 2 == 1 && j / 2 >= 2 && j / 2 - 2 < C::NI) {
-                            if (more_v) fetch_v_pieces(i + NB - 1, VNEW, j / 2 - 2, j / 2 - 1);
-                        }
-                        if constexpr (j + 2 < NSL) f[(j + 2) % 3] = frag(j + 2);
-                        if constexpr (j < 2 * KS) {
-                            s_nxt[j / KS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[j % 3], qf[j % KS], s_nxt[j / KS], 0, 0, 0);
+                        if constexpr (j < NS) {
+                            s_nxt[j / KS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[j % (AH + 1)], qf[j % KS], s_nxt[j / KS], 0, 0, 0);
                         } else {
-                            constexpr int t4 = (j - 2 * KS) / DB, db = (j - 2 * KS) % DB;
-                            o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[j % 3], __builtin_bit_cast(bf16x8, pw[t4]), o[db], 0, 0, 0);
+                            constexpr int t4 = (j - NS) / DB, db = (j - NS) % DB;
+                            o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[j % (AH + 1)], __builtin_bit_cast(bf16x8, pw[t4]), o[db], 0, 0, 0);
                         }
-                        if constexpr (j < KS) {
-#pragma unroll
-                            for (int v = j * (16 / KS); v < (j + 1) * (16 / KS); ++v) mx = fmaxf(fmaxf(mx, s_cur[0][v]), s_cur[1][v]);
-                            FDD_PIN(mx);
-                            if constexpr (j == KS - 1) {
+                        FDD_SCHED_FENCE();
+                        if constexpr (j % 2 == 1) {
+                            constexpr int r = j / 2;
+                            const std::integral_constant<int, r % C::NI> p0;
+                            const std::integral_constant<int, r % C::NI + 1> p1;
+                            if constexpr (r < C::NI) request(is_k, i + NB, KNEW, p0, p1);
+                            else if constexpr (r < 2 * C::NI) request(is_v, i + NB - 1, VNEW, p0, p1);
+                            FDD_SCHED_FENCE();
+                        }
+                        auto tick = [&](auto tc) {
+                            constexpr int t = decltype(tc)::value;
+                            if constexpr (t * SPAN / NT == j) {
+                                if constexpr (t < 32) expo(t);
                                 FDD_SCHED_FENCE();
-                                update_reference(mx);
-                                mc = m_ref * a.c;
+                                if constexpr (t % 2 == 0 && t > 0) round_pair(t / 2 - 1);
+                                if constexpr (t + 2 < 32) scale(t + 2);
                                 FDD_SCHED_FENCE();
-                                scale_pair(0);
                             }
-                        } else if constexpr (j <= KS + NEXP) {
-                            constexpr int k = j - KS;          // exponentials of pair k, with the stages before and after beside it
-                            if constexpr (k < 16) exp_pair(k);
-                            FDD_SCHED_FENCE();
-                            if constexpr (k >= 1) round_pair(k - 1);
-                            FDD_SCHED_FENCE();
-                            if constexpr (k < 15) scale_pair(k + 1);
-                            FDD_SCHED_FENCE();
-                            if constexpr (k >= 1) sum_pair(k - 1);
-                        } else if constexpr (j == KS + NEXP + 1) {
-                            l_run += acc;
+                        };
+                        for_slots(tick, std::make_integer_sequence<int, NT>());
+                        if constexpr (j >= NS + 2) {
+                            constexpr int q = j - NS - 2, NQ = NPV - 2;
+#pragma unroll
+                            for (int v = q * 16 / NQ; v < (q + 1) * 16 / NQ; ++v) {
+                                mx = fmaxf(fmaxf(mx, s_nxt[0][v]), s_nxt[1][v]);
+                                FDD_PIN(mx);
+                            }
                         }
                         FDD_SCHED_FENCE();
                     };
                     for_slots(slot, std::make_integer_sequence<int, NSL>());
-                } else {
-                if (more_k) fetch_k(i + NB, KNEW);
-                if (more_v) fetch_v(i + NB - 1, VNEW);
-                FDD_SCHED_FENCE();
-
-                // ---- slots 0-7 ----
-                f[0] = kfrag(0, 0);
-                f[1] = kfrag(0, 1);
+                    // the row sum is taken over the probabilities as they enter P V (rounded to bf16): numerator and denominator then
+                    // see the same values
+                    float acc0 = 0.f, acc1 = 0.f;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) s_nxt[0][v] = 0.f;
-#pragma unroll
-                for (int j = 0; j < KS; ++j) {
-                    if (j + 2 < KS) f[(j + 2) % 3] = kfrag(0, j + 2);
-                    s_nxt[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[j % 3], qf[j], s_nxt[0], 0, 0, 0);
-#pragma unroll
-                    for (int v = j * (16 / KS); v < (j + 1) * (16 / KS); ++v) {
-                        mx = fmaxf(fmaxf(mx, s_cur[0][v]), s_cur[1][v]);
+                    for (int k = 0; k < 16; k += 2) {
+                        acc0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)pw[k / 4][k % 4]), ones, acc0, false);
+                        acc1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)pw[(k + 1) / 4][(k + 1) % 4]), ones, acc1, false);
                     }
-                    FDD_PIN(mx);
-                    FDD_SCHED_FENCE();
-                }
-                update_reference(mx);
-                mc = m_ref * a.c;
-                // four probabilities of block kb (registers 4e .. 4e+3), rounded into the B operands
-                auto exp_quad = [&](int kb, int e) {
-                    float pr[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) pr[t] = fast_exp2(fmaf(s_cur[kb][4 * e + t], a.c, -mc));
-                    bf16x2 lo = {(__bf16)pr[0], (__bf16)pr[1]}, hi = {(__bf16)pr[2], (__bf16)pr[3]};
-                    // the row sum is taken over the probabilities as they enter P V (rounded to bf16):
-                    // numerator and denominator then see the same values, and a pair costs one instruction
-                    acc = __builtin_amdgcn_fdot2_f32_bf16(lo, ones, acc, false);
-                    acc = __builtin_amdgcn_fdot2_f32_bf16(hi, ones, acc, false);
-                    uint32_t ulo = __builtin_bit_cast(uint32_t, lo), uhi = __builtin_bit_cast(uint32_t, hi);
-                    FDD_PIN(ulo);
-                    FDD_PIN(uhi);
-                    FDD_PIN(acc);
-                    pw[kb * 2 + e / 2][(e & 1) * 2] = ulo;
-                    pw[kb * 2 + e / 2][(e & 1) * 2 + 1] = uhi;
+                    l_run += acc0 + acc1;
+                    wait_step();
+                    wg_barrier();
                 };
-                FDD_SCHED_FENCE();
-
-                // ---- slots 8-15 ----
-                f[0] = kfrag(1, 0);
-                f[1] = kfrag(1, 1);
-#pragma unroll
-                for (int v = 0; v < 16; ++v) s_nxt[1][v] = 0.f;
-#pragma unroll
-                for (int j = 0; j < KS; ++j) {
-                    if (j + 2 < KS) f[(j + 2) % 3] = kfrag(1, j + 2);
-                    s_nxt[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[j % 3], qf[j], s_nxt[1], 0, 0, 0);
-                    if ((j * 4) % KS == 0) exp_quad(0, j * 4 / KS);
-                    FDD_SCHED_FENCE();
-                }
-                p[0] = __builtin_bit_cast(bf16x8, pw[0]);
-                p[1] = __builtin_bit_cast(bf16x8, pw[1]);
-
-                // ---- slots 16-23 ----
-                constexpr int PVS = 2 * DB;      // P V MFMAs per 32-key block
-                f[0] = vfrag(0, 0);
-                f[1] = vfrag(0, 1);
-#pragma unroll
-                for (int j = 0; j < PVS; ++j) {
-                    if (j + 2 < PVS) f[(j + 2) % 3] = vfrag(0, j + 2);
-                    o[j % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[j % 3], p[j / DB], o[j % DB], 0, 0, 0);
-                    if ((j * 4) % PVS == 0) exp_quad(1, j * 4 / PVS);
-                    FDD_SCHED_FENCE();
-                }
-                p[2] = __builtin_bit_cast(bf16x8, pw[2]);
-                p[3] = __builtin_bit_cast(bf16x8, pw[3]);
-                l_run += acc;
-
-                // ---- slots 24-31 ----
-                f[0] = vfrag(1, 0);
-                f[1] = vfrag(1, 1);
-#pragma unroll
-                for (int j = 0; j < PVS; ++j) {
-                    if (j + 2 < PVS) f[(j + 2) % 3] = vfrag(1, j + 2);
-                    o[j % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[j % 3], p[2 + j / DB], o[j % DB], 0, 0, 0);
-                    FDD_SCHED_FENCE();
-                }
-                }
-                wait_step(i);
-                wg_barrier();
-            };
-            const std::integral_constant<int, 0> r0;
-            const std::integral_constant<int, 1> r1;
-            const std::integral_constant<int, 2> r2;
-            const std::integral_constant<int, 3> r3;
-            for (int i = 0;;) {
-                step(r0, i, sa, sb);
-                if (++i == F) break;
-                step(r1, i, sb, sa);
-                if (++i == F) break;
-                if constexpr (NB == 4) {
-                    step(r2, i, sa, sb);
+                const std::integral_constant<int, 0> r0;
+                const std::integral_constant<int, 1> r1;
+                const std::integral_constant<int, 2> r2;
+                const std::integral_constant<int, 3> r3;
+                for (int i = 0;;) {
+                    step(r0, i, sa, sb);
                     if (++i == F) break;
-                    step(r3, i, sb, sa);
+                    step(r1, i, sb, sa);
                     if (++i == F) break;
+                    if constexpr (NB == 4) {
+                        step(r2, i, sa, sb);
+                        if (++i == F) break;
+                        step(r3, i, sb, sa);
+                        if (++i == F) break;
+                    }
                 }
             }
-            landed = issued - 1;     // the last step waits for everything requested
+            // (only requests without a tile are still on their way; masked tiles requested before the loop have landed)
+            issued = max(issued, F);
+        } else {
+            wait_vm<0>();
+            wg_barrier();
         }
+        landed = issued - 1;
 
         // ---- masked tiles: ragged last prefix tile and the in-block tail ------------
         // On entry to iteration j tile j has landed.
@@ -963,7 +892,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                         acc += pr;
                         p[kb * 2 + v / 8][v % 8] = (__bf16)pr;
                     }
-                    read_ahead<2 * DB, RA>([&](int x) { return v_frag_tr_at(vtr_off_ring + kbase, 2 * kb + x / DB, x % DB); },
+                    read_ahead<2 * DB, RA>([&](int x) { return v_frag_tr(kbase, 2 * kb + x / DB, x % DB); },
                                            [&](int x, const bf16x8& f) {
                                                o[x % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, p[2 * kb + x / DB], o[x % DB], 0, 0, 0);
                                            });
@@ -1221,12 +1150,12 @@ __global__ __launch_bounds__(256) void attn_merge_bf16_kernel(MergeArgs a)
     *reinterpret_cast<bf16x4*>(op + 8) = hi;
 }
 
-template <int D, int WAVES, bool PACKED>
+template <int D, int WAVES, int SLOTS, bool PACKED>
 hipError_t launch(const Args& a, bool pack_now, hipStream_t stream, hipEvent_t before_main)
 {
-    using C = Cfg<D, WAVES>;
+    using C = Cfg<D, WAVES, SLOTS>;
     const size_t lds_bytes = C::LDS_BYTES;
-    const auto kern = &attn_bf16_kernel<D, WAVES, PACKED>;
+    const auto kern = &attn_bf16_kernel<D, WAVES, SLOTS, PACKED>;
     // the LDS limit of this instantiation is raised once per device (bit d of `done`: device d)
     static std::atomic<uint64_t> done{0};
     int dev = 0;
@@ -1305,14 +1234,17 @@ hipError_t launch_attn_bf16(const fdd_attn_params& p, const AttnPlan& plan, floa
     // (with 2..16 pieces of 32 units or more a shift of 3 % is at least one unit)
     a.w_even = 100;
     a.w_odd = (a.S >= 2 && a.S <= 16 && a.TPU >= 32 * a.S) ? ODD_XCD_WEIGHT : 100;
-    auto go = [&](auto waves) {
-        constexpr int WAVES = decltype(waves)::value;
+    auto go = [&](auto waves, auto slots) {
+        constexpr int WAVES = decltype(waves)::value, SLOTS = decltype(slots)::value;
         if (plan.packed)
-            return p.D == 128 ? launch<128, WAVES, true>(a, pack_now, s, before_main) : launch<64, WAVES, true>(a, pack_now, s, before_main);
-        return p.D == 128 ? launch<128, WAVES, false>(a, false, s, before_main) : launch<64, WAVES, false>(a, false, s, before_main);
+            return p.D == 128 ? launch<128, WAVES, SLOTS, true>(a, pack_now, s, before_main) : launch<64, WAVES, SLOTS, true>(a, pack_now, s, before_main);
+        return p.D == 128 ? launch<128, WAVES, SLOTS, false>(a, false, s, before_main) : launch<64, WAVES, SLOTS, false>(a, false, s, before_main);
     };
-    if (plan.mtile_rows == 256) return go(std::integral_constant<int, 8>());
-    if (plan.mtile_rows == 128) return go(std::integral_constant<int, 4>());
+    const std::integral_constant<int, 8> w8;
+    const std::integral_constant<int, 4> w4, s4;
+    const std::integral_constant<int, 2> s2;
+    if (plan.mtile_rows == 256) return go(w8, s4);
+    if (plan.mtile_rows == 128) return plan.slots == 2 ? go(w4, s2) : go(w4, s4);
     return hipErrorInvalidValue;
 }
 

@@ -50,6 +50,7 @@ struct AttnPlan {
     int G;            // query heads per KV head
     int R;            // stacked rows per KV head
     int mtile_rows;   // rows per M-tile
+    int slots;        // bf16 path: ring slots per operand in LDS
     int MT;           // M-tiles per KV head
     int key_tile;     // keys per streamed tile
     int TP;           // prefix tiles = ceil(L / key_tile)
