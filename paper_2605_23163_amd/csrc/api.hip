@@ -133,19 +133,20 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
     bool partials;
     auto cut_bf16 = [&](int rows) {
         set_rows(rows);
-        // The private tiles of an M-tile (extension and block of every rollout its rows belong to) are done
-        // by the workgroup that ends the M-tile's key range, one after the other and at about 1.8 times the
-        // cost of a pipelined prefix tile.  They are booked as `wt` extra units at the end of the M-tile's
-        // unit range, so that this workgroup gets correspondingly fewer prefix tiles.
+        // The private tiles of an M-tile (extension and block of every rollout its rows belong to) go through the masked path at
+        // about 1.8 times the cost of a pipelined prefix tile.  They are booked as `wt` extra units behind the M-tile's prefix tiles
+        // (up to 64) and dealt to the workgroups with them.
         // (with a list of query positions a rollout contributes fewer rows: its average share stands in for B)
         const long long BG = p.n_q_positions > 0 ? std::max(1ll, (long long)p.n_q_positions * pl.G / p.N) : (long long)p.B * pl.G;
         const long long span_lo = (pl.mtile_rows + BG - 1) / BG;                 // rollouts an M-tile spans at least
         const long long span = span_lo + ((pl.mtile_rows % BG) != 0 && BG < (long long)pl.R ? 1 : 0);
         const long long private_tiles = (span < p.N ? span : p.N) *
                                         ((p.E + pl.key_tile - 1) / pl.key_tile + (p.B + pl.key_tile - 1) / pl.key_tile);
-        long long wt = (private_tiles * 9 + 4) / 5;
-        if (wt < 1) wt = 1;
-        if (wt > 64) wt = 64;
+        long long wt = std::min(std::max((private_tiles * 9 + 4) / 5, 1ll), 64ll);
+        // Up to one and a half times a workgroup's share of the units they are left to one workgroup: booked as its whole share, no
+        // piece lies inside them.  (Cut from one share on, N=14, B=64, L=75, Hq=14, Hkv=2 13.3 -> 15.1 us, from two on N=4, B=32, L=1024 12.7
+        // -> 12.9 and N=5, B=40, L=5003, D=64, E=37 not at all: two steps 56.4 -> 60.7; the mean over 200 drawn calls 1.186, 1.183 and 1.178.)
+        auto share = [&](long long per) { if (wt > per && 2 * wt <= 3 * per) wt = std::max(per, 1ll); };
         auto pieces_for = [&](long long tpu) {
             // equal pieces per M-tile, of two units or more (one of them may have less); the fewest pieces that reach the shortest critical path
             long long smax = NM > 0 ? kNumCU / NM : 0;
@@ -172,8 +173,7 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
             // 13.5/12.6).  Otherwise equal contiguous unit ranges (stream-K).
             long long s = pieces_for(pl.TP + wt);
             if (s >= 1) {
-                const long long per = (pl.TP + wt) / s;       // a piece must not lie inside the booked units only
-                if (wt > per) wt = per > 1 ? per : 1;
+                share((pl.TP + wt) / s);
                 s = pieces_for(pl.TP + wt);
             }
             pl.TPU = pl.TP + (int)wt;
@@ -183,8 +183,7 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
                 w = NM * s;
                 pl.uniform = (int)s;
             } else {
-                // (ranges are short here: book at most two units, so that no range lies inside them only)
-                if (wt > 2) wt = 2;
+                share(std::max(2ll, NM * (pl.TP + wt) / kNumCU));
                 pl.TPU = pl.TP + (int)wt;
                 const long long U = NM * pl.TPU;
                 w = U < 2 * kNumCU ? (U + 1) / 2 : kNumCU;

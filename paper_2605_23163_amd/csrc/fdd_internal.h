@@ -55,7 +55,7 @@ struct AttnPlan {
     int key_tile;     // keys per streamed tile
     int TP;           // prefix tiles = ceil(L / key_tile)
     int splits;       // fp32 path: workgroups per M-tile
-    int TPU;          // bf16 path: units per M-tile = max(TP, 1)
+    int TPU;          // bf16 path: units per M-tile = TP + the units booked for private tiles
     int W;            // bf16 path: workgroups
     int uniform;      // bf16 path: > 0 when W = Hkv*MT*uniform, i.e. equal pieces per M-tile
     long long U;      // bf16 path: units in total

@@ -40,3 +40,36 @@ def test_ring(oracle, D, E, causal, splits):
                 err = np.abs(to_f64(out) - ref).max()
                 assert np.isfinite(err) and err <= 3 * 2.0**-9 * v_max
                 assert row_error(to_f64(out), ref) <= ROW_TOL
+
+
+# N, B, Hkv, L, E: more private tiles than a workgroup's share of the units (they are dealt to several), up to more than are booked
+# (64 units), a list of positions, and pieces without any tile
+MANY = [(40, 1, 2, 300, 0), (130, 1, 1, 64, 0), (130, 1, 1, 0, 70), (24, 3, 2, 200, 130), (5, 40, 2, 700, 37), (33, 1, 8, 1408, 1), (9, 96, 1, 130, 192)]
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("shape", MANY)
+def test_many_private_tiles(oracle, shape, D):
+    import paper_2605_23163_amd as F
+    N, B, Hkv, L, E = shape
+    print_case(test="attn_private", shape=shape, D=D)
+    rng = np.random.default_rng(N * 31 + L + E + D)
+    d = rand_attn(rng, N, B, L, 2 * Hkv, Hkv, D, W.BF16)
+    t = {k: to_dev(v) for k, v in d.items()}
+    kw, okw = {}, {}
+    if E:
+        e = [W.to_storage(rng.standard_normal((N, E, Hkv, D)).astype(np.float32), W.BF16) for _ in "kv"]
+        kw, okw = dict(ext_k=to_dev(e[0]), ext_v=to_dev(e[1]), E=E), dict(ext_k=e[0], ext_v=e[1], E=E)
+    ref = oracle.block_attn(d["q"], d["prefix_k"], d["prefix_v"], d["block_k"], d["block_v"], **okw).reshape(N * B, 2 * Hkv, D)
+    v_max = max(np.abs(to_f64(x)).max() for x in (t["block_v"], *([t["prefix_v"]] if L else []), *([kw["ext_v"]] if E else [])))
+    some = torch.arange(0, N * B, 3 if N * B > 50 else 2, dtype=torch.int32, device="cuda")
+    for pos in (None, some):
+        at = np.arange(N * B) if pos is None else pos.cpu().numpy()
+        out = torch.zeros_like(t["q"])
+        F.fdd_block_attn(t["q"], t["prefix_k"], t["prefix_v"], t["block_k"], t["block_v"], out=out,
+                         **kw, **({} if pos is None else dict(q_positions=pos)))
+        torch.cuda.synchronize()
+        got = to_f64(out).reshape(N * B, 2 * Hkv, D)[at]
+        err = np.abs(got - ref[at]).max()
+        assert np.isfinite(err) and err <= 3 * 2.0**-9 * v_max
+        assert row_error(got, ref[at]) <= ROW_TOL
