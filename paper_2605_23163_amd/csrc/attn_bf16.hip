@@ -500,13 +500,12 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
             // other, 1.5 to 2 us each, when the other workgroups had ended.  us per call: N=33, B=1, L=1408, Hq=8, Hkv=8, E=1 93.7 -> 14.4;
             // N=9, B=1, L=11904, D=64, E=37 32.6 -> 10.4; 200 drawn calls 1.18 in the geometric mean.)
             if (t_end > a.TP) {
-                n_tail = (wg_n_hi - wg_n_lo + 1) * ttpr;
+                n_tail = key_tiles(0, ttpr, wg_n_lo, wg_n_hi);
                 if (t_begin > a.TP || t_end < a.TPU) {
                     const FastDiv by = a.dBooked;
-                    const int q_ = fast_div(n_tail, by), r_ = n_tail - q_ * a.booked;
-                    auto tiles_before = [&](int unit) { return q_ * unit + fast_div(r_ * unit, by); };
-                    tail0 = tiles_before(max(t_begin - a.TP, 0));
-                    n_tail = tiles_before(t_end - a.TP) - tail0;
+                    const int all = n_tail;
+                    tail0 = key_cut(all, max(t_begin - a.TP, 0), a.booked, by);
+                    n_tail = key_cut(all, t_end - a.TP, a.booked, by) - tail0;
                 }
             }
         }

@@ -97,17 +97,19 @@ __host__ __device__ __forceinline__ int fast_div(int n, const FastDiv& f)
     return (int)((uint32_t)(((uint64_t)((uint32_t)n + 1u) * f.mul) >> 32) >> f.shift);
 }
 
-// fp32 path: key tiles of a row tile whose first and last row belong to rollouts n_lo and n_hi: `prefix` ones, and `per` for every
+// Key tiles of a row tile whose first and last row belong to rollouts n_lo and n_hi: `prefix` ones, and `per` for every
 // rollout from one to the other.  (A list of positions in another order than ascending gives undefined values, but may not
-// lead out of the arrays: where n_hi is below n_lo these are n_lo's private tiles, not a negative number of them.)
+// lead out of the arrays: where n_hi is below n_lo these are n_lo's private tiles, not a negative number of them.)  The bf16
+// path counts an M-tile's private tiles with it, whose prefix tiles are dealt separately.
 __host__ __device__ inline int key_tiles(int prefix, int per, int n_lo, int n_hi)
 {
     return prefix + ((n_hi > n_lo ? n_hi - n_lo : 0) + 1) * per;
 }
 
-// fp32 path: first key tile of wavefront `part` of the `parts` that share a row tile's n_tiles, floor(n_tiles part / parts).
+// First key tile of part `part` of the `parts` among which n_tiles are cut, floor(n_tiles part / parts).  fp32 path: the
+// wavefronts or workgroups that share a row tile; bf16 path: the units booked for an M-tile's private tiles.  n_tiles >= 0.
 // (A list of two far positions makes a row tile walk the private tiles of every rollout between them, up to 2^26 in all:
-// n_tiles * part may pass 2^31, the remainder's product stays below parts^2 = 2^18.)
+// n_tiles * part may pass 2^31, the remainder's product stays below parts^2 <= 2^18.)
 __host__ __device__ inline int key_cut(int n_tiles, int part, int parts, const FastDiv& by_parts)
 {
     const int base = fast_div(n_tiles, by_parts), rem = n_tiles - base * parts;

@@ -1,5 +1,6 @@
-// Checks the cut of an fp32 row tile's key tiles among its wavefronts (key_tiles and key_cut in fdd_internal.h, which the
-// kernels call) against 64-bit arithmetic, up to the most tiles a call can have, and for lists of positions in any order.  Host code only; built and run by
+// Checks the cut of a row tile's key tiles among those that share them (key_tiles and key_cut in fdd_internal.h, which the
+// kernels call): fp32, among wavefronts, against 64-bit arithmetic, up to the most tiles a call can have; bf16, an M-tile's
+// private tiles among the units booked for them; both for lists of positions in any order.  Host code only; built and run by
 // tests/test_f32_limits.py.
 #include <cstdio>
 
@@ -39,6 +40,24 @@ int main()
                         }
                         if (n_hi >= n_lo && n != prefix + (n_hi - n_lo + 1) * per && bad++ < 5) std::printf("%d tiles\n", n);
                     }
+    // bf16: whatever number of units is booked, the cuts at their borders ascend from none to all, so the segments of an M-tile
+    // have disjoint shares that add up, and no tile is of a rollout that there is not
+    for (int booked = 1; booked <= 64; ++booked) {
+        const FastDiv d = make_fastdiv((uint32_t)booked);
+        for (int per : {1, 2, 3, 1 << 18})
+            for (int n_lo = 0; n_lo < N; ++n_lo)
+                for (int n_hi = 0; n_hi < N; ++n_hi) {
+                    const int n = key_tiles(0, per, n_lo, n_hi);
+                    int before = 0;
+                    bool ok = n > 0 && n <= (N - n_lo) * per && (n_hi < n_lo || n == (n_hi - n_lo + 1) * per) && key_cut(n, 0, booked, d) == 0;
+                    for (int unit = 1; unit <= booked; ++unit) {
+                        const int t = key_cut(n, unit, booked, d);
+                        ok = ok && t >= before && t <= n;
+                        before = t;
+                    }
+                    if ((!ok || before != n) && bad++ < 5) std::printf("%d units booked, rollouts %d to %d, %d tiles each\n", booked, n_lo, n_hi, per);
+                }
+    }
     if (bad) return 1;
     std::puts("key cut: ok");
     return 0;

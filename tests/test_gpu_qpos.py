@@ -89,13 +89,16 @@ def test_degenerate_lists(F, oracle, dtype):
     assert torch.equal(out, full)
 
 
-@pytest.mark.parametrize("shape", [(9, 40, 33, 4, 2, 64), (9, 40, 2200, 14, 2, 128)])     # tiles of 16 or 32 rows, of 128
-def test_descending_lists_stay_within_the_arrays(F, shape):
-    # (undefined values, fp32: the number of a row tile's keys came out negative, and where to cut it far outside)
+# fp32: tiles of 16 or 32 rows, of 128.  bf16: M-tiles of 128 rows and, in the last shape, of 256, in pieces that end within the
+# units booked for private tiles
+@pytest.mark.parametrize("dtype", [W.BF16, W.F32])
+@pytest.mark.parametrize("shape", [(9, 40, 33, 4, 2, 64), (9, 40, 2200, 14, 2, 128), (40, 3, 300, 8, 4, 128), (64, 8, 700, 64, 8, 128)])
+def test_descending_lists_stay_within_the_arrays(F, shape, dtype):
+    # (undefined values: the number of a row tile's keys came out negative, and where to cut it far outside)
     N, B, L, Hq, Hkv, D = shape
-    print_case(test="qpos_descending", shape=shape)
+    print_case(test="qpos_descending", shape=shape, dtype=dtype)
     rng = np.random.default_rng(8)
-    d = rand_attn(rng, N, B, L, Hq, Hkv, D, W.F32)
+    d = rand_attn(rng, N, B, L, Hq, Hkv, D, dtype)
     t = {k: to_dev(v) for k, v in d.items()}
     pos = np.arange(N * B)[::-3].astype(np.int32).copy()
     rest = np.ones(N * B, dtype=bool)
