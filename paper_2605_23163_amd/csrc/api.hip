@@ -115,7 +115,7 @@ static F32Cut f32_cut(bool wide, long long row_tiles, long long tiles, int D, in
     return best;
 }
 
-bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
+bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool ample)
 {
     AttnPlan pl;
     pl.slots = 0;
@@ -131,22 +131,23 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
         NM = (long long)p.Hkv * batch * pl.MT;
     };
     bool partials;
-    auto cut_bf16 = [&](int rows) {
+    // Cuts for M-tiles of `rows` rows, with the private tiles of an M-tile at the workgroup that ends its units or (`deal`) wherever
+    // their units lie.  `longest`: units of the longest workgroup; `booked_all`: dealing them out would be the same cut.
+    long long longest;
+    bool booked_all;
+    auto cut_units = [&](int rows, bool deal) {
         set_rows(rows);
         // The private tiles of an M-tile (extension and block of every rollout its rows belong to) go through the masked path at
         // about 1.8 times the cost of a pipelined prefix tile.  They are booked as `wt` extra units behind the M-tile's prefix tiles
-        // (up to 64) and dealt to the workgroups with them.
+        // (up to 64) and go to the workgroups that these units go to.
         // (with a list of query positions a rollout contributes fewer rows: its average share stands in for B)
         const long long BG = p.n_q_positions > 0 ? std::max(1ll, (long long)p.n_q_positions * pl.G / p.N) : (long long)p.B * pl.G;
         const long long span_lo = (pl.mtile_rows + BG - 1) / BG;                 // rollouts an M-tile spans at least
         const long long span = span_lo + ((pl.mtile_rows % BG) != 0 && BG < (long long)pl.R ? 1 : 0);
         const long long private_tiles = (span < p.N ? span : p.N) *
                                         ((p.E + pl.key_tile - 1) / pl.key_tile + (p.B + pl.key_tile - 1) / pl.key_tile);
-        long long wt = std::min(std::max((private_tiles * 9 + 4) / 5, 1ll), 64ll);
-        // Up to one and a half times a workgroup's share of the units they are left to one workgroup: booked as its whole share, no
-        // piece lies inside them.  (Cut from one share on, N=14, B=64, L=75, Hq=14, Hkv=2 13.3 -> 15.1 us, from two on N=4, B=32, L=1024 12.7
-        // -> 12.9 and N=5, B=40, L=5003, D=64, E=37 not at all: two steps 56.4 -> 60.7; the mean over 200 drawn calls 1.186, 1.183 and 1.178.)
-        auto share = [&](long long per) { if (wt > per && 2 * wt <= 3 * per) wt = std::max(per, 1ll); };
+        const long long cost = std::max((private_tiles * 9 + 4) / 5, 1ll);
+        long long wt = std::min(cost, 64ll);
         auto pieces_for = [&](long long tpu) {
             // equal pieces per M-tile, of two units or more (one of them may have less); the fewest pieces that reach the shortest critical path
             long long smax = NM > 0 ? kNumCU / NM : 0;
@@ -172,8 +173,9 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
             // results for its two units (us per call, ranges / pieces: N=1, L=64 13.5/9.3; N=8, L=64 17.3/11.7; N=1, L=700
             // 13.5/12.6).  Otherwise equal contiguous unit ranges (stream-K).
             long long s = pieces_for(pl.TP + wt);
-            if (s >= 1) {
-                share((pl.TP + wt) / s);
+            if (s >= 1 && !deal) {
+                const long long per = (pl.TP + wt) / s;       // a piece must not lie inside the booked units only
+                if (wt > per) wt = per > 1 ? per : 1;
                 s = pieces_for(pl.TP + wt);
             }
             pl.TPU = pl.TP + (int)wt;
@@ -183,7 +185,8 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
                 w = NM * s;
                 pl.uniform = (int)s;
             } else {
-                share(std::max(2ll, NM * (pl.TP + wt) / kNumCU));
+                // (ranges are short here: book at most two units, so that no range lies inside them only)
+                if (wt > 2 && !deal) wt = 2;
                 pl.TPU = pl.TP + (int)wt;
                 const long long U = NM * pl.TPU;
                 w = U < 2 * kNumCU ? (U + 1) / 2 : kNumCU;
@@ -200,9 +203,38 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
         const long long upw = pl.U / pl.W;
         pl.max_seg = pl.uniform > 0 ? pl.uniform : (int)((pl.TPU + upw - 1) / upw) + 1;
         partials = pl.W != NM;
+        // (what is not booked comes on top, with every M-tile that ends in a range)
+        longest = (pl.U + w - 1) / w;
+        longest += deal ? 0 : (cost - wt) * ((longest + pl.TPU - 1) / pl.TPU);
+        booked_all = wt == std::min(cost, 64ll);
     };
-    if (p.dtype == FDD_BF16) {
-        cut_bf16(256);
+    // Private tiles are dealt out where that shortens the longest workgroup by more than the further segments cost, each a set-up and
+    // a partial result: a unit for pieces of 128 rows; four for pieces of 256, whose wavefronts pass over the private tiles of
+    // other rollouts, so that these cost less than they are booked with; three for ranges, some of which then end in one more
+    // M-tile.  Never if equal pieces would become ranges.  us per call, one place / dealt, in brackets the units of the longest workgroup,
+    // Hq = 28, Hkv = 4, D = 128 unless said:
+    //   pieces of 128 rows: N=1, B=32, L=192 [3/2] 10.0/9.0; N=4, B=32, L=1024 [4/3] 14.1/13.0; N=8, B=32, L=128 [4/2] 10.9/11.2; N=16,
+    //   L=128 [4/3] 12.9/13.1; N=2, B=64, L=192 [5/2] 12.7/10.3; Hq = 16, N=10, B=32, L=173 [3/2] 11.6/12.1; D = 64, Hq = 14, Hkv = 2: N=8,
+    //   B=40, L=3008, E=40 [9/8] 15.3/14.4; N=16, B=32, L=100 [4/2] 9.3/9.7; many rollouts, Hq = Hkv = 8, N=33, B=1, L=1408, E=1 [119/3]
+    //   93.4/12.9; drawn calls that gain one unit 1.02 in the geometric mean (23), two 1.05 (30), three 1.12 (24), four to seven 1.21 (48);
+    //   pieces of 256: Hq = 14, Hkv = 2, N=41, B=32, L=151, D = 64 [5/3] 11.9/12.5; half of the positions of N=31, B=32, L=24 [6/3] 17.2/18.4;
+    //   N=50, B=8, L=108 [11/3] 18.2/18.4; N=9, B=65, L=585, E=65, listed [13/5] 20.2/18.4; N=7, B=70, L=320, Hq = 32, Hkv = 8, E=140, listed
+    //   [24/7] 26.0/21.7;
+    //   ranges: N=55, B=32, L=64 [7/6] 25.6/28.2; N=41, B=32, L=326 [9/7] 28.5/29.4; Hq = 32, Hkv = 8, N=15, B=70, L=100 [9/6] 29.4/27.8;
+    //   Hq = 32, Hkv = 8, N=41, B=64, L=1152, E=128 [34/31] 82.4/79.2;
+    //   Hq = 14, Hkv = 2, N=24, B=65, L=4864, E=130 [43/32] 74.5/64.4; a gain of one unit or two
+    //   0.97 (17 drawn calls), of three or four 1.04 (11);
+    //   pieces to ranges: Hq = 14, Hkv = 2, N=14, B=64, L=75 13.4/15.1; N=44, B=40, L=94 20.5/23.9.
+    auto cut_bf16 = [&](int rows, bool may_deal) {
+        cut_units(rows, false);
+        if (!may_deal || booked_all) return;
+        const long long whole = longest;
+        const bool pieces = pl.uniform > 0;
+        cut_units(rows, true);
+        if (longest + (!pieces ? 3 : rows == 128 ? 1 : 4) > whole || (pieces && pl.uniform == 0)) cut_units(rows, false);
+    };
+    auto cut_rows = [&](bool may_deal) {
+        cut_bf16(256, may_deal);
         // M-tiles of 128 rows (workgroups of 4 wavefronts, one per SIMD) while the call is short: alone in a compute unit such a
         // workgroup takes 0.68 us a tile where one of 8 takes 1.09 (D = 128), starts on fewer tiles, and its segments are half as
         // large; long calls fetch K and V twice as often.  Up to 9 units per compute unit of the 256-row plan, D = 64 5 (either is within a
@@ -217,9 +249,18 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
         //   17.2/16.7, plain 17.3/17.5; N=8, L=6000 [10.9] 20.3/22.2; N=16, L=4096 [15], plain 24.9/27.5.
         const int uniform256 = pl.uniform;
         if (pl.U <= (p.D == 128 ? 9 : 5) * (long long)kNumCU) {
-            cut_bf16(128);
-            if (pl.uniform == 0 && (uniform256 > 0 || NM > kNumCU)) cut_bf16(256);
+            cut_bf16(128, may_deal);
+            if (pl.uniform == 0 && (uniform256 > 0 || NM > kNumCU)) cut_bf16(256, may_deal);
         }
+    };
+    if (p.dtype == FDD_BF16) {
+        // Calls that have one workgroup for each M-tile with its private tiles in one place stay so: their sums are in fp32 up to the one
+        // rounding of the output (off from 64 bits by 2.0e-3 in norm, with averages that go through the workspace in bf16 2.6e-3), and
+        // they need neither scratch nor a merge.  With short prefixes the second launch costs what the shorter workgroups save: us per
+        // call, one workgroup / dealt, Hq = 28, Hkv = 4, B = 32: L=64, N=2 9.7/8.9, N=8 10.0/10.9; L=0, N=4 8.5/9.2, N=16 9.2/12.3; D = 64,
+        // Hq = 14, Hkv = 2, L=64, N=4 7.4/8.2.  (With many rollouts an M-tile it would not: B=1, L=8, N=10 18.4/10.5.)
+        cut_rows(false);
+        if (ample && p.splits == 0 && partials && !booked_all) cut_rows(true);
         // Ring slots per operand: four hide more of the memory's latency, two start earlier, with fewer requests in flight, and do
         // better where nearly every request goes to memory (one M-tile per KV head).  us per call, prefixes from memory, 4 / 2 slots, in
         // brackets the units per workgroup: several M-tiles, D = 128, N=1, L=2048 [2] 10.4/10.1; N=3, L=1279, Hq=32, Hkv=8 [2]
@@ -257,7 +298,7 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide)
             // (a larger scale multiplies what those products lose of keys below 2^-110; a smaller one gives weight to scores that
             // overflow with their factor on Q)
             const bool usual_scale = !(p.scale > 0.f) || (p.scale >= 0x1p-30f && p.scale <= 0x1p10f);
-            if (f32_wide && usual_scale && fits && wide_tiles >= 2 * wide.splits && wide.us < narrow.us + (narrow.splits > 1 ? 3.0 : 0.0)) {
+            if (ample && usual_scale && fits && wide_tiles >= 2 * wide.splits && wide.us < narrow.us + (narrow.splits > 1 ? 3.0 : 0.0)) {
                 s = wide.splits;
                 tiles = wide_tiles;
             } else {
@@ -376,16 +417,17 @@ fdd_status fdd_block_attn(const fdd_attn_params* p)
     make_attn_plan(*p, &plan);
     size_t need = plan.ws_o_bytes + plan.ws_ml_bytes + plan.ws_vt_bytes;
     const size_t given = p->workspace && (reinterpret_cast<uintptr_t>(p->workspace) & 255u) == 0 ? p->workspace_bytes : 0;
-    if (need >= given + 256 && p->dtype == FDD_F32 && plan.mtile_rows == kF32WideRowTile) {
-        // 128-row tiles always leave partial results, the smaller ones fewer and often none: a call that brings what those need
-        // (less than the query says, which asks for the faster ones) runs on them.  (Sizes come in steps of 256 bytes: one that misses the
-        // query's by less is a slip of the caller's and refused, as it always was.)
-        AttnPlan narrow;
-        make_attn_plan(*p, &narrow, false);
-        const size_t narrow_need = narrow.ws_o_bytes + narrow.ws_ml_bytes;
-        if (narrow_need <= given) {
-            plan = narrow;
-            need = narrow_need;
+    if (need >= given + 256 && (p->dtype == FDD_BF16 || plan.mtile_rows == kF32WideRowTile)) {
+        // A call that brings less than the query says, which asks for the fastest plan, but what the plan without 128-row tiles (fp32,
+        // which always leave partial results) or with an M-tile's private tiles in one place (bf16: fewer segments, often one)
+        // needs, runs on that.  (Sizes come in steps of 256 bytes: one that misses the query's by less is a slip of the
+        // caller's and refused, as it always was.)
+        AttnPlan small;
+        make_attn_plan(*p, &small, false);
+        const size_t small_need = small.ws_o_bytes + small.ws_ml_bytes + small.ws_vt_bytes;
+        if (small_need <= given) {
+            plan = small;
+            need = small_need;
         }
     }
     if (need > 0) {

@@ -66,8 +66,9 @@ struct AttnPlan {
     bool packed;         // bf16 path: the kernel reads repacked V (from the workspace or from the caller)
 };
 
-// `f32_wide`: fp32 calls may take 128-row tiles
-bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool f32_wide = true);
+// Without `ample` the plan for calls that bring less scratch than they are asked for: fp32 calls take no 128-row tiles, bf16
+// calls leave the private tiles of an M-tile to one workgroup.
+bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool ample = true);
 
 // Records the message fdd_last_error() returns on this thread; returns `code`.
 fdd_status set_error(fdd_status code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));

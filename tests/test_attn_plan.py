@@ -1,0 +1,57 @@
+"""How bf16 attention calls are cut (make_attn_plan): which keep one workgroup for each M-tile and need no scratch, and what calls with
+less scratch than they are asked for run on.  Host arithmetic, checked without a GPU."""
+import collections
+import os
+
+import pytest
+
+from tests.test_f32_limits import ROOT, run_host
+
+Plan = collections.namedtuple("Plan", "rows slots W pieces units prefix need small_need")
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    from paper_2605_23163_amd import binding, build
+    if not os.path.exists(binding.library_path()):
+        build.build()
+    lib = os.path.join(ROOT, "paper_2605_23163_amd")
+
+    def run(shapes):
+        """Plans of calls (N, B, L, Hq, Hkv, D[, E[, length of the list[, splits]]])."""
+        args = [str(x) for s in shapes for x in (*s, 0, 0, 0)[:9]]
+        out = run_host("attn_plan_main", tmp_path_factory.mktemp("plan"), ["-L" + lib, "-lfdd", "-Wl,-rpath," + lib], args)
+        return [Plan(*map(int, line.split())) for line in out.splitlines()]
+    return run
+
+
+def test_short_prefixes_need_no_scratch(plans):
+    # (two launches and an average rounded to bf16 on its way through the workspace would cost more than the shorter workgroups save)
+    shapes = [(N, B, L, Hq, Hkv, D) for Hq, Hkv in ((28, 4), (14, 2)) for D in (64, 128) for B in (32, 64) for N in (1, 2, 4)
+              for L in (0, 1, 32, 64)] + [(8, 32, L, 28, 4, 128) for L in (0, 32, 64)] + [(16, 32, 0, 28, 4, 128), (130, 1, 64, 2, 1, 128)]
+    for shape, p in zip(shapes, plans(shapes)):
+        assert p.need == 0 and p.pieces == 1, (shape, p)
+
+
+def test_private_tiles_are_dealt_out_where_that_pays(plans):
+    # one unit less in the longest of the 128-row pieces; more of them in pieces of 256 rows and in ranges, where fewer do not pay;
+    # pieces do not become ranges.  (pieces, units, prefix units)
+    want = {(1, 32, 192, 28, 4, 128): (3, 5, 3), (4, 32, 1024, 28, 4, 128): (7, 20, 16), (33, 1, 1408, 8, 8, 128, 1): (29, 86, 22),
+            (41, 32, 151, 14, 2, 64): (3, 6, 3), (9, 65, 585, 28, 4, 128, 65, 409): (5, 25, 10), (41, 32, 326, 28, 4, 128): (0, 8, 6),
+            (24, 65, 4864, 14, 2, 128, 130): (0, 94, 76), (14, 64, 75, 14, 2, 128): (2, 5, 2), (44, 40, 94, 14, 2, 128): (2, 5, 2)}
+    got = plans(list(want))
+    for (shape, w), p in zip(want.items(), got):
+        assert (p.pieces, p.units, p.prefix) == w, (shape, p)
+
+
+def test_no_call_needs_scratch_for_the_sake_of_its_private_tiles(plans):
+    import random
+    rng = random.Random(4)
+    shapes = []
+    for _ in range(600):
+        Hq, Hkv = rng.choice(((28, 4), (14, 2), (32, 8), (16, 4), (8, 8), (4, 1), (64, 64)))
+        N, B = int(2 ** rng.uniform(0, 8)), rng.choice((1, 3, 8, 32, 40, 65, 200))
+        shapes.append((N, B, rng.choice((0, rng.randrange(400), int(2 ** rng.uniform(6, 15)))), Hq, Hkv, rng.choice((64, 128)),
+                       rng.choice((0, 0, B, 37, 300)), rng.choice((0, 0, max(1, N * B // 3))), rng.choice((0, 0, 0, 3))))
+    for shape, p in zip(shapes, plans(shapes)):
+        assert (p.need == 0) == (p.small_need == 0), (shape, p)

@@ -9,14 +9,14 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def run_host(name, tmp_path):
+def run_host(name, tmp_path, link=(), args=()):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if not (os.path.exists(hipcc) or shutil.which(hipcc)):
         pytest.skip("hipcc not found")
     exe = str(tmp_path / name)
     for cmd in ([hipcc, "--offload-host-only", "-O1", "-std=c++17", "-I" + os.path.join(ROOT, "include"),
                  "-I" + os.path.join(ROOT, "paper_2605_23163_amd", "csrc"), "-x", "hip",
-                 os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", exe], [exe]):
+                 os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", exe, *link], [exe, *args]):
         p = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         assert p.returncode == 0, " ".join(cmd) + "\n" + p.stdout[-4000:]
     return p.stdout

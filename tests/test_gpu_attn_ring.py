@@ -73,3 +73,45 @@ def test_many_private_tiles(oracle, shape, D):
         err = np.abs(got - ref[at]).max()
         assert np.isfinite(err) and err <= 3 * 2.0**-9 * v_max
         assert row_error(got, ref[at]) <= ROW_TOL
+
+
+# N, B, Hq, Hkv, L, E, D, pieces of an M-tile (128 rows) with its private tiles in one place
+LESS = [(20, 1, 28, 4, 138, 37, 128, 3), (40, 3, 8, 4, 300, 0, 64, 3)]
+
+
+@pytest.mark.parametrize("shape", LESS)
+def test_less_scratch(oracle, shape):
+    # a call whose scratch is too small for the many pieces that its private tiles are dealt to, but enough for the few that there are
+    # without, runs on those
+    import ctypes as C
+
+    import paper_2605_23163_amd.binding as b
+    N, B, Hq, Hkv, L, E, D, pieces = shape
+    print_case(test="attn_less_scratch", shape=shape)
+    rng = np.random.default_rng(N + L)
+    d = rand_attn(rng, N, B, L, Hq, Hkv, D, W.BF16)
+    t = {k: to_dev(v) for k, v in d.items()}
+    ext = [W.to_storage(rng.standard_normal((N, max(E, 1), Hkv, D)).astype(np.float32), W.BF16) for _ in "kv"]
+    kw = dict(ext_k=ext[0], ext_v=ext[1], E=E) if E else {}
+    ref = oracle.block_attn(d["q"], d["prefix_k"], d["prefix_v"], d["block_k"], d["block_v"], **kw)
+    dev_ext = [to_dev(x) for x in ext]
+    out = torch.empty_like(t["q"])
+    p = b._attn_params(*(t[k] for k in ("q", "prefix_k", "prefix_v", "block_k", "block_v")), None, out, None, 0)
+    p.stream = torch.cuda.current_stream().cuda_stream
+    if E:
+        p.ext_k, p.ext_v, p.E, p.ext_capacity = dev_ext[0].data_ptr(), dev_ext[1].data_ptr(), E, E
+    lib, ok, refused = b.load_library(), 0, 5
+    need = lib.fdd_block_attn_workspace(C.byref(p))
+    small = Hkv * (-(-N * B * (Hq // Hkv) // 128)) * pieces * 128 * (2 * D + 8)
+    assert small < need
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    assert ws.data_ptr() % 256 == 0
+    for size, status in ((need, ok), (need - 1, refused), (need - 256, ok), (small, ok), (small - 256, refused), (0, refused)):
+        out.fill_(7.0)
+        p.workspace, p.workspace_bytes = ws.data_ptr(), size
+        assert lib.fdd_block_attn(C.byref(p)) == status, size
+        torch.cuda.synchronize()
+        if status == ok:
+            assert row_error(to_f64(out), ref) <= ROW_TOL
+        else:
+            assert bool((out == 7.0).all())
