@@ -261,14 +261,21 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool ample)
         // Hq = 14, Hkv = 2, L=64, N=4 7.4/8.2.  (With many rollouts an M-tile it would not: B=1, L=8, N=10 18.4/10.5.)
         cut_rows(false);
         if (ample && p.splits == 0 && partials && !booked_all) cut_rows(true);
-        // Ring slots per operand: four hide more of the memory's latency, two start earlier, with fewer requests in flight, and do
-        // better where nearly every request goes to memory (one M-tile per KV head).  us per call, prefixes from memory, 4 / 2 slots, in
-        // brackets the units per workgroup: several M-tiles, D = 128, N=1, L=2048 [2] 10.4/10.1; N=3, L=1279, Hq=32, Hkv=8 [2]
-        // 12.9/12.5; N=1, L=6518 [3.2] 13.6/13.1; B=70, L=3008, Hq=32, Hkv=8 [4.4] 16.1/15.7; N=2, L=6239 [6.1] 16.3/16.1; B=40, L=14464,
-        // Hq=16 [7.1] 17.2/18.2; N=2, L=18304, Hq=16 [8.9] 20.6/21.9; N=3, B=8, L=24960 [12] 21.3/24.4; N=8, L=4096, V laid out [16]
-        // 23.6/28.7; D = 64, N=8, L=1024 [4] 10.2/10.1, L=2048 [8] 12.5/13.2, N=1, L=20000 [10] 14.4/16.1; one M-tile, D = 128, Hkv=8, N=2,
-        // B=8, L=14976, Hq=8 [7.3] 16.9/16.4, N=2, B=64, L=13888, E=64, Hq=8 [6.9] 22.6/21.0.
-        pl.slots = pl.mtile_rows == 128 && (pl.MT == 1 || pl.U < 6ll * pl.W) ? 2 : 4;
+        // Ring slots per operand: four hide more of the memory's latency, two start earlier, with fewer requests in flight, do better
+        // where nearly every request goes to memory (one M-tile per KV head), and leave room for a second workgroup on a compute unit
+        // (D = 128: 80 KB of LDS against 144), which a call of more workgroups than compute units has.  us per call, prefixes from
+        // memory, 4 / 2 slots, in brackets the units per workgroup:
+        //   several M-tiles, D = 128, N=1, L=2048 [2] 10.4/10.1; N=3, L=1279, Hq=32, Hkv=8 [2] 12.9/12.5; N=1, L=6518 [3.2] 13.6/13.1;
+        //   B=70, L=3008, Hq=32, Hkv=8 [4.4] 16.1/15.7; N=2, L=6239 [6.1] 16.3/16.1; B=40, L=14464, Hq=16 [7.1] 17.2/18.2; N=2, L=18304,
+        //   Hq=16 [8.9] 20.6/21.9; N=3, B=8, L=24960 [12] 21.3/24.4; N=8, L=4096, V laid out [16] 23.6/28.7; D = 64, N=8, L=1024 [4]
+        //   10.2/10.1, L=2048 [8] 12.5/13.2, N=1, L=20000 [10] 14.4/16.1;
+        //   one M-tile, D = 128, plain / V laid out: Hq = Hkv = 8, N=2, B=64, L=8000 [4.0] 19.9/17.3, 18.7/16.1, L=14976 [7.4] 24.5/23.0,
+        //   21.7/20.8, B=8, L=8000 13.9/14.1, 13.3/13.6, L=14976 19.1/20.1, 17.0/16.7; Hq = 28, Hkv = 4, N=1, B=16, L=14976 [3.7] 19.5/16.1,
+        //   18.1/15.2, L=30000 [7.4] 24.1/22.9, 20.4/20.0; Hq = Hkv = 16, N=1, B=32, L=2000 [2.1] 11.4/10.7, L=8000 [7.9] 19.6/20.5,
+        //   17.2/18.2; D = 64 within 4 % of each other (longer ones, from 9 and 5 units on, have 256 rows);
+        //   more workgroups than compute units (`splits`): N=8, L=4096 in 5 pieces 37.1/30.1, 6 34.0/27.4, 8 32.4/26.3; N=16, L=2000 in 4
+        //   31.1/26.8; D = 64, Hq = 14, Hkv = 2, N=16, L=2000 in 5 16.6/16.0.
+        pl.slots = pl.mtile_rows == 128 && (pl.MT == 1 || pl.U < 6ll * pl.W || pl.W > kNumCU) ? 2 : 4;
     } else {
         auto cut_f32 = [&](int rows, int key_tile) {
             set_rows(rows);

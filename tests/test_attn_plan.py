@@ -44,6 +44,17 @@ def test_private_tiles_are_dealt_out_where_that_pays(plans):
         assert (p.pieces, p.units, p.prefix) == w, (shape, p)
 
 
+def test_ring_slots(plans):
+    # four slots per operand for workgroups of 256 rows, and of 128 with 6 units or more where several M-tiles share a prefix and there are
+    # no more workgroups than compute units (two of four slots do not fit one)
+    want = {(1, 32, 2048, 28, 4, 128): 2, (8, 32, 4096, 28, 4, 128): 4, (2, 64, 14976, 8, 8, 128): 2, (1, 16, 14976, 28, 4, 128): 2,
+            (3, 44, 64 * 4, 2, 1, 128, 0, 0, 1): 4, (3, 44, 64 * 3, 2, 1, 128, 0, 0, 1): 2, (8, 32, 1024, 28, 4, 64): 2, (8, 32, 2048, 28, 4, 64): 4,
+            (8, 32, 4096, 28, 4, 128, 0, 0, 4): 4, (8, 32, 4096, 28, 4, 128, 0, 0, 5): 2, (8, 32, 4096, 28, 4, 128, 0, 0, 8): 2,
+            (16, 64, 16384, 28, 4, 128): 4, (16, 64, 16384, 28, 4, 128, 0, 0, 4): 4}
+    for (shape, slots), p in zip(want.items(), plans(list(want))):
+        assert p.slots == slots and (p.rows == 256) == (shape[0] == 16), (shape, p)
+
+
 def test_no_call_needs_scratch_for_the_sake_of_its_private_tiles(plans):
     import random
     rng = random.Random(4)
