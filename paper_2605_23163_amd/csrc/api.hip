@@ -253,14 +253,34 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool ample)
             if (pl.uniform == 0 && (uniform256 > 0 || NM > kNumCU)) cut_bf16(256, may_deal);
         }
     };
+    // stacked rows, over all KV heads, of M-tiles that several workgroups work on
+    auto shared_rows = [&]() -> long long {
+        if (pl.uniform > 0) return pl.uniform == 1 ? 0 : (long long)p.Hkv * batch * pl.R;
+        long long n = 0, last = -1;
+        for (long long w = 1, base = pl.U / pl.W, rem = pl.U % pl.W; w < pl.W; ++w) {
+            const long long u = w * base + std::min(w, rem), m = u / pl.TPU;       // (ranges: 256 at most)
+            if (u == m * pl.TPU || m == last) continue;
+            n += m % pl.MT == pl.MT - 1 ? pl.R - (pl.MT - 1) * pl.mtile_rows : pl.mtile_rows;
+            last = m;
+        }
+        return n;
+    };
     if (p.dtype == FDD_BF16) {
         // Calls that have one workgroup for each M-tile with its private tiles in one place stay so: their sums are in fp32 up to the one
         // rounding of the output (off from 64 bits by 2.0e-3 in norm, with averages that go through the workspace in bf16 2.6e-3), and
         // they need neither scratch nor a merge.  With short prefixes the second launch costs what the shorter workgroups save: us per
         // call, one workgroup / dealt, Hq = 28, Hkv = 4, B = 32: L=64, N=2 9.7/8.9, N=8 10.0/10.9; L=0, N=4 8.5/9.2, N=16 9.2/12.3; D = 64,
         // Hq = 14, Hkv = 2, L=64, N=4 7.4/8.2.  (With many rollouts an M-tile it would not: B=1, L=8, N=10 18.4/10.5.)
+        // Nor do ranges that end with their M-tiles move into them: as many rows as before have fp32 sums.  (One call in 120 of a sweep;
+        // us per call, one place / dealt: N=27, B=96, L=91, Hq=32, Hkv=8 38.6/44.7; D = 64: N=45, B=96, L=74, Hq=32, Hkv=8 33.8/37.3, N=43,
+        // B=40, L=64, E=80 22.5/24.4, N=32, B=65, L=72, Hq=32, Hkv=8, E=65 33.4/30.7; N=36, B=70, L=284, E=70 49.9/48.5, off from 64 bits by
+        // 2.47e-3/2.66e-3.)
         cut_rows(false);
-        if (ample && p.splits == 0 && partials && !booked_all) cut_rows(true);
+        if (ample && p.splits == 0 && partials && !booked_all) {
+            const long long shared = shared_rows();
+            cut_rows(true);
+            if (shared_rows() > shared) cut_rows(false);
+        }
         // Ring slots per operand: four hide more of the memory's latency, two start earlier, with fewer requests in flight, do better
         // where nearly every request goes to memory (one M-tile per KV head), and leave room for a second workgroup on a compute unit
         // (D = 128: 80 KB of LDS against 144), which a call of more workgroups than compute units has.  us per call, prefixes from
