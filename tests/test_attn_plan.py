@@ -9,6 +9,12 @@ from tests.test_f32_limits import ROOT, run_host
 
 Plan = collections.namedtuple("Plan", "rows slots W pieces units prefix need small_need finished small_finished")
 
+# N, B, L, Hq, Hkv, D, E: more private tiles than prefix tiles, cut inside the units booked for them, in every form of plan: (rows of
+# an M-tile, ring slots, equal pieces or 0: ranges).  tests/test_gpu_attn_ring.py runs them.
+DEALT = {(33, 1, 1408, 8, 8, 128, 1): (128, 2, 29), (33, 2, 64, 32, 8, 128, 130): (128, 4, 10), (33, 2, 64, 32, 8, 64, 130): (128, 4, 10),
+         (77, 8, 40, 28, 4, 128, 37): (128, 4, 0), (33, 8, 64, 32, 8, 128, 130): (256, 4, 6), (96, 4, 64, 56, 8, 128, 37): (256, 4, 0),
+         (96, 4, 64, 56, 8, 64, 37): (256, 4, 0)}
+
 
 @pytest.fixture(scope="module")
 def plans(tmp_path_factory):
@@ -42,6 +48,13 @@ def test_private_tiles_are_dealt_out_where_that_pays(plans):
     got = plans(list(want))
     for (shape, w), p in zip(want.items(), got):
         assert (p.pieces, p.units, p.prefix) == w, (shape, p)
+
+
+def test_every_form_of_plan_deals_private_tiles_out(plans):
+    for (shape, form), p in zip(DEALT.items(), plans(list(DEALT))):
+        m_tiles = shape[4] * -(-shape[0] * shape[1] * (shape[3] // shape[4]) // p.rows)
+        booked, longest = p.units - p.prefix, -(-m_tiles * p.units // p.W)
+        assert (p.rows, p.slots, p.pieces) == form and booked > longest > 2, (shape, p)
 
 
 def test_ring_slots(plans):

@@ -8,6 +8,7 @@ import torch
 
 import fdd_workloads as W
 from tests.gpu_util import ROW_TOL, print_case, rand_attn, row_error, to_dev, to_f64
+from tests.test_attn_plan import DEALT
 
 pytestmark = pytest.mark.gpu
 
@@ -73,6 +74,26 @@ def test_many_private_tiles(oracle, shape, D):
         err = np.abs(got - ref[at]).max()
         assert np.isfinite(err) and err <= 3 * 2.0**-9 * v_max
         assert row_error(got, ref[at]) <= ROW_TOL
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("shape", DEALT)
+def test_every_form_of_plan(oracle, shape, causal):
+    import paper_2605_23163_amd as F
+    N, B, L, Hq, Hkv, D, E = shape
+    print_case(test="attn_dealt", shape=shape, causal=causal)
+    rng = np.random.default_rng(N + L + E + D)
+    d = rand_attn(rng, N, B, L, Hq, Hkv, D, W.BF16)
+    t = {k: to_dev(v) for k, v in d.items()}
+    e = [W.to_storage(rng.standard_normal((N, E + 3, Hkv, D)).astype(np.float32), W.BF16) for _ in "kv"]
+    kw = dict(ext_k=to_dev(e[0]), ext_v=to_dev(e[1]), E=E, causal_block=causal)
+    ref = oracle.block_attn(d["q"], d["prefix_k"], d["prefix_v"], d["block_k"], d["block_v"], causal_block=causal, ext_k=e[0], ext_v=e[1], E=E)
+    v_max = max(np.abs(to_f64(x)).max() for x in (t["prefix_v"], t["block_v"], kw["ext_v"]))
+    for pk in (None, F.fdd_prefix_pack(t["prefix_v"]) if L >= 64 else None):
+        got = to_f64(F.fdd_block_attn(t["q"], t["prefix_k"], t["prefix_v"], t["block_k"], t["block_v"], prefix_v_packed=pk, **kw))
+        err = np.abs(got - ref).max()
+        assert np.isfinite(err) and err <= 3 * 2.0**-9 * v_max
+        assert row_error(got, ref) <= ROW_TOL
 
 
 # N, B, Hq, Hkv, L, E, D, pieces of an M-tile (128 rows) with its private tiles in one place
