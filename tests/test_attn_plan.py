@@ -64,8 +64,16 @@ def test_ring_slots(plans):
             (3, 44, 64 * 4, 2, 1, 128, 0, 0, 1): 4, (3, 44, 64 * 3, 2, 1, 128, 0, 0, 1): 2, (8, 32, 1024, 28, 4, 64): 2, (8, 32, 2048, 28, 4, 64): 4,
             (8, 32, 4096, 28, 4, 128, 0, 0, 4): 4, (8, 32, 4096, 28, 4, 128, 0, 0, 5): 2, (8, 32, 4096, 28, 4, 128, 0, 0, 8): 2,
             (16, 64, 16384, 28, 4, 128): 4, (16, 64, 16384, 28, 4, 128, 0, 0, 4): 4}
+    want.update({(1, 140, 64 * t, 20, 20, D): slots for D in (64, 128) for t, slots in ((29, 2), (30, 4))})
     for (shape, slots), p in zip(want.items(), plans(list(want))):
         assert p.slots == slots and (p.rows == 256) == (shape[0] == 16), (shape, p)
+
+
+def test_rows_of_an_m_tile(plans):
+    # 128 up to 9 units per compute unit of the plan with 256 rows at D = 128, 5 at D = 64 (64 KV heads of one M-tile, 2 units for the block)
+    want = {(1, 2, 64 * t, 64, 64, D): rows for D, t, rows in ((64, 18, 128), (64, 19, 256), (128, 34, 128), (128, 35, 256))}
+    for (shape, rows), p in zip(want.items(), plans(list(want))):
+        assert p.rows == rows, (shape, p)
 
 
 def test_ranges_that_end_with_their_m_tiles(plans):

@@ -1,7 +1,8 @@
-"""Both M-tile sizes of the bf16 path, 256 rows (8 wavefronts, ring of 4 tiles) and 128 (4 wavefronts, ring of 2): row counts
-at the edges of a wavefront's 32 and of both tiles, key runs of 0 full tiles and more, ragged ends, several pieces, and calls
-on both sides of the lines between the two sizes (more than 256 M-tiles of 128 rows; with V laid out 9 units per compute unit at
-D = 128, 5 at D = 64: 64 KV heads of 34 / 35 and 18 / 19 prefix tiles; with plain V 6 and 4: 22 / 23 and 14 / 15).
+"""Both M-tile sizes of the bf16 path, 256 rows (8 wavefronts, four ring slots per operand) and 128 (4 wavefronts, two slots or
+four): row counts at the edges of a wavefront's 32 and of both tiles, key runs of 0 full tiles and more, ragged ends, several
+pieces, and calls on both sides of the lines between them: more than 256 M-tiles of 128 rows; 9 units per compute unit at D = 128, 5
+at D = 64 (64 KV heads of 34 / 35 and 18 / 19 prefix tiles); 6 units a workgroup, from which on it has four slots (20 KV heads of
+29 / 30 tiles).  test_attn_plan.py checks on the host that these are the two sides.
 
 Tolerance: probabilities, averages and outputs are each rounded to bf16, 2^-9 of a value that is no larger than the largest
 element of V: 3 x 2^-9 of that in all; and each row to its own norm."""
@@ -20,10 +21,11 @@ LARGE = [(1, 300, 100, L) for L in (0, 40, 64, 130, 192, 256, 321, 600)] + \
 SMALL = [(1, B, 3, L) for B in (1, 31, 32, 33, 127, 128, 129, 160) for L in (64, 500)] + \
         [(1, 70, 2, L) for L in (0, 10, 63, 65, 128, 129, 1024, 2049)] + [(5, 50, 2, 700), (7, 18, 1, 333)]
 LINE = [(1, 2, 64, 64 * t) for t in (14, 15, 18, 19, 22, 23, 34, 35)]
+SLOTS = [(1, 140, 20, 64 * t) for t in (29, 30)]
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("shape", LARGE + SMALL + LINE)
+@pytest.mark.parametrize("shape", LARGE + SMALL + LINE + SLOTS)
 def test_rows_and_tiles(oracle, shape, D):
     import paper_2605_23163_amd as F
     N, B, Hkv, L = shape
