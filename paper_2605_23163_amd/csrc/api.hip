@@ -3,6 +3,7 @@
 #include <cstdint>
 #include <cstdarg>
 #include <cstdio>
+#include <numeric>
 
 #include "fdd_internal.h"
 #include <algorithm>
@@ -144,8 +145,8 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool ample)
         const long long BG = p.n_q_positions > 0 ? std::max(1ll, (long long)p.n_q_positions * pl.G / p.N) : (long long)p.B * pl.G;
         const long long span_lo = (pl.mtile_rows + BG - 1) / BG;                 // rollouts an M-tile spans at least
         const long long span = span_lo + ((pl.mtile_rows % BG) != 0 && BG < (long long)pl.R ? 1 : 0);
-        const long long private_tiles = (span < p.N ? span : p.N) *
-                                        ((p.E + pl.key_tile - 1) / pl.key_tile + (p.B + pl.key_tile - 1) / pl.key_tile);
+        const long long per_rollout = (p.E + pl.key_tile - 1) / pl.key_tile + (p.B + pl.key_tile - 1) / pl.key_tile;
+        const long long private_tiles = (span < p.N ? span : p.N) * per_rollout;
         const long long cost = std::max((private_tiles * 9 + 4) / 5, 1ll);
         long long wt = std::min(cost, 64ll);
         auto pieces_for = [&](long long tpu) {
@@ -203,20 +204,29 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool ample)
         const long long upw = pl.U / pl.W;
         pl.max_seg = pl.uniform > 0 ? pl.uniform : (int)((pl.TPU + upw - 1) / upw) + 1;
         partials = pl.W != NM;
-        // (what is not booked comes on top, with every M-tile that ends in a range)
+        // (What is not booked comes on top, with every M-tile that ends in a range; of the rollouts that an M-tile can span: the
+        // first row's place in its rollout is a multiple of what row counts of both have in common.)
         longest = (pl.U + w - 1) / w;
-        longest += deal ? 0 : (cost - wt) * ((longest + pl.TPU - 1) / pl.TPU);
+        if (!deal) {
+            const long long most = p.n_q_positions > 0 ? span : (BG - std::gcd(BG, (long long)rows) + rows - 1) / BG + 1;
+            const long long units = (std::min(most, (long long)p.N) * per_rollout * 9 + 4) / 5;
+            longest += std::max(0ll, units - wt) * ((longest + pl.TPU - 1) / pl.TPU);
+        }
         booked_all = wt == std::min(cost, 64ll);
     };
-    // Private tiles are dealt out where that shortens the longest workgroup by more than the further segments cost, each a set-up and
-    // a partial result: a unit for pieces of 128 rows; four for pieces of 256, whose wavefronts pass over the private tiles of
+    // Private tiles are dealt out where that shortens the longest workgroup by more than the further segments cost: pieces of 128 rows by
+    // a unit, one more if there are more of them than two and than before, and one more if the merge kernel then needs another round of
+    // loads; four for pieces of 256, whose wavefronts pass over the private tiles of
     // other rollouts, so that these cost less than they are booked with; three for ranges, some of which then end in one more
-    // M-tile.  Never if equal pieces would become ranges.  us per call, one place / dealt, in brackets the units of the longest workgroup,
-    // Hq = 28, Hkv = 4, D = 128 unless said:
-    //   pieces of 128 rows: N=1, B=32, L=192 [3/2] 10.0/9.0; N=4, B=32, L=1024 [4/3] 14.1/13.0; N=8, B=32, L=128 [4/2] 10.9/11.2; N=16,
-    //   L=128 [4/3] 12.9/13.1; N=2, B=64, L=192 [5/2] 12.7/10.3; Hq = 16, N=10, B=32, L=173 [3/2] 11.6/12.1; D = 64, Hq = 14, Hkv = 2: N=8,
-    //   B=40, L=3008, E=40 [9/8] 15.3/14.4; N=16, B=32, L=100 [4/2] 9.3/9.7; many rollouts, Hq = Hkv = 8, N=33, B=1, L=1408, E=1 [119/3]
-    //   93.4/12.9; drawn calls that gain one unit 1.02 in the geometric mean (23), two 1.05 (30), three 1.12 (24), four to seven 1.21 (48);
+    // M-tile.  Never if equal pieces would become ranges.  us per call, one place / dealt, in brackets the units of the longest workgroup and
+    // the pieces, Hq = 28, Hkv = 4, D = 128 unless said:
+    //   pieces of 128 rows, dealt: N=1, B=32, L=192 [3/2, 2/3] 9.9/8.5; N=8, L=128 [4/2, 2/3] 10.4/10.7; N=1, B=40, L=3968, E=37 [5/4, 17/17]
+    //   14.6/13.7; Hkv = Hq = 8, N=2, B=20, L=716 [4/2, 7/8] 10.6/9.9; D = 64: Hq = 32, Hkv = 8, B=72, L=1197 [5/3, 7/8] 12.2/10.0; Hq = 14,
+    //   Hkv = 2, N=8, B=40, L=3008, E=40 [9/8] 15.3/14.4; many rollouts, Hq = Hkv = 8, N=33, B=1, L=1408, E=1 [119/3] 93.4/12.9;
+    //   in one place: Hq = 32, Hkv = 8, N=1, B=32, L=2360 [3/2, 19/20] 12.2/13.0; another round of the merge: Hq = 14, Hkv = 2, B=1, L=943
+    //   [3/2, 8/9] 9.7/10.3, N=4, B=32, L=855 [4/2, 8/9] 13.3/13.9, Hq = 4, Hkv = 1, N=8, B=31, L=365 [4/2, 4/6] 10.5/11.6, but Hq = 32,
+    //   Hkv = 8, N=2, B=1, L=384 [4/2, 4/5] 9.3/8.7;
+    //   478 drawn calls: 451 dealt (1.36 in the geometric mean, ten of them slower by more than 2 %), 27 in one place (0.99);
     //   pieces of 256: Hq = 14, Hkv = 2, N=41, B=32, L=151, D = 64 [5/3] 11.9/12.5; half of the positions of N=31, B=32, L=24 [6/3] 17.2/18.4;
     //   N=50, B=8, L=108 [11/3] 18.2/18.4; N=9, B=65, L=585, E=65, listed [13/5] 20.2/18.4; N=7, B=70, L=320, Hq = 32, Hkv = 8, E=140, listed
     //   [24/7] 26.0/21.7;
@@ -229,9 +239,15 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool ample)
         cut_units(rows, false);
         if (!may_deal || booked_all) return;
         const long long whole = longest;
-        const bool pieces = pl.uniform > 0;
+        const int pieces = pl.uniform;
         cut_units(rows, true);
-        if (longest + (!pieces ? 3 : rows == 128 ? 1 : 4) > whole || (pieces && pl.uniform == 0)) cut_units(rows, false);
+        long long least = 3;
+        if (pieces > 0) {
+            const long long chunks = (long long)p.Hkv * batch * pl.R * (p.D / 8);
+            const MergeCut a = merge_cut(chunks, pieces), b = merge_cut(chunks, pl.uniform);
+            least = rows == 256 ? 4 : 1 + (pieces > 2 && pl.uniform > pieces) + (b.rounds > a.rounds);
+        }
+        if (longest + least > whole || (pieces > 0 && pl.uniform == 0)) cut_units(rows, false);
     };
     auto cut_rows = [&](bool may_deal) {
         cut_bf16(256, may_deal);

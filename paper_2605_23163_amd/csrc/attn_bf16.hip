@@ -1284,16 +1284,7 @@ hipError_t launch_attn_merge_bf16(const fdd_attn_params& p, const AttnPlan& plan
     a.dBase = make_fastdiv((uint32_t)(base > 0 ? base : 1));
     a.dBase1 = make_fastdiv((uint32_t)(base + 1));
     a.c = scale * 1.4426950408889634f;
-    // SG threads per chunk: more of them while the chunks of a call leave most of the chip's lanes idle and each still has
-    // four segments or more to request.  us per call (replayed) with 1, 2, 4, 8 of them, Hq = 28, Hkv = 4, D = 128, B = 32: N=1
-    // (14 k chunks), L=512 (5 segments) 10.8, 10.4, 10.5, 11.0, L=2048 (17) 13.1, 12.0, 11.0, 11.6, L=16384 (29) 24.1, 21.5, 20.1,
-    // 20.5; N=2 (29 k), L=8192 (15) 21.1, 19.9, 19.8, 20.4, L=32768 (31) 43.1, 40.9, 40.5, 40.8; N=4 (57 k), L=8192 (9) 27.5, 26.8, 27.4,
-    // 28.5; N=8 (115 k), L=4096 (4) 27.0, 27.3, 29.1, 31.9, L=6000 (9) 35.1, 36.3, 36.0, 39.1; N=16 (229 k), L=4096 (4) 41.1, 42.2, 44.9,
-    // 50.8; one head, N=1, B=4, L=20000 (64 chunks, 157 segments) 37.9, 26.1, 17.4, 14.9.
-    const long long chunks = (long long)p.Hkv * batch * plan.R * (p.D / 8);
-    const int n = plan.uniform > 0 ? plan.uniform : plan.max_seg;
-    int sg = 1;
-    while (sg < 8 && sg * 8 <= n && chunks * sg * 2 <= (1 << 17)) sg *= 2;
+    const MergeCut cut = merge_cut((long long)p.Hkv * batch * plan.R * (p.D / 8), plan.uniform > 0 ? plan.uniform : plan.max_seg);
     auto go = [&](auto d, auto sgc, auto ux) {
         constexpr int D = decltype(d)::value, SG = decltype(sgc)::value, UX = decltype(ux)::value;
         const dim3 grid((unsigned)(p.Hkv * batch * plan.MT), (unsigned)(plan.mtile_rows / 32 * 2 * (D / 32) * SG / 4));
@@ -1305,10 +1296,10 @@ hipError_t launch_attn_merge_bf16(const fdd_attn_params& p, const AttnPlan& plan
         const std::integral_constant<int, 2> i2;
         const std::integral_constant<int, 4> i4;
         const std::integral_constant<int, 8> i8;
-        if (sg == 8) go(d, i8, i8);
-        else if (sg == 4) go(d, i4, i8);
-        else if (sg == 2) go(d, i2, i4);
-        else if (n > 2) go(d, i1, i4);
+        if (cut.sg == 8) go(d, i8, i8);
+        else if (cut.sg == 4) go(d, i4, i8);
+        else if (cut.sg == 2) go(d, i2, i4);
+        else if (cut.ux == 4) go(d, i1, i4);
         else go(d, i1, i2);
     };
     if (p.D == 128) sized(std::integral_constant<int, 128>());

@@ -98,6 +98,24 @@ __host__ __device__ __forceinline__ int fast_div(int n, const FastDiv& f)
     return (int)((uint32_t)(((uint64_t)((uint32_t)n + 1u) * f.mul) >> 32) >> f.shift);
 }
 
+// bf16 path: how the merge kernel takes the segments of an M-tile: `sg` threads per 16-byte chunk, each with `ux` segments at a time, in
+// so many rounds of loads.  sg: more threads while the chunks of a call leave most of the chip's lanes idle and each still has
+// four segments or more to request.  us per call (replayed) with 1, 2, 4, 8 of them, Hq = 28, Hkv = 4, D = 128, B = 32: N=1
+// (14 k chunks), L=512 (5 segments) 10.8, 10.4, 10.5, 11.0, L=2048 (17) 13.1, 12.0, 11.0, 11.6, L=16384 (29) 24.1, 21.5, 20.1,
+// 20.5; N=2 (29 k), L=8192 (15) 21.1, 19.9, 19.8, 20.4, L=32768 (31) 43.1, 40.9, 40.5, 40.8; N=4 (57 k), L=8192 (9) 27.5, 26.8, 27.4,
+// 28.5; N=8 (115 k), L=4096 (4) 27.0, 27.3, 29.1, 31.9, L=6000 (9) 35.1, 36.3, 36.0, 39.1; N=16 (229 k), L=4096 (4) 41.1, 42.2, 44.9,
+// 50.8; one head, N=1, B=4, L=20000 (64 chunks, 157 segments) 37.9, 26.1, 17.4, 14.9.
+struct MergeCut {
+    int sg, ux, rounds;
+};
+inline MergeCut merge_cut(long long chunks, int segments)
+{
+    int sg = 1;
+    while (sg < 8 && sg * 8 <= segments && chunks * sg * 2 <= (1 << 17)) sg *= 2;
+    const int ux = sg >= 4 ? 8 : segments > 2 || sg == 2 ? 4 : 2;
+    return {sg, ux, (segments + sg * ux - 1) / (sg * ux)};
+}
+
 // Key tiles of a row tile whose first and last row belong to rollouts n_lo and n_hi: `prefix` ones, and `per` for every
 // rollout from one to the other.  (A list of positions in another order than ascending gives undefined values, but may not
 // lead out of the arrays: where n_hi is below n_lo these are n_lo's private tiles, not a negative number of them.)  The bf16

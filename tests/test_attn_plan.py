@@ -40,10 +40,12 @@ def test_short_prefixes_need_no_scratch(plans):
 
 
 def test_private_tiles_are_dealt_out_where_that_pays(plans):
-    # one unit less in the longest of the 128-row pieces; more of them in pieces of 256 rows and in ranges, where fewer do not pay;
-    # pieces do not become ranges.  (pieces, units, prefix units)
+    # One unit less in the longest of the 128-row pieces, two if there are more of them, three if the merge then needs another round;
+    # more of them in pieces of 256 rows and in ranges, where fewer do not pay; pieces do not become ranges.  (pieces, units, prefix units)
     want = {(1, 32, 192, 28, 4, 128): (3, 5, 3), (4, 32, 1024, 28, 4, 128): (7, 20, 16), (33, 1, 1408, 8, 8, 128, 1): (29, 86, 22),
             (41, 32, 151, 14, 2, 64): (3, 6, 3), (9, 65, 585, 28, 4, 128, 65, 409): (5, 25, 10), (41, 32, 326, 28, 4, 128): (0, 8, 6),
+            (1, 40, 3968, 28, 4, 128, 37): (17, 66, 62), (2, 20, 716, 8, 8, 128): (8, 16, 12), (1, 32, 2360, 32, 8, 128): (19, 38, 37),
+            (1, 1, 943, 14, 2, 128): (8, 16, 15), (4, 32, 855, 28, 4, 128): (8, 16, 14), (8, 31, 365, 4, 1, 128): (4, 8, 6),
             (24, 65, 4864, 14, 2, 128, 130): (0, 94, 76), (14, 64, 75, 14, 2, 128): (2, 5, 2), (44, 40, 94, 14, 2, 128): (2, 5, 2)}
     got = plans(list(want))
     for (shape, w), p in zip(want.items(), got):
