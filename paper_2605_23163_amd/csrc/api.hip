@@ -253,8 +253,11 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool ample)
         cut_bf16(256, may_deal);
         // M-tiles of 128 rows (workgroups of 4 wavefronts, one per SIMD) while the call is short: alone in a compute unit such a
         // workgroup takes 0.68 us a tile where one of 8 takes 1.09 (D = 128), starts on fewer tiles, and its segments are half as
-        // large; long calls fetch K and V twice as often.  Up to 9 units per compute unit of the 256-row plan, D = 64 5 (either is within a
-        // few per cent of the other up to 11 and 8); not where only the larger tiles cut into equal pieces that fill the chip.  us per call,
+        // large; long calls fetch K and V twice as often.  Up to 9 units per compute unit of the 256-row plan, D = 64 5; not where only the
+        // larger tiles cut into equal pieces that fill the chip.  By the figures below 128 rows would be 1 to 6 % ahead up to 11 units at
+        // D = 128, and within 3 % either way up to 8 at D = 64.  The lines stand lower because these few shapes are all that was measured
+        // beyond them, and because the tests of the 256-row kernels have their shapes there (9.2 to 9.9 units): they would have to grow
+        // first.  us per call,
         // prefixes from memory (30 calls in rotation), 256 / 128 rows, Hq = 28, Hkv = 4, B = 32, in brackets the units per compute unit:
         //   D = 128, V laid out: N=8, L=2048 [3.9] 19.8/17.1; L=4096 [7.7] 25.6/23.6; N=4, L=8192 [8.4] 25.8/24.2; N=2, L=18000 [8.9]
         //   27.3/26.2; N=12, L=3000 [9.1] 27.4/25.8; N=4, L=9500 [9.7] 27.6/26.3; N=8, L=6000 [10.9] 31.0/30.8; N=16, L=4096 [15]

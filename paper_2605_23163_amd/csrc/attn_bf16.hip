@@ -21,7 +21,7 @@
 //     scalar multiply.
 //   * Every K/V tile goes from global memory straight into LDS
 //     (buffer_load ... lds: no registers, no vector ALU work, no LDS writes by
-//     the waves) into a ring of 4 K slots and 4 V slots.  K tiles lie
+//     the waves) into a ring of SLOTS slots for K and as many for V.  K tiles lie
 //     [key][d] with the 16-byte pieces of a row XOR-swizzled by the row index,
 //     which keeps the K fragment reads conflict-free without padding.
 //   * O^T += V^T P^T needs, per lane, 8 keys of one channel, i.e. V with the
@@ -38,17 +38,17 @@
 //     by the row on the global side of the load, which makes those reads
 //     conflict-free too.
 //   * Full prefix tiles run through a software-pipelined loop written as 32
-//     slots per tile, one per MFMA.  Each slot also carries a slice of vector
+//     steps per tile (D = 64: 16), one per MFMA.  Each also carries a slice of vector
 //     ALU work that does not depend on that MFMA: while the matrix pipe
 //     produces the scores of tile i+1 and then the P V products of tile i,
 //     the vector ALUs take the exponentials of tile i, round them to bf16 and
-//     find the row maximum of tile i+1.  V of tile i+3 and K of tile
-//     i+4 are requested in step i (K is read one step before V,
+//     find the row maximum of tile i+1.  V of tile i+SLOTS-1 and K of tile
+//     i+SLOTS are requested in step i (K is read one step before V,
 //     so its slot is free one step earlier) and waits are counted (the loads
-//     of a wavefront complete in issue order), so four half tiles stay in
-//     flight across a step boundary; LDS
+//     of a wavefront complete in issue order): with four slots four half tiles stay in
+//     flight across a step boundary, with two none; LDS
 //     fragments are requested three MFMAs before their use.  The loop is
-//     unrolled four times so that ring slots are immediate offsets.
+//     unrolled SLOTS times so that ring slots are immediate offsets.
 //   * The softmax reference value of a row is only raised when the running
 //     maximum outgrows it by more than 2^8; in between probabilities may
 //     exceed 1, which fp32 sums and bf16 relative precision do not mind, and
@@ -497,8 +497,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
             ttpr = a.ttpr;                         // private tiles per rollout: extension, then block
             // The private tiles lie evenly over the booked units, each with the segment that holds the last of its own.  (All on
             // the M-tile's last segment, a rollout's extension and block and those of the rollouts after it were done one after the
-            // other, 1.5 to 2 us each, when the other workgroups had ended.  us per call: N=33, B=1, L=1408, Hq=8, Hkv=8, E=1 93.7 -> 14.4;
-            // N=9, B=1, L=11904, D=64, E=37 32.6 -> 10.4; 200 drawn calls 1.18 in the geometric mean.)
+            // other, 1.5 to 2 us each, when the other workgroups had ended.  us per call: N=33, B=1, L=1408, Hq=8, Hkv=8, E=1 93.7 -> 12.9;
+            // N=9, B=1, L=11904, D=64, E=37 32.6 -> 10.4.  Which calls deal them out: make_attn_plan.)
             if (t_end > a.TP) {
                 n_tail = key_tiles(0, ttpr, wg_n_lo, wg_n_hi);
                 if (t_begin > a.TP || t_end < a.TPU) {
@@ -709,7 +709,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_bf16_kern
                 float mx = -INFINITY;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) mx = fmaxf(fmaxf(mx, sa[0][v]), sa[1][v]);
-                // Step 0 requests K of tile 4 into the slot that the scores above were read from: no wavefront may get
+                // Step 0 requests K of tile SLOTS into the slot that the scores above were read from: no wavefront may get
                 // there while another one is still reading.  (They can be far apart here: the first workgroups of a
                 // launch fetch these instructions from memory.)
                 FDD_SCHED_FENCE();
