@@ -37,8 +37,8 @@
 //     consecutive keys of channel i); their 32-byte columns are XOR-swizzled
 //     by the row on the global side of the load, which makes those reads
 //     conflict-free too.
-//   * Full prefix tiles run through a software-pipelined loop written as 32
-//     steps per tile (D = 64: 16), one per MFMA.  Each also carries a slice of vector
+//   * Full prefix tiles run through a software-pipelined loop of 32 MFMAs per
+//     tile (D = 64: 16).  Beside each of them stands a slice of vector
 //     ALU work that does not depend on that MFMA: while the matrix pipe
 //     produces the scores of tile i+1 and then the P V products of tile i,
 //     the vector ALUs take the exponentials of tile i, round them to bf16 and
