@@ -272,15 +272,26 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool ample)
             if (pl.uniform == 0 && (uniform256 > 0 || NM > kNumCU)) cut_bf16(256, may_deal);
         }
     };
-    // stacked rows, over all KV heads, of M-tiles that several workgroups work on
-    auto shared_rows = [&]() -> long long {
-        if (pl.uniform > 0) return pl.uniform == 1 ? 0 : (long long)p.Hkv * batch * pl.R;
-        long long n = 0, last = -1;
-        for (long long w = 1, base = pl.U / pl.W, rem = pl.U % pl.W; w < pl.W; ++w) {
-            const long long u = w * base + std::min(w, rem), m = u / pl.TPU;       // (ranges: 256 at most)
-            if (u == m * pl.TPU || m == last) continue;
-            n += m % pl.MT == pl.MT - 1 ? pl.R - (pl.MT - 1) * pl.mtile_rows : pl.mtile_rows;
-            last = m;
+    // Stacked rows, over all KV heads, of M-tiles that several workgroups work on.  (Ranges, 256 at most, are walked without a division
+    // each: for both plans of such a call 2 us of the host's, 3.2 with divisions; the call takes 17 and more on the GPU.)
+    auto shared_rows = [&](const AttnPlan& a) -> long long {
+        if (a.uniform > 0) return a.uniform == 1 ? 0 : (long long)p.Hkv * batch * a.R;
+        const int last_rows = a.R - (a.MT - 1) * a.mtile_rows, rem = (int)(a.U % a.W);
+        const long long base = a.U / a.W;
+        const int tiles = (int)(base / a.TPU), units = (int)(base % a.TPU), tiles_in_head = tiles % a.MT;
+        long long n = 0, shared = -1, m = 0;     // the last shared M-tile; the one that range w begins in
+        int mt = 0, u = 0;                       // its place in its KV head, the unit in it
+        for (int w = 1; w < a.W; ++w) {
+            u += units + (w <= rem ? 1 : 0);
+            const int over = u >= a.TPU ? 1 : 0;
+            u -= over ? a.TPU : 0;
+            m += tiles + over;
+            mt += tiles_in_head + over;
+            mt -= mt >= a.MT ? a.MT : 0;
+            const bool cut = (u != 0) & (m != shared);
+            const int rows = mt == a.MT - 1 ? last_rows : a.mtile_rows;
+            n += cut ? rows : 0;
+            shared = cut ? m : shared;
         }
         return n;
     };
@@ -296,9 +307,10 @@ bool make_attn_plan(const fdd_attn_params& p, AttnPlan* plan, bool ample)
         // 2.47e-3/2.66e-3.)
         cut_rows(false);
         if (ample && p.splits == 0 && partials && !booked_all) {
-            const long long shared = shared_rows();
+            const AttnPlan one_place = pl;
             cut_rows(true);
-            if (shared_rows() > shared) cut_rows(false);
+            const bool other = pl.TPU != one_place.TPU || pl.mtile_rows != one_place.mtile_rows;
+            if (other && shared_rows(pl) > shared_rows(one_place)) cut_rows(false);
         }
         // Ring slots per operand: four hide more of the memory's latency, two start earlier, with fewer requests in flight, do better
         // where nearly every request goes to memory (one M-tile per KV head), and leave room for a second workgroup on a compute unit
